@@ -34,6 +34,7 @@ struct BatchState {
     int kind = -1;
     int nbmax = 1;
     int bp_px = 2;                   // R^T pixels per lane for the whole batch
+    int bp_forms = 0;                // forms of R^T among the slices (bp_form)
     size_t lds_rows = 0, lds_cols = 0;
     std::vector<SliceDev> hs;        // host copies; per-call pointers filled in each call
     DevBuf arena, sl, items, scal, trace_d;
@@ -58,7 +59,7 @@ struct sp_ctx {
     sp_geometry geom{};
     GeomDev G{};
     std::vector<AngleDev> ang_h;
-    DevBuf ang, pwave, xp, xTp, yp, ypd, seg, pord, blob_tab;
+    DevBuf ang, quad, pwave, xp, xTp, yp, ypd, seg, pord, blob_tab;
 
     // preconditioner cache
     int fftP = 0;
@@ -100,6 +101,7 @@ struct sp_ctx {
     // the event after their last upload (the next call waits on it before
     // writing them again)
     std::vector<AngleDev> na_tab;
+    std::vector<BpAngle> na_quad;
     hipEvent_t na_ev = nullptr;
     BatchState* batch = nullptr;
     int n_cu = 0;
@@ -305,6 +307,14 @@ int setup_geometry(sp_ctx* c, const sp_geometry* g) {
                               hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(c->ang.ptr, tab.data(), tab.size() * sizeof(AngleDev),
                               hipMemcpyHostToDevice, c->stream));
+    std::vector<BpAngle> quad;
+    if (G.bp_quad && G.cls[2] > 0) {
+        quad.resize((size_t)G.cls[2]);
+        (void)bp_quad_table(G, tab.data(), quad.data());
+        if ((rc = ensure(c, c->quad, quad.size() * sizeof(BpAngle)))) return rc;
+        HIP_TRY(c, hipMemcpyAsync(c->quad.ptr, quad.data(), quad.size() * sizeof(BpAngle),
+                                  hipMemcpyHostToDevice, c->stream));
+    }
     const std::vector<int32_t> ord = project_order(G, tab.data(), waves.data(), c->n_cu);
     if ((rc = ensure(c, c->pord, ord.size() * sizeof(int32_t)))) return rc;
     HIP_TRY(c, hipMemcpyAsync(c->pord.ptr, ord.data(), ord.size() * sizeof(int32_t),
@@ -756,7 +766,7 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
     std::vector<std::vector<AngleDev>> tabs(n);
     // sizes
     struct Off {
-        size_t ang, pwave, pord, xp, xTp, rpd, seg, dvec, vec, sq, S, tw, pf, pgp, pqq, ptg, ptt, pts;
+        size_t ang, quad, pwave, pord, xp, xTp, rpd, seg, dvec, vec, sq, S, tw, pf, pgp, pqq, ptg, ptt, pts;
     };
     std::vector<Off> off(n);
     size_t total = 0;
@@ -795,6 +805,7 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
             return at;
         };
         o.ang = take(tabs[s].size() * sizeof(AngleDev));
+        o.quad = take(G.bp_quad ? (size_t)G.cls[2] * sizeof(BpAngle) : 0);
         o.pwave = take((size_t)G.nwaves * sizeof(WaveDev));
         o.pord = take((size_t)G.nwg * sizeof(int32_t));
         o.xp = take((size_t)G.rows * G.pitchX * 8);
@@ -819,8 +830,12 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
     // depend on it, so batched and single solves stay bitwise equal)
     {
         long waves4 = 0;
-        for (const SliceDev& S : B.hs) waves4 += (long)backproject_tiles(S.G, 4) * 4;
-        B.bp_px = waves4 >= (long)c->n_cu * 16 ? 4 : 2;
+        B.bp_forms = 0;
+        for (const SliceDev& S : B.hs) {
+            waves4 += (long)backproject_tiles(S.G, 4) * 4;
+            B.bp_forms |= bp_form(S.G);
+        }
+        B.bp_px = !(B.bp_forms & BP_FORM_PIXEL) || waves4 >= (long)c->n_cu * 16 ? 4 : 2;
         // tuned shapes that agree for every slice take precedence
         int tpx = 0;
         bool all = true;
@@ -843,6 +858,15 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         SliceDev& S = B.hs[s];
         const Off& o = off[s];
         S.ang = reinterpret_cast<const AngleDev*>(base + o.ang);
+        S.quad = nullptr;
+        std::vector<BpAngle> quad;
+        if (S.G.bp_quad && S.G.cls[2] > 0) {
+            quad.resize((size_t)S.G.cls[2]);
+            (void)bp_quad_table(S.G, tabs[s].data(), quad.data());
+            S.quad = reinterpret_cast<const BpAngle*>(base + o.quad);
+            HIP_TRY(c, hipMemcpyAsync(base + o.quad, quad.data(), quad.size() * sizeof(BpAngle),
+                                      hipMemcpyHostToDevice, c->stream));
+        }
         std::vector<WaveDev> waves((size_t)S.G.nwaves);
         project_waves(S.G, waves.data());
         S.pwave = reinterpret_cast<const WaveDev*>(base + o.pwave);
@@ -926,7 +950,7 @@ void batch_stage(sp_ctx* c, int stage, int order, int wpc, double mu, double rho
     switch (stage) {
     case BS_PREP: launch_prep_b(st, sl, t, BV_XH); break;
     case BS_PROJECT: launch_project_b(st, sl, t, table(c, BS_PROJ_COMB, order, 0), true); break;
-    case BS_BACKPROJECT: launch_backproject_b(st, sl, t, B.nbmax, B.bp_px); break;
+    case BS_BACKPROJECT: launch_backproject_b(st, sl, t, B.nbmax, B.bp_px, B.bp_forms); break;
     case BS_ROWS:
         launch_precond_b(st, sl, t, table(c, BS_COLS, order, wpc), B.lds_rows, B.lds_cols, mu, rho);
         break;
@@ -1016,6 +1040,7 @@ int sp_ctx_create(int device, void* hip_stream, sp_ctx** out) {
         c->n_cu < 1)
         c->n_cu = 256;
     c->na_tab.resize(NOALLOC_MAX_ANGLES);
+    c->na_quad.resize(NOALLOC_MAX_ANGLES);
     if (hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) != hipSuccess) {
         delete c;
         return SP_ERR_HIP;
@@ -1031,7 +1056,7 @@ int sp_ctx_destroy(sp_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     (void)drain_pending(c);
-    for (DevBuf* b : {&c->ang, &c->pwave, &c->xp, &c->xTp, &c->yp, &c->ypd, &c->seg, &c->pord, &c->blob_tab, &c->tw, &c->S, &c->vx, &c->vxh, &c->vp, &c->vq, &c->vw, &c->ox, &c->oxh, &c->oscal,
+    for (DevBuf* b : {&c->ang, &c->quad, &c->pwave, &c->xp, &c->xTp, &c->yp, &c->ypd, &c->seg, &c->pord, &c->blob_tab, &c->tw, &c->S, &c->vx, &c->vxh, &c->vp, &c->vq, &c->vw, &c->ox, &c->oxh, &c->oscal,
                       &c->vg, &c->vz, &c->vtb, &c->vtb2, &c->stv_y, &c->vtmp, &c->part_f, &c->part_zh, &c->part_gp,
                       &c->part_qq, &c->part_g, &c->part_t, &c->part_s, &c->part_misc, &c->part_se, &c->stored_xT, &c->art_u, &c->art_nrm, &c->art_sum, &c->scal,
                       &c->trace_d, &c->replay_d, &c->trials_tmp})
@@ -1274,8 +1299,8 @@ int sp_backproject(sp_ctx* c, const sp_geometry* g, const float* y, float* x) {
     launch_pad_sino(c->stream, G, dptr<AngleDev>(c->ang), y, dptr<float>(c->yp));
     {
         ProfScope ps(c, SP_PROF_BACKPROJECT);
-        launch_backproject(c->stream, G, dptr<AngleDev>(c->ang), dptr<float>(c->yp), x, nullptr,
-                           nullptr, nullptr);
+        launch_backproject(c->stream, G, dptr<AngleDev>(c->ang), dptr<BpAngle>(c->quad),
+                           dptr<float>(c->yp), x, nullptr);
     }
     return check_launch(c);
 }
@@ -1306,12 +1331,18 @@ int sp_backproject_noalloc(sp_ctx* c, const sp_geometry* g, const float* y, floa
     if ((rc = build_geometry_into(c, g, G, c->na_tab.data()))) return rc;
     char* base = static_cast<char*>(scr);
     AngleDev* ang = reinterpret_cast<AngleDev*>(base);
+    BpAngle* quad = reinterpret_cast<BpAngle*>(base + NOALLOC_SCRATCH_BYTES);
+    if (G.bp_quad && G.cls[2] > 0) {
+        (void)bp_quad_table(G, c->na_tab.data(), c->na_quad.data());
+        HIP_TRY(c, hipMemcpyAsync(quad, c->na_quad.data(), (size_t)G.cls[2] * sizeof(BpAngle),
+                                  hipMemcpyHostToDevice, c->stream));
+    }
     float* yp = reinterpret_cast<float*>(base + off_yp);
     HIP_TRY(c, hipMemcpyAsync(ang, c->na_tab.data(), (size_t)g->n_angles * sizeof(AngleDev),
                               hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipEventRecord(c->na_ev, c->stream));
     launch_pad_sino(c->stream, G, ang, y, yp);   // every entry of the rows, pads included
-    launch_backproject(c->stream, G, ang, yp, x, nullptr, nullptr, nullptr);
+    launch_backproject(c->stream, G, ang, quad, yp, x, nullptr);
     return check_launch(c);
 }
 
@@ -1468,8 +1499,8 @@ int sp_gradient(sp_ctx* c, const sp_geometry* g, const float* x, const float* b,
                    dptr<double>(c->xTp), b,
                    nullptr, 0, nullptr, dptr<double>(c->ypd), dptr<double>(c->part_f),
                    dptr<double>(c->seg), dptr<int>(c->pord), nullptr);
-    launch_backproject(c->stream, G, dptr<AngleDev>(c->ang), dptr<double>(c->ypd),
-                       grad, nullptr, nullptr, nullptr);
+    launch_backproject(c->stream, G, dptr<AngleDev>(c->ang), dptr<BpAngle>(c->quad), dptr<double>(c->ypd),
+                       grad, nullptr);
     if (f) launch_reduce(c->stream, dptr<double>(c->part_f), project_blocks(G), f);
     return check_launch(c);
 }
@@ -1726,6 +1757,7 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
     double* rpd = dptr<double>(c->ypd);
     const WaveDev* waves = dptr<WaveDev>(c->pwave);
     const AngleDev* ang = dptr<AngleDev>(c->ang);
+    const BpAngle* quad = dptr<BpAngle>(c->quad);
     double* pf = dptr<double>(c->part_f);
     double* pzh = dptr<double>(c->part_zh);
     double* pgp = dptr<double>(c->part_gp);
@@ -1748,7 +1780,7 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
         launch_prep(st, G, xh, xp, xTp, halt);
         launch_project(st, G, ang, waves, xp, xTp, b, nullptr, 0, nullptr, rpd, pf, seg, pord, halt);
         launch_scalar(st, OP_F0, sc, tr, pf, nf, nullptr, 0);
-        launch_backproject(st, G, ang, rpd, gv, nullptr, nullptr, halt);
+        launch_backproject(st, G, ang, quad, rpd, gv, halt);
         int nzh = 0;
         if ((rc = enqueue_precond(c, pc, gv, z, nullptr, pzh, nzh, true, xp, xTp))) return rc;   // + R's copies of z
         launch_project(st, G, ang, waves, xp, xTp, nullptr, nullptr, 0, nullptr, nullptr, pf, seg, pord,
@@ -1774,7 +1806,7 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
     };
     auto backproject = [&](float* out, const ScalarRide& ride) {
         ProfScope ps(c, SP_PROF_BACKPROJECT);
-        launch_backproject(st, G, ang, rpd, out, nullptr, nullptr, halt, ride);
+        launch_backproject(st, G, ang, quad, rpd, out, halt, ride);
     };
     // g = R^T r also carries f(x_{k+1/2}) (and the S_TV step norm when K > 0)
     ScalarRide ride_f;
@@ -2598,7 +2630,7 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
     launch_prep_b(st, sl, tprep, BV_XH);
     launch_project_b(st, sl, tproj, tcomb, true);
     launch_scalar_b(st, sl, tone, OP_F0);
-    launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px);
+    launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms);
     batch_precond(c, mu, rho);
     launch_prep_b(st, sl, tprep, BV_Z);
     launch_project_b(st, sl, tproj, tcomb, false);                // w = R z
@@ -2627,7 +2659,7 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
         }
         launch_project_b(st, sl, tproj, tcomb, true);
         launch_scalar_b(st, sl, tone, OP_F);
-        launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px);
+        launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms);
         batch_precond(c, mu, rho);
         launch_prep_b(st, sl, tprep, BV_Z);
         launch_project_b(st, sl, tproj, tcomb, false);            // w = R z, (R z)^T q

@@ -128,6 +128,9 @@ int project_parts(int rows, int cols, int nwaves, int resident_waves) {
 }
 
 int backproject_tiles(const GeomDev& G, int px) {
+    if (G.bp_quad)
+        return ((G.cols + G.bp_nq * BPQ_TILE - 1) / (G.bp_nq * BPQ_TILE)) * ((G.rows + BPQ_TILE - 1) / BPQ_TILE) *
+               (px == 2 ? 2 : 1);
     return ((G.cols + 8 * px - 1) / (8 * px)) * ((G.rows + BP_TILE - 1) / BP_TILE);
 }
 
@@ -139,6 +142,67 @@ int backproject_px(int rows, int cols, int resident_waves) {
     G.rows = rows;
     G.cols = cols;
     return (long)backproject_tiles(G, 4) * BP_SPLIT >= resident_waves / 2 ? 4 : 2;
+}
+
+// Slack of the candidate windows (pixel units), far above the rounding of the
+// window indices.
+static double bp_margin(const GeomDev& G) { return 1e-3 + 4e-7 * (double)(G.rows + G.cols + G.nB); }
+
+bool bp_quad_table(const GeomDev& G, const AngleDev* tab, BpAngle* out) {
+    const double mg = bp_margin(G);
+    const int n = G.cls[2];
+    for (int a = n - 1; a >= 0; --a) {
+        const AngleDev& A = tab[a];
+        const double ac = std::fabs(A.c), as = std::fabs(A.s), S = ac + as;
+        const double mn = std::min(ac, as), mx = std::max(ac, as), ds = G.ds;
+        // bin q (0, 1, 2) of the block sits at phi + q ds above the block's lower
+        // edge, 0 < phi <= ds; A's centre is at mg + S / 2 and its footprint S wide
+        if (!(2.0 * S + 2.0 * mg <= 3.0 * ds)) return false;       // the block within three bins
+        if (!(S + 2.0 * mg <= 2.0 * ds)) return false;             // A: bin 2 outside
+        if (!(0.5 * S + mg < ds)) return false;                    // A: bin 1 above its centre
+        if (!(ds <= S)) return false;                              // D: bin 0 outside
+        if (!(0.5 * S + mn + mg < 2.0 * ds)) return false;         // B: bin 2 above its centre
+        if (!(ds < 0.5 * S + mx)) return false;                    // C: bin 0 below its centre
+        if (!(0.5 * S + mx + mg < 2.0 * ds)) return false;         // C: bin 2 above its centre
+        if (!out) continue;
+        BpAngle& Q = out[a];
+        const double inv = A.inv, K = ds * inv;
+        Q.cids = A.cids;
+        Q.sids = A.sids;
+        Q.kb = -(G.s0 + S + mg) / ds + 1.0 + PAD;
+        Q.nk = -K;
+        Q.wc = (ds - 0.5 * S - mg) * inv;
+        Q.einv = A.einv;
+        Q.eK = A.einv - K;
+        Q.dD1 = (ds - S) * inv;
+        Q.dD2 = (2.0 * ds - S) * inv;
+        Q.dB0 = -mn * inv;
+        Q.dB1 = (ds - mn) * inv;
+        Q.eB2 = A.einv - (2.0 * ds - mn) * inv;
+        Q.eC0 = A.einv - mx * inv;
+        Q.dC1 = (ds - mx) * inv;
+        Q.eC2 = A.einv - (2.0 * ds - mx) * inv;
+        Q.row = A.row;
+        const int code = (A.c < 0.0 ? BP_FLIP_X : 0) | (A.s > 0.0 ? BP_FLIP_Y : 0) |
+                         ((A.flags & ANG_HORIZ) ? 0 : BP_VERT);
+        const bool same = a + 1 < n && (out[a + 1].run & ((1 << BP_CODE_BITS) - 1)) == code;
+        const int end = same ? out[a + 1].run >> BP_CODE_BITS : a + 1;
+        Q.run = (end << BP_CODE_BITS) | code;
+    }
+    return true;
+}
+
+void backproject_shape(GeomDev& G, int resident_waves) {
+    // Waves of 16 x 16 tiles: enough shares of the angles to fill the wave
+    // slots, no more (a share costs its reduction).  Measured, float64 residual
+    // form, 4 / 8 / 16 shares: 243^2 x 360 32.7 / 19.7 / 13.6 us, 512^2 x 720
+    // 101 / 59 / 61, 1024^2 x 1432 422 / 415 / 410, 2048^2 x 2864 3578 / 3592 /
+    // 3729.  Two tiles side by side per wave share an angle's constants but
+    // halve the waves: 2048^2 at 4 shares 3.58 -> 3.31 ms, 512^2 slower.
+    G.bp_nq = 1;
+    const int tiles = backproject_tiles(G, 4);
+    G.bp_shares = 12L * tiles < resident_waves ? 16 : (tiles < resident_waves ? 8 : 4);
+    G.bp_nq = tiles < resident_waves ? 1 : 2;
 }
 
 int project_comb_blocks(const GeomDev& G) { return G.nA * ((G.nB + 255) / 256); }
@@ -165,7 +229,7 @@ int build_geometry_into(const sp_geometry* g, int n_cu, GeomDev& G, AngleDev* ta
     G.pitchX = g->cols + 2 * PAD;
     G.pitchXT = g->rows + 2 * PAD;
     G.pitchB = g->n_bins + 2 * PAD;
-    const double margin = 1e-3 + 4e-7 * (double)(g->rows + g->cols + g->n_bins);
+    const double margin = bp_margin(G);
     G.nbmax = 1;
     for (int q = 0; q <= 4; ++q) G.cls[q] = 0;
     for (int a = 0; a < g->n_angles; ++a) {
@@ -186,7 +250,9 @@ int build_geometry_into(const sp_geometry* g, int n_cu, GeomDev& G, AngleDev* ta
     G.nwaves = project_wave_count(G);
     G.nwg = (G.nwaves + 3) / 4;
     G.parts = project_parts(g->rows, g->cols, G.nwaves, n_cu * 32);
-    G.bp_px = backproject_px(g->rows, g->cols, n_cu * 32);
+    G.bp_quad = bp_quad_table(G, tab, nullptr) ? 1 : 0;
+    G.bp_px = G.bp_quad ? 4 : backproject_px(g->rows, g->cols, n_cu * 32);
+    if (G.bp_quad) backproject_shape(G, n_cu * 32);
     return SP_OK;
 }
 

@@ -1,6 +1,8 @@
 // Device scratch of the allocation-free backprojection entry point
 // (sp_backproject_noalloc): one statically sized array per GPU, in place of
-// the buffers the context would allocate.  Its device address is looked up
+// the buffers the context would allocate (the angle table and the padded
+// sinogram share the first NOALLOC_SCRATCH_BYTES, the block constants of R^T
+// follow).  Its device address is looked up
 // once per device, with that device current; host code never passes the
 // array's own name to a kernel (on the host it only stands for the symbol).
 #include <mutex>
@@ -9,7 +11,7 @@
 
 namespace sp {
 
-static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES + NOALLOC_MAX_ANGLES * sizeof(BpAngle)];
 
 namespace {
 constexpr int MAX_DEVICES = 64;

@@ -48,6 +48,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 namespace sp {
@@ -648,26 +649,22 @@ __device__ __forceinline__ void bp_class(const GeomDev& G, const AngleDev* __res
     }
 }
 
-__device__ __forceinline__ void split_range(int beg, int end, int w, int& b, int& e) {
+// Share w of n of the range [beg, end).
+__device__ __forceinline__ void split_range(int beg, int end, int w, int n, int& b, int& e) {
     const int len = end - beg;
-    b = beg + (len * w) / BP_SPLIT;
-    e = beg + (len * (w + 1)) / BP_SPLIT;
+    b = beg + (len * w) / n;
+    e = beg + (len * (w + 1)) / n;
 }
 
-// out[i][j] = (R^T y)_{ij} from the padded sinogram yp; with dotv != nullptr
-// also the float64 partial sum of out * dotv per 8 x 16 sub-tile.  A
-// workgroup owns an 8 x 8PX pixel tile (PX pixels, 8 columns apart, per lane);
-// its wave w sums the w-th quarter of every angle class, and the four partial
-// sums are added in wave order through LDS.
+// out[i][j] = (R^T y)_{ij} from the padded sinogram yp.  A workgroup owns an
+// 8 x 8PX pixel tile (PX pixels, 8 columns apart, per lane); its wave w sums
+// the w-th quarter of every angle class, and the four partial sums are added
+// in wave order through LDS.
 template <int NB, class TY, int PX>
 __device__ __forceinline__ void backproject_body(const GeomDev& G, const AngleDev* __restrict__ ang,
                                                  const TY* __restrict__ yp,
-                                                 float* __restrict__ out,
-                                                 const double* __restrict__ dotv,
-                                                 double* __restrict__ partials, int bx, int by) {
-    constexpr int NS = PX / 2;   // 8 x 16 sub-tiles per tile
+                                                 float* __restrict__ out, int bx, int by) {
     __shared__ double part[BP_SPLIT][PX][64];
-    __shared__ double red[4 * NS];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = by * BP_TILE + (lane >> 3);
@@ -680,70 +677,271 @@ __device__ __forceinline__ void backproject_body(const GeomDev& G, const AngleDe
         xj[u] = (double)(j0 + 8 * u) - G.xoff;
     }
     int b, e;
-    split_range(G.cls[0], G.cls[2], w, b, e);   // oblique angles of both orientations
+    split_range(G.cls[0], G.cls[2], w, BP_SPLIT, b, e);   // oblique angles of both orientations
     bp_class<false, NB, TY, PX>(G, ang, b, e, yp, xj, yi, acc);
-    split_range(G.cls[2], G.cls[4], w, b, e);   // axis-parallel angles
+    split_range(G.cls[2], G.cls[4], w, BP_SPLIT, b, e);   // axis-parallel angles
     bp_class<true, NB, TY, PX>(G, ang, b, e, yp, xj, yi, acc);
 #pragma unroll
     for (int u = 0; u < PX; ++u) part[w][u][lane] = acc[u];
     __syncthreads();
-    double v[NS];
-#pragma unroll
-    for (int q = 0; q < NS; ++q) v[q] = 0.0;
     if (w == 0) {
 #pragma unroll
         for (int u = 0; u < PX; ++u) {
             const int j = j0 + 8 * u;
             const double tot =
                 ((part[0][u][lane] + part[1][u][lane]) + part[2][u][lane]) + part[3][u][lane];
-            const float val = (float)(tot * G.pixel);
-            if (i < G.rows && j < G.cols) {
-                out[(size_t)i * G.cols + j] = val;
-                if (dotv) v[u / 2] += (double)val * dotv[(size_t)i * G.cols + j];
+            if (i < G.rows && j < G.cols) out[(size_t)i * G.cols + j] = (float)(tot * G.pixel);
+        }
+    }
+}
+
+// ---- 2 x 2 pixel blocks --------------------------------------------------------
+// The oblique angles [beg, end) for the lane's NQ blocks of 2 x 2 pixels with
+// centres (xc[n], yc).  Bound: the float64 VALU (about 9 instructions per pixel
+// and angle).  A pixel at a time costs a window index and a gather each, and
+// the vector L1's access rate (16 or more accesses per gather whatever its
+// width) held R^T at 11 instructions and one gather per pixel.  At about unit
+// bin spacing a block's four footprints lie within three bins (bp_quad_table
+// checks it), so one index and one 12-byte gather (24 bytes in two from a
+// float64 sinogram) serve four pixels; only 10 of the 12 pixel-bin pairs can
+// meet, and half of those lie on a known side of the pixel's centre, where
+// the weight is one add with output clamp.  512^2 x 720 x 725, float64
+// residual: 0.106 -> 0.059 ms (189M pixel-angles, 3.2e12 per second); float32
+// sinogram with its padding pass 0.097 -> 0.070; 2048^2 x 2864: 5.3 -> 3.3 ms.
+// The accumulators are kept in the order A, B, C, D of BpAngle, which only
+// changes between runs of angles (the signs of cos and sin, and which is
+// larger); acc holds each block's pixels 2 r + c (row r, column c).  PX = 2:
+// the pixels with r + c even (diag 0; pixels 0 and 3) or odd (diag 1; pixels 1
+// and 2), which are A and D or B and C, with the same arithmetic.  One angle
+// per iteration with two blocks, or many waves of one, hides the scalar loads
+// of its constants; two angles per iteration ran out of scalar registers.
+template <class TY>
+struct QuadBins;
+template <>
+struct QuadBins<float> {
+    static __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int o, double (&v)[3]) {
+        typedef float f3v __attribute__((ext_vector_type(3)));
+        const f3v t = __builtin_bit_cast(f3v, __builtin_amdgcn_raw_buffer_load_b96(r, 4u * (unsigned)o, 0, 0));
+        v[0] = (double)t.x;
+        v[1] = (double)t.y;
+        v[2] = (double)t.z;
+    }
+};
+template <>
+struct QuadBins<double> {
+    static __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int o, double (&v)[3]) {
+        const unsigned off = 8u * (unsigned)o;
+        const d2v t = __builtin_bit_cast(d2v, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+        v[0] = t.x;
+        v[1] = t.y;
+        v[2] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off + 16u, 0, 0));
+    }
+};
+
+__device__ __forceinline__ void swap_acc(double& a, double& b) {
+    const double t = a;
+    a = b;
+    b = t;
+}
+
+template <class TY, int PX, int NQ>
+__device__ __forceinline__ void bp_quads(const GeomDev& G, const BpAngle* __restrict__ quad, int beg, int end,
+                                         const TY* __restrict__ yp, const double (&xc)[NQ], double yc, int diag,
+                                         double (&acc)[NQ][PX]) {
+    const int rowbytes = G.pitchB * (int)sizeof(TY);
+    for (int a = beg; a < end;) {
+        const int run = quad[a].run;
+        const int stop = min(end, run >> BP_CODE_BITS);
+        // to the corners' order (bp_quad_corner), and back after the run
+        const bool fx = run & BP_FLIP_X, fy = run & BP_FLIP_Y, vert = run & BP_VERT;
+        const int c0 = bp_quad_corner(run, diag);   // PX = 2: the first pixel's corner
+        const bool ad = c0 == 0 || c0 == 3, swap2 = c0 >= 2;
+        auto to_corners = [&](double (&v)[PX]) {
+            if constexpr (PX == 4) {
+                if (fx) swap_acc(v[0], v[1]), swap_acc(v[2], v[3]);
+                if (fy) swap_acc(v[0], v[2]), swap_acc(v[1], v[3]);
+                if (vert) swap_acc(v[1], v[2]);
+            } else {
+                if (swap2) swap_acc(v[0], v[1]);
             }
-        }
-    }
-    if (dotv) {
-        // partial of 8 x 16 sub-tile (by, NS bx + q) at by * gx16 + NS bx + q
-        block_sum_n<NS>(v, red);
-        const int gx16 = (G.cols + BP_TW - 1) / BP_TW;
-        if (threadIdx.x == 0) {
+        };
+        auto to_pixels = [&](double (&v)[PX]) {
+            if constexpr (PX == 4) {
+                if (vert) swap_acc(v[1], v[2]);
+                if (fy) swap_acc(v[0], v[2]), swap_acc(v[1], v[3]);
+                if (fx) swap_acc(v[0], v[1]), swap_acc(v[2], v[3]);
+            } else {
+                if (swap2) swap_acc(v[0], v[1]);
+            }
+        };
 #pragma unroll
-            for (int q = 0; q < NS; ++q)
-                if (NS * bx + q < gx16) partials[by * gx16 + NS * bx + q] = v[q];
-        }
+        for (int n = 0; n < NQ; ++n) to_corners(acc[n]);
+        auto angles = [&](auto first, auto second) {   // A and D / B and C
+#pragma unroll 1
+            for (int q = a; q < stop; ++q) {
+                const BpAngle Q = quad[q];
+                const __amdgpu_buffer_rsrc_t rs = row_rsrc(yp + (size_t)Q.row * G.pitchB, rowbytes);
+                double v[NQ][3], w[NQ];
+#pragma unroll
+                for (int n = 0; n < NQ; ++n) {
+                    const double kf = bp_quad_kf(xc[n], yc, Q);
+                    QuadBins<TY>::load(rs, (int)kf, v[n]);
+                    w[n] = bp_quad_w(__builtin_amdgcn_fract(kf), Q);
+                }
+#pragma unroll
+                for (int n = 0; n < NQ; ++n) {
+                    double u2[2], u3[3];
+                    double &aA = acc[n][0], &aB = acc[n][PX == 4 ? 1 : 0], &aC = acc[n][PX == 4 ? 2 : 1],
+                           &aD = acc[n][PX - 1];
+                    if constexpr (decltype(first)::value) {
+                        bp_quad_a(Q, w[n], u2);
+                        aA = fma(u2[0], v[n][0], aA);
+                        aA = fma(u2[1], v[n][1], aA);
+                        bp_quad_d(Q, w[n], u2);
+                        aD = fma(u2[0], v[n][1], aD);
+                        aD = fma(u2[1], v[n][2], aD);
+                    }
+                    if constexpr (decltype(second)::value) {
+                        bp_quad_b(Q, w[n], u3);
+                        aB = fma(u3[0], v[n][0], aB);
+                        aB = fma(u3[1], v[n][1], aB);
+                        aB = fma(u3[2], v[n][2], aB);
+                        bp_quad_c(Q, w[n], u3);
+                        aC = fma(u3[0], v[n][0], aC);
+                        aC = fma(u3[1], v[n][1], aC);
+                        aC = fma(u3[2], v[n][2], aC);
+                    }
+                }
+            }
+        };
+        if constexpr (PX == 4) angles(std::true_type{}, std::true_type{});
+        else if (ad) angles(std::true_type{}, std::false_type{});
+        else angles(std::false_type{}, std::true_type{});
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) to_pixels(acc[n]);
+        a = stop;
     }
+}
+
+// R^T over 2 x 2 blocks: a workgroup owns NQ 16 x 16 pixel tiles side by side
+// (tile `id` in the order of bp_tile_of; PX = 2: two workgroups per tile,
+// one per diagonal), lane l block (l / 8, l % 8) of each.  The angles are
+// split into G.bp_shares shares; wave w of the workgroup's NW sums shares w,
+// w + NW, ..., and the shares are added in order through LDS, so the result
+// does not depend on NW, NQ or PX.
+template <class TY, int PX, int NW, int NQ>
+__device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* __restrict__ ang,
+                                             const BpAngle* __restrict__ quad, const TY* __restrict__ yp,
+                                             float* __restrict__ out, int id) {
+    extern __shared__ double part[];   // [shares][NQ][PX][64]
+    const int gx = (G.cols + NQ * BPQ_TILE - 1) / (NQ * BPQ_TILE), gy = (G.rows + BPQ_TILE - 1) / BPQ_TILE;
+    const int diag = PX == 2 && id >= gx * gy ? 1 : 0;
+    int bx, by;
+    bp_tile_of(id - diag * gx * gy, gx, gy, bx, by);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i0 = by * BPQ_TILE + 2 * (lane >> 3), j0 = bx * NQ * BPQ_TILE + 2 * (lane & 7);
+    const double yc = G.yoff - ((double)i0 + 0.5);
+    double xc[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) xc[n] = (double)(j0 + n * BPQ_TILE) + 0.5 - G.xoff;
+    auto pixel = [&](int u) { return PX == 4 ? u : (diag ? 1 + u : 3 * u); };   // 2 r + c
+    const int shares = G.bp_shares;
+    for (int sh = wave; sh < shares; sh += NW) {
+        double acc[NQ][PX];
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+#pragma unroll
+            for (int u = 0; u < PX; ++u) acc[n][u] = 0.0;
+        int b, e;
+        split_range(G.cls[0], G.cls[2], sh, shares, b, e);   // oblique angles of both orientations
+        bp_quads<TY, PX, NQ>(G, quad, b, e, yp, xc, yc, diag, acc);
+        split_range(G.cls[2], G.cls[4], sh, shares, b, e);   // axis-parallel angles
+        if (b < e) {
+#pragma unroll
+            for (int n = 0; n < NQ; ++n)
+#pragma unroll
+                for (int u = 0; u < PX; ++u) {
+                    const int p = pixel(u);
+                    const double xj[1] = {xc[n] + ((p & 1) ? 0.5 : -0.5)};
+                    bp_class<true, 2, TY, 1>(G, ang, b, e, yp, xj, yc + ((p & 2) ? -0.5 : 0.5), &acc[n][u]);
+                }
+        }
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+#pragma unroll
+            for (int u = 0; u < PX; ++u) part[((sh * NQ + n) * PX + u) * 64 + lane] = acc[n][u];
+    }
+    __syncthreads();
+    for (int m = wave; m < NQ * PX; m += NW) {
+        const int n = m / PX, p = pixel(m % PX);
+        double tot = part[m * 64 + lane];
+        for (int sh = 1; sh < shares; ++sh) tot += part[(sh * NQ * PX + m) * 64 + lane];
+        const int i = i0 + (p >> 1), j = j0 + n * BPQ_TILE + (p & 1);
+        if (i < G.rows && j < G.cols) out[(size_t)i * G.cols + j] = (float)(tot * G.pixel);
+    }
+}
+
+size_t bp_quad_lds(int shares, int px, int nq) { return (size_t)shares * px * nq * 64 * sizeof(double); }
+
+__device__ __forceinline__ void run_ride(const ScalarRide& ride) {
+    if (ride.ps) scalar_body(OP_SNORM, ride.sc, ride.tr, ride.ps, ride.ns, nullptr, 0);
+    if (ride.pf) scalar_body(OP_F, ride.sc, ride.tr, ride.pf, ride.nf, nullptr, 0);
 }
 
 template <int NB, class TY, int PX>
 __global__ __launch_bounds__(256) void k_backproject(GeomDev G, const AngleDev* __restrict__ ang,
                                                      const TY* __restrict__ yp,
                                                      float* __restrict__ out,
-                                                     const double* __restrict__ dotv,
-                                                     double* __restrict__ partials,
                                                      ScalarRide ride,
                                                      const int* __restrict__ halt) {
     if (halt && *halt) return;
     int bx, by;
     bp_tile_of(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, bx, by);
-    backproject_body<NB, TY, PX>(G, ang, yp, out, dotv, partials, bx, by);
-    if (ride.sc && blockIdx.x == 0 && blockIdx.y == 0) {
-        if (ride.ps) scalar_body(OP_SNORM, ride.sc, ride.tr, ride.ps, ride.ns, nullptr, 0);
-        if (ride.pf) scalar_body(OP_F, ride.sc, ride.tr, ride.pf, ride.nf, nullptr, 0);
+    backproject_body<NB, TY, PX>(G, ang, yp, out, bx, by);
+    if (ride.sc && blockIdx.x == 0 && blockIdx.y == 0) run_ride(ride);
+}
+
+template <class TY, int PX, int NW, int NQ>
+__global__ __launch_bounds__(64 * NW) void k_backproject_quad(GeomDev G, const AngleDev* __restrict__ ang,
+                                                              const BpAngle* __restrict__ quad,
+                                                              const TY* __restrict__ yp,
+                                                              float* __restrict__ out, ScalarRide ride,
+                                                              const int* __restrict__ halt) {
+    if (halt && *halt) return;
+    bp_quad_body<TY, PX, NW, NQ>(G, ang, quad, yp, out, blockIdx.x);
+    if (ride.sc && blockIdx.x == 0) {
+        if (threadIdx.x >= 256) return;   // the scalar steps are those of a 256-thread workgroup
+        run_ride(ride);
     }
 }
 
 // g = R^T rpd from the float64 residual.  NB is the largest candidate count of
-// the batch (extra candidates weigh exactly 0).
+// the batch (extra candidates weigh exactly 0).  Each of this kernel and the
+// two of kb_backproject_quad sums the slices of its own form.
 template <int NB, int PX>
 __global__ __launch_bounds__(256) void kb_backproject(const SliceDev* __restrict__ sl, ItemTable t) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
-        if (gmem(S.sc)->halt) return;
+        if (S.G.bp_quad || gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         int bx, by;
         bp_tile_of(lin, (G.cols + 8 * PX - 1) / (8 * PX), (G.rows + BP_TILE - 1) / BP_TILE, bx, by);
-        backproject_body<NB, double, PX>(G, cmem(S.ang), gmem(S.rpd), gmem(S.g), nullptr, nullptr, bx, by);
+        backproject_body<NB, double, PX>(G, cmem(S.ang), gmem(S.rpd), gmem(S.g), bx, by);
+    });
+}
+
+// NW waves per workgroup, each summing every NW-th share: 8 for one tile per
+// wave (slices of 16 shares take two turns, so that their workgroups, of small
+// images, last about as long as those of 8 shares; with 4 waves the 16-slice
+// batch of 128^2 to 512^2 was 8% slower than pixel by pixel), 4 for two.
+template <int PX, int NW, int NQ>
+__global__ __launch_bounds__(64 * NW) void kb_backproject_quad(const SliceDev* __restrict__ sl, ItemTable t) {
+    for_items(t, [&](int s, int lin) {
+        const SliceDev& S = sl[s];
+        if (!S.G.bp_quad || S.G.bp_nq != NQ || gmem(S.sc)->halt) return;
+        const GeomDev G = S.G;
+        bp_quad_body<double, PX, NW, NQ>(G, cmem(S.ang), cmem(S.quad), gmem(S.rpd), gmem(S.g), lin);
     });
 }
 
@@ -757,35 +955,69 @@ void launch_bp_b_px(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax) 
     }
 }
 
-void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px) {
+template <int PX>
+void launch_bp_b_quads(hipStream_t st, const SliceDev* sl, ItemTable t, int forms) {
+    if (forms & BP_FORM_QUAD)
+        hipLaunchKernelGGL((kb_backproject_quad<PX, 8, 1>), dim3(t.grid), dim3(512),
+                           bp_quad_lds(BPQ_MAX_SHARES, PX, 1), st, sl, t);
+    if (forms & BP_FORM_QUAD2)
+        hipLaunchKernelGGL((kb_backproject_quad<PX, 4, 2>), dim3(t.grid), dim3(256), bp_quad_lds(4, PX, 2), st, sl,
+                           t);
+}
+
+void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms) {
+    if (px == 4) launch_bp_b_quads<4>(st, sl, t, forms);
+    else launch_bp_b_quads<2>(st, sl, t, forms);
+    if (!(forms & BP_FORM_PIXEL)) return;
     if (px == 4) launch_bp_b_px<4>(st, sl, t, nbmax);
     else launch_bp_b_px<2>(st, sl, t, nbmax);
 }
 
 template <class TY, int PX>
 void launch_bp_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const TY* yp, float* out,
-                  const double* dotv, double* partials, const int* halt, const ScalarRide& ride) {
+                  const int* halt, const ScalarRide& ride) {
     dim3 grid((G.cols + 8 * PX - 1) / (8 * PX), (G.rows + BP_TILE - 1) / BP_TILE);
     switch (G.nbmax) {
-    case 1: hipLaunchKernelGGL((k_backproject<1, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, dotv, partials, ride, halt); break;
-    case 2: hipLaunchKernelGGL((k_backproject<2, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, dotv, partials, ride, halt); break;
-    case 3: hipLaunchKernelGGL((k_backproject<3, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, dotv, partials, ride, halt); break;
-    default: hipLaunchKernelGGL((k_backproject<4, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, dotv, partials, ride, halt); break;
+    case 1: hipLaunchKernelGGL((k_backproject<1, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, ride, halt); break;
+    case 2: hipLaunchKernelGGL((k_backproject<2, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, ride, halt); break;
+    case 3: hipLaunchKernelGGL((k_backproject<3, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, ride, halt); break;
+    default: hipLaunchKernelGGL((k_backproject<4, TY, PX>), grid, dim3(256), 0, st, G, ang, yp, out, ride, halt); break;
     }
 }
 
-void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const float* yp,
-                        float* out, const double* dotv, double* partials, const int* halt,
-                        const ScalarRide& ride) {
-    if (G.bp_px == 4) launch_bp_px<float, 4>(st, G, ang, yp, out, dotv, partials, halt, ride);
-    else launch_bp_px<float, 2>(st, G, ang, yp, out, dotv, partials, halt, ride);
+template <class TY, int PX, int NW, int NQ>
+void launch_bp_quad(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
+                    float* out, const int* halt, const ScalarRide& ride) {
+    hipLaunchKernelGGL((k_backproject_quad<TY, PX, NW, NQ>), dim3(backproject_tiles(G, PX)), dim3(64 * NW),
+                       bp_quad_lds(G.bp_shares, PX, NQ), st, G, ang, quad, yp, out, ride, halt);
 }
 
-void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const double* yp,
-                        float* out, const double* dotv, double* partials, const int* halt,
-                        const ScalarRide& ride) {
-    if (G.bp_px == 4) launch_bp_px<double, 4>(st, G, ang, yp, out, dotv, partials, halt, ride);
-    else launch_bp_px<double, 2>(st, G, ang, yp, out, dotv, partials, halt, ride);
+// One wave per share (two tiles per wave go with 4 shares, see backproject_shape).
+template <class TY, int PX>
+void launch_bp_quad_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
+                       float* out, const int* halt, const ScalarRide& ride) {
+    if (G.bp_nq == 2) launch_bp_quad<TY, PX, 4, 2>(st, G, ang, quad, yp, out, halt, ride);
+    else if (G.bp_shares == 8) launch_bp_quad<TY, PX, 8, 1>(st, G, ang, quad, yp, out, halt, ride);
+    else launch_bp_quad<TY, PX, 16, 1>(st, G, ang, quad, yp, out, halt, ride);
+}
+
+template <class TY>
+void launch_bp(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
+               float* out, const int* halt, const ScalarRide& ride) {
+    if (G.bp_quad && G.bp_px == 4) launch_bp_quad_px<TY, 4>(st, G, ang, quad, yp, out, halt, ride);
+    else if (G.bp_quad) launch_bp_quad_px<TY, 2>(st, G, ang, quad, yp, out, halt, ride);
+    else if (G.bp_px == 4) launch_bp_px<TY, 4>(st, G, ang, yp, out, halt, ride);
+    else launch_bp_px<TY, 2>(st, G, ang, yp, out, halt, ride);
+}
+
+void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
+                        const float* yp, float* out, const int* halt, const ScalarRide& ride) {
+    launch_bp(st, G, ang, quad, yp, out, halt, ride);
+}
+
+void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
+                        const double* yp, float* out, const int* halt, const ScalarRide& ride) {
+    launch_bp(st, G, ang, quad, yp, out, halt, ride);
 }
 
 }  // namespace sp

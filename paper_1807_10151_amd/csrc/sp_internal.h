@@ -54,11 +54,42 @@ struct GeomDev {
     int nbmax;          // max backprojection candidates over the angles
     int parts;          // parts each ray's step range is split into by R (1: whole rays)
     int bp_px;          // pixels per lane of R^T (2 or 4, see backproject_px)
+    int bp_quad;        // 1: R^T sums oblique angles over 2 x 2 pixel blocks (see BpAngle)
+    int bp_shares;      // shares each angle range is split into by R^T's blocks (4, 8 or 16)
+    int bp_nq;          // 16 x 16 tiles side by side per wave of R^T's blocks (1 or 2)
     int cls[5];         // angle-table class boundaries: vertical, horizontal,
                         // vertical axis, horizontal axis
     int nwaves;         // waves of R's wave table (see WaveDev)
     int nwg;            // R's ray workgroups, four waves each: ceil(nwaves / 4)
 };
+
+// R^T's constants of one oblique angle for a 2 x 2 block of pixels (G.bp_quad),
+// whose four footprints on the detector lie within three bins.  With S =
+// |c| + |s| (a footprint's width), ds the bin spacing, K = ds inv, and the
+// block's pixels named by the projections of their centres on the normal:
+// A the smallest, B = A + min(|c|, |s|), C = A + max(|c|, |s|), D = A + S.
+// kf = fma(x, cids, fma(y, sids, kb)) of the block's centre (x, y) has the
+// first of the three bins as its truncated (padded) index, and w = fma(fract(kf),
+// nk, wc) is inv times that bin's offset from A's centre; a weight is the
+// trapezoid clamp(einv - |w + shift|, 0, 1) (chord_u), without the absolute
+// value where the sign of the offset is known.
+struct alignas(64) BpAngle {
+    double cids, sids, kb;
+    int32_t row;        // sinogram row
+    int32_t run;        // BP_CODE bits: which corner is A and whether B is beside or
+                        // below it; above them the end of the run of table
+                        // entries that share the code
+    double nk, wc;
+    double einv;        // |offset| = w: bin 0 of A, and with the shifts below
+    double eK;          // A, bin 1: clamp(eK - w)
+    double dD1, dD2;    // D, bins 1 and 2: shifts
+    double dB0, dB1;    // B, bins 0 and 1: shifts
+    double eB2;         // B, bin 2: clamp(eB2 - w)
+    double eC0;         // C, bin 0: clamp(eC0 + w)
+    double dC1;         // C, bin 1: shift
+    double eC2;         // C, bin 2: clamp(eC2 - w)
+};
+constexpr int BP_FLIP_X = 1, BP_FLIP_Y = 2, BP_VERT = 4, BP_CODE_BITS = 3;
 
 // One wave of R: 64 rays, one per lane, of one angle class.  Kinds (`tail`):
 //  WAVE_BLOCK: WAVE_ANGLES consecutive angles by WAVE_BINS consecutive bins:
@@ -191,19 +222,21 @@ void launch_project(hipStream_t st, const GeomDev& G, const AngleDev* ang, const
 // Padded copy of y for R^T with each row scaled by its angle's wmax.
 void launch_pad_sino(hipStream_t st, const GeomDev& G, const AngleDev* ang, const float* y,
                      float* yp);
-// ride: scalar steps workgroup (0, 0) runs after its tile (see ScalarRide).
-void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const float* yp,
-                        float* out, const double* dotv, double* partials, const int* halt,
+// quad: bp_quad_table's entries (with G.bp_quad).  ride: scalar steps
+// workgroup 0 runs after its tile (see ScalarRide).
+void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
+                        const float* yp, float* out, const int* halt,
                         const ScalarRide& ride = ScalarRide{});
-void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const double* yp,
-                        float* out, const double* dotv, double* partials, const int* halt,
+void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
+                        const double* yp, float* out, const int* halt,
                         const ScalarRide& ride = ScalarRide{});
 
 // R^T's workgroup: a tile of BP_TILE rows by 8 PX columns, BP_SPLIT waves each
-// over a share of the angles; dot-product partials per BP_TILE x BP_TW sub-tile.
+// over a share of the angles; with G.bp_quad BPQ_TILE rows by BPQ_TILE columns.
 constexpr int BP_TILE = 8;
-constexpr int BP_TW = 16;
 constexpr int BP_SPLIT = 4;
+constexpr int BPQ_TILE = 16;
+constexpr int BPQ_MAX_SHARES = 16;
 
 // ---- host geometry (geometry.cpp) ------------------------------------------------
 // cos/sin of angle index a, exact at multiples of pi/4.
@@ -244,10 +277,18 @@ int project_comb_blocks(const GeomDev& G);
 // Number of float64 f partials R's residual form writes: one per combine
 // workgroup when the rays are split in parts, else one per ray workgroup.
 int project_blocks(const GeomDev& G);
-// Number of R^T's float64 dot partials: one per 8 x 16 pixel sub-tile.
-// R^T workgroups (8 x 8 px pixel tiles) for px pixels per lane.
+// R^T workgroups for px pixels per lane: 8 x 8 px pixel tiles, or with G.bp_quad
+// 16 x 16 G.bp_nq pixel tiles of 2 x 2 blocks (px = 4: a lane sums its blocks
+// whole; px = 2: half of them, two workgroups per tile).
 int backproject_tiles(const GeomDev& G, int px);
-// Pixels per lane R^T uses for an image: 4 when that grid still fills half
+// R^T's block constants for the oblique angles tab[0 .. G.cls[2]) (out: that
+// many entries); false, with out incomplete, for geometries whose footprints
+// do not fit three bins as BpAngle assumes.  out may be NULL (check only).
+bool bp_quad_table(const GeomDev& G, const AngleDev* tab, BpAngle* out);
+// Sets R^T's block shape: bp_shares and bp_nq, from the image size (the sums
+// depend on the shares, so single and batched solves take the same).
+void backproject_shape(GeomDev& G, int resident_waves);
+// Pixels per lane of R^T without G.bp_quad: 4 when that grid still fills half
 // the device's wave slots, else 2.  The result does not depend on it.
 int backproject_px(int rows, int cols, int resident_waves);
 
@@ -435,6 +476,7 @@ struct SliceDev {
     GeomDev G;
     FFTPlan F;
     const AngleDev* ang;
+    const BpAngle* quad;    // R^T's block constants (G.bp_quad)
     const WaveDev* pwave;   // R's wave table
     const float* b;
     const float* x0;   // nullable: zero start
@@ -498,8 +540,11 @@ void launch_prep_b(hipStream_t st, const SliceDev* sl, ItemTable t, int which);
 // residual: rpd = R xh - b with the f partials in pf; else w = R z (from the
 // prepared z) with the (R z)^T q partials in pf.
 void launch_project_b(hipStream_t st, const SliceDev* sl, ItemTable t, ItemTable tc, bool residual);
-// px: pixels per lane of every slice in the launch (their G.bp_px).
-void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px);
+// px: pixels per lane of every slice in the launch (their G.bp_px); forms: the
+// forms of R^T among the slices (bp_form).
+enum BpForm : int { BP_FORM_PIXEL = 1, BP_FORM_QUAD = 2, BP_FORM_QUAD2 = 4 };
+inline int bp_form(const GeomDev& G) { return !G.bp_quad ? BP_FORM_PIXEL : (G.bp_nq == 2 ? BP_FORM_QUAD2 : BP_FORM_QUAD); }
+void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms);
 // fft.hip (z = M g)
 void launch_precond_b(hipStream_t st, const SliceDev* sl, ItemTable rows, ItemTable cols,
                       size_t lds_rows, size_t lds_cols, double mu, double rho);

@@ -103,6 +103,41 @@ __host__ __device__ inline double bp_kf_oblique(double xj, double kc, const Angl
     return fma(xj, A.cids, kc);
 }
 
+// R^T over 2 x 2 blocks (see BpAngle): the window index of the block with
+// centre (xc, yc), the scaled offset w of the window's first bin from pixel
+// A's centre, and the weights of each pixel's bins in the three-bin window.
+__host__ __device__ inline double bp_quad_kf(double xc, double yc, const BpAngle& Q) {
+    return fma(xc, Q.cids, fma(yc, Q.sids, Q.kb));
+}
+__host__ __device__ inline double bp_quad_w(double fract_kf, const BpAngle& Q) {
+    return fma(fract_kf, Q.nk, Q.wc);
+}
+__host__ __device__ inline double clamp01(double v) { return fmin(fmax(v, 0.0), 1.0); }
+__host__ __device__ inline void bp_quad_a(const BpAngle& Q, double w, double (&u)[2]) {   // bins 0, 1
+    u[0] = clamp01(Q.einv - fabs(w));
+    u[1] = clamp01(Q.eK - w);
+}
+__host__ __device__ inline void bp_quad_b(const BpAngle& Q, double w, double (&u)[3]) {
+    u[0] = clamp01(Q.einv - fabs(w + Q.dB0));
+    u[1] = clamp01(Q.einv - fabs(w + Q.dB1));
+    u[2] = clamp01(Q.eB2 - w);
+}
+__host__ __device__ inline void bp_quad_c(const BpAngle& Q, double w, double (&u)[3]) {
+    u[0] = clamp01(Q.eC0 + w);
+    u[1] = clamp01(Q.einv - fabs(w + Q.dC1));
+    u[2] = clamp01(Q.eC2 - w);
+}
+__host__ __device__ inline void bp_quad_d(const BpAngle& Q, double w, double (&u)[2]) {   // bins 1, 2
+    u[0] = clamp01(Q.einv - fabs(w + Q.dD1));
+    u[1] = clamp01(Q.einv - fabs(w + Q.dD2));
+}
+// Corner (A 0, B 1, C 2, D 3) of the block's pixel p = 2 r + c (row r, column c).
+__host__ __device__ inline int bp_quad_corner(int run, int p) {
+    const int n = p ^ (run & (BP_FLIP_X | BP_FLIP_Y));   // bit 0: towards larger t along x, bit 1: along y
+    const bool vert = run & BP_VERT;                     // |c| >= |s|: B is the neighbour along y
+    return n == 0 || n == 3 ? n : ((n == 2) == vert ? 1 : 2);
+}
+
 // Tile (bx, by) of R^T's gx x gy tile grid that launch-order workgroup `id`
 // takes.  Workgroups go to the 8 XCDs round-robin in launch order (id mod 8);
 // when the grid splits into 4 x 2 equal regions, XCD q takes region
