@@ -38,7 +38,8 @@
  *    by the cancellation in R^T r, is what moves a float32 iterate away from
  *    the float64 one); so are R z and R p, through which the solvers take
  *    Algorithm 2's h = A p (z^T h = (R z)^T (R p), p^T h = ||R p||^2; h itself
- *    is never formed).  The gradient g, M g and the TV direction are float32.
+ *    is never formed), and with the Fourier M the gradient g and M g.  The TV
+ *    direction is float32, and so are g and M g with M = I or a learned M.
  *    Images passed in and out are float32.
  */
 #ifndef SUPPCG_H
@@ -440,9 +441,10 @@ int sp_blobart_solve(sp_ctx* ctx, const sp_geometry* g, const float* b, double r
  * equal (a batch takes 4 pixels per lane for all slices only if all of them
  * agree on it).  Updating the table between the two halves of a resumed run
  * changes R's rounding between them.
- * sp_tune_shapes: times sp_project for each part count (with the default
- * pixels per lane) and then sp_backproject for 2 and 4 pixels per lane on the
- * context's stream, keeps the fastest (the default wins ties within 2%), and
+ * sp_tune_shapes: times sp_project (and, where a float32 image takes another
+ * form of R than the solvers' float64 vectors, that form too: their mean) for
+ * each part count (with the default pixels per lane) and then sp_backproject
+ * for 2 and 4 pixels per lane on the context's stream, keeps the fastest (the default wins ties within 2%), and
  * stores it; ms (HOST double[6], nullable) receives the best-of-5 times of R
  * at 1, 2, 4, 8 parts and of R^T at 2, 4 pixels per lane.  Synchronises.
  * sp_tuning_set: stores a choice (parts 1..8, px 2 or 4; both 0 erases the

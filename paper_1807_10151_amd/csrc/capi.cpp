@@ -59,7 +59,7 @@ struct sp_ctx {
     sp_geometry geom{};
     GeomDev G{};
     std::vector<AngleDev> ang_h;
-    DevBuf ang, quad, pwave, xp, xTp, yp, ypd, seg, pord, blob_tab;
+    DevBuf ang, quad, pwave, fwave, ford, xp, xTp, zp, zTp, yp, ypd, seg, pord, blob_tab;
 
     // preconditioner cache
     int fftP = 0;
@@ -70,10 +70,11 @@ struct sp_ctx {
     // resume); the standalone operators use ox, oxh and oscal instead.
     DevBuf vx, vxh, vp;                   // float64 x_k, x_{k+1/2}, p
     DevBuf vq, vw;                        // float64 q = R p and w = R z (nA x nB)
-    DevBuf vg, vz, vtb, vtmp;
+    DevBuf vg, vz, vtb;                   // float64 g and z = M g; float32 t_bar
+    DevBuf vgf, vzf;                      // float32 g and z of a learned M
     DevBuf vtb2, stv_y;                   // S_TV ping-pong: second t_bar (float), iterate (float64)
     DevBuf ox, oxh, oscal;                // sp_tv, sp_tv_grad, sp_tv_perturb
-    DevBuf part_f, part_zh, part_gp, part_qq, part_g, part_t, part_s, part_misc, part_se;
+    DevBuf part_f, part_gp, part_qq, part_g, part_t, part_s, part_misc, part_se;
     DevBuf stored_xT;                     // transposed image for the stored R product
     DevBuf art_u, art_nrm, art_sum;       // ART: auxiliary vector, ||R_i||^2, sum of b
     DevBuf scal, trace_d, replay_d, trials_tmp;
@@ -261,7 +262,7 @@ int build_geometry_into(sp_ctx* c, const sp_geometry* g, GeomDev& G, AngleDev* t
     if (rc) return fail(c, rc, "%s", msg);
     int parts, px;
     if (shape_lookup(*g, parts, px)) {
-        G.parts = parts;
+        G.parts = G.fparts = parts;
         G.bp_px = px;
     }
     return SP_OK;
@@ -286,16 +287,19 @@ int setup_geometry(sp_ctx* c, const sp_geometry* g) {
     if ((rc = ensure(c, c->ang, tab.size() * sizeof(AngleDev)))) return rc;
     const bool relayout = !c->have_geom || c->G.pitchX != G.pitchX || c->G.pitchXT != G.pitchXT ||
                           c->G.pitchB != G.pitchB || c->G.rows != G.rows || c->G.cols != G.cols ||
-                          c->G.nA != G.nA;
+                          c->G.nA != G.nA || c->G.pair != G.pair;
     if ((rc = ensure(c, c->xp, nX * 8))) return rc;
     if ((rc = ensure(c, c->xTp, nXT * 8))) return rc;
+    if (G.pair && ((rc = ensure(c, c->zp, nX * 4)) || (rc = ensure(c, c->zTp, nXT * 4)))) return rc;
     if ((rc = ensure(c, c->yp, nY * 4))) return rc;
     if ((rc = ensure(c, c->ypd, nY * 8))) return rc;
-    if (G.parts > 1 && (rc = ensure(c, c->seg, (size_t)G.parts * g->n_angles * g->n_bins * 8)))
-        return rc;
+    const int segs = std::max(G.parts, G.pair ? G.fparts : 1);
+    if (segs > WG_PARTS && (rc = ensure(c, c->seg, (size_t)segs * g->n_angles * g->n_bins * 8))) return rc;
     if (relayout) {
         HIP_TRY(c, hipMemsetAsync(c->xp.ptr, 0, c->xp.bytes, c->stream));
         HIP_TRY(c, hipMemsetAsync(c->xTp.ptr, 0, c->xTp.bytes, c->stream));
+        for (DevBuf* b : {&c->zp, &c->zTp})
+            if (b->ptr) HIP_TRY(c, hipMemsetAsync(b->ptr, 0, b->bytes, c->stream));
         HIP_TRY(c, hipMemsetAsync(c->yp.ptr, 0, c->yp.bytes, c->stream));
         HIP_TRY(c, hipMemsetAsync(c->ypd.ptr, 0, c->ypd.bytes, c->stream));
     }
@@ -315,10 +319,23 @@ int setup_geometry(sp_ctx* c, const sp_geometry* g) {
         HIP_TRY(c, hipMemcpyAsync(c->quad.ptr, quad.data(), quad.size() * sizeof(BpAngle),
                                   hipMemcpyHostToDevice, c->stream));
     }
-    const std::vector<int32_t> ord = project_order(G, tab.data(), waves.data(), c->n_cu);
+    const std::vector<int32_t> ord = project_order(G, tab.data(), waves.data(), G.nwaves, c->n_cu);
     if ((rc = ensure(c, c->pord, ord.size() * sizeof(int32_t)))) return rc;
     HIP_TRY(c, hipMemcpyAsync(c->pord.ptr, ord.data(), ord.size() * sizeof(int32_t),
                               hipMemcpyHostToDevice, c->stream));
+    std::vector<WaveDev> fwaves;
+    std::vector<int32_t> ford;
+    if (G.pair) {
+        fwaves.resize((size_t)G.fwaves);
+        project_pair_waves(G, fwaves.data());
+        ford = project_order(G, tab.data(), fwaves.data(), G.fwaves, c->n_cu);
+        if ((rc = ensure(c, c->fwave, fwaves.size() * sizeof(WaveDev)))) return rc;
+        if ((rc = ensure(c, c->ford, ford.size() * sizeof(int32_t)))) return rc;
+        HIP_TRY(c, hipMemcpyAsync(c->fwave.ptr, fwaves.data(), fwaves.size() * sizeof(WaveDev),
+                                  hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->ford.ptr, ford.data(), ford.size() * sizeof(int32_t),
+                                  hipMemcpyHostToDevice, c->stream));
+    }
     HIP_TRY(c, hipStreamSynchronize(c->stream));  // host tables must outlive the copies
     c->G = G;
     c->geom = *g;
@@ -403,9 +420,9 @@ int check_tv(sp_ctx* c, const sp_tv_params* p) {
 int ensure_vectors(sp_ctx* c, size_t n) {
     int rc;
     const size_t m = (size_t)c->G.nA * c->G.nB;
-    for (DevBuf* b : {&c->vg, &c->vz, &c->vtb, &c->vtb2, &c->vtmp})
+    for (DevBuf* b : {&c->vgf, &c->vzf, &c->vtb, &c->vtb2})
         if ((rc = ensure(c, *b, n * sizeof(float)))) return rc;
-    for (DevBuf* b : {&c->vx, &c->vxh, &c->vp, &c->stv_y})
+    for (DevBuf* b : {&c->vx, &c->vxh, &c->vp, &c->vg, &c->vz, &c->stv_y})
         if ((rc = ensure(c, *b, n * sizeof(double)))) return rc;
     for (DevBuf* b : {&c->vq, &c->vw})
         if ((rc = ensure(c, *b, m * sizeof(double)))) return rc;
@@ -416,9 +433,8 @@ int ensure_partials(sp_ctx* c) {
     const GeomDev& G = c->G;
     const int n = G.rows * G.cols;
     int rc;
-    if ((rc = ensure(c, c->part_f, (size_t)project_blocks(G) * 8))) return rc;
+    if ((rc = ensure(c, c->part_f, (size_t)std::max(project_blocks(G), G.pair ? project32_blocks(G) : 0) * 8))) return rc;
     if ((rc = ensure(c, c->part_qq, (size_t)vec_blocks(G.nA * G.nB) * 8))) return rc;
-    if ((rc = ensure(c, c->part_zh, (size_t)std::max((G.rows + 1) / 2, vec_blocks(n)) * 8))) return rc;
     if ((rc = ensure(c, c->part_gp, (size_t)vec_blocks(n) * 8))) return rc;
     if ((rc = ensure(c, c->part_g, (size_t)tv_blocks(G.rows, G.cols) * 8))) return rc;
     if ((rc = ensure(c, c->part_t, (size_t)tv_blocks(G.rows, G.cols) * 9 * 8))) return rc;
@@ -608,55 +624,68 @@ int lp_enqueue_apply(sp_ctx* c, sp_learned* net, int B, int H, int W, const floa
     return SP_OK;
 }
 
-// z = M g (partial dots z^T dotv when dotv != NULL).  In the solver
-// (solver = true) every launch honours the halt flag, and a learned M is
-// checked (g^T z > 0 and finite) with the Fourier M as fallback.  With xp,
-// R's padded copies of z (xp, xTp) are written too: by the Fourier M's last
-// kernel, else by a prep launch.
-int enqueue_precond(sp_ctx* c, const sp_precond* pc, const float* g, float* z, const float* dotv,
-                    double* partials, int& nparts, bool solver, double* xp = nullptr,
-                    double* xTp = nullptr) {
+// R's padded copies of a float32 image: float32 ones where the two-ray form
+// takes them, else float64.
+void prep_image(sp_ctx* c, const float* x) {
+    if (c->G.pair) launch_prep32(c->stream, c->G, x, dptr<float>(c->zp), dptr<float>(c->zTp), nullptr);
+    else launch_prep(c->stream, c->G, x, dptr<double>(c->xp), dptr<double>(c->xTp), nullptr);
+}
+// R of the float32 image prepared by prep_image; o.partials is set here.
+// Returns the number of partials.
+int project_image(sp_ctx* c, RayOut o) {
+    const GeomDev& G = c->G;
+    o.partials = dptr<double>(c->part_f);
+    if (G.pair) {
+        launch_project32(c->stream, G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->fwave), dptr<float>(c->zp),
+                         dptr<float>(c->zTp), o, dptr<double>(c->seg), dptr<int>(c->ford), nullptr);
+        return project32_blocks(G);
+    }
+    launch_project(c->stream, G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->pwave), dptr<double>(c->xp),
+                   dptr<double>(c->xTp), o, dptr<double>(c->seg), dptr<int>(c->pord), nullptr);
+    return project_blocks(G);
+}
+
+// g is a float64 vector; its values are rounded to float32 where M passes them
+// on as they are (M = I) or works in float32 itself (learned).  The Fourier M
+// transforms in float64 and takes and gives unrounded values.
+bool gradient_is_f32(const sp_precond* pc) { return pc->kind != SP_PRECOND_RAMP; }
+
+// The solver's z = M g in float64 and R's padded copies of it (written by the
+// Fourier M's last kernel, else by a prep launch); every launch honours the halt
+// flag.  A learned M works in float32 and is checked (g^T z > 0 and finite)
+// with the Fourier M as fallback.
+int enqueue_solver_precond(sp_ctx* c, const sp_precond* pc, const double* g, double* z) {
     const GeomDev& G = c->G;
     const int n = G.rows * G.cols;
     Scalars* sc = dptr<Scalars>(c->scal);
-    const int* halt = solver ? &sc->halt : nullptr;
+    const int* halt = &sc->halt;
+    double *xp = dptr<double>(c->xp), *xTp = dptr<double>(c->xTp);
     if (pc->kind == SP_PRECOND_NONE) {
-        if (g != z) launch_copy(c->stream, n, g, z, halt);
-        if (dotv) launch_dot(c->stream, n, z, dotv, partials, halt);
-        if (xp) launch_prep(c->stream, G, z, xp, xTp, halt);
-        nparts = vec_blocks(n);
+        launch_copy(c->stream, n, g, z, halt);
+        launch_prep(c->stream, G, z, xp, xTp, halt);
         return SP_OK;
     }
     FFTPlan F{};
     int rc = setup_fft(c, F);
     if (rc) return rc;
+    ProfScope ps(c, SP_PROF_PRECOND);
     if (pc->kind == SP_PRECOND_LEARNED) {
         sp_learned* net = const_cast<sp_learned*>(pc->net);
-        ProfScope ps(c, SP_PROF_PRECOND);
-        if ((rc = lp_enqueue_apply(c, net, 1, G.rows, G.cols, g, z, halt,
-                                   solver ? &sc->gate_learned : nullptr)))
-            return rc;
-        if (solver) {
-            double* pg = dptr<double>(c->part_misc);
-            launch_dot(c->stream, n, g, z, pg, halt);
-            TraceDev none{};
-            launch_scalar(c->stream, OP_LCHECK, sc, none, pg, vec_blocks(n), nullptr, 0);
-            launch_precond(c->stream, F, pc->mu, pc->rho, g, z, nullptr, nullptr, halt, &sc->gate_ramp);
-        }
-        if (dotv) launch_dot(c->stream, n, z, dotv, partials, halt);
-        if (xp) launch_prep(c->stream, G, z, xp, xTp, halt);
-        nparts = vec_blocks(n);
+        float *gf = dptr<float>(c->vgf), *zf = dptr<float>(c->vzf);
+        launch_narrow(c->stream, n, g, gf, halt);
+        if ((rc = lp_enqueue_apply(c, net, 1, G.rows, G.cols, gf, zf, halt, &sc->gate_learned))) return rc;
+        double* pg = dptr<double>(c->part_misc);
+        launch_dot(c->stream, n, gf, zf, pg, halt);
+        TraceDev none{};
+        launch_scalar(c->stream, OP_LCHECK, sc, none, pg, vec_blocks(n), nullptr, 0);
+        launch_widen(c->stream, n, zf, z, halt, &sc->gate_learned);
+        launch_precond(c->stream, F, pc->mu, pc->rho, nullptr, nullptr, g, z, halt, &sc->gate_ramp);
+        launch_prep(c->stream, G, z, xp, xTp, halt);
         return SP_OK;
     }
-    {
-        ProfScope ps(c, SP_PROF_PRECOND);
-        launch_precond(c->stream, F, pc->mu, pc->rho, g, z, dotv, partials, halt, nullptr, xp ? &G : nullptr,
-                       xp, xTp);
-    }
-    nparts = precond_dot_blocks(F);
+    launch_precond(c->stream, F, pc->mu, pc->rho, nullptr, nullptr, g, z, halt, nullptr, &G, xp, xTp);
     return SP_OK;
 }
-
 
 // ---- batched solve -----------------------------------------------------------
 
@@ -670,8 +699,8 @@ int stage_blocks(const SliceDev& S, int stage) {
     const GeomDev& G = S.G;
     switch (stage) {
     case BS_PREP: return ((G.cols + 31) / 32) * ((G.rows + 31) / 32);
-    case BS_PROJECT: return G.nwg * G.parts;
-    case BS_PROJ_COMB: return G.parts > 1 ? project_comb_blocks(G) : 0;
+    case BS_PROJECT: return G.nwg * (G.parts > WG_PARTS ? G.parts : 1);
+    case BS_PROJ_COMB: return G.parts > WG_PARTS ? project_comb_blocks(G) : 0;
     case BS_BACKPROJECT: return backproject_tiles(G, G.bp_px);
     case BS_ROWS: return (G.rows + 1) / 2;
     case BS_COLS: return S.F.P ? (S.F.SP + S.F.CB - 1) / S.F.CB : 0;
@@ -688,7 +717,7 @@ int stage_blocks(const SliceDev& S, int stage) {
 double item_cost(const SliceDev& S, int stage) {
     const GeomDev& G = S.G;
     switch (stage) {
-    case BS_PROJECT: return (double)std::max(G.rows, G.cols) / G.parts;
+    case BS_PROJECT: return (double)std::max(G.rows, G.cols) / (G.parts > WG_PARTS ? G.parts : 1);
     case BS_PROJ_COMB: return (double)G.parts;
     case BS_BACKPROJECT: return (double)G.nA;
     case BS_ROWS:
@@ -811,9 +840,9 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         o.xp = take((size_t)G.rows * G.pitchX * 8);
         o.xTp = take((size_t)G.cols * G.pitchXT * 8);
         o.rpd = take((size_t)G.nA * G.pitchB * 8);
-        o.seg = take(G.parts > 1 ? (size_t)G.parts * G.nA * G.nB * 8 : 0);
-        o.dvec = take((size_t)S.n * 8 * 3);  // x, x_half, p (float64)
-        o.vec = take((size_t)S.n * 4 * 3);   // g, z, t_bar
+        o.seg = take(G.parts > WG_PARTS ? (size_t)G.parts * G.nA * G.nB * 8 : 0);
+        o.dvec = take((size_t)S.n * 8 * 5);  // x, x_half, p, g, z (float64)
+        o.vec = take((size_t)S.n * 4);       // t_bar
         o.sq = take((size_t)S.m * 8 * 2);    // q = R p, w = R z
         o.S = kind == SP_PRECOND_RAMP ? take((size_t)G.rows * S.F.SP * sizeof(double2)) : 0;
         o.tw = kind == SP_PRECOND_RAMP ? take((size_t)(S.F.P / 2) * sizeof(double2)) : 0;
@@ -872,7 +901,7 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         S.pwave = reinterpret_cast<const WaveDev*>(base + o.pwave);
         HIP_TRY(c, hipMemcpyAsync(base + o.pwave, waves.data(), waves.size() * sizeof(WaveDev),
                                   hipMemcpyHostToDevice, c->stream));
-        const std::vector<int32_t> ord = project_order(S.G, tabs[s].data(), waves.data(), c->n_cu);
+        const std::vector<int32_t> ord = project_order(S.G, tabs[s].data(), waves.data(), S.G.nwaves, c->n_cu);
         S.pord = reinterpret_cast<const int*>(base + o.pord);
         HIP_TRY(c, hipMemcpyAsync(base + o.pord, ord.data(), ord.size() * sizeof(int32_t),
                                   hipMemcpyHostToDevice, c->stream));
@@ -880,15 +909,15 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         S.xp = reinterpret_cast<double*>(base + o.xp);
         S.xTp = reinterpret_cast<double*>(base + o.xTp);
         S.rpd = reinterpret_cast<double*>(base + o.rpd);
-        S.seg = S.G.parts > 1 ? reinterpret_cast<double*>(base + o.seg) : nullptr;
+        S.seg = S.G.parts > WG_PARTS ? reinterpret_cast<double*>(base + o.seg) : nullptr;
         double* dv = reinterpret_cast<double*>(base + o.dvec);
         S.x = dv;
         S.xh = dv + (size_t)S.n;
         S.p = dv + 2 * (size_t)S.n;
         float* v = reinterpret_cast<float*>(base + o.vec);
-        S.g = v;
-        S.z = v + (size_t)S.n;
-        S.tb = v + 2 * (size_t)S.n;
+        S.g = dv + 3 * (size_t)S.n;
+        S.z = dv + 4 * (size_t)S.n;
+        S.tb = v;
         S.q = reinterpret_cast<double*>(base + o.sq);
         S.w = S.q + (size_t)S.m;
         if (kind == SP_PRECOND_RAMP) {
@@ -950,7 +979,7 @@ void batch_stage(sp_ctx* c, int stage, int order, int wpc, double mu, double rho
     switch (stage) {
     case BS_PREP: launch_prep_b(st, sl, t, BV_XH); break;
     case BS_PROJECT: launch_project_b(st, sl, t, table(c, BS_PROJ_COMB, order, 0), true); break;
-    case BS_BACKPROJECT: launch_backproject_b(st, sl, t, B.nbmax, B.bp_px, B.bp_forms); break;
+    case BS_BACKPROJECT: launch_backproject_b(st, sl, t, B.nbmax, B.bp_px, B.bp_forms, false); break;
     case BS_ROWS:
         launch_precond_b(st, sl, t, table(c, BS_COLS, order, wpc), B.lds_rows, B.lds_cols, mu, rho);
         break;
@@ -1056,8 +1085,8 @@ int sp_ctx_destroy(sp_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     (void)drain_pending(c);
-    for (DevBuf* b : {&c->ang, &c->quad, &c->pwave, &c->xp, &c->xTp, &c->yp, &c->ypd, &c->seg, &c->pord, &c->blob_tab, &c->tw, &c->S, &c->vx, &c->vxh, &c->vp, &c->vq, &c->vw, &c->ox, &c->oxh, &c->oscal,
-                      &c->vg, &c->vz, &c->vtb, &c->vtb2, &c->stv_y, &c->vtmp, &c->part_f, &c->part_zh, &c->part_gp,
+    for (DevBuf* b : {&c->ang, &c->quad, &c->pwave, &c->fwave, &c->ford, &c->xp, &c->xTp, &c->zp, &c->zTp, &c->yp, &c->ypd, &c->seg, &c->pord, &c->blob_tab, &c->tw, &c->S, &c->vx, &c->vxh, &c->vp, &c->vq, &c->vw, &c->ox, &c->oxh, &c->oscal,
+                      &c->vg, &c->vgf, &c->vzf, &c->vz, &c->vtb, &c->vtb2, &c->stv_y, &c->part_f, &c->part_gp,
                       &c->part_qq, &c->part_g, &c->part_t, &c->part_s, &c->part_misc, &c->part_se, &c->stored_xT, &c->art_u, &c->art_nrm, &c->art_sum, &c->scal,
                       &c->trace_d, &c->replay_d, &c->trials_tmp})
         release(*b);
@@ -1277,14 +1306,12 @@ int sp_project(sp_ctx* c, const sp_geometry* g, const float* x, float* y) {
     HIP_TRY(c, hipSetDevice(c->device));
     int rc = setup_geometry(c, g);
     if (rc) return rc;
-    const GeomDev& G = c->G;
-    launch_prep(c->stream, G, x, dptr<double>(c->xp), dptr<double>(c->xTp), nullptr);
+    prep_image(c, x);
     {
         ProfScope ps(c, SP_PROF_PROJECT);
-        launch_project(c->stream, G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->pwave),
-                       dptr<double>(c->xp), dptr<double>(c->xTp),
-                       nullptr, y, G.nB, nullptr, nullptr, nullptr, dptr<double>(c->seg),
-                       dptr<int>(c->pord), nullptr);
+        RayOut o;
+        o.out = y;
+        project_image(c, o);
     }
     return check_launch(c);
 }
@@ -1381,6 +1408,12 @@ int sp_tune_shapes(sp_ctx* c, const sp_geometry* g, int32_t* parts_out, int32_t*
             const int q = back ? sp_backproject(c, g, dptr<float>(yb), dptr<float>(xb))
                                : sp_project(c, g, dptr<float>(xb), dptr<float>(yb));
             if (q) return q;
+            if (!back && c->G.pair) {   // a loop body's other R: the float64 iterate, ray by ray
+                RayOut o;
+                o.out = dptr<float>(yb);
+                launch_project(c->stream, c->G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->pwave), dptr<double>(c->xp),
+                               dptr<double>(c->xTp), o, dptr<double>(c->seg), dptr<int>(c->pord), nullptr);
+            }
             (void)hipEventRecord(e1, c->stream);
             if (hipEventSynchronize(e1) != hipSuccess) return fail(c, SP_ERR_HIP, "timing the launch shapes failed");
             float t = 0.0f;
@@ -1396,6 +1429,7 @@ int sp_tune_shapes(sp_ctx* c, const sp_geometry* g, int32_t* parts_out, int32_t*
     for (int i = 0; i < 4 && !rc; ++i) {
         shape_store(*g, parts_c[i], def_px);
         rc = time_call(false, tr[i]);
+        if (c->G.pair) tr[i] *= 0.5f;   // the mean of the two forms
     }
     if (!rc) {
         // the default wins ties within 2%
@@ -1474,13 +1508,12 @@ int sp_residual(sp_ctx* c, const sp_geometry* g, const float* x, const float* b,
     int rc = setup_geometry(c, g);
     if (rc) return rc;
     if ((rc = ensure_partials(c))) return rc;
-    const GeomDev& G = c->G;
-    launch_prep(c->stream, G, x, dptr<double>(c->xp), dptr<double>(c->xTp), nullptr);
-    launch_project(c->stream, G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->pwave), dptr<double>(c->xp),
-                   dptr<double>(c->xTp), b, r,
-                   G.nB, nullptr, nullptr, dptr<double>(c->part_f), dptr<double>(c->seg),
-                   dptr<int>(c->pord), nullptr);
-    launch_reduce(c->stream, dptr<double>(c->part_f), project_blocks(G), f);
+    prep_image(c, x);
+    RayOut o;
+    o.b = b;
+    o.out = r;
+    const int np = project_image(c, o);
+    launch_reduce(c->stream, dptr<double>(c->part_f), np, f);
     return check_launch(c);
 }
 
@@ -1494,14 +1527,14 @@ int sp_gradient(sp_ctx* c, const sp_geometry* g, const float* x, const float* b,
     if ((rc = ensure_partials(c))) return rc;
     const GeomDev& G = c->G;
     // the solvers' path: the residual stays float64 between R and R^T
-    launch_prep(c->stream, G, x, dptr<double>(c->xp), dptr<double>(c->xTp), nullptr);
-    launch_project(c->stream, G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->pwave), dptr<double>(c->xp),
-                   dptr<double>(c->xTp), b,
-                   nullptr, 0, nullptr, dptr<double>(c->ypd), dptr<double>(c->part_f),
-                   dptr<double>(c->seg), dptr<int>(c->pord), nullptr);
+    prep_image(c, x);
+    RayOut o;
+    o.b = b;
+    o.outpd = dptr<double>(c->ypd);
+    const int np = project_image(c, o);
     launch_backproject(c->stream, G, dptr<AngleDev>(c->ang), dptr<BpAngle>(c->quad), dptr<double>(c->ypd),
-                       grad, nullptr);
-    if (f) launch_reduce(c->stream, dptr<double>(c->part_f), project_blocks(G), f);
+                       grad, nullptr, false, nullptr);
+    if (f) launch_reduce(c->stream, dptr<double>(c->part_f), np, f);
     return check_launch(c);
 }
 
@@ -1513,8 +1546,20 @@ int sp_precond_apply(sp_ctx* c, const sp_geometry* g, const sp_precond* pc, cons
     if (rc) return rc;
     if ((rc = check_precond(c, pc))) return rc;
     if ((rc = ensure_partials(c))) return rc;
-    int np = 0;
-    if ((rc = enqueue_precond(c, pc, gin, z, nullptr, nullptr, np, false))) return rc;
+    const int n = c->G.rows * c->G.cols;
+    if (pc->kind == SP_PRECOND_NONE) {
+        if (gin != z) launch_copy(c->stream, n, gin, z, nullptr);
+        return check_launch(c);
+    }
+    FFTPlan F{};
+    if ((rc = setup_fft(c, F))) return rc;   // (a learned M's solves fall back to it)
+    ProfScope ps(c, SP_PROF_PRECOND);
+    if (pc->kind == SP_PRECOND_LEARNED) {
+        if ((rc = lp_enqueue_apply(c, const_cast<sp_learned*>(pc->net), 1, g->rows, g->cols, gin, z, nullptr, nullptr)))
+            return rc;
+    } else {
+        launch_precond(c->stream, F, pc->mu, pc->rho, gin, z, nullptr, nullptr, nullptr);
+    }
     return check_launch(c);
 }
 
@@ -1748,8 +1793,9 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
     double* p = dptr<double>(c->vp);
     double* q = dptr<double>(c->vq);                    // R p
     double* w = dptr<double>(c->vw);                    // R z
-    float* gv = dptr<float>(c->vg);
-    float* z = dptr<float>(c->vz);
+    double* gv = dptr<double>(c->vg);
+    double* z = dptr<double>(c->vz);
+    const bool g32 = gradient_is_f32(pc);
     double* xp = dptr<double>(c->xp);
     double* xTp = dptr<double>(c->xTp);
     double* seg = dptr<double>(c->seg);
@@ -1759,11 +1805,18 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
     const AngleDev* ang = dptr<AngleDev>(c->ang);
     const BpAngle* quad = dptr<BpAngle>(c->quad);
     double* pf = dptr<double>(c->part_f);
-    double* pzh = dptr<double>(c->part_zh);
     double* pgp = dptr<double>(c->part_gp);
     double* pqq = dptr<double>(c->part_qq);
     const int m = G.nA * G.nB;
     const int nf = project_blocks(G), nqq = vec_blocks(m), ngp = vec_blocks(n);
+
+    RayOut out_r, out_z;   // r = R x - b with the partials of f; w = R z with those of w^T q
+    out_r.b = b;
+    out_r.outpd = rpd;
+    out_r.partials = pf;
+    out_z.dq = q;
+    out_z.wout = w;
+    out_z.partials = pf;
 
     const double se_ah = want_se ? trace->se_axes[0] : 0.0, se_av = want_se ? trace->se_axes[1] : 0.0;
     auto se_of_x = [&](double* dst, double* dst_body, const int* hflag) {
@@ -1778,13 +1831,11 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
         // p_0 = -z_0; h_0 = A p_0, carried as q = R p_0 = -R z_0; alpha;
         // x_1 = x_0 + alpha p_0; k = 1; l_1 = 0).
         launch_prep(st, G, xh, xp, xTp, halt);
-        launch_project(st, G, ang, waves, xp, xTp, b, nullptr, 0, nullptr, rpd, pf, seg, pord, halt);
+        launch_project(st, G, ang, waves, xp, xTp, out_r, seg, pord, halt);
         launch_scalar(st, OP_F0, sc, tr, pf, nf, nullptr, 0);
-        launch_backproject(st, G, ang, quad, rpd, gv, halt);
-        int nzh = 0;
-        if ((rc = enqueue_precond(c, pc, gv, z, nullptr, pzh, nzh, true, xp, xTp))) return rc;   // + R's copies of z
-        launch_project(st, G, ang, waves, xp, xTp, nullptr, nullptr, 0, nullptr, nullptr, pf, seg, pord,
-                       halt, q, w);                                                // w = R z_0
+        launch_backproject(st, G, ang, quad, rpd, nullptr, gv, g32, halt);
+        if ((rc = enqueue_solver_precond(c, pc, gv, z))) return rc;                  // + R's copies of z
+        launch_project(st, G, ang, waves, xp, xTp, out_z, seg, pord, halt);          // w = R z_0
         launch_update_pq_beta(st, n, m, z, p, gv, w, q, sc, tr, pf, nf, pgp, pqq);   // p_0, q
         launch_update_x_alpha(st, n, xh, p, x, sc, tr, pqq, nqq, pgp, ngp, OP_ALPHA0);
         if (want_se) se_of_x(se_body + cap + 1, nullptr, halt);                      // SE(x_1)
@@ -1798,15 +1849,13 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
     // the body can be replayed from a captured graph.
     // r = R x - b goes to the float64 sinogram rpd with the f partials in pf;
     // w = R z to the float64 w with the partials of w^T q in pf
-    auto project = [&](const float* bb) {
+    auto project = [&](const RayOut& o) {
         ProfScope ps(c, SP_PROF_PROJECT);
-        if (bb) launch_project(st, G, ang, waves, xp, xTp, bb, nullptr, 0, nullptr, rpd, pf, seg, pord, halt);
-        else launch_project(st, G, ang, waves, xp, xTp, nullptr, nullptr, 0, nullptr, nullptr, pf, seg, pord,
-                            halt, q, w);
+        launch_project(st, G, ang, waves, xp, xTp, o, seg, pord, halt);
     };
-    auto backproject = [&](float* out, const ScalarRide& ride) {
+    auto backproject = [&](double* out, const ScalarRide& ride) {
         ProfScope ps(c, SP_PROF_BACKPROJECT);
-        launch_backproject(st, G, ang, quad, rpd, out, halt, ride);
+        launch_backproject(st, G, ang, quad, rpd, nullptr, out, g32, halt, ride);
     };
     // g = R^T r also carries f(x_{k+1/2}) (and the S_TV step norm when K > 0)
     ScalarRide ride_f;
@@ -1828,13 +1877,12 @@ int sp_suppcg_solve(sp_ctx* c, const sp_geometry* g, const float* b, const float
             launch_tv_apply_prep(st, G, x, xh, nullptr, sc, nullptr, nullptr, xp, xTp, halt);
         }
         // U_PCG(x_{k+1/2}, p_{k-1}, h_{k-1}), h_{k-1} carried as q = R p_{k-1}
-        project(b);                                                               // r = R x - b
+        project(out_r);                                                           // r = R x - b
         backproject(gv, ride_f);                                      // g = R^T r, f(x_{k+1/2})
         if (snap) launch_snap(st, n, gv, snap, snap_count, sc);
-        int nz = 0;
-        int r2 = enqueue_precond(c, pc, gv, z, nullptr, pzh, nz, true, xp, xTp);  // z = M g, R's copies of z
+        int r2 = enqueue_solver_precond(c, pc, gv, z);  // z = M g, R's copies of z
         if (r2) return r2;
-        project(nullptr);                                              // w = R z, z^T h = w^T q
+        project(out_z);                                                // w = R z, z^T h = w^T q
         launch_update_pq_beta(st, n, m, z, p, gv, w, q, sc, tr, pf, nf, pgp, pqq);  // beta; p, q
         launch_update_x_alpha(st, n, xh, p, x, sc, tr, pqq, nqq, pgp, ngp, OP_ALPHA);  // alpha; x += alpha p
         if (want_se) se_of_x(nullptr, se_body, halt);                             // SE(x_{k+1})
@@ -2581,6 +2629,7 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
                 return fail(c, rc, "slice %d: tuning its launch shapes: %s", s, c->err);
         }
     }
+    const bool g32 = gradient_is_f32(pc);
     if ((rc = batch_setup(c, n, geoms, pc->kind))) return rc;
     BatchState& B = *c->batch;
     const int K = (tv && tv->K > 0) ? tv->K : 0;
@@ -2630,10 +2679,10 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
     launch_prep_b(st, sl, tprep, BV_XH);
     launch_project_b(st, sl, tproj, tcomb, true);
     launch_scalar_b(st, sl, tone, OP_F0);
-    launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms);
+    launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms, g32);
     batch_precond(c, mu, rho);
     launch_prep_b(st, sl, tprep, BV_Z);
-    launch_project_b(st, sl, tproj, tcomb, false);                // w = R z
+    launch_project_b(st, sl, tproj, tcomb, false);     // w = R z
     launch_scalar_b(st, sl, tone, OP_BETA);
     launch_update_pq_b(st, sl, tpq);                             // p = -z, q = R p = -w
     launch_scalar_b(st, sl, tone, OP_ALPHA0);
@@ -2659,10 +2708,10 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
         }
         launch_project_b(st, sl, tproj, tcomb, true);
         launch_scalar_b(st, sl, tone, OP_F);
-        launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms);
+        launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms, g32);
         batch_precond(c, mu, rho);
         launch_prep_b(st, sl, tprep, BV_Z);
-        launch_project_b(st, sl, tproj, tcomb, false);            // w = R z, (R z)^T q
+        launch_project_b(st, sl, tproj, tcomb, false); // w = R z, (R z)^T q
         launch_scalar_b(st, sl, tone, OP_BETA);
         launch_update_pq_b(st, sl, tpq);
         launch_scalar_b(st, sl, tone, OP_ALPHA);

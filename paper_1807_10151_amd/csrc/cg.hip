@@ -8,8 +8,8 @@
 // q <- -R z + beta q, which costs one projection of z per loop body in place
 // of a projection and a backprojection of p.
 //
-// The iterate x, x_{k+1/2}, the direction p and q are float64 vectors; g and z
-// are float32.  Dot products are float64 partial sums per workgroup (fixed
+// The iterate x, x_{k+1/2}, the direction p, the gradient g, z = M g and q are
+// float64 vectors.  Dot products are float64 partial sums per workgroup (fixed
 // order); a single
 // workgroup (k_scalar) sums them and updates the device-resident scalars, so a
 // loop body needs no host synchronisation and can be captured in a graph.
@@ -54,8 +54,8 @@ void launch_dot(hipStream_t st, int n, const float* a, const float* b, double* p
 //   bx < vec_blocks(m): q <- -w + beta q over its share of the m rays
 //     (w = R z, q = R p), with the partial of q^T q in pqq[bx].
 // The first direction (no previous p) is p = -z, q = -w.
-__device__ __forceinline__ void update_pq_body(int n, int m, const float* __restrict__ z,
-                                               double* __restrict__ p, const float* __restrict__ g,
+__device__ __forceinline__ void update_pq_body(int n, int m, const double* __restrict__ z,
+                                               double* __restrict__ p, const double* __restrict__ g,
                                                const double* __restrict__ w,
                                                double* __restrict__ q, double beta, bool first,
                                                double* __restrict__ pgp, double* __restrict__ pqq,
@@ -65,9 +65,9 @@ __device__ __forceinline__ void update_pq_body(int n, int m, const float* __rest
     if (bx < gp) {
         double acc = 0.0;
         for (int i = bx * 256 + threadIdx.x; i < n; i += gp * 256) {
-            const double v = first ? -(double)z[i] : fma(beta, p[i], -(double)z[i]);
+            const double v = first ? -z[i] : fma(beta, p[i], -z[i]);
             p[i] = v;
-            acc += (double)g[i] * v;
+            acc += g[i] * v;
         }
         const double tot = block_sum(acc, red);
         if (threadIdx.x == 0) pgp[bx] = tot;
@@ -90,9 +90,9 @@ int pq_blocks(int n, int m) { return vec_blocks(n > m ? n : m); }
 // partials (pdot) in the same fixed order, so all use the beta that workgroup
 // 0 commits to the scalars (and trace).  A non-finite beta halts without an
 // update, as the separate scalar step would.
-__global__ __launch_bounds__(256) void k_update_pq_beta(int n, int m, const float* __restrict__ z,
+__global__ __launch_bounds__(256) void k_update_pq_beta(int n, int m, const double* __restrict__ z,
                                                         double* __restrict__ p,
-                                                        const float* __restrict__ g,
+                                                        const double* __restrict__ g,
                                                         const double* __restrict__ w,
                                                         double* __restrict__ q,
                                                         Scalars* __restrict__ sc, TraceDev tr,
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void k_update_pq_beta(int n, int m, const floa
     update_pq_body(n, m, z, p, g, w, q, beta, first, pgp, pqq, blockIdx.x);
 }
 
-void launch_update_pq_beta(hipStream_t st, int n, int m, const float* z, double* p, const float* g,
+void launch_update_pq_beta(hipStream_t st, int n, int m, const double* z, double* p, const double* g,
                            const double* w, double* q, Scalars* sc, TraceDev tr, const double* pdot,
                            int ndot, double* pgp, double* pqq) {
     hipLaunchKernelGGL(k_update_pq_beta, dim3(pq_blocks(n, m)), dim3(256), 0, st, n, m, z, p, g, w, q,
@@ -171,37 +171,41 @@ void launch_copy(hipStream_t st, int n, const double* src, double* dst, const in
 }
 
 __global__ __launch_bounds__(256) void k_widen(int n, const float* __restrict__ src,
-                                               double* __restrict__ dst) {
+                                               double* __restrict__ dst, const int* __restrict__ halt,
+                                               const int* __restrict__ run) {
+    if (halt && *halt) return;
+    if (run && !*run) return;
     for (int q = blockIdx.x * 256 + threadIdx.x; q < n; q += gridDim.x * 256)
         dst[q] = src ? (double)src[q] : 0.0;
 }
 
-void launch_widen(hipStream_t st, int n, const float* src, double* dst) {
-    hipLaunchKernelGGL(k_widen, dim3(vec_blocks(n)), dim3(256), 0, st, n, src, dst);
+void launch_widen(hipStream_t st, int n, const float* src, double* dst, const int* halt, const int* run) {
+    hipLaunchKernelGGL(k_widen, dim3(vec_blocks(n)), dim3(256), 0, st, n, src, dst, halt, run);
 }
 
 __global__ __launch_bounds__(256) void k_narrow(int n, const double* __restrict__ src,
-                                                float* __restrict__ dst) {
+                                                float* __restrict__ dst, const int* __restrict__ halt) {
+    if (halt && *halt) return;
     for (int q = blockIdx.x * 256 + threadIdx.x; q < n; q += gridDim.x * 256) dst[q] = (float)src[q];
 }
 
-void launch_narrow(hipStream_t st, int n, const double* src, float* dst) {
-    hipLaunchKernelGGL(k_narrow, dim3(vec_blocks(n)), dim3(256), 0, st, n, src, dst);
+void launch_narrow(hipStream_t st, int n, const double* src, float* dst, const int* halt) {
+    hipLaunchKernelGGL(k_narrow, dim3(vec_blocks(n)), dim3(256), 0, st, n, src, dst, halt);
 }
 
 // dst[iter][:] = src for the loop body index iter held in the scalars, while
 // iter < count.
-__global__ __launch_bounds__(256) void k_snap(int n, const float* __restrict__ src,
+__global__ __launch_bounds__(256) void k_snap(int n, const double* __restrict__ src,
                                               float* __restrict__ dst, int count,
                                               const Scalars* __restrict__ sc) {
     if (sc->halt) return;
     const int it = sc->iter;
     if (it < 0 || it >= count) return;
     float* d = dst + (size_t)it * n;
-    for (int q = blockIdx.x * 256 + threadIdx.x; q < n; q += gridDim.x * 256) d[q] = src[q];
+    for (int q = blockIdx.x * 256 + threadIdx.x; q < n; q += gridDim.x * 256) d[q] = (float)src[q];
 }
 
-void launch_snap(hipStream_t st, int n, const float* src, float* dst, int count, const Scalars* sc) {
+void launch_snap(hipStream_t st, int n, const double* src, float* dst, int count, const Scalars* sc) {
     hipLaunchKernelGGL(k_snap, dim3(vec_blocks(n)), dim3(256), 0, st, n, src, dst, count, sc);
 }
 
@@ -284,8 +288,8 @@ __global__ __launch_bounds__(256) void kb_copy_gz(const SliceDev* __restrict__ s
         const SliceDev& S = sl[s];
         if (gmem(S.sc)->halt) return;
         const int gx = vec_blocks_dev(S.n);
-        const float* g = gmem(S.g);
-        float* z = gmem(S.z);
+        const double* g = gmem(S.g);
+        double* z = gmem(S.z);
         for (int q = lin * 256 + threadIdx.x; q < S.n; q += gx * 256) z[q] = g[q];
     });
 }

@@ -10,10 +10,11 @@
 //     keep rows < l;
 //  3. rows inverse: two rows rebuilt from their half spectra as one complex
 //     row, inverse FFT; real part -> row r, imaginary part -> row r+1; crop to c
-//     columns.  Optionally the float64 partial dot of the result with `dotv`.
+//     columns.
 //
 // The output is real because D is real and even in both frequencies.
-// Arithmetic and scratch are float64 (input and output float32): with mu = 1e-5
+// Arithmetic and scratch are float64 (input and output float32, in the solvers
+// float64): with mu = 1e-5
 // the window spans five decades, and a float32 transform's rounding swamps the
 // low-frequency part of z.
 #include "sp_internal.h"
@@ -186,14 +187,15 @@ __device__ __forceinline__ const double2* stage_twiddles(const FFTPlan& F, doubl
         else kind(buf, F.P, F.logP, ncol, F.tw, sign);                            \
     } while (0)
 
-__device__ __forceinline__ void rows_fwd_body(const FFTPlan& F, const float* __restrict__ g,
+template <class T>
+__device__ __forceinline__ void rows_fwd_body(const FFTPlan& F, const T* __restrict__ g,
                                               double2* raw, int bx) {
     const LdsBuf buf{raw, fft_lds_shift(F.P, 1)};
     const int r0 = 2 * bx, r1 = r0 + 1;
     const bool twl = tw_in_lds(F.P, 1);
     if (twl) stage_twiddles(F, raw, 1);
     for (int nidx = threadIdx.x; nidx < F.P; nidx += blockDim.x) {
-        float re = 0.0f, im = 0.0f;
+        T re = 0, im = 0;
         if (nidx < F.cols) {
             re = g[(size_t)r0 * F.cols + nidx];
             if (r1 < F.rows) im = g[(size_t)r1 * F.cols + nidx];
@@ -213,7 +215,8 @@ __device__ __forceinline__ void rows_fwd_body(const FFTPlan& F, const float* __r
     }
 }
 
-__global__ __launch_bounds__(512) void k_rows_fwd(FFTPlan F, const float* __restrict__ g, const int* __restrict__ run,
+template <class T>
+__global__ __launch_bounds__(512) void k_rows_fwd(FFTPlan F, const T* __restrict__ g, const int* __restrict__ run,
                                                   const int* __restrict__ halt) {
     if (halt && *halt) return;
     if (run && !*run) return;
@@ -266,17 +269,15 @@ __global__ __launch_bounds__(512) void k_cols(FFTPlan F, double mu, double rho, 
     cols_body(F, mu, rho, buf, blockIdx.x);
 }
 
-// With xp, z is also written to R's padded float64 copies (xp row-major with
-// row pitch pitchX, xTp transposed with pitch pitchXT, both PAD-offset), as
-// R's prep would write them.
-__device__ __forceinline__ void rows_inv_body(const FFTPlan& F, float* __restrict__ z,
-                                              const float* __restrict__ dotv,
-                                              double* __restrict__ partials, double2* raw, int bx,
+// T: the type of z (float32 results are rounded once).  With xp, z is also
+// written to R's padded float64 copies (xp row-major with row pitch pitchX, xTp
+// transposed with pitch pitchXT, both PAD-offset), as R's prep would write them.
+template <class T>
+__device__ __forceinline__ void rows_inv_body(const FFTPlan& F, T* __restrict__ z, double2* raw, int bx,
                                               double* __restrict__ xp = nullptr,
                                               double* __restrict__ xTp = nullptr, int pitchX = 0,
                                               int pitchXT = 0) {
     const LdsBuf buf{raw, fft_lds_shift(F.P, 1)};
-    double* red = reinterpret_cast<double*>(raw);   // reused after the transform is read
     const int r0 = 2 * bx, r1 = r0 + 1;
     const bool has1 = r1 < F.rows;
     const bool twl = tw_in_lds(F.P, 1);
@@ -300,42 +301,33 @@ __device__ __forceinline__ void rows_inv_body(const FFTPlan& F, float* __restric
     __syncthreads();
     SP_FFT(fft_dit, 1, 1.0f);
     const double scale = 1.0 / ((double)F.P * (double)F.P);
-    double dot = 0.0;
     for (int j = threadIdx.x; j < F.cols; j += blockDim.x) {
         const double2 v = buf[j];
-        const float a = (float)(v.x * scale);
-        z[(size_t)r0 * F.cols + j] = a;
-        if (dotv) dot += (double)a * (double)dotv[(size_t)r0 * F.cols + j];
+        const double a = v.x * scale, bv = v.y * scale;
+        z[(size_t)r0 * F.cols + j] = (T)a;
         if (xp) {
-            xp[(size_t)r0 * pitchX + PAD + j] = (double)a;
-            xTp[(size_t)j * pitchXT + PAD + r0] = (double)a;
+            xp[(size_t)r0 * pitchX + PAD + j] = a;
+            xTp[(size_t)j * pitchXT + PAD + r0] = a;
         }
         if (has1) {
-            const float bv = (float)(v.y * scale);
-            z[(size_t)r1 * F.cols + j] = bv;
-            if (dotv) dot += (double)bv * (double)dotv[(size_t)r1 * F.cols + j];
+            z[(size_t)r1 * F.cols + j] = (T)bv;
             if (xp) {
-                xp[(size_t)r1 * pitchX + PAD + j] = (double)bv;
-                xTp[(size_t)j * pitchXT + PAD + r1] = (double)bv;
+                xp[(size_t)r1 * pitchX + PAD + j] = bv;
+                xTp[(size_t)j * pitchXT + PAD + r1] = bv;
             }
         }
     }
-    if (dotv) {
-        const double tot = block_sum(dot, red);
-        if (threadIdx.x == 0) partials[bx] = tot;
-    }
 }
 
-__global__ __launch_bounds__(256) void k_rows_inv(FFTPlan F, float* __restrict__ z, const int* __restrict__ run,
-                                                  const float* __restrict__ dotv,
-                                                  double* __restrict__ partials,
+template <class T>
+__global__ __launch_bounds__(256) void k_rows_inv(FFTPlan F, T* __restrict__ z, const int* __restrict__ run,
                                                   const int* __restrict__ halt,
                                                   double* __restrict__ xp, double* __restrict__ xTp,
                                                   int pitchX, int pitchXT) {
     if (halt && *halt) return;
     if (run && !*run) return;
     extern __shared__ double2 buf[];
-    rows_inv_body(F, z, dotv, partials, buf, blockIdx.x, xp, xTp, pitchX, pitchXT);
+    rows_inv_body(F, z, buf, blockIdx.x, xp, xTp, pitchX, pitchXT);
 }
 
 // Batched: z = M g per slice.
@@ -347,7 +339,7 @@ __global__ __launch_bounds__(512) void kb_rows_fwd(const SliceDev* __restrict__ 
         FFTPlan F = S.F;
         F.S = gmem(F.S);
         F.tw = cmem(F.tw);
-        rows_fwd_body(F, gmem(S.g), buf, lin);
+        rows_fwd_body(F, (const double*)gmem(S.g), buf, lin);
     });
 }
 
@@ -372,7 +364,7 @@ __global__ __launch_bounds__(256) void kb_rows_inv(const SliceDev* __restrict__ 
         FFTPlan F = S.F;
         F.S = gmem(F.S);
         F.tw = cmem(F.tw);
-        rows_inv_body(F, gmem(S.z), nullptr, nullptr, buf, lin);
+        rows_inv_body(F, (double*)gmem(S.z), buf, lin);
     });
 }
 
@@ -383,23 +375,26 @@ void launch_precond_b(hipStream_t st, const SliceDev* sl, ItemTable rows, ItemTa
     hipLaunchKernelGGL(kb_rows_inv, dim3(rows.grid), dim3(256), lds_rows, st, sl, rows);
 }
 
-int precond_dot_blocks(const FFTPlan& F) { return (F.rows + 1) / 2; }
-
 size_t fft_lds_bytes(int P, int ncol) {
     return (fft_data_len(P, ncol) + (tw_in_lds(P, ncol) ? P / 2 : 0)) * sizeof(double2);
 }
 
-void launch_precond(hipStream_t st, const FFTPlan& F, double mu, double rho, const float* g,
-                    float* z, const float* dotv, double* partials, const int* halt, const int* run,
-                    const GeomDev* G, double* xp, double* xTp) {
+void launch_precond(hipStream_t st, const FFTPlan& F, double mu, double rho, const float* g, float* z,
+                    const double* gd, double* zd, const int* halt, const int* run, const GeomDev* G,
+                    double* xp, double* xTp) {
     const int nrow = (F.rows + 1) / 2;
     const size_t row_lds = fft_lds_bytes(F.P, 1);
-    hipLaunchKernelGGL(k_rows_fwd, dim3(nrow), dim3(512), row_lds, st, F, g, run, halt);
+    if (gd) hipLaunchKernelGGL(k_rows_fwd<double>, dim3(nrow), dim3(512), row_lds, st, F, gd, run, halt);
+    else hipLaunchKernelGGL(k_rows_fwd<float>, dim3(nrow), dim3(512), row_lds, st, F, g, run, halt);
     const int ncb = (F.SP + F.CB - 1) / F.CB;
     hipLaunchKernelGGL(k_cols, dim3(ncb), dim3(512), fft_lds_bytes(F.P, F.CB), st, F, mu, rho, run,
                        halt);
-    hipLaunchKernelGGL(k_rows_inv, dim3(nrow), dim3(256), row_lds, st, F, z, run, dotv, partials, halt,
-                       G ? xp : nullptr, G ? xTp : nullptr, G ? G->pitchX : 0, G ? G->pitchXT : 0);
+    if (zd)
+        hipLaunchKernelGGL(k_rows_inv<double>, dim3(nrow), dim3(256), row_lds, st, F, zd, run, halt,
+                           G ? xp : nullptr, G ? xTp : nullptr, G ? G->pitchX : 0, G ? G->pitchXT : 0);
+    else
+        hipLaunchKernelGGL(k_rows_inv<float>, dim3(nrow), dim3(256), row_lds, st, F, z, run, halt,
+                           (double*)nullptr, (double*)nullptr, 0, 0);
 }
 
 }  // namespace sp

@@ -80,9 +80,9 @@ int geom_fail(char* err, size_t n, const char* fmt, ...) {
 }
 }  // namespace
 
-int project_wave_count(const GeomDev& G) { return project_waves(G, nullptr); }
-
-int project_waves(const GeomDev& G, WaveDev* out) {
+namespace {
+// The wave table of R's one-ray form, or of its two-ray form over pairs of bins.
+int wave_table(const GeomDev& G, bool pair, WaveDev* out) {
     // Oblique classes: waves of WAVE_ANGLES angles by WAVE_BINS bins, a
     // workgroup's four waves the four 16-bin sub-chunks of one 64-bin chunk
     // for the same four neighbouring angles (rays that cross nearly the same
@@ -91,7 +91,8 @@ int project_waves(const GeomDev& G, WaveDev* out) {
     // angle.  The dispatch order sorts workgroups by cost and keeps this
     // order among equal costs, so workgroups that run side by side on the GPU
     // read neighbouring parts of the image.
-    const int r = G.nB % WAVE_BINS, full = G.nB / WAVE_BINS;
+    const int nB = pair ? (G.nB + 1) / 2 : G.nB, kind = pair ? WAVE_PAIR_BLOCK : WAVE_BLOCK;
+    const int r = nB % WAVE_BINS, full = nB / WAVE_BINS;
     int w = 0;
     auto put = [&](const WaveDev& W) {
         if (out) out[w] = W;
@@ -101,19 +102,24 @@ int project_waves(const GeomDev& G, WaveDev* out) {
         for (int q = 0; q < 2; ++q) {
             const int a0 = G.cls[q], a1 = G.cls[q + 1];
             for (int g0 = a0; g0 < a1; g0 += WAVE_ANGLES)
-                for (int j = c; j < std::min(full, c + 4); ++j) put(WaveDev{g0, WAVE_BINS * j, a1, WAVE_BLOCK});
+                for (int j = c; j < std::min(full, c + 4); ++j) put(WaveDev{g0, WAVE_BINS * j, a1, kind});
         }
     for (int q = 0; q < 2; ++q) {
         const int a0 = G.cls[q], a1 = G.cls[q + 1];
         if (r == 0) continue;
         const int stream = (a1 - a0) * r;
-        for (int e = 0; e < stream; e += 64) put(WaveDev{a0, e, a1, WAVE_TAIL});
+        for (int e = 0; e < stream; e += 64) put(WaveDev{a0, e, a1, kind + (WAVE_TAIL - WAVE_BLOCK)});
     }
     for (int q = 2; q < 4; ++q)
         for (int a = G.cls[q]; a < G.cls[q + 1]; ++a)
             for (int k0 = 0; k0 < G.nB; k0 += 64) put(WaveDev{a, k0, a + 1, WAVE_ROW});
     return w;
 }
+}  // namespace
+
+int project_wave_count(const GeomDev& G) { return project_waves(G, nullptr); }
+int project_waves(const GeomDev& G, WaveDev* out) { return wave_table(G, false, out); }
+int project_pair_waves(const GeomDev& G, WaveDev* out) { return wave_table(G, true, out); }
 
 int project_parts(int rows, int cols, int nwaves, int resident_waves) {
     // Large images: 8 parts keep the resident waves on a band of the float64
@@ -125,6 +131,16 @@ int project_parts(int rows, int cols, int nwaves, int resident_waves) {
     if (10L * nwaves >= 9L * resident_waves) return 1;
     const long p = (resident_waves + nwaves - 1) / nwaves;
     return p > 4 ? 4 : (int)p;
+}
+
+int project32_parts(int nwaves, int resident_waves) {
+    // Four waves per SIMD with four gathers in flight each keep the two-ray
+    // form busy: split the rays of grids that stay below that.  Measured, 1 / 2
+    // / 4 parts: 64^2 12.5 / 10.7 / 10.8 us, 243^2 x 340 28.8 / 21.0 / 19.7,
+    // 300^2 x 424 37.0 / 34.2 / 37.1, 430^2 x 600 62.2 / 61.4 / 69.2, 512^2 x 720
+    // 88.3 / 89.5 / 99.9, 2048^2 x 2048 (8 in its place) 2315 / 2318 / 2478.
+    if (8L * nwaves <= resident_waves) return WG_PARTS;
+    return 2L * nwaves < resident_waves ? 2 : 1;
 }
 
 int backproject_tiles(const GeomDev& G, int px) {
@@ -208,7 +224,10 @@ void backproject_shape(GeomDev& G, int resident_waves) {
 int project_comb_blocks(const GeomDev& G) { return G.nA * ((G.nB + 255) / 256); }
 
 int project_blocks(const GeomDev& G) {
-    return G.parts > 1 ? project_comb_blocks(G) : G.nwg;
+    return G.parts > WG_PARTS ? project_comb_blocks(G) : G.nwg;
+}
+int project32_blocks(const GeomDev& G) {
+    return G.fparts > WG_PARTS ? project_comb_blocks(G) : G.fwg;
 }
 
 int build_geometry_into(const sp_geometry* g, int n_cu, GeomDev& G, AngleDev* tab, char* err,
@@ -247,9 +266,14 @@ int build_geometry_into(const sp_geometry* g, int n_cu, GeomDev& G, AngleDev* ta
             const AngleDev A = angle_entry(*g, a, ds, s0, margin);
             if (angle_class(A) == q) tab[pos++] = A;
         }
+    G.pair = 1;
+    for (int a = 0; a < G.cls[2]; ++a) G.pair &= pair_fits(G, tab[a]) ? 1 : 0;
     G.nwaves = project_wave_count(G);
     G.nwg = (G.nwaves + 3) / 4;
+    G.fwaves = project_pair_waves(G, nullptr);
+    G.fwg = (G.fwaves + 3) / 4;
     G.parts = project_parts(g->rows, g->cols, G.nwaves, n_cu * 32);
+    G.fparts = project32_parts(G.fwaves, n_cu * 32);
     G.bp_quad = bp_quad_table(G, tab, nullptr) ? 1 : 0;
     G.bp_px = G.bp_quad ? 4 : backproject_px(g->rows, g->cols, n_cu * 32);
     if (G.bp_quad) backproject_shape(G, n_cu * 32);
@@ -275,11 +299,16 @@ long wave_steps(const GeomDev& G, const AngleDev* tab, const WaveDev& W) {
     int lo = 1 << 30, hi = -1;
     auto add = [&](int lane) {
         int ai, k, l, h;
-        if (!wave_ray(W, lane, G.nB, ai, k)) return false;
-        if (!lane_steps(G, tab[ai], k, l, h)) return false;
-        lo = std::min(lo, l);
-        hi = std::max(hi, h);
-        return true;
+        const bool pair = W.tail == WAVE_PAIR_BLOCK || W.tail == WAVE_PAIR_TAIL;
+        if (!(pair ? wave_pair(W, lane, G.nB, ai, k) : wave_ray(W, lane, G.nB, ai, k))) return false;
+        bool met = false;
+        for (int q = k; q <= k + (pair ? 1 : 0) && q < G.nB; ++q) {
+            if (!lane_steps(G, tab[ai], q, l, h)) continue;
+            lo = std::min(lo, l);
+            hi = std::max(hi, h);
+            met = true;
+        }
+        return met;
     };
     if (W.tail != WAVE_ROW) {
         for (int l = 0; l < 64; ++l) add(l);
@@ -297,10 +326,10 @@ long wave_steps(const GeomDev& G, const AngleDev* tab, const WaveDev& W) {
 }
 
 std::vector<int32_t> project_order(const GeomDev& G, const AngleDev* tab, const WaveDev* waves,
-                                   int n_cu) {
-    const int nwg = G.nwg;
+                                   int nwaves, int n_cu) {
+    const int nwg = (nwaves + 3) / 4;
     std::vector<long> cost((size_t)nwg, 0);
-    for (int w = 0; w < G.nwaves; ++w) cost[(size_t)(w / 4)] += 16 + wave_steps(G, tab, waves[w]);
+    for (int w = 0; w < nwaves; ++w) cost[(size_t)(w / 4)] += 16 + wave_steps(G, tab, waves[w]);
     std::vector<int32_t> ord((size_t)nwg);
     for (int b = 0; b < nwg; ++b) ord[(size_t)b] = b;
     std::stable_sort(ord.begin(), ord.end(),

@@ -33,7 +33,9 @@
 // waves are four consecutive table entries (the four 16-bin parts of one
 // 64-bin chunk of the same angles), and the workgroups run in a
 // host-computed order (project_order).  Horizontal angles walk columns of a zero-padded
-// transposed copy.
+// transposed copy.  R of a float32 image (the standalone operators') gives
+// a lane two neighbouring rays where the bin spacing allows it (ray_pair); the
+// solvers' float64 vectors keep one.
 //
 // Backward gather.  A lane owns PX (2 or 4) pixels of one row, 8 columns
 // apart, and loops over the angles, which are sorted into four classes
@@ -54,10 +56,11 @@
 namespace sp {
 
 // 32 x 32 tile (bx, by): padded copy and padded transposed copy of a float32
-// image or of a float64 iterate.
-template <class T>
+// image (float32 copies for the two-ray form, else float64) or of a float64
+// iterate.
+template <class T, class C>
 __device__ __forceinline__ void prep_body(const GeomDev& G, const T* __restrict__ x,
-                                          double* __restrict__ xp, double* __restrict__ xTp, int bx,
+                                          C* __restrict__ xp, C* __restrict__ xTp, int bx,
                                           int by) {
     __shared__ T tile[32][33];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -68,7 +71,7 @@ __device__ __forceinline__ void prep_body(const GeomDev& G, const T* __restrict_
         T v = 0;
         if (i < G.rows && j < G.cols) {
             v = x[(size_t)i * G.cols + j];
-            xp[(size_t)i * G.pitchX + PAD + j] = (double)v;
+            xp[(size_t)i * G.pitchX + PAD + j] = (C)v;
         }
         tile[ty + r][tx] = v;
     }
@@ -78,13 +81,13 @@ __device__ __forceinline__ void prep_body(const GeomDev& G, const T* __restrict_
     for (int r = 0; r < 32; r += 8) {
         const int jj = bx * 32 + ty + r;
         if (ii < G.rows && jj < G.cols)
-            xTp[(size_t)jj * G.pitchXT + PAD + ii] = (double)tile[tx][ty + r];
+            xTp[(size_t)jj * G.pitchXT + PAD + ii] = (C)tile[tx][ty + r];
     }
 }
 
-template <class T>
+template <class T, class C>
 __global__ __launch_bounds__(256) void k_prep(GeomDev G, const T* __restrict__ x,
-                                              double* __restrict__ xp, double* __restrict__ xTp,
+                                              C* __restrict__ xp, C* __restrict__ xTp,
                                               const int* __restrict__ halt) {
     if (halt && *halt) return;
     prep_body(G, x, xp, xTp, blockIdx.x, blockIdx.y);
@@ -96,8 +99,7 @@ __global__ __launch_bounds__(256) void kb_prep(const SliceDev* __restrict__ sl, 
         if (gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         const int gx = (G.cols + 31) / 32;
-        if (which == BV_Z) prep_body(G, (const float*)gmem(S.z), gmem(S.xp), gmem(S.xTp), lin % gx, lin / gx);
-        else prep_body(G, (const double*)batch_vec(S, which), gmem(S.xp), gmem(S.xTp), lin % gx, lin / gx);
+        prep_body(G, (const double*)batch_vec(S, which), gmem(S.xp), gmem(S.xTp), lin % gx, lin / gx);
     });
 }
 
@@ -108,13 +110,19 @@ void launch_prep_b(hipStream_t st, const SliceDev* sl, ItemTable t, int which) {
 void launch_prep(hipStream_t st, const GeomDev& G, const float* x, double* xp, double* xTp,
                  const int* halt) {
     dim3 grid((G.cols + 31) / 32, (G.rows + 31) / 32);
-    hipLaunchKernelGGL(k_prep<float>, grid, dim3(256), 0, st, G, x, xp, xTp, halt);
+    hipLaunchKernelGGL((k_prep<float, double>), grid, dim3(256), 0, st, G, x, xp, xTp, halt);
 }
 
 void launch_prep(hipStream_t st, const GeomDev& G, const double* x, double* xp, double* xTp,
                  const int* halt) {
     dim3 grid((G.cols + 31) / 32, (G.rows + 31) / 32);
-    hipLaunchKernelGGL(k_prep<double>, grid, dim3(256), 0, st, G, x, xp, xTp, halt);
+    hipLaunchKernelGGL((k_prep<double, double>), grid, dim3(256), 0, st, G, x, xp, xTp, halt);
+}
+
+void launch_prep32(hipStream_t st, const GeomDev& G, const float* x, float* zp, float* zTp,
+                   const int* halt) {
+    dim3 grid((G.cols + 31) / 32, (G.rows + 31) / 32);
+    hipLaunchKernelGGL((k_prep<float, float>), grid, dim3(256), 0, st, G, x, zp, zTp, halt);
 }
 
 __device__ __forceinline__ int wave_min(int v) {
@@ -193,21 +201,18 @@ __device__ __forceinline__ void row_load(RowRef r, unsigned e, T (&v)[N]) {
     for (int i = 0; i < N; ++i) v[i] = q[i];
 }
 // ---- forward walk ----------------------------------------------------------
-// The wave's common step range from the lanes' own ranges: lanes without a
-// ray, or whose ray misses the image, take no part.  Then part `part` of it.
-__device__ __forceinline__ bool wave_steps_dev(int l, int h, bool valid, int nmaj, int part,
-                                               int nparts, int& lo, int& hi) {
+// The wave's common step range [lo, hi) from the lanes' own ranges: lanes
+// without a ray, or whose ray misses the image, take no part.
+__device__ __forceinline__ void wave_range(int l, int h, bool valid, int nmaj, int& lo, int& hi) {
     if (!valid || l >= h) {
         l = nmaj;
         h = 0;
     }
     lo = __builtin_amdgcn_readfirstlane(wave_min(l));
     hi = __builtin_amdgcn_readfirstlane(wave_max(h));
-    part_range(lo, hi, part, nparts);
-    return lo < hi;
 }
 
-// One axis-parallel ray's sum, or part `part` of nparts of it, with the
+// One axis-parallel ray's sum over the steps [lo, hi), with the
 // trapezoid per candidate (its half weight for a ray on a pixel edge).
 // HORIZ = walk columns of the transposed copy.  img points at element PAD of
 // row 0 of the padded copy.  Candidate q of step m is minor index
@@ -220,17 +225,12 @@ __device__ __forceinline__ bool wave_steps_dev(int l, int h, bool valid, int nma
 // Axis-parallel rays cross the whole image, so their waves are among the
 // longest of the launch: U steps per iteration keep U gathers in flight, as a
 // wave's walk is otherwise bound by the latency of its chain of gathers.
-template <bool HORIZ>
+template <bool HORIZ, class T>
 __device__ __forceinline__ double ray_sum_axis(const GeomDev& G, const AngleDev& A, double sk,
-                                               const double* __restrict__ img, bool valid,
-                                               int part, int nparts) {
+                                               const T* __restrict__ img, int lo, int hi) {
     constexpr int NC = 2, U = 4;
-    const int nmaj = HORIZ ? G.cols : G.rows;
     const int pitch = HORIZ ? G.pitchXT : G.pitchX;
-    int l, h, lo, hi;
-    ray_steps<HORIZ>(G, A, sk, l, h);
     double acc = 0.0;
-    if (!wave_steps_dev(l, h, valid, nmaj, part, nparts, lo, hi)) return acc;
     const double start = walk_start<HORIZ>(G, A, sk);
     const double fm = HORIZ ? A.s : A.c;   // factor of the per-candidate fma
     const double c2 = HORIZ ? G.yoff + (double)PAD : -(double)PAD - G.xoff;
@@ -238,26 +238,26 @@ __device__ __forceinline__ double ray_sum_axis(const GeomDev& G, const AngleDev&
     const double dM = HORIZ ? 1.0 : -1.0;  // major coordinate step
     double cM = HORIZ ? (double)lo - G.xoff : G.yoff - (double)lo;
     double nf = fma((double)lo, A.slope, start + (double)(1 + PAD));
-    const int rowbytes = pitch * 8;
+    const int rowbytes = pitch * (int)sizeof(T);
     const char* rowp = reinterpret_cast<const char*>(img - PAD) + (size_t)lo * rowbytes;
-    auto step = [&](const double (&v)[NC], int o, double cMv) {
+    auto step = [&](const T (&v)[NC], int o, double cMv) {
         const double P = cMv * fM;
         const double cm0 = HORIZ ? c2 - (double)o : (double)o + c2;
 #pragma unroll
         for (int q = 0; q < NC; ++q) {
             const double cm = HORIZ ? cm0 - (double)q : cm0 + (double)q;
             const double d = sk - fma(cm, fm, P);
-            acc = fma(chord_u<true>(d, A.einv, A.inv), v[q], acc);
+            acc = fma(chord_u<true>(d, A.einv, A.inv), (double)v[q], acc);
         }
     };
     int m = lo;
     for (; m + U <= hi; m += U) {
         int o[U];
-        double v[U][NC];
+        T v[U][NC];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             o[u] = (int)nf;
-            row_load<double, NC>(row_ref(rowp + u * rowbytes, rowbytes), (unsigned)o[u], v[u]);
+            row_load<T, NC>(row_ref(rowp + u * rowbytes, rowbytes), (unsigned)o[u], v[u]);
             nf += A.slope;
         }
 #pragma unroll
@@ -269,8 +269,8 @@ __device__ __forceinline__ double ray_sum_axis(const GeomDev& G, const AngleDev&
     }
     for (; m < hi; ++m) {
         const int o = (int)nf;
-        double v[NC];
-        row_load<double, NC>(row_ref(rowp, rowbytes), (unsigned)o, v);
+        T v[NC];
+        row_load<T, NC>(row_ref(rowp, rowbytes), (unsigned)o, v);
         step(v, o, cM);
         nf += A.slope;
         cM += dM;
@@ -279,7 +279,7 @@ __device__ __forceinline__ double ray_sum_axis(const GeomDev& G, const AngleDev&
     return acc;
 }
 
-// One oblique ray's sum of u-weighted values, or part `part` of it, by
+// One oblique ray's sum of u-weighted values over the steps [lo, hi), by
 // splitting each major step's band at the pixel boundary.  With |slope| <= 1
 // the ray crosses a band (an image row for vertical angles, a column of the
 // transposed copy for horizontal ones) over a minor-axis interval of length
@@ -296,14 +296,9 @@ __device__ __forceinline__ double ray_sum_axis(const GeomDev& G, const AngleDev&
 // gathers, so U steps' gathers are issued before their math.
 template <bool HORIZ>
 __device__ __forceinline__ double ray_split(const GeomDev& G, const AngleDev& A, double sk,
-                                            const double* __restrict__ img, bool valid, int part,
-                                            int nparts) {
-    const int nmaj = HORIZ ? G.cols : G.rows;
+                                            const double* __restrict__ img, int lo, int hi) {
     const int pitch = HORIZ ? G.pitchXT : G.pitchX;
-    int l, h, lo, hi;
-    ray_steps<HORIZ>(G, A, sk, l, h);
     double acc = 0.0;
-    if (!wave_steps_dev(l, h, valid, nmaj, part, nparts, lo, hi)) return acc;
     constexpr int U = 2;   // steps per iteration: their gathers are in flight together
     const double sig = A.slope;
     const double isg = 1.0 / fabs(sig);
@@ -337,108 +332,269 @@ __device__ __forceinline__ double ray_split(const GeomDev& G, const AngleDev& A,
     return acc;
 }
 
+// Two neighbouring oblique rays of one angle from a float32 image over the steps
+// [lo, hi): acc[0] the one with the smaller minor coordinate.  From about unit
+// bin spacing up the two rays' bands are 1 to 2 pixels apart (pair_fits), so
+// the four pixels j .. j + 3 that one 16-byte gather brings serve both, where
+// ray_split gathers 16 bytes per ray and band and the vector L1 paces it.
+// Bound: the L1's return path (about 23 cycles per gather; 0.87 busy at
+// 1024^2) with the float64 VALU (0.82) beside it, 10.5 instructions per ray
+// and band.  Range-checked buffer loads save the index clamp and the 64-bit
+// address (2-9%).  Four bands per iteration (512^2: two 102, three 93, four
+// 88 us) with four waves per SIMD; half as many waves as one ray per lane.
+// R with its copies: 512^2 x 720 98 -> 88 us, 724^2 x 1016 273 -> 188, 1024^2 x
+// 1432 644 -> 436, 2048^2 x 2048 3.52 -> 2.31 ms (uniform random image).
+template <bool HORIZ>
+__device__ __forceinline__ void ray_pair(const GeomDev& G, const AngleDev& A, double sk,
+                                         const float* __restrict__ img, int lo, int hi, double (&acc)[2]) {
+    const int pitch = HORIZ ? G.pitchXT : G.pitchX;
+    constexpr int U = 4;   // bands per iteration
+    const double sig = A.slope;
+    const double isg = 1.0 / fabs(sig), delta = pair_delta(G, A);
+    double lp = fma((double)lo, sig, split_b0<HORIZ>(G, A, sk));
+    const int rowbytes = pitch * 4;
+    const char* rowp = reinterpret_cast<const char*>(img - PAD) + (size_t)lo * rowbytes;
+    acc[0] = acc[1] = 0.0;
+    auto step = [&](const float (&v)[4], double lpv) {
+        double f, g1, g2;
+        pair_shares(__builtin_amdgcn_fract(lpv), isg, delta, f, g1, g2);
+        const double v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+        const double d12 = v1 - v2;
+        acc[0] += fma(f, v0 - v1, v1);
+        acc[1] += fma(g1, d12, fma(g2, v2 - v3, v3));
+    };
+    int m = lo;
+    for (; m + U <= hi; m += U) {
+        double lpu[U];
+        float v[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            lpu[u] = lp;
+            row_load<float, 4>(row_rsrc(rowp + u * rowbytes, rowbytes), (unsigned)(int)lp, v[u]);
+            lp += sig;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) step(v[u], lpu[u]);
+        rowp += U * rowbytes;
+    }
+    for (; m < hi; ++m) {
+        float v[4];
+        row_load<float, 4>(row_rsrc(rowp, rowbytes), (unsigned)(int)lp, v);
+        step(v, lp);
+        lp += sig;
+        rowp += rowbytes;
+    }
+}
+
 // Stores ray (row a, bin k): v = (R x)_{a,k}, or the residual r = R x - b when
-// b != nullptr, with the float64 sum of r^2 over the workgroup in
-// partials[pidx].  The value goes, rounded to float32, to out[a*out_pitch + k];
-// the padded sinograms that feed R^T get it times the angle's wmax (see
-// bp_class), rounded to float32 in outp[a*pitchB + PAD + k] and unrounded in
-// the float64 outpd (each nullable).  With dq (and no b), the workgroup's sum
-// of v dq[a*nB + k] goes to partials[pidx] instead; wout (nullable) receives v
-// unrounded at a*nB + k.
-__device__ __forceinline__ void project_store(const GeomDev& G, int a, double wmax, int k,
-                                              bool valid, double acc,
-                                              const float* __restrict__ b, float* __restrict__ out,
-                                              int out_pitch, float* __restrict__ outp,
-                                              double* __restrict__ outpd,
-                                              double* __restrict__ partials, int pidx,
-                                              const double* __restrict__ dq,
-                                              double* __restrict__ wout) {
-    __shared__ double red[4];
+// o.b != nullptr.  The value goes, rounded to float32, to o.out[a*nB + k]; the
+// padded sinogram that feeds R^T gets it times the angle's wmax (see bp_class)
+// unrounded in o.outpd[a*pitchB + PAD + k]; o.wout receives v unrounded at
+// a*nB + k (each nullable).  Returns the ray's term of the workgroup's float64
+// partial: r^2, or with dq (and no b) v dq[a*nB + k].
+__device__ __forceinline__ double project_value(const GeomDev& G, int a, double wmax, int k,
+                                                bool valid, double acc, const RayOut& o) {
     double r2 = 0.0;
     if (valid) {
         double v;
         const size_t i = (size_t)a * G.nB + k;
-        if (b) {
-            v = fma(acc, G.pixel, -(double)b[i]);
+        if (o.b) {
+            v = fma(acc, G.pixel, -(double)o.b[i]);
             r2 = v * v;
         } else {
             v = acc * G.pixel;
-            if (dq) r2 = v * dq[i];
+            if (o.dq) r2 = v * o.dq[i];
         }
-        if (out) out[(size_t)a * out_pitch + k] = (float)v;
-        if (wout) wout[i] = v;
-        const double vs = v * wmax;
-        if (outp) outp[(size_t)a * G.pitchB + PAD + k] = (float)vs;
-        if (outpd) outpd[(size_t)a * G.pitchB + PAD + k] = vs;
+        if (o.out) o.out[i] = (float)v;
+        if (o.wout) o.wout[i] = v;
+        if (o.outpd) o.outpd[(size_t)a * G.pitchB + PAD + k] = v * wmax;
     }
-    if (b || dq) {
-        const double tot = block_sum(r2, red);
-        if (threadIdx.x == 0) partials[pidx] = tot;
-    }
+    return r2;
+}
+// The workgroup's partial (its first 256 threads; the others have ended).
+__device__ __forceinline__ void project_partial(double r2, const RayOut& o, int pidx) {
+    __shared__ double red[4];
+    if (!o.b && !o.dq) return;
+    const double tot = block_sum(r2, red);
+    if (threadIdx.x == 0) o.partials[pidx] = tot;
 }
 
-// Rays of ray workgroup wg: its wave w runs entry 4 wg + w of the wave table
-// (lane l one ray of it, see WaveDev).  With seg == nullptr each ray is summed
-// whole and stored by project_store (partials index wg).  Otherwise
-// (G.parts > 1) only part `part` of each ray is summed and its float64 value
-// goes to seg[(part*nA + ai)*nB + k] (ai: class-sorted table index); the
-// combine step adds the parts in order.  Splitting the rays keeps the image
-// rows that the resident waves read close together and makes the work items
-// shorter and more even.
+// The rays of one lane of R, and the wave's common step range.  T: the type of
+// the padded copies, and with it the form: one ray from float64 copies, two
+// neighbouring ones, k and k + 1, from float32 ones (one for axis-parallel
+// angles).
+template <class T>
+struct LaneRays {
+    static constexpr bool PAIR = sizeof(T) == 4;
+    AngleDev A;
+    int ai, k, flags, lo, hi;
+    bool valid, valid2;
+    double s0, s1;
+
+    // Entry wi of the form's wave table of nw entries (lane l one or two of its
+    // rays, see WaveDev).
+    __device__ __forceinline__ void set(const GeomDev& G, const AngleDev* __restrict__ ang,
+                                        const WaveDev* __restrict__ waves, int wi, int nw) {
+        const bool wvalid = wi < nw;
+        const WaveDev W = waves[wvalid ? wi : 0];
+        flags = ang[W.a0].flags;   // the wave's class (wave-uniform)
+        const bool two = PAIR && !(flags & ANG_AXIS);
+        valid = wvalid && (two ? wave_pair(W, threadIdx.x & 63, G.nB, ai, k)
+                               : wave_ray(W, threadIdx.x & 63, G.nB, ai, k));
+        if (!valid) {   // no ray: a valid angle of the wave's class, summing nothing
+            ai = W.a0;
+            k = 0;
+        }
+        valid2 = two && valid && k + 1 < G.nB;
+        A = ang[ai];
+        s0 = bin_pos((double)k, G);
+        s1 = bin_pos((double)(k + 1), G);
+        int l, h;
+        auto steps = [&](double s, int& a, int& b) {
+            if (flags & ANG_HORIZ) ray_steps<true>(G, A, s, a, b);
+            else ray_steps<false>(G, A, s, a, b);
+        };
+        steps(s0, l, h);
+        if (PAIR && valid2) {   // the union of the two rays' nonempty ranges
+            int l1, h1;
+            steps(s1, l1, h1);
+            if (l1 < h1) {
+                h = l < h ? max(h, h1) : h1;
+                l = l < h ? min(l, l1) : l1;
+            }
+        }
+        wave_range(l, h, valid, (flags & ANG_HORIZ) ? G.cols : G.rows, lo, hi);
+    }
+
+    // Sums of the rays over part `part` of np of the steps; SEQ: over all np, one
+    // part after another.
+    template <bool SEQ>
+    __device__ __forceinline__ void sum(const GeomDev& G, const T* __restrict__ xp, const T* __restrict__ xTp,
+                                        int part, int np, double (&acc)[2]) const {
+        auto parts = [&](auto walk) {   // walk(l, h, v): u-weighted sums over [l, h) (see chord_u)
+            if constexpr (SEQ) {
+                acc[0] = acc[1] = -0.0;   // (-0 + v is v)
+#pragma unroll 1
+                for (int p = 0; p < np; ++p) {
+                    int l = lo, h = hi;
+                    part_range(l, h, p, np);
+                    double v[2] = {0.0, 0.0};
+                    if (l < h) walk(l, h, v);
+                    acc[0] += v[0] * A.wmax;
+                    acc[1] += v[1] * A.wmax;
+                }
+            } else {
+                int l = lo, h = hi;
+                part_range(l, h, part, np);
+                acc[0] = acc[1] = 0.0;
+                if (l < h) walk(l, h, acc);
+                acc[0] *= A.wmax;
+                acc[1] *= A.wmax;
+            }
+        };
+        const bool horiz = flags & ANG_HORIZ;
+        if (flags & ANG_AXIS) {
+            if (horiz) parts([&](int l, int h, double (&v)[2]) { v[0] = ray_sum_axis<true>(G, A, s0, xTp + PAD, l, h); });
+            else parts([&](int l, int h, double (&v)[2]) { v[0] = ray_sum_axis<false>(G, A, s0, xp + PAD, l, h); });
+        } else if constexpr (PAIR) {
+            auto pair = [&](auto hz, const T* img) {
+                constexpr bool H = decltype(hz)::value;
+                const bool sw = pair_swap<H>(A);
+                parts([&](int l, int h, double (&v)[2]) {
+                    double w[2];
+                    ray_pair<H>(G, A, sw ? s1 : s0, img, l, h, w);
+                    v[0] = sw ? w[1] : w[0];
+                    v[1] = sw ? w[0] : w[1];
+                });
+            };
+            if (horiz) pair(std::true_type{}, xTp + PAD);
+            else pair(std::false_type{}, xp + PAD);
+        } else {
+            if (horiz) parts([&](int l, int h, double (&v)[2]) { v[0] = ray_split<true>(G, A, s0, xTp + PAD, l, h); });
+            else parts([&](int l, int h, double (&v)[2]) { v[0] = ray_split<false>(G, A, s0, xp + PAD, l, h); });
+        }
+    }
+
+    // Stores the rays whose whole sums are acc (partials index pidx).
+    __device__ __forceinline__ void store(const GeomDev& G, const double (&acc)[2], const RayOut& o, int pidx) const {
+        double r2 = project_value(G, A.row, A.wmax, k, valid, acc[0], o);
+        if (PAIR) r2 += project_value(G, A.row, A.wmax, k + 1, valid2, acc[1], o);
+        project_partial(r2, o, pidx);
+    }
+};
+
+// Parts, waves and ray workgroups of the form that copies of type T take.
+template <class T>
+__host__ __device__ inline int ray_parts(const GeomDev& G) { return sizeof(T) == 4 ? G.fparts : G.parts; }
+template <class T>
+__host__ __device__ inline int ray_waves(const GeomDev& G) { return sizeof(T) == 4 ? G.fwaves : G.nwaves; }
+template <class T>
+inline int ray_wgs(const GeomDev& G) { return sizeof(T) == 4 ? G.fwg : G.nwg; }
+
+// Rays of ray workgroup wg (entries 4 wg .. 4 wg + 3 of the wave table), whole.
+// With at most WG_PARTS parts a workgroup has four waves per part: waves 4 p ..
+// sum part p, and the parts are added in order through LDS (no pass over
+// memory, no second launch).  The batched form (SEQ) has one wave per table
+// entry, which sums the parts one after another: the same sums.
+template <bool SEQ, class T>
 __device__ __forceinline__ void project_body(const GeomDev& G, const AngleDev* __restrict__ ang,
                                              const WaveDev* __restrict__ waves,
-                                             const double* __restrict__ xp,
-                                             const double* __restrict__ xTp,
-                                             const float* __restrict__ b, float* __restrict__ out,
-                                             int out_pitch, float* __restrict__ outp,
-                                             double* __restrict__ outpd,
-                                             double* __restrict__ partials,
-                                             double* __restrict__ seg, int wg, int part,
-                                             const double* __restrict__ dq = nullptr,
-                                             double* __restrict__ wout = nullptr) {
-    const int wi = 4 * wg + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool wvalid = wi < G.nwaves;
-    const WaveDev W = waves[wvalid ? wi : 0];
-    int ai, k;
-    bool valid = wvalid && wave_ray(W, threadIdx.x & 63, G.nB, ai, k);
-    if (!valid) {   // no ray: a valid angle of the wave's class, summing nothing
-        ai = W.a0;
-        k = 0;
-    }
-    const AngleDev A = ang[ai];
-    const int flags = ang[W.a0].flags;   // the wave's class (wave-uniform)
-    const double sk = bin_pos((double)k, G);
-    const int np = seg ? G.parts : 1;
-    double acc;
-    if (!(flags & ANG_HORIZ)) {
-        acc = (flags & ANG_AXIS) ? ray_sum_axis<false>(G, A, sk, xp + PAD, valid, part, np)
-                                 : ray_split<false>(G, A, sk, xp + PAD, valid, part, np);
+                                             const T* __restrict__ xp,
+                                             const T* __restrict__ xTp,
+                                             const RayOut& o, int wg) {
+    constexpr int NR = LaneRays<T>::PAIR ? 2 : 1;
+    __shared__ double parts[WG_PARTS - 1][NR][256];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int np = ray_parts<T>(G);
+    LaneRays<T> R;
+    R.set(G, ang, waves, 4 * wg + (w & 3), ray_waves<T>(G));
+    double acc[2];
+    if constexpr (SEQ) {
+        R.template sum<true>(G, xp, xTp, 0, np, acc);
     } else {
-        acc = (flags & ANG_AXIS) ? ray_sum_axis<true>(G, A, sk, xTp + PAD, valid, part, np)
-                                 : ray_split<true>(G, A, sk, xTp + PAD, valid, part, np);
+        R.template sum<false>(G, xp, xTp, w >> 2, np, acc);
+        if (np > 1) {
+            const int t = threadIdx.x & 255;
+            if (w >= 4) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) parts[(w >> 2) - 1][r][t] = acc[r];
+            }
+            __syncthreads();
+            if (w >= 4) return;
+            for (int p = 1; p < np; ++p) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) acc[r] += parts[p - 1][r][t];
+            }
+        }
     }
-    acc *= A.wmax;   // the ray sums u-weighted values (see chord_u)
-    if (seg) {
-        if (valid) seg[((size_t)part * G.nA + ai) * G.nB + k] = acc;
-        return;
-    }
-    project_store(G, A.row, A.wmax, k, valid, acc, b, out, out_pitch, outp, outpd, partials, wg, dq,
-                  wout);
+    R.store(G, acc, o, wg);
+}
+
+// Part `part` of the rays of workgroup wg (more than WG_PARTS parts), to
+// seg[(part*nA + ai)*nB + k] (ai: class-sorted table index); the combine step
+// adds the parts in order.  The parts of a large image run one after another
+// (part the slowest grid index), so the resident waves read a band of it.
+template <class T>
+__device__ __forceinline__ void project_part_body(const GeomDev& G, const AngleDev* __restrict__ ang,
+                                                  const WaveDev* __restrict__ waves,
+                                                  const T* __restrict__ xp,
+                                                  const T* __restrict__ xTp,
+                                                  double* __restrict__ seg, int wg, int part) {
+    LaneRays<T> R;
+    R.set(G, ang, waves, 4 * wg + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ray_waves<T>(G));
+    double acc[2];
+    R.template sum<false>(G, xp, xTp, part, ray_parts<T>(G), acc);
+    double* v = seg + ((size_t)part * G.nA + R.ai) * G.nB + R.k;
+    if (R.valid) v[0] = acc[0];
+    if (R.PAIR && R.valid2) v[1] = acc[1];
 }
 
 // Sum of the parts of the rays of combine block (bx, by): angle bx of the
 // class-sorted table, 256-bin chunk by; then the store (partials index
 // by * gx + bx).
 __device__ __forceinline__ void project_comb_body(const GeomDev& G, const AngleDev* __restrict__ ang,
-                                                  const double* __restrict__ seg,
-                                                  const float* __restrict__ b,
-                                                  float* __restrict__ out, int out_pitch,
-                                                  float* __restrict__ outp,
-                                                  double* __restrict__ outpd,
-                                                  double* __restrict__ partials, int bx, int by,
-                                                  int gx, const double* __restrict__ dq = nullptr,
-                                                  double* __restrict__ wout = nullptr) {
-    const int a = ang[bx].row;
+                                                  const double* __restrict__ seg, const RayOut& o,
+                                                  int parts, int bx, int by, int gx) {
     const double wmax = ang[bx].wmax;
     const int k = by * 256 + threadIdx.x;
     const bool valid = k < G.nB;
@@ -446,83 +602,88 @@ __device__ __forceinline__ void project_comb_body(const GeomDev& G, const AngleD
     if (valid) {
         const double* v = seg + (size_t)bx * G.nB + k;
         const size_t stride = (size_t)G.nA * G.nB;
-        for (int j = 0; j < G.parts; ++j) acc += v[j * stride];
+        for (int j = 0; j < parts; ++j) acc += v[j * stride];
     }
-    project_store(G, a, wmax, k, valid, acc, b, out, out_pitch, outp, outpd, partials,
-                  by * gx + bx, dq, wout);
+    project_partial(project_value(G, ang[bx].row, wmax, k, valid, acc, o), o, by * gx + bx);
 }
 
-__global__ __launch_bounds__(256, 8) void k_project(GeomDev G, const AngleDev* __restrict__ ang,
-                                                 const WaveDev* __restrict__ waves,
-                                                 const double* __restrict__ xp,
-                                                 const double* __restrict__ xTp,
-                                                 const float* __restrict__ b,
-                                                 float* __restrict__ out, int out_pitch,
-                                                 float* __restrict__ outp,
-                                                 double* __restrict__ outpd,
-                                                 double* __restrict__ partials,
-                                                 const int* __restrict__ ord,
-                                                 const int* __restrict__ halt,
-                                                 const double* __restrict__ dq,
-                                                 double* __restrict__ wout) {
+// 256 threads per part (at most WG_PARTS), one workgroup per ray workgroup.
+template <class T>
+__global__ __launch_bounds__(256 * WG_PARTS, sizeof(T) == 4 ? 4 : 8) void k_project(GeomDev G, const AngleDev* __restrict__ ang,
+                                                              const WaveDev* __restrict__ waves,
+                                                              const T* __restrict__ xp,
+                                                              const T* __restrict__ xTp,
+                                                              RayOut o, const int* __restrict__ ord,
+                                                              const int* __restrict__ halt) {
     if (halt && *halt) return;
-    project_body(G, ang, waves, xp, xTp, b, out, out_pitch, outp, outpd, partials, nullptr,
-                 ord[blockIdx.x], 0, dq, wout);
+    project_body<false, T>(G, ang, waves, xp, xTp, o, ord[blockIdx.x]);
 }
 
 // grid (ray workgroups, parts): blockIdx.y is the part, so the parts run in order.
-__global__ __launch_bounds__(256, 8) void k_project_part(GeomDev G, const AngleDev* __restrict__ ang,
+template <class T>
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 8) void k_project_part(GeomDev G, const AngleDev* __restrict__ ang,
                                                       const WaveDev* __restrict__ waves,
-                                                      const double* __restrict__ xp,
-                                                      const double* __restrict__ xTp,
+                                                      const T* __restrict__ xp,
+                                                      const T* __restrict__ xTp,
                                                       double* __restrict__ seg,
                                                       const int* __restrict__ ord,
                                                       const int* __restrict__ halt) {
     if (halt && *halt) return;
-    project_body(G, ang, waves, xp, xTp, nullptr, nullptr, 0, nullptr, nullptr, nullptr, seg,
-                 ord[blockIdx.x], blockIdx.y);
+    project_part_body<T>(G, ang, waves, xp, xTp, seg, ord[blockIdx.x], blockIdx.y);
 }
 
 __global__ __launch_bounds__(256) void k_project_comb(GeomDev G, const AngleDev* __restrict__ ang,
-                                                      const double* __restrict__ seg,
-                                                      const float* __restrict__ b,
-                                                      float* __restrict__ out, int out_pitch,
-                                                      float* __restrict__ outp,
-                                                      double* __restrict__ outpd,
-                                                      double* __restrict__ partials,
-                                                      const int* __restrict__ halt,
-                                                      const double* __restrict__ dq,
-                                                      double* __restrict__ wout) {
+                                                      const double* __restrict__ seg, RayOut o, int parts,
+                                                      const int* __restrict__ halt) {
     if (halt && *halt) return;
-    project_comb_body(G, ang, seg, b, out, out_pitch, outp, outpd, partials, blockIdx.x,
-                      blockIdx.y, gridDim.x, dq, wout);
+    project_comb_body(G, ang, seg, o, parts, blockIdx.x, blockIdx.y, gridDim.x);
 }
 
 // residual: rpd = R xh - b (float64) with f partials; else w = R z (float64)
-// with the partials of w^T q, both into pf.  Item lin = part * G.nwg + i runs
-// ray workgroup S.pord[i].
+// with the partials of w^T q, both into pf.
+__device__ __forceinline__ RayOut batch_out(const SliceDev& S, bool residual) {
+    RayOut o;
+    o.partials = gmem(S.pf);
+    if (residual) {
+        o.b = gmem(S.b);
+        o.outpd = gmem(S.rpd);
+    } else {
+        o.dq = gmem(S.q);
+        o.wout = gmem(S.w);
+    }
+    return o;
+}
+
+// The slices with at most WG_PARTS parts: item lin runs ray workgroup lin of the
+// order, whole.  Apart from the split slices' body, and with the loop over the
+// parts inside each walk, it fits eight waves per SIMD (one kernel for both,
+// six: 16 slices of 128^2 to 512^2 246 -> 217 us; part sums through memory and
+// a second launch 223 + 22).
 __global__ __launch_bounds__(256, 8) void kb_project(const SliceDev* __restrict__ sl, ItemTable t,
                                                   int residual) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
-        if (gmem(S.sc)->halt) return;
+        if (S.G.parts > WG_PARTS || gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
-        if (G.parts > 1) {
-            project_body(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), nullptr, nullptr,
-                         0, nullptr, nullptr, nullptr, gmem(S.seg), cmem(S.pord)[lin % G.nwg],
-                         lin / G.nwg);
-        } else if (residual) {
-            project_body(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), gmem(S.b), nullptr,
-                         0, nullptr, gmem(S.rpd), gmem(S.pf), nullptr, cmem(S.pord)[lin], 0);
-        } else {
-            project_body(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), nullptr, nullptr,
-                         0, nullptr, nullptr, gmem(S.pf), nullptr, cmem(S.pord)[lin], 0, gmem(S.q),
-                         gmem(S.w));
-        }
+        project_body<true, double>(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), batch_out(S, residual),
+                                   cmem(S.pord)[lin]);
     });
 }
 
-// The combine step of the slices with G.parts > 1; virtual block by * nA + bx.
+// The others: item lin = part * (ray workgroups) + i runs that part of ray
+// workgroup i of the order.
+__global__ __launch_bounds__(256, 8) void kb_project_part(const SliceDev* __restrict__ sl, ItemTable t) {
+    for_items(t, [&](int s, int lin) {
+        const SliceDev& S = sl[s];
+        if (S.G.parts <= WG_PARTS || gmem(S.sc)->halt) return;
+        const GeomDev G = S.G;
+        project_part_body<double>(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), gmem(S.seg),
+                                  cmem(S.pord)[lin % G.nwg], lin / G.nwg);
+    });
+}
+
+// The combine step of the slices with more than WG_PARTS parts; virtual block
+// by * nA + bx.
 __global__ __launch_bounds__(256) void kb_project_comb(const SliceDev* __restrict__ sl, ItemTable t,
                                                        int residual) {
     for_items(t, [&](int s, int lin) {
@@ -530,37 +691,45 @@ __global__ __launch_bounds__(256) void kb_project_comb(const SliceDev* __restric
         if (gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         const int gx = G.nA;
-        if (residual)
-            project_comb_body(G, cmem(S.ang), gmem(S.seg), gmem(S.b), nullptr, 0, nullptr,
-                              gmem(S.rpd), gmem(S.pf), lin % gx, lin / gx, gx);
-        else
-            project_comb_body(G, cmem(S.ang), gmem(S.seg), nullptr, nullptr, 0, nullptr, nullptr,
-                              gmem(S.pf), lin % gx, lin / gx, gx, gmem(S.q), gmem(S.w));
+        project_comb_body(G, cmem(S.ang), gmem(S.seg), batch_out(S, residual), G.parts, lin % gx, lin / gx, gx);
     });
 }
 
-void launch_project_b(hipStream_t st, const SliceDev* sl, ItemTable t, ItemTable tc,
-                      bool residual) {
-    hipLaunchKernelGGL(kb_project, dim3(t.grid), dim3(256), 0, st, sl, t, residual ? 1 : 0);
-    if (tc.n > 0)
-        hipLaunchKernelGGL(kb_project_comb, dim3(tc.grid), dim3(256), 0, st, sl, tc,
-                           residual ? 1 : 0);
+void launch_project_b(hipStream_t st, const SliceDev* sl, ItemTable t, ItemTable tc, bool residual) {
+    const int r = residual ? 1 : 0;
+    hipLaunchKernelGGL(kb_project, dim3(t.grid), dim3(256), 0, st, sl, t, r);
+    if (tc.n > 0) {
+        hipLaunchKernelGGL(kb_project_part, dim3(t.grid), dim3(256), 0, st, sl, t);
+        hipLaunchKernelGGL(kb_project_comb, dim3(tc.grid), dim3(256), 0, st, sl, tc, r);
+    }
+}
+
+template <class T>
+void launch_project_form(hipStream_t st, const GeomDev& G, const AngleDev* ang, const WaveDev* waves,
+                         const T* xp, const T* xTp, const RayOut& o, double* seg, const int* ord,
+                         const int* halt) {
+    const int parts = ray_parts<T>(G);
+    if (parts > WG_PARTS) {
+        hipLaunchKernelGGL((k_project_part<T>), dim3(ray_wgs<T>(G), parts), dim3(256), 0, st, G, ang, waves, xp,
+                           xTp, seg, ord, halt);
+        hipLaunchKernelGGL(k_project_comb, dim3(G.nA, (G.nB + 255) / 256), dim3(256), 0, st, G,
+                           ang, (const double*)seg, o, parts, halt);
+        return;
+    }
+    hipLaunchKernelGGL((k_project<T>), dim3(ray_wgs<T>(G)), dim3(256 * parts), 0, st, G, ang, waves, xp, xTp, o, ord,
+                       halt);
 }
 
 void launch_project(hipStream_t st, const GeomDev& G, const AngleDev* ang, const WaveDev* waves,
-                    const double* xp, const double* xTp, const float* b, float* out, int out_pitch,
-                    float* outp, double* outpd, double* partials, double* seg, const int* ord,
-                    const int* halt, const double* dq, double* wout) {
-    if (G.parts > 1) {
-        hipLaunchKernelGGL(k_project_part, dim3(G.nwg, G.parts), dim3(256), 0, st, G, ang, waves, xp,
-                           xTp, seg, ord, halt);
-        hipLaunchKernelGGL(k_project_comb, dim3(G.nA, (G.nB + 255) / 256), dim3(256), 0, st, G,
-                           ang, (const double*)seg, b, out, out_pitch, outp, outpd, partials, halt,
-                           dq, wout);
-        return;
-    }
-    hipLaunchKernelGGL(k_project, dim3(G.nwg), dim3(256), 0, st, G, ang, waves, xp, xTp, b, out,
-                       out_pitch, outp, outpd, partials, ord, halt, dq, wout);
+                    const double* xp, const double* xTp, const RayOut& o, double* seg, const int* ord,
+                    const int* halt) {
+    launch_project_form<double>(st, G, ang, waves, xp, xTp, o, seg, ord, halt);
+}
+
+void launch_project32(hipStream_t st, const GeomDev& G, const AngleDev* ang, const WaveDev* waves,
+                      const float* zp, const float* zTp, const RayOut& o, double* seg, const int* ord,
+                      const int* halt) {
+    launch_project_form<float>(st, G, ang, waves, zp, zTp, o, seg, ord, halt);
 }
 
 // Padded copy of a caller's sinogram for R^T, each row times its angle's wmax
@@ -656,14 +825,25 @@ __device__ __forceinline__ void split_range(int beg, int end, int w, int n, int&
     e = beg + (len * (w + 1)) / n;
 }
 
+// Where R^T's image goes: float32 (f), or float64 (d), there rounded to a
+// float32 value with round.
+struct BpOut {
+    float* f;
+    double* d;
+    bool round;
+    __device__ __forceinline__ void put(size_t p, double v) const {
+        if (d) d[p] = round ? (double)(float)v : v;
+        else f[p] = (float)v;
+    }
+};
+
 // out[i][j] = (R^T y)_{ij} from the padded sinogram yp.  A workgroup owns an
 // 8 x 8PX pixel tile (PX pixels, 8 columns apart, per lane); its wave w sums
 // the w-th quarter of every angle class, and the four partial sums are added
 // in wave order through LDS.
 template <int NB, class TY, int PX>
 __device__ __forceinline__ void backproject_body(const GeomDev& G, const AngleDev* __restrict__ ang,
-                                                 const TY* __restrict__ yp,
-                                                 float* __restrict__ out, int bx, int by) {
+                                                 const TY* __restrict__ yp, BpOut out, int bx, int by) {
     __shared__ double part[BP_SPLIT][PX][64];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -690,7 +870,7 @@ __device__ __forceinline__ void backproject_body(const GeomDev& G, const AngleDe
             const int j = j0 + 8 * u;
             const double tot =
                 ((part[0][u][lane] + part[1][u][lane]) + part[2][u][lane]) + part[3][u][lane];
-            if (i < G.rows && j < G.cols) out[(size_t)i * G.cols + j] = (float)(tot * G.pixel);
+            if (i < G.rows && j < G.cols) out.put((size_t)i * G.cols + j, tot * G.pixel);
         }
     }
 }
@@ -832,7 +1012,7 @@ __device__ __forceinline__ void bp_quads(const GeomDev& G, const BpAngle* __rest
 template <class TY, int PX, int NW, int NQ>
 __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* __restrict__ ang,
                                              const BpAngle* __restrict__ quad, const TY* __restrict__ yp,
-                                             float* __restrict__ out, int id) {
+                                             BpOut out, int id) {
     extern __shared__ double part[];   // [shares][NQ][PX][64]
     const int gx = (G.cols + NQ * BPQ_TILE - 1) / (NQ * BPQ_TILE), gy = (G.rows + BPQ_TILE - 1) / BPQ_TILE;
     const int diag = PX == 2 && id >= gx * gy ? 1 : 0;
@@ -878,7 +1058,7 @@ __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* _
         double tot = part[m * 64 + lane];
         for (int sh = 1; sh < shares; ++sh) tot += part[(sh * NQ * PX + m) * 64 + lane];
         const int i = i0 + (p >> 1), j = j0 + n * BPQ_TILE + (p & 1);
-        if (i < G.rows && j < G.cols) out[(size_t)i * G.cols + j] = (float)(tot * G.pixel);
+        if (i < G.rows && j < G.cols) out.put((size_t)i * G.cols + j, tot * G.pixel);
     }
 }
 
@@ -891,8 +1071,7 @@ __device__ __forceinline__ void run_ride(const ScalarRide& ride) {
 
 template <int NB, class TY, int PX>
 __global__ __launch_bounds__(256) void k_backproject(GeomDev G, const AngleDev* __restrict__ ang,
-                                                     const TY* __restrict__ yp,
-                                                     float* __restrict__ out,
+                                                     const TY* __restrict__ yp, BpOut out,
                                                      ScalarRide ride,
                                                      const int* __restrict__ halt) {
     if (halt && *halt) return;
@@ -905,8 +1084,8 @@ __global__ __launch_bounds__(256) void k_backproject(GeomDev G, const AngleDev* 
 template <class TY, int PX, int NW, int NQ>
 __global__ __launch_bounds__(64 * NW) void k_backproject_quad(GeomDev G, const AngleDev* __restrict__ ang,
                                                               const BpAngle* __restrict__ quad,
-                                                              const TY* __restrict__ yp,
-                                                              float* __restrict__ out, ScalarRide ride,
+                                                              const TY* __restrict__ yp, BpOut out,
+                                                              ScalarRide ride,
                                                               const int* __restrict__ halt) {
     if (halt && *halt) return;
     bp_quad_body<TY, PX, NW, NQ>(G, ang, quad, yp, out, blockIdx.x);
@@ -920,14 +1099,15 @@ __global__ __launch_bounds__(64 * NW) void k_backproject_quad(GeomDev G, const A
 // the batch (extra candidates weigh exactly 0).  Each of this kernel and the
 // two of kb_backproject_quad sums the slices of its own form.
 template <int NB, int PX>
-__global__ __launch_bounds__(256) void kb_backproject(const SliceDev* __restrict__ sl, ItemTable t) {
+__global__ __launch_bounds__(256) void kb_backproject(const SliceDev* __restrict__ sl, ItemTable t, int round) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
         if (S.G.bp_quad || gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         int bx, by;
         bp_tile_of(lin, (G.cols + 8 * PX - 1) / (8 * PX), (G.rows + BP_TILE - 1) / BP_TILE, bx, by);
-        backproject_body<NB, double, PX>(G, cmem(S.ang), gmem(S.rpd), gmem(S.g), bx, by);
+        backproject_body<NB, double, PX>(G, cmem(S.ang), gmem(S.rpd),
+                                         BpOut{nullptr, gmem(S.g), round != 0}, bx, by);
     });
 }
 
@@ -936,45 +1116,49 @@ __global__ __launch_bounds__(256) void kb_backproject(const SliceDev* __restrict
 // images, last about as long as those of 8 shares; with 4 waves the 16-slice
 // batch of 128^2 to 512^2 was 8% slower than pixel by pixel), 4 for two.
 template <int PX, int NW, int NQ>
-__global__ __launch_bounds__(64 * NW) void kb_backproject_quad(const SliceDev* __restrict__ sl, ItemTable t) {
+__global__ __launch_bounds__(64 * NW) void kb_backproject_quad(const SliceDev* __restrict__ sl, ItemTable t,
+                                                           int round) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
         if (!S.G.bp_quad || S.G.bp_nq != NQ || gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
-        bp_quad_body<double, PX, NW, NQ>(G, cmem(S.ang), cmem(S.quad), gmem(S.rpd), gmem(S.g), lin);
+        bp_quad_body<double, PX, NW, NQ>(G, cmem(S.ang), cmem(S.quad), gmem(S.rpd),
+                                     BpOut{nullptr, gmem(S.g), round != 0}, lin);
     });
 }
 
 template <int PX>
-void launch_bp_b_px(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax) {
+void launch_bp_b_px(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int round) {
     switch (nbmax) {
-    case 1: hipLaunchKernelGGL((kb_backproject<1, PX>), dim3(t.grid), dim3(256), 0, st, sl, t); break;
-    case 2: hipLaunchKernelGGL((kb_backproject<2, PX>), dim3(t.grid), dim3(256), 0, st, sl, t); break;
-    case 3: hipLaunchKernelGGL((kb_backproject<3, PX>), dim3(t.grid), dim3(256), 0, st, sl, t); break;
-    default: hipLaunchKernelGGL((kb_backproject<4, PX>), dim3(t.grid), dim3(256), 0, st, sl, t); break;
+    case 1: hipLaunchKernelGGL((kb_backproject<1, PX>), dim3(t.grid), dim3(256), 0, st, sl, t, round); break;
+    case 2: hipLaunchKernelGGL((kb_backproject<2, PX>), dim3(t.grid), dim3(256), 0, st, sl, t, round); break;
+    case 3: hipLaunchKernelGGL((kb_backproject<3, PX>), dim3(t.grid), dim3(256), 0, st, sl, t, round); break;
+    default: hipLaunchKernelGGL((kb_backproject<4, PX>), dim3(t.grid), dim3(256), 0, st, sl, t, round); break;
     }
 }
 
 template <int PX>
-void launch_bp_b_quads(hipStream_t st, const SliceDev* sl, ItemTable t, int forms) {
+void launch_bp_b_quads(hipStream_t st, const SliceDev* sl, ItemTable t, int forms, int round) {
     if (forms & BP_FORM_QUAD)
         hipLaunchKernelGGL((kb_backproject_quad<PX, 8, 1>), dim3(t.grid), dim3(512),
-                           bp_quad_lds(BPQ_MAX_SHARES, PX, 1), st, sl, t);
+                           bp_quad_lds(BPQ_MAX_SHARES, PX, 1), st, sl, t, round);
     if (forms & BP_FORM_QUAD2)
         hipLaunchKernelGGL((kb_backproject_quad<PX, 4, 2>), dim3(t.grid), dim3(256), bp_quad_lds(4, PX, 2), st, sl,
-                           t);
+                           t, round);
 }
 
-void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms) {
-    if (px == 4) launch_bp_b_quads<4>(st, sl, t, forms);
-    else launch_bp_b_quads<2>(st, sl, t, forms);
+void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms,
+                          bool round) {
+    const int rd = round ? 1 : 0;
+    if (px == 4) launch_bp_b_quads<4>(st, sl, t, forms, rd);
+    else launch_bp_b_quads<2>(st, sl, t, forms, rd);
     if (!(forms & BP_FORM_PIXEL)) return;
-    if (px == 4) launch_bp_b_px<4>(st, sl, t, nbmax);
-    else launch_bp_b_px<2>(st, sl, t, nbmax);
+    if (px == 4) launch_bp_b_px<4>(st, sl, t, nbmax, rd);
+    else launch_bp_b_px<2>(st, sl, t, nbmax, rd);
 }
 
 template <class TY, int PX>
-void launch_bp_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const TY* yp, float* out,
+void launch_bp_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const TY* yp, BpOut out,
                   const int* halt, const ScalarRide& ride) {
     dim3 grid((G.cols + 8 * PX - 1) / (8 * PX), (G.rows + BP_TILE - 1) / BP_TILE);
     switch (G.nbmax) {
@@ -987,7 +1171,7 @@ void launch_bp_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const T
 
 template <class TY, int PX, int NW, int NQ>
 void launch_bp_quad(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
-                    float* out, const int* halt, const ScalarRide& ride) {
+                    BpOut out, const int* halt, const ScalarRide& ride) {
     hipLaunchKernelGGL((k_backproject_quad<TY, PX, NW, NQ>), dim3(backproject_tiles(G, PX)), dim3(64 * NW),
                        bp_quad_lds(G.bp_shares, PX, NQ), st, G, ang, quad, yp, out, ride, halt);
 }
@@ -995,7 +1179,7 @@ void launch_bp_quad(hipStream_t st, const GeomDev& G, const AngleDev* ang, const
 // One wave per share (two tiles per wave go with 4 shares, see backproject_shape).
 template <class TY, int PX>
 void launch_bp_quad_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
-                       float* out, const int* halt, const ScalarRide& ride) {
+                       BpOut out, const int* halt, const ScalarRide& ride) {
     if (G.bp_nq == 2) launch_bp_quad<TY, PX, 4, 2>(st, G, ang, quad, yp, out, halt, ride);
     else if (G.bp_shares == 8) launch_bp_quad<TY, PX, 8, 1>(st, G, ang, quad, yp, out, halt, ride);
     else launch_bp_quad<TY, PX, 16, 1>(st, G, ang, quad, yp, out, halt, ride);
@@ -1003,7 +1187,7 @@ void launch_bp_quad_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, co
 
 template <class TY>
 void launch_bp(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
-               float* out, const int* halt, const ScalarRide& ride) {
+               BpOut out, const int* halt, const ScalarRide& ride) {
     if (G.bp_quad && G.bp_px == 4) launch_bp_quad_px<TY, 4>(st, G, ang, quad, yp, out, halt, ride);
     else if (G.bp_quad) launch_bp_quad_px<TY, 2>(st, G, ang, quad, yp, out, halt, ride);
     else if (G.bp_px == 4) launch_bp_px<TY, 4>(st, G, ang, yp, out, halt, ride);
@@ -1012,12 +1196,13 @@ void launch_bp(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAn
 
 void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
                         const float* yp, float* out, const int* halt, const ScalarRide& ride) {
-    launch_bp(st, G, ang, quad, yp, out, halt, ride);
+    launch_bp(st, G, ang, quad, yp, BpOut{out, nullptr, false}, halt, ride);
 }
 
 void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
-                        const double* yp, float* out, const int* halt, const ScalarRide& ride) {
-    launch_bp(st, G, ang, quad, yp, out, halt, ride);
+                        const double* yp, float* out, double* outd, bool round, const int* halt,
+                        const ScalarRide& ride) {
+    launch_bp(st, G, ang, quad, yp, BpOut{out, outd, round}, halt, ride);
 }
 
 }  // namespace sp

@@ -59,8 +59,11 @@ struct GeomDev {
     int bp_nq;          // 16 x 16 tiles side by side per wave of R^T's blocks (1 or 2)
     int cls[5];         // angle-table class boundaries: vertical, horizontal,
                         // vertical axis, horizontal axis
-    int nwaves;         // waves of R's wave table (see WaveDev)
-    int nwg;            // R's ray workgroups, four waves each: ceil(nwaves / 4)
+    int nwaves;         // waves of R's one-ray wave table (see WaveDev)
+    int nwg;            // its ray workgroups, four waves each: ceil(nwaves / 4)
+    int pair;           // 1: R of a float32 image sums two neighbouring rays per lane (see pair_fits)
+    int fwaves, fwg;    // nwaves and nwg of that two-ray form
+    int fparts;         // its parts
 };
 
 // R^T's constants of one oblique angle for a 2 x 2 block of pixels (G.bp_quad),
@@ -105,7 +108,10 @@ constexpr int BP_FLIP_X = 1, BP_FLIP_Y = 2, BP_VERT = 4, BP_CODE_BITS = 3;
 // Angles are indices of the class-sorted table.
 constexpr int WAVE_BINS = 16;
 constexpr int WAVE_ANGLES = 4;
-enum WaveKind : int32_t { WAVE_BLOCK = 0, WAVE_TAIL = 1, WAVE_ROW = 2 };
+// The two-ray form of R numbers pairs of bins (2 q, 2 q + 1) as q; its
+// oblique waves are WAVE_PAIR_BLOCK and WAVE_PAIR_TAIL, which are WAVE_BLOCK
+// and WAVE_TAIL over the ceil(nB / 2) pairs.
+enum WaveKind : int32_t { WAVE_BLOCK = 0, WAVE_TAIL = 1, WAVE_ROW = 2, WAVE_PAIR_BLOCK = 3, WAVE_PAIR_TAIL = 4 };
 struct WaveDev {
     int32_t a0, k0, aend, tail;
 };
@@ -202,33 +208,50 @@ hipError_t noalloc_scratch(int device, void** ptr);
 // The padded copies of the image (xp, xTp) are float64 widenings of the
 // float32 image or of the solvers' float64 vectors: the forward gathers then
 // feed the float64 FMAs without a conversion per candidate.  The padded
-// sinogram of R p (yp) is float32, that of the residual float64.
+// sinogram of a caller's data (yp) is float32, that of the residual float64.
 void launch_prep(hipStream_t st, const GeomDev& G, const float* x, double* xp, double* xTp,
                  const int* halt);
 void launch_prep(hipStream_t st, const GeomDev& G, const double* x, double* xp, double* xTp,
                  const int* halt);
-// With G.parts > 1, seg (parts * nA * nB float64) receives the per-part sums
-// before they are combined.  outp / outpd: float32 / float64 padded sinograms
-// (nullable); the residual's float64 values feed R^T without a float32
-// rounding (its cancellation in R^T r amplifies that rounding).  waves: the
-// device copy of R's wave table (project_waves); ord: the device copy of
-// project_order(G, ...), the ray workgroup each launched workgroup runs.
-// With dq (nA x nB float64, b == nullptr) the partials are those of
-// (R x)^T dq, and wout (nA x nB float64, nullable) receives R x unrounded.
+// Where R's rays go (each nullable): out float32 [nA][nB]; outpd the padded
+// float64 sinogram R^T reads (the residual's float64 values feed R^T without a
+// float32 rounding: its cancellation in R^T r amplifies that rounding); wout
+// R x unrounded, nA x nB.  With b the values are R x - b and the partials
+// (project_blocks of them) ||R x - b||^2; with dq (nA x nB float64, no b) they
+// are (R x)^T dq.
+struct RayOut {
+    const float* b = nullptr;
+    float* out = nullptr;
+    double* outpd = nullptr;
+    double* partials = nullptr;
+    const double* dq = nullptr;
+    double* wout = nullptr;
+};
+// R's parts that one workgroup sums and adds; with more, seg (parts * nA * nB
+// float64) receives the per-part sums before a second launch adds them.
+constexpr int WG_PARTS = 4;
+// waves: the device copy of R's wave table (project_waves); ord: the device copy of
+// project_order, the ray workgroup each launched workgroup runs.
 void launch_project(hipStream_t st, const GeomDev& G, const AngleDev* ang, const WaveDev* waves,
-                    const double* xp, const double* xTp, const float* b, float* out, int out_pitch,
-                    float* outp, double* outpd, double* partials, double* seg, const int* ord,
-                    const int* halt, const double* dq = nullptr, double* wout = nullptr);
+                    const double* xp, const double* xTp, const RayOut& o, double* seg, const int* ord,
+                    const int* halt);
+// R of a float32 image in the two-ray form, from float32 padded copies (G.pair
+// only); waves and ord: of project_pair_waves.
+void launch_prep32(hipStream_t st, const GeomDev& G, const float* x, float* zp, float* zTp, const int* halt);
+void launch_project32(hipStream_t st, const GeomDev& G, const AngleDev* ang, const WaveDev* waves,
+                      const float* zp, const float* zTp, const RayOut& o, double* seg, const int* ord,
+                      const int* halt);
 // Padded copy of y for R^T with each row scaled by its angle's wmax.
 void launch_pad_sino(hipStream_t st, const GeomDev& G, const AngleDev* ang, const float* y,
                      float* yp);
-// quad: bp_quad_table's entries (with G.bp_quad).  ride: scalar steps
-// workgroup 0 runs after its tile (see ScalarRide).
+// quad: bp_quad_table's entries (with G.bp_quad).  outd != nullptr: the image in
+// float64 there, with round of float32 values, instead of float32 in out.  ride:
+// scalar steps workgroup 0 runs after its tile (see ScalarRide).
 void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
                         const float* yp, float* out, const int* halt,
                         const ScalarRide& ride = ScalarRide{});
 void launch_backproject(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad,
-                        const double* yp, float* out, const int* halt,
+                        const double* yp, float* out, double* outd, bool round, const int* halt,
                         const ScalarRide& ride = ScalarRide{});
 
 // R^T's workgroup: a tile of BP_TILE rows by 8 PX columns, BP_SPLIT waves each
@@ -259,24 +282,29 @@ void bin_sk_fill(const GeomDev& G, double* t);
 int project_wave_count(const GeomDev& G);
 // Writes the entries when out != nullptr; returns their number.
 int project_waves(const GeomDev& G, WaveDev* out);
+// The same of the two-ray form.
+int project_pair_waves(const GeomDev& G, WaveDev* out);
 // Steps a wave of R walks: the union of its lanes' nonempty step ranges.
 long wave_steps(const GeomDev& G, const AngleDev* tab, const WaveDev& W);
-// Dispatch order of R's ray workgroups (G.nwg entries, a permutation):
+// Dispatch order of the ray workgroups of a table of nwaves entries (a permutation):
 // workgroups by decreasing step count, with every other band of n_cu entries
 // reversed so the first workgroups of each compute unit sum to about the same
 // work.  Only the order of the work changes; every sum and its partials index
 // stay the same.
 std::vector<int32_t> project_order(const GeomDev& G, const AngleDev* tab, const WaveDev* waves,
-                                   int n_cu);
+                                   int nwaves, int n_cu);
 // Parts R splits each ray's step range into, chosen from the geometry and the
 // device's wave slots (both the single-slice and the batched solver use it,
-// so their sums agree).
+// so their sums agree): of a float64 image, and of a float32 image in the
+// two-ray form.
+int project32_parts(int nwaves, int resident_waves);
 int project_parts(int rows, int cols, int nwaves, int resident_waves);
-// Combine workgroups (G.parts > 1): one angle by one 256-bin chunk each.
+// Combine workgroups (more than WG_PARTS parts): one angle by one 256-bin chunk each.
 int project_comb_blocks(const GeomDev& G);
-// Number of float64 f partials R's residual form writes: one per combine
-// workgroup when the rays are split in parts, else one per ray workgroup.
+// Number of float64 partials R writes: one per combine workgroup with more than
+// WG_PARTS parts, else one per ray workgroup.
 int project_blocks(const GeomDev& G);
+int project32_blocks(const GeomDev& G);   // of launch_project32
 // R^T workgroups for px pixels per lane: 8 x 8 px pixel tiles, or with G.bp_quad
 // 16 x 16 G.bp_nq pixel tiles of 2 x 2 blocks (px = 4: a lane sums its blocks
 // whole; px = 2: half of them, two workgroups per tile).
@@ -298,13 +326,12 @@ struct FFTPlan {
     double2* S;           // [rows][SP] complex float64 scratch
     const double2* tw;    // [P/2] twiddles exp(-2 pi i k / P)
 };
-// With G, z is also written to R's padded copies xp / xTp of geometry G (as
-// launch_prep of z would write them).
-void launch_precond(hipStream_t st, const FFTPlan& F, double mu, double rho, const float* g,
-                    float* z, const float* dotv, double* partials, const int* halt,
-                    const int* run = nullptr, const GeomDev* G = nullptr, double* xp = nullptr,
-                    double* xTp = nullptr);
-int precond_dot_blocks(const FFTPlan& F);
+// g float32 and z float32, or (gd, zd) both float64; with G (float64 form only) z
+// is also written to R's padded copies xp / xTp of geometry G (as launch_prep of
+// z would write them).
+void launch_precond(hipStream_t st, const FFTPlan& F, double mu, double rho, const float* g, float* z,
+                    const double* gd, double* zd, const int* halt, const int* run = nullptr,
+                    const GeomDev* G = nullptr, double* xp = nullptr, double* xTp = nullptr);
 // Dynamic LDS of an FFT workgroup holding ncol length-P transforms (plus the
 // twiddle table when it fits).
 size_t fft_lds_bytes(int P, int ncol);
@@ -344,7 +371,7 @@ void launch_tv_apply_grad(hipStream_t st, int rows, int cols, const double* src,
                           const float* tb_in, float* tb_out, const Scalars* sc, double* partials,
                           const int* halt);
 
-// cg.hip (p, x and x_{k+1/2} in float64; g, z, h float32)
+// cg.hip (p, g, z, x and x_{k+1/2} in float64)
 int vec_blocks(int n);
 void launch_dot(hipStream_t st, int n, const float* a, const float* b, double* partials,
                 const int* halt);
@@ -354,7 +381,7 @@ void launch_dot(hipStream_t st, int n, const float* a, const float* b, double* p
 // (partials of q^T q, vec_blocks(m) of them), with the beta step (OP_BETA,
 // (R z)^T q from the ndot partials pdot) folded in; pq_blocks(n, m) workgroups.
 int pq_blocks(int n, int m);
-void launch_update_pq_beta(hipStream_t st, int n, int m, const float* z, double* p, const float* g,
+void launch_update_pq_beta(hipStream_t st, int n, int m, const double* z, double* p, const double* g,
                            const double* w, double* q, Scalars* sc, TraceDev tr, const double* pdot,
                            int ndot, double* pgp, double* pqq);
 void launch_update_x_alpha(hipStream_t st, int n, const double* xh, const double* p, double* x,
@@ -363,9 +390,10 @@ void launch_update_x_alpha(hipStream_t st, int n, const double* xh, const double
 void launch_copy(hipStream_t st, int n, const float* src, float* dst, const int* halt);
 void launch_copy(hipStream_t st, int n, const double* src, double* dst, const int* halt);
 // dst = src widened to float64 (src == nullptr: zeros); dst = src rounded to float32
-void launch_widen(hipStream_t st, int n, const float* src, double* dst);
-void launch_narrow(hipStream_t st, int n, const double* src, float* dst);
-void launch_snap(hipStream_t st, int n, const float* src, float* dst, int count, const Scalars* sc);
+void launch_widen(hipStream_t st, int n, const float* src, double* dst, const int* halt = nullptr,
+                  const int* run = nullptr);
+void launch_narrow(hipStream_t st, int n, const double* src, float* dst, const int* halt = nullptr);
+void launch_snap(hipStream_t st, int n, const double* src, float* dst, int count, const Scalars* sc);
 void launch_reduce(hipStream_t st, const double* partials, int np, double* out);
 // x = xh if the run stopped on a breakdown after its initial step; *k_out = k
 // (nullable): the end of a solve that does not return to the host.
@@ -481,11 +509,12 @@ struct SliceDev {
     const float* b;
     const float* x0;   // nullable: zero start
     double *xh, *x, *p;  // iterate, x_{k+1/2} and search direction (float64)
-    float *g, *z, *tb;
+    double *g, *z;      // gradient and M g (float64)
+    float* tb;
     double *q, *w;      // R p and R z, nA x nB (float64)
     double *xp, *xTp;   // float64 padded copies
     double* rpd;        // float64 padded sinogram (residual)
-    double* seg;        // R's per-part ray sums, [parts][nA][nB] (G.parts > 1)
+    double* seg;        // R's per-part ray sums, [parts][nA][nB] (more than WG_PARTS parts)
     const int* pord;    // R's ray-workgroup order (project_order)
     double *pf, *pgp, *pqq, *ptg, *ptt, *pts;   // pf: f, then (R z)^T q
     Scalars* sc;
@@ -494,7 +523,7 @@ struct SliceDev {
 };
 
 // Stage selectors of the batched kernels.
-enum BatchVec : int { BV_XH = 0, BV_X = 1, BV_P = 2, BV_Z = 3 };   // BV_Z: the float32 z
+enum BatchVec : int { BV_XH = 0, BV_X = 1, BV_P = 2, BV_Z = 3 };
 enum BatchStage : int {
     BS_PREP = 0, BS_PROJECT, BS_BACKPROJECT, BS_ROWS, BS_COLS, BS_TV, BS_VEC, BS_SLICE, BS_PROJ_COMB,
     BS_PQ, BS_TVT, BS_TVG, BS_COUNT
@@ -532,7 +561,7 @@ __device__ __forceinline__ const T* cmem(const T* p) {
 }
 
 __device__ __forceinline__ double* batch_vec(const SliceDev& S, int which) {
-    return gmem(which == BV_XH ? S.xh : (which == BV_X ? S.x : S.p));
+    return gmem(which == BV_XH ? S.xh : (which == BV_X ? S.x : (which == BV_Z ? S.z : S.p)));
 }
 
 // projector.hip
@@ -544,7 +573,8 @@ void launch_project_b(hipStream_t st, const SliceDev* sl, ItemTable t, ItemTable
 // forms of R^T among the slices (bp_form).
 enum BpForm : int { BP_FORM_PIXEL = 1, BP_FORM_QUAD = 2, BP_FORM_QUAD2 = 4 };
 inline int bp_form(const GeomDev& G) { return !G.bp_quad ? BP_FORM_PIXEL : (G.bp_nq == 2 ? BP_FORM_QUAD2 : BP_FORM_QUAD); }
-void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms);
+// round: see launch_backproject.
+void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms, bool round);
 // fft.hip (z = M g)
 void launch_precond_b(hipStream_t st, const SliceDev* sl, ItemTable rows, ItemTable cols,
                       size_t lds_rows, size_t lds_cols, double mu, double rho);

@@ -30,6 +30,15 @@ __host__ __device__ inline bool wave_ray(const WaveDev& W, int lane, int nB, int
     return ai < W.aend;
 }
 
+// First ray (ai, k) of lane `lane`'s pair (k, k + 1) in wave W of the two-ray
+// form's oblique kinds; the second ray exists when k + 1 < nB.
+__host__ __device__ inline bool wave_pair(const WaveDev& W, int lane, int nB, int& ai, int& k) {
+    int q;
+    const bool ok = wave_ray(WaveDev{W.a0, W.k0, W.aend, W.tail - WAVE_PAIR_BLOCK}, lane, (nB + 1) / 2, ai, q);
+    k = 2 * q;
+    return ok;
+}
+
 // Fractional minor index where ray (A, sk) crosses the centre line of major
 // step 0 (row 0 for vertical angles, column 0 for horizontal ones), minus the
 // half-width hw of its nonzero band: the axis walk's candidate reference.
@@ -77,6 +86,30 @@ __host__ __device__ inline void ray_steps(const GeomDev& G, const AngleDev& A, d
     const int nmin = HORIZ ? G.rows : G.cols;
     step_range(walk_start<HORIZ>(G, A, sk), A.slope, -(double)(A.nc + 1), (double)(nmin + 1), nmaj,
                lo, hi);
+}
+
+// The two-ray form.  pair_swap: the pair's ray of bin k has the larger padded
+// minor coordinate.  The lower ray walks as ray_split's; the upper one is
+// `delta` further, 1 <= delta < 2, so with j the lower ray's first pixel the
+// two meet at most pixels j .. j + 1 and j + 1 .. j + 3.
+template <bool HORIZ>
+__host__ __device__ inline bool pair_swap(const AngleDev& A) {
+    return HORIZ ? A.s > 0.0 : A.c < 0.0;
+}
+__host__ __device__ inline double pair_delta(const GeomDev& G, const AngleDev& A) { return G.ds * A.wmax; }
+__host__ __device__ inline bool pair_fits(const GeomDev& G, const AngleDev& A) {
+    const double d = pair_delta(G, A);
+    return G.ds >= 1.0 && d >= 1.0 && d < 2.0 - 1e-6;
+}
+// Shares of a band's path length, from the fraction fr of the lower ray's
+// padded minor coordinate and isg = 1 / |slope|: f, of the lower ray in pixel
+// j (the rest in j + 1); g1, of the upper ray in pixels up to j + 1, and g2, up
+// to j + 2 (the rest in j + 3).
+__host__ __device__ inline void pair_shares(double fr, double isg, double delta, double& f, double& g1,
+                                            double& g2) {
+    f = fmin(fmax(fma(fr, -isg, isg), 0.0), 1.0);
+    g1 = fmin(fmax(fma(fr, -isg, (2.0 - delta) * isg), 0.0), 1.0);
+    g2 = fmin(fmax(fma(fr, -isg, (3.0 - delta) * isg), 0.0), 1.0);
 }
 
 // Steps [lo, hi) of part `part` of nparts of a wave's common range [lo, hi).
