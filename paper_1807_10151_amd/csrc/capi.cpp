@@ -35,7 +35,8 @@ struct BatchState {
     int nbmax = 1;
     int bp_px = 2;                   // R^T pixels per lane for the whole batch
     int bp_forms = 0;                // forms of R^T among the slices (bp_form)
-    size_t lds_rows = 0, lds_cols = 0;
+    int fft_threads = 0;             // of the preconditioner's workgroups
+    int fft_forms = 0;               // its forms among the slices (fft_form)
     std::vector<SliceDev> hs;        // host copies; per-call pointers filled in each call
     DevBuf arena, sl, items, scal, trace_d;
     size_t off[BS_COUNT][2] = {};    // item-table offsets (entries) per stage and order
@@ -375,7 +376,7 @@ int setup_fft(sp_ctx* c, FFTPlan& F) {
     F.SP = SP;
     F.rows = g.rows;
     F.cols = g.cols;
-    F.CB = std::max(1, 2048 / P);
+    F.NF = fft_per_group(P, fft_threads(P));
     F.S = dptr<double2>(c->S);
     F.tw = dptr<double2>(c->tw);
     return SP_OK;
@@ -679,11 +680,11 @@ int enqueue_solver_precond(sp_ctx* c, const sp_precond* pc, const double* g, dou
         TraceDev none{};
         launch_scalar(c->stream, OP_LCHECK, sc, none, pg, vec_blocks(n), nullptr, 0);
         launch_widen(c->stream, n, zf, z, halt, &sc->gate_learned);
-        launch_precond(c->stream, F, pc->mu, pc->rho, nullptr, nullptr, g, z, halt, &sc->gate_ramp);
+        launch_precond(c->stream, F, pc->mu, pc->rho, g, z, halt, &sc->gate_ramp);
         launch_prep(c->stream, G, z, xp, xTp, halt);
         return SP_OK;
     }
-    launch_precond(c->stream, F, pc->mu, pc->rho, nullptr, nullptr, g, z, halt, nullptr, &G, xp, xTp);
+    launch_precond(c->stream, F, pc->mu, pc->rho, g, z, halt, nullptr, &G, xp, xTp);
     return SP_OK;
 }
 
@@ -702,8 +703,8 @@ int stage_blocks(const SliceDev& S, int stage) {
     case BS_PROJECT: return G.nwg * (G.parts > WG_PARTS ? G.parts : 1);
     case BS_PROJ_COMB: return G.parts > WG_PARTS ? project_comb_blocks(G) : 0;
     case BS_BACKPROJECT: return backproject_tiles(G, G.bp_px);
-    case BS_ROWS: return (G.rows + 1) / 2;
-    case BS_COLS: return S.F.P ? (S.F.SP + S.F.CB - 1) / S.F.CB : 0;
+    case BS_ROWS: return S.F.P ? ((G.rows + 1) / 2 + S.F.NF - 1) / S.F.NF : (G.rows + 1) / 2;
+    case BS_COLS: return S.F.P ? (S.F.SP + S.F.NF - 1) / S.F.NF : 0;
     case BS_TV: return tv_blocks(G.rows, G.cols);
     case BS_TVT: return tv_tpx_blocks(G.rows, G.cols);
     case BS_TVG: return tv_grad_blocks(G.rows, G.cols);
@@ -791,7 +792,8 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
     for (int s = 0; s < BS_COUNT; ++s) B.order[s] = B.wpc[s] = 0;
     B.hs.assign(n, SliceDev{});
     B.nbmax = 1;
-    B.lds_rows = B.lds_cols = 0;
+    B.fft_threads = 256;   // 512 where a transform needs them
+    B.fft_forms = 0;
     std::vector<std::vector<AngleDev>> tabs(n);
     // sizes
     struct Off {
@@ -815,9 +817,7 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
             S.F.SP = P / 2 + 1;
             S.F.rows = G.rows;
             S.F.cols = G.cols;
-            S.F.CB = std::max(1, 2048 / P);
-            B.lds_rows = std::max(B.lds_rows, fft_lds_bytes(P, 1));
-            B.lds_cols = std::max(B.lds_cols, fft_lds_bytes(P, S.F.CB));
+            B.fft_threads = std::max(B.fft_threads, fft_threads(P));
         }
         S.m = G.nA * G.nB;
         S.nf = project_blocks(G);
@@ -853,7 +853,6 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         o.ptt = take((size_t)S.ntv * 9 * 8);
         o.pts = take((size_t)std::max(S.ntv, S.nsn) * 8);
     }
-    if (B.lds_cols > 65536) return fail(c, SP_ERR_ARG, "FFT column tile exceeds the LDS");
     // one R^T tile shape for the whole batch: four pixels per lane when the
     // batch's 4-pixel tiles still fill half the wave slots (the sums do not
     // depend on it, so batched and single solves stay bitwise equal)
@@ -876,6 +875,11 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         if (all && tpx) B.bp_px = tpx;
         for (SliceDev& S : B.hs) S.G.bp_px = B.bp_px;
     }
+    for (SliceDev& S : B.hs)
+        if (S.F.P) {
+            S.F.NF = fft_per_group(S.F.P, B.fft_threads);
+            B.fft_forms |= fft_form(S.F);
+        }
     // a fresh zero-filled arena: the pads of the padded copies must be zero
     release(B.arena);
     if ((rc = ensure(c, B.arena, total))) return rc;
@@ -981,7 +985,7 @@ void batch_stage(sp_ctx* c, int stage, int order, int wpc, double mu, double rho
     case BS_PROJECT: launch_project_b(st, sl, t, table(c, BS_PROJ_COMB, order, 0), true); break;
     case BS_BACKPROJECT: launch_backproject_b(st, sl, t, B.nbmax, B.bp_px, B.bp_forms, false); break;
     case BS_ROWS:
-        launch_precond_b(st, sl, t, table(c, BS_COLS, order, wpc), B.lds_rows, B.lds_cols, mu, rho);
+        launch_precond_b(st, sl, t, table(c, BS_COLS, order, wpc), B.fft_threads, B.fft_forms, mu, rho);
         break;
     case BS_TV:
         launch_tv_grad_b(st, sl, t, BV_X);
@@ -1043,7 +1047,7 @@ void batch_precond(sp_ctx* c, double mu, double rho) {
     BatchState& B = *c->batch;
     const SliceDev* sl = dptr<SliceDev>(B.sl);
     if (B.kind == SP_PRECOND_RAMP)
-        launch_precond_b(c->stream, sl, table(c, BS_ROWS), table(c, BS_COLS), B.lds_rows, B.lds_cols,
+        launch_precond_b(c->stream, sl, table(c, BS_ROWS), table(c, BS_COLS), B.fft_threads, B.fft_forms,
                          mu, rho);
     else
         launch_copy_gz_b(c->stream, sl, table(c, BS_VEC));
@@ -1558,7 +1562,7 @@ int sp_precond_apply(sp_ctx* c, const sp_geometry* g, const sp_precond* pc, cons
         if ((rc = lp_enqueue_apply(c, const_cast<sp_learned*>(pc->net), 1, g->rows, g->cols, gin, z, nullptr, nullptr)))
             return rc;
     } else {
-        launch_precond(c->stream, F, pc->mu, pc->rho, gin, z, nullptr, nullptr, nullptr);
+        launch_precond(c->stream, F, pc->mu, pc->rho, gin, z, nullptr);
     }
     return check_launch(c);
 }

@@ -322,19 +322,25 @@ int backproject_px(int rows, int cols, int resident_waves);
 
 // fft.hip
 struct FFTPlan {
-    int P, logP, SP, rows, cols, CB;
+    int P, logP, SP, rows, cols;
+    int NF;               // row pairs, and columns, per workgroup
     double2* S;           // [rows][SP] complex float64 scratch
     const double2* tw;    // [P/2] twiddles exp(-2 pi i k / P)
 };
-// g float32 and z float32, or (gd, zd) both float64; with G (float64 form only) z
-// is also written to R's padded copies xp / xTp of geometry G (as launch_prep of
-// z would write them).
+// With G, z is also written to R's padded copies xp / xTp of geometry G (as
+// launch_prep of z would write them).
 void launch_precond(hipStream_t st, const FFTPlan& F, double mu, double rho, const float* g, float* z,
-                    const double* gd, double* zd, const int* halt, const int* run = nullptr,
-                    const GeomDev* G = nullptr, double* xp = nullptr, double* xTp = nullptr);
-// Dynamic LDS of an FFT workgroup holding ncol length-P transforms (plus the
-// twiddle table when it fits).
-size_t fft_lds_bytes(int P, int ncol);
+                    const int* halt, const int* run = nullptr);
+void launch_precond(hipStream_t st, const FFTPlan& F, double mu, double rho, const double* g, double* z,
+                    const int* halt, const int* run = nullptr, const GeomDev* G = nullptr, double* xp = nullptr,
+                    double* xTp = nullptr);
+// The kernels' form: images of one or two pixels a side (P < 8) have their own.
+enum FftForm : int { FFT_FORM_LARGE = 1, FFT_FORM_SMALL = 2 };
+inline int fft_form(const FFTPlan& F) { return F.logP < 3 ? FFT_FORM_SMALL : FFT_FORM_LARGE; }
+// Threads of a workgroup of one image, and the length-P transforms a workgroup of
+// `threads` holds (a batch has one thread count).
+int fft_threads(int P);
+int fft_per_group(int P, int threads);
 
 // tv.hip (images y, x_{k+1/2} and x_k in float64; t_bar float32)
 // t_bar and its ||.||^2 partials: tv_blocks of them for an S_TV call's first
@@ -575,9 +581,9 @@ enum BpForm : int { BP_FORM_PIXEL = 1, BP_FORM_QUAD = 2, BP_FORM_QUAD2 = 4 };
 inline int bp_form(const GeomDev& G) { return !G.bp_quad ? BP_FORM_PIXEL : (G.bp_nq == 2 ? BP_FORM_QUAD2 : BP_FORM_QUAD); }
 // round: see launch_backproject.
 void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms, bool round);
-// fft.hip (z = M g)
-void launch_precond_b(hipStream_t st, const SliceDev* sl, ItemTable rows, ItemTable cols,
-                      size_t lds_rows, size_t lds_cols, double mu, double rho);
+// fft.hip (z = M g); forms: those among the slices (fft_form)
+void launch_precond_b(hipStream_t st, const SliceDev* sl, ItemTable rows, ItemTable cols, int threads, int forms,
+                      double mu, double rho);
 // tv.hip
 void launch_tv_grad_b(hipStream_t st, const SliceDev* sl, ItemTable t, int src);
 void launch_tv_trials_b(hipStream_t st, const SliceDev* sl, ItemTable t, int src);
