@@ -11,19 +11,20 @@
 // [16][16][3][3], d [16]; tap t = 3 ky + kx reads the input at offset
 // (ky - 1, kx - 1).
 //
-// The 16 -> 16 layers run as implicit GEMM on MFMA: a wave computes tiles of
-// 16 consecutive pixels of one image row for all 16 output channels with
-// v_mfma_f32_16x16x4f32 (A = 16 pixels x 4 input channels of one tap,
-// B = 4 input channels x 16 output channels), 9 taps x 4 channel groups =
-// 36 MFMAs per tile.  MFMA cg takes input channel 4 kq + cg from lane group
-// kq, so each lane reads its 4 channels of a pixel as one 16-byte load; a wave
-// keeps the weights in registers over TPW tiles (4 for large grids, 1 for
-// small ones, which need the waves more) with independent
-// accumulators.  The 16 -> 16 weight gradients are MFMA products over the
-// pixels of a tile; the 1 <-> 16 layers, the first layer's weight gradient,
+// The layers run as implicit GEMM on MFMA (v_mfma_f32_16x16x4f32).  16 -> 16: a
+// wave walks strips of 16 columns down the rows, a tile of 16 pixels of a row by
+// the 16 output channels at a time (A = 16 pixels x 4 input channels of one
+// tap, B = 4 input channels x 16 output channels), 9 taps x 4 channel groups =
+// 36 MFMAs per tile.  MFMA cg takes input channel 4 kq + cg from lane group kq,
+// so each lane reads its 4 channels of a pixel as one 16-byte load, and a row's
+// three shifted tiles stay in registers for the three rows that need them.  The
+// 1 -> 16 layer takes the taps as the contracted index, its adjoint the
+// channels.  The weight gradients are MFMA products over the pixels of a tile;
 // the loss and Adam are plain VALU kernels.
 #include "sp_internal.h"
 #include "sp_reduce.h"
+
+#include <algorithm>
 
 namespace sp {
 
@@ -35,12 +36,31 @@ __device__ __forceinline__ bool in_img(int h, int w, int H, int W) {
     return h >= 0 && h < H && w >= 0 && w < W;
 }
 
+// Quotient of a wave-uniform index; 32-bit arithmetic where the index allows it.
+__device__ __forceinline__ unsigned long udiv(unsigned long n, unsigned d) {
+    return n >> 32 ? n / d : (unsigned long)((unsigned)n / d);
+}
+
+// Buffer resource over n pixels of activations from p (reads past either end give
+// 0, writes are dropped).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t act_pixels(const float* p, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, n * LF * 4, 0x00020000);
+}
+
 // ---- 16 -> 16 correlation on MFMA --------------------------------------------
 // out[b,h,w,j] = sum_{t, ci} in[b, h+dy_t, w+dx_t, ci] * K[j][ci][t], with
 // K = W (TRANS = false) or K[j][ci][t] = W[ci][j][8 - t] (TRANS: the adjoint).
 // If scale != nullptr, out2 = scale[j] * out as well.
-template <bool TRANS, int TPW>
-__global__ __launch_bounds__(256) void k_lp_conv_mid(int B, int H, int W,
+//
+// Bound: the MFMAs (36 of 32 cycles per tile of 16 pixels: 7.7 us at 512^2, 31 at
+// 256 x 64^2) and the activations' traffic (27 us there at the copy rate); at
+// 512^2 as much again goes into the launch, the weights' way to the lanes and
+// the last stores.  What stood in between: 64-bit divisions for each tile (now
+// one per strip, uniform), nine loads per tile (three, the next row's under
+// way during a row's MFMAs), a wave's 36 weight loads of 64 cache lines each (now
+// through LDS), rows shared across XCDs.  512^2: 25 -> 17 us; 256 x 64^2: 84 -> 48.
+template <bool TRANS>
+__global__ __launch_bounds__(256) void k_lp_conv_mid(int B, int H, int W, int S,
                                                      const float* __restrict__ in,
                                                      float* __restrict__ out,
                                                      const float* __restrict__ Wl,
@@ -51,78 +71,87 @@ __global__ __launch_bounds__(256) void k_lp_conv_mid(int B, int H, int W,
     if (halt && *halt) return;
     if (run && !*run) return;
     const int lane = threadIdx.x & 63;
-    const int wtiles = (W + 15) >> 4;
-    const long ntiles = (long)B * H * wtiles;
-    const long tile0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * TPW;
-    if (tile0 >= ntiles) return;                    // whole wave; no barriers below
     const int i = lane & 15;     // A row (pixel) / B column (out channel)
     const int kq = lane >> 4;    // A column / B row within a group of 4 input channels
-    float wr[36];
+    const int wtiles = (W + 15) >> 4, hs = (H + S - 1) / S, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long ntasks = (long)B * hs * wtiles, nwaves = (long)gridDim.x * 4;
+    // neighbouring strips on one XCD, whose L2 then serves the rows they share
+    long task = ((long)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 4 + wave;
+    // a task: columns tw .. of rows y0 .. y1 - 1 of an image; all uniform
+    int tw, y0, y1, voff;
+    size_t img;   // element of the image's first pixel
+    f4v a[4][3];  // rows y - 1, y, y + 1 and, on its way, y + 2
+    // the three shifted tiles of row y: channels 4 kq .. 4 kq + 3 of the pixel in one
+    // 16-byte load each
+    auto load = [&](int y, f4v (&v)[3]) {
+        const int x0 = max(tw - 1, 0);
+        const __amdgpu_buffer_rsrc_t row =
+            act_pixels(in + img + ((ptrdiff_t)y * W + x0) * LF, y >= 0 && y < H ? min(W - x0, 18) : 0);
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg) {
-            const int ci = 4 * kq + cg;   // MFMA cg: lane kq supplies input channel 4 kq + cg
-            wr[t * 4 + cg] = TRANS ? Wl[(ci * LF + i) * 9 + (8 - t)] : Wl[(i * LF + ci) * 9 + t];
-        }
+        for (int dx = 0; dx < 3; ++dx)
+            v[dx] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(row, voff + (dx - 1) * LF * 4, 0, 0));
+    };
+    auto begin = [&] {
+        const long br = (long)udiv((unsigned long)task, wtiles), b = (long)udiv((unsigned long)br, hs);
+        tw = (int)(task - br * wtiles) * 16;
+        y0 = (int)(br - b * hs) * S;
+        y1 = min(H, y0 + S);
+        img = (size_t)b * H * W * LF;
+        voff = (((tw > 0 ? 1 : 0) + i) * LF + 4 * kq) * 4;   // from pixel max(tw - 1, 0)
+        load(y0 - 1, a[0]);
+        load(y0, a[1]);
+        load(y0 + 1, a[2]);
+    };
+    if (task < ntasks) begin();   // on its way while the weights are staged
+    // ws[t][lane][cg]: lane's weight of MFMA (t, cg), whose input channel is 4 kq + cg
+    __shared__ float ws[9 * 64 * 4];
+    for (int e = threadIdx.x; e < LF * LF * 9; e += 256) {
+        const int t = e % 9, c1 = e / 9 % LF, c0 = e / (9 * LF);   // Wl[c0][c1][t]
+        const int ci = TRANS ? c0 : c1, co = TRANS ? c1 : c0, tt = TRANS ? 8 - t : t;
+        ws[(tt * 64 + (ci >> 2) * 16 + co) * 4 + (ci & 3)] = Wl[e];
     }
-    // TPW consecutive tiles per wave (weights loaded once, independent
-    // accumulators); tile j = (b, h, w0) of tile0 + j
-    int tb[TPW], th[TPW], tw0[TPW];
-    bool tv[TPW];
+    __syncthreads();
+    f4v wr[9];
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-        const long tile = tile0 + j;
-        tv[j] = tile < ntiles;
-        const long tt = tv[j] ? tile : tile0;
-        tw0[j] = (int)(tt % wtiles) * 16;
-        const long bh = tt / wtiles;
-        th[j] = (int)(bh % H);
-        tb[j] = (int)(bh / H);
-    }
-    f4v acc[TPW];
-#pragma unroll
-    for (int j = 0; j < TPW; ++j) acc[j] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        f4v a[TPW];
-#pragma unroll
-        for (int j = 0; j < TPW; ++j) {
-            const int hh = th[j] + t / 3 - 1;
-            const int ww = tw0[j] + i + t % 3 - 1;
-            const bool ok = tv[j] && in_img(hh, ww, H, W);
-            // channels 4 kq .. 4 kq + 3 of the pixel: one 16-byte load
-            const f4v* p = reinterpret_cast<const f4v*>(
-                in + (((size_t)tb[j] * H + (ok ? hh : 0)) * W + (ok ? ww : 0)) * LF + 4 * kq);
-            a[j] = ok ? *p : f4v{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg) {
-#pragma unroll
-            for (int j = 0; j < TPW; ++j)
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][cg], wr[t * 4 + cg], acc[j], 0, 0, 0);
-        }
-    }
-    // lane holds D[4*(lane>>4) + r][lane & 15]: pixel w0 + 4*kq + r, channel i
+    for (int t = 0; t < 9; ++t) wr[t] = *reinterpret_cast<const f4v*>(&ws[(t * 64 + lane) * 4]);
     const float sc = scale ? scale[i] : 0.0f;
+    while (task < ntasks) {
+        for (int y = y0; y < y1; y += 4) {
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-        if (!tv[j]) continue;
+            for (int u = 0; u < 4; ++u) {
+                if (y + u >= y1) break;
+                if (y + u + 1 < y1) load(y + u + 2, a[(u + 3) & 3]);
+                f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int px = tw0[j] + 4 * kq + r;
-            if (px < W) {
-                const size_t o = (((size_t)tb[j] * H + th[j]) * W + px) * LF + i;
-                if (out) out[o] = acc[j][r];
-                if (out2) out2[o] = acc[j][r] * sc;
+                for (int t = 0; t < 9; ++t) {
+#pragma unroll
+                    for (int cg = 0; cg < 4; ++cg)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[(u + t / 3) & 3][t % 3][cg], wr[t][cg], acc, 0, 0, 0);
+                }
+                // lane holds D[4*(lane>>4) + r][lane & 15]: pixel tw + 4*kq + r, channel i
+                const int off = (4 * kq * LF + i) * 4;
+                auto put = [&](float* dst, float f) {
+                    const __amdgpu_buffer_rsrc_t row = act_pixels(dst + img + ((size_t)(y + u) * W + tw) * LF, min(W - tw, 16));
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, acc[r] * f), row, off + r * LF * 4, 0, 0);
+                };
+                if (out) put(out, 1.0f);
+                if (out2) put(out2, sc);
             }
         }
+        task += nwaves;
+        if (task < ntasks) begin();
     }
 }
 
 // ---- 1 -> 16 (first layer) and its adjoint 16 -> 1 ------------------------------
 // out[b,h,w,co] = sum_t W1[co][t] * in[src(b), h+dy, w+dx]; src(b) = idx[b] if idx.
-__global__ __launch_bounds__(256) void k_lp_conv_in(int B, int H, int W, const float* __restrict__ in,
+// On MFMA as well: 16 pixels x taps (three groups of four, the last three of them
+// zero) by taps x 16 channels, so a pixel costs a lane three loads and the
+// result leaves in whole cache lines.  Bound: the activations written (512^2,
+// 17 MB: 17 us with a pixel per thread before, now 13; 256 x 64^2, 67 MB: 22, 17).
+__global__ __launch_bounds__(256) void k_lp_conv_in(int B, int H, int W, int S, const float* __restrict__ in,
                                                     const int32_t* __restrict__ idx, int nsrc,
                                                     float* __restrict__ out,
                                                     const float* __restrict__ W1,
@@ -130,33 +159,63 @@ __global__ __launch_bounds__(256) void k_lp_conv_in(int B, int H, int W, const f
                                                     const int* __restrict__ run) {
     if (halt && *halt) return;
     if (run && !*run) return;
-    __shared__ float w[LF * 9];
-    for (int q = threadIdx.x; q < LF * 9; q += 256) w[q] = W1[q];
-    __syncthreads();
-    const long p = (long)blockIdx.x * 256 + threadIdx.x;
-    if (p >= (long)B * H * W) return;
-    const int x = (int)(p % W);
-    const long bh = p / W;
-    const int y = (int)(bh % H);
-    const int b = (int)(bh / H);
-    const int src = idx ? min(max(idx[b], 0), nsrc - 1) : b;
-    float v[9];
+    const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+    float wr[3];
+    int dy[3], dx[3];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        const int yy = y + t / 3 - 1, xx = x + t % 3 - 1;
-        v[t] = in_img(yy, xx, H, W) ? in[((size_t)src * H + yy) * W + xx] : 0.0f;
+    for (int s = 0; s < 3; ++s) {
+        const int t = 4 * s + kq;   // (t >= 9: no tap)
+        wr[s] = t < 9 ? W1[i * 9 + t] : 0.0f;
+        dy[s] = t < 9 ? t / 3 - 1 : -(1 << 30);   // outside any image
+        dx[s] = t % 3 - 1;
     }
-    float* o = out + (size_t)p * LF;
+    const int wtiles = (W + 15) >> 4, hs = (H + S - 1) / S, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long ntasks = (long)B * hs * wtiles;
+    const long blk = (long)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);   // as k_lp_conv_mid
+    for (long task = blk * 4 + wave; task < ntasks; task += (long)gridDim.x * 4) {
+        const long br = (long)udiv((unsigned long)task, wtiles), b = (long)udiv((unsigned long)br, hs);
+        const int tw = (int)(task - br * wtiles) * 16, y0 = (int)(br - b * hs) * S, y1 = min(H, y0 + S);
+        const int src = idx ? min(max(idx[b], 0), nsrc - 1) : (int)b;
+        const float* img = in + (size_t)src * H * W;
+        for (int y = y0; y < y1; y += 4) {   // four rows' loads in flight
+            float v[4][3];
 #pragma unroll
-    for (int co = 0; co < LF; ++co) {
-        float s = 0.0f;
+            for (int u = 0; u < 4; ++u) {
 #pragma unroll
-        for (int t = 0; t < 9; ++t) s = fmaf(w[co * 9 + t], v[t], s);
-        o[co] = s;
+                for (int s = 0; s < 3; ++s) {
+                    const bool ok = in_img(y + u + dy[s], tw + i + dx[s], H, W);
+                    const float x = img[ok ? (y + u + dy[s]) * W + tw + i + dx[s] : 0];
+                    v[u][s] = ok ? x : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (y + u >= y1) break;
+                f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int s = 0; s < 3; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][s], wr[s], acc, 0, 0, 0);
+                // lane holds pixel tw + 4 kq + r, channel i
+                const __amdgpu_buffer_rsrc_t row = act_pixels(out + (((size_t)b * H + y + u) * W + tw) * LF, min(W - tw, 16));
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float f = acc[r];   // (a bit cast of the element itself takes element 0)
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, f), row,
+                                                          ((4 * kq + r) * LF + i) * 4, 0, 0);
+                }
+            }
+        }
     }
 }
 
-// out[b,h,w] = sum_co sum_t W1[co][t] * in[b, h-dy, w-dx, co]   (adjoint of k_lp_conv_in)
+// out[b,h,w] = sum_co sum_t W1[co][t] * in[b, h-dy, w-dx, co]   (adjoint of
+// k_lp_conv_in).  A workgroup makes 16 x 16 pixels: each of the 18 x 18 pixels
+// around them is read once and multiplied by all taps on MFMA (16 pixels x 16
+// channels by 16 channels x 9 taps), and the taps are summed through LDS.
+// Bound: the activations read (a thread per pixel gathered each of its 9
+// neighbours' 64 bytes through the vector L1: 512^2 13 -> 6 us, 256 x 64^2
+// 25 -> 15).
+constexpr int LP_OUT = 16, LP_OUTH = LP_OUT + 2;
+
 __global__ __launch_bounds__(256) void k_lp_conv_out(int B, int H, int W, const float* __restrict__ in,
                                                      float* __restrict__ out,
                                                      const float* __restrict__ W1,
@@ -164,31 +223,45 @@ __global__ __launch_bounds__(256) void k_lp_conv_out(int B, int H, int W, const 
                                                      const int* __restrict__ run) {
     if (halt && *halt) return;
     if (run && !*run) return;
-    __shared__ float w[LF * 9];
-    for (int q = threadIdx.x; q < LF * 9; q += 256) w[q] = W1[q];
-    __syncthreads();
-    const long p = (long)blockIdx.x * 256 + threadIdx.x;
-    if (p >= (long)B * H * W) return;
-    const int x = (int)(p % W);
-    const long bh = p / W;
-    const int y = (int)(bh % H);
-    const int b = (int)(bh / H);
-    float s = 0.0f;
+    constexpr int NP = LP_OUTH * LP_OUTH, NT = (NP + 15) / 16;
+    __shared__ float s[NT * 16][9];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, kq = lane >> 4;
+    const int tx = (W + LP_OUT - 1) / LP_OUT, ty = (H + LP_OUT - 1) / LP_OUT;
+    const unsigned b = blockIdx.x / (unsigned)(tx * ty), rem = blockIdx.x - b * (unsigned)(tx * ty);
+    const int y0 = (int)(rem / (unsigned)tx) * LP_OUT, x0 = (int)(rem % (unsigned)tx) * LP_OUT;
+    f4v wr;   // channel 4 kq + cg, tap i
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        const int yy = y - (t / 3 - 1), xx = x - (t % 3 - 1);
-        if (!in_img(yy, xx, H, W)) continue;
-        const float4* q = reinterpret_cast<const float4*>(in + (((size_t)b * H + yy) * W + xx) * LF);
+    for (int cg = 0; cg < 4; ++cg) wr[cg] = i < 9 ? W1[(4 * kq + cg) * 9 + i] : 0.0f;
+    const float* img = in + (size_t)b * H * W * LF;
+    constexpr int PW = (NT + 3) / 4;   // tiles per wave
+    f4v a[PW];
 #pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-            const float4 u = q[c4];
-            s = fmaf(w[(4 * c4 + 0) * 9 + t], u.x, s);
-            s = fmaf(w[(4 * c4 + 1) * 9 + t], u.y, s);
-            s = fmaf(w[(4 * c4 + 2) * 9 + t], u.z, s);
-            s = fmaf(w[(4 * c4 + 3) * 9 + t], u.w, s);
+    for (int q = 0; q < PW; ++q) {
+        const int p = (4 * q + wave) * 16 + i;   // pixel of the 18 x 18
+        const int y = y0 - 1 + p / LP_OUTH, x = x0 - 1 + p % LP_OUTH;
+        const bool ok = p < NP && in_img(y, x, H, W);
+        const f4v v = *reinterpret_cast<const f4v*>(img + (ok ? ((size_t)y * W + x) * LF : 0) + 4 * kq);
+        a[q] = ok ? v : f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int q = 0; q < PW; ++q) {
+        const int tile = 4 * q + wave;
+        if (tile >= NT) break;
+        f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int cg = 0; cg < 4; ++cg) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][cg], wr[cg], acc, 0, 0, 0);
+        // lane holds pixel 4 kq + r of the tile, tap i
+        if (i < 9) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[tile * 16 + 4 * kq + r][i] = acc[r];
         }
     }
-    out[p] = s;
+    __syncthreads();
+    const int py = threadIdx.x / LP_OUT, px = threadIdx.x % LP_OUT;
+    float sum = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) sum += s[(py + 2 - t / 3) * LP_OUTH + px + 2 - t % 3][t];
+    if (y0 + py < H && x0 + px < W) out[(size_t)b * H * W + (size_t)(y0 + py) * W + x0 + px] = sum;
 }
 
 // out = scale[c] * in, channels-last
@@ -428,29 +501,35 @@ __global__ __launch_bounds__(256) void k_lp_adam(int n, float* __restrict__ thet
 // ---- launchers ------------------------------------------------------------------
 static inline unsigned nblk(long n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// Strips of S rows by 16 columns (k_lp_conv_mid), a wave each in turn: as many
+// rows, up to 16, as leave two strips per SIMD (256 x 64^2 with 4, 8, 16, 32 rows:
+// 58, 58, 48, 48 us; 512^2 with 2, 4, 8, 16: 22, 18, 17, 18).
+struct ConvGrid {
+    int S;
+    unsigned grid;
+};
+static ConvGrid conv_grid(int B, int H, int W) {
+    const long wt = (W + 15) / 16;
+    const int S = (int)std::min<long>(16, std::max<long>(1, (long)B * H * wt / 2048));
+    const long tasks = (long)B * ((H + S - 1) / S) * wt;
+    return {S, (std::min(nblk(tasks, 4), 2048u) + 7) / 8 * 8};
+}
+
 void lp_conv_mid(hipStream_t st, bool trans, int B, int H, int W, const float* in, float* out,
                  const float* Wl, const float* scale, float* out2, const int* halt, const int* run) {
-    const long tiles = (long)B * H * ((W + 15) / 16);
-    // four tiles per wave once the grid has enough of them to fill the GPU
-    if (tiles >= 16384) {
-        const unsigned g = nblk(tiles, 16);
-        if (trans)
-            hipLaunchKernelGGL((k_lp_conv_mid<true, 4>), dim3(g), dim3(256), 0, st, B, H, W, in, out, Wl, scale, out2, halt, run);
-        else
-            hipLaunchKernelGGL((k_lp_conv_mid<false, 4>), dim3(g), dim3(256), 0, st, B, H, W, in, out, Wl, scale, out2, halt, run);
-    } else {
-        const unsigned g = nblk(tiles, 4);
-        if (trans)
-            hipLaunchKernelGGL((k_lp_conv_mid<true, 1>), dim3(g), dim3(256), 0, st, B, H, W, in, out, Wl, scale, out2, halt, run);
-        else
-            hipLaunchKernelGGL((k_lp_conv_mid<false, 1>), dim3(g), dim3(256), 0, st, B, H, W, in, out, Wl, scale, out2, halt, run);
-    }
+    const ConvGrid cg = conv_grid(B, H, W);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(cg.grid), dim3(256), 0, st, B, H, W, cg.S, in, out, Wl, scale, out2, halt, run);
+    };
+    if (trans) go(k_lp_conv_mid<true>);
+    else go(k_lp_conv_mid<false>);
 }
 
 void lp_conv_in(hipStream_t st, int B, int H, int W, const float* in, const int32_t* idx, int nsrc,
                 float* out, const float* W1, const int* halt, const int* run) {
-    hipLaunchKernelGGL(k_lp_conv_in, dim3(nblk((long)B * H * W, 256)), dim3(256), 0, st, B, H, W, in,
-                       idx, nsrc, out, W1, halt, run);
+    const ConvGrid cg = conv_grid(B, H, W);
+    hipLaunchKernelGGL(k_lp_conv_in, dim3(cg.grid), dim3(256), 0, st, B, H, W, cg.S, in, idx, nsrc, out, W1, halt,
+                       run);
 }
 
 __global__ __launch_bounds__(256) void k_lp_gather(int B, int HW, const float* __restrict__ src,
@@ -470,7 +549,8 @@ void lp_gather(hipStream_t st, int B, int HW, const float* src, const int32_t* i
 
 void lp_conv_out(hipStream_t st, int B, int H, int W, const float* in, float* out, const float* W1,
                  const int* halt, const int* run) {
-    hipLaunchKernelGGL(k_lp_conv_out, dim3(nblk((long)B * H * W, 256)), dim3(256), 0, st, B, H, W,
+    const long g = (long)B * ((H + LP_OUT - 1) / LP_OUT) * ((W + LP_OUT - 1) / LP_OUT);
+    hipLaunchKernelGGL(k_lp_conv_out, dim3((unsigned)g), dim3(256), 0, st, B, H, W,
                        in, out, W1, halt, run);
 }
 
