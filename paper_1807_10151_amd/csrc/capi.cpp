@@ -139,7 +139,7 @@ struct sp_learned {
     DevBuf theta, adam_m, adam_v, spsg;   // spsg: softplus(d) [16], sigmoid(d) [16]
     size_t cap_pix = 0;                   // pixels the activation buffers hold
     std::vector<DevBuf> act;              // training: a_1..a_L, b_1..b_L, e_1..e_L
-    DevBuf a0, z, e0, ping, pong, partial, rtmp, lpart, gdpart;
+    DevBuf a0, z, e0, ping, pong, partial, lpart, gdpart;
     int woff(int l) const { return l == 1 ? 0 : 144 + (l - 2) * 2304; }   // W_l offset
     int doff() const { return 144 + (layers - 1) * 2304; }
 };
@@ -584,10 +584,7 @@ int lp_reserve(sp_ctx* c, sp_learned* net, size_t npix, bool train, int B, int H
         if ((rc = ensure(c, b, a16))) return rc;
     for (DevBuf* b : {&net->a0, &net->z, &net->e0})
         if ((rc = ensure(c, *b, npix * sizeof(float)))) return rc;
-    if ((rc = ensure(c, net->partial, (size_t)lp_wgrad_blocks(B, H, W) * 2304 * sizeof(float)))) return rc;
-    if ((rc = ensure(c, net->rtmp,
-                     (size_t)lp_reduce_chunks(lp_wgrad_blocks(B, H, W)) * 2304 * sizeof(double))))
-        return rc;
+    if ((rc = ensure(c, net->partial, (size_t)lp_wgrad_blocks(B, H, W) * 2304 * sizeof(double)))) return rc;
     if ((rc = ensure(c, net->lpart, (size_t)B * sizeof(double)))) return rc;
     if ((rc = ensure(c, net->gdpart, (size_t)lp_gd_blocks() * 16 * sizeof(double)))) return rc;
     return SP_OK;
@@ -1154,7 +1151,7 @@ int sp_lp_destroy(sp_learned* net) {
     (void)hipSetDevice(net->device);
     (void)hipDeviceSynchronize();
     for (DevBuf* b : {&net->theta, &net->adam_m, &net->adam_v, &net->spsg, &net->a0, &net->z,
-                      &net->e0, &net->ping, &net->pong, &net->partial, &net->rtmp, &net->lpart,
+                      &net->e0, &net->ping, &net->pong, &net->partial, &net->lpart,
                       &net->gdpart})
         release(*b);
     for (auto& b : net->act) release(b);
@@ -1233,8 +1230,7 @@ int sp_lp_loss_grad(sp_ctx* c, sp_learned* net, int32_t rows, int32_t cols, cons
     auto Bb = [&](int l) { return dptr<float>(net->act[L + l - 1]); };
     auto E = [&](int l) { return l == 0 ? dptr<float>(net->e0) : dptr<float>(net->act[2 * L + l - 1]); };
     float* Z = dptr<float>(net->z);
-    float* part = dptr<float>(net->partial);
-    double* rtmp = dptr<double>(net->rtmp);
+    double* part = dptr<double>(net->partial);
     const int nwb = lp_wgrad_blocks(B, H, W);
     lp_softplus(st, th + net->doff(), sps, sg);
     // forward chain a_l = C_l a_{l-1}, b_L = softplus(d) a_L, back chain b_{l-1} = C_l^T b_l
@@ -1252,21 +1248,22 @@ int sp_lp_loss_grad(sp_ctx* c, sp_learned* net, int32_t rows, int32_t cols, cons
     launch_reduce(st, dptr<double>(net->lpart), B, loss);
     // e_l = C_l e_{l-1}; the back chain contributes wgrad(b_l, e_{l-1}) to W_l
     lp_conv_in(st, B, H, W, E(0), nullptr, B, E(1), th + net->woff(1), nullptr, nullptr);
-    for (int l = 2; l <= L; ++l)
+    for (int l = 2; l < L; ++l)
         lp_conv_mid(st, false, B, H, W, E(l - 1), E(l), th + net->woff(l), nullptr, nullptr, nullptr, nullptr);
     for (int l = 1; l <= L; ++l) {
         const int fi = l == 1 ? 1 : 16;
         lp_wgrad(st, fi, B, H, W, Bb(l), E(l - 1), part);
-        lp_reduce(st, nwb, 16 * fi * 9, part, false, grad + net->woff(l), rtmp);
+        lp_reduce(st, nwb, 16 * fi * 9, part, false, grad + net->woff(l));
     }
-    // d: sigmoid(d) * sum e_L a_L; then f_L = softplus(d) e_L (into b_L's buffer)
+    // e_L and f_L = softplus(d) e_L (into b_L's buffer); d: sigmoid(d) * sum e_L a_L
+    if (L == 1) lp_scale(st, (long)npix, E(1), sps, Bb(1));
+    else lp_conv_mid(st, false, B, H, W, E(L - 1), E(L), th + net->woff(L), sps, Bb(L), nullptr, nullptr);
     lp_gd(st, (long)npix, E(L), A(L), dptr<double>(net->gdpart), sg, grad + net->doff());
-    lp_scale(st, (long)npix, E(L), sps, Bb(L));
     // forward chain: wgrad(f_l, a_{l-1}) into W_l, f_{l-1} = C_l^T f_l
     for (int l = L; l >= 1; --l) {
         const int fi = l == 1 ? 1 : 16;
         lp_wgrad(st, fi, B, H, W, Bb(l), A(l - 1), part);
-        lp_reduce(st, nwb, 16 * fi * 9, part, true, grad + net->woff(l), rtmp);
+        lp_reduce(st, nwb, 16 * fi * 9, part, true, grad + net->woff(l));
         if (l >= 2)
             lp_conv_mid(st, true, B, H, W, Bb(l), Bb(l - 1), th + net->woff(l), nullptr, nullptr, nullptr, nullptr);
     }

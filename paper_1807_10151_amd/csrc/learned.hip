@@ -319,132 +319,154 @@ __global__ __launch_bounds__(256) void k_lp_loss(int B, int H, int W, int margin
 }
 
 // ---- weight gradients ----------------------------------------------------------
-// partial[blk][o][i][t] = sum over the block's pixels p of G[p][o] * X[p + t][i]
-// (X zero outside the image).  G: [B][H][W][16]; X: [B][H][W][FI].  A block
-// covers LP_WG_TILES consecutive 16 x 16 pixel tiles of one tile row of one
-// image, each staged in LDS in turn (one: more blocks in flight outweigh the
-// smaller reduction that larger blocks leave).
-constexpr int LP_WG_TILES = 1;
+// partial[blk][o][ci][t] = sum over the block's tiles' pixels p of G[p][o] *
+// X[p + t][ci] (X zero outside the image).  G: [B][H][W][16]; X: [B][H][W][FI].
+// A tile is 16 x 16 pixels of one image, staged in LDS; per tap t its share of
+// dW_t is a [16 x 256] x [256 x FI] MFMA product over its pixels (FI = 1: one
+// product with the taps as columns).  Wave w takes pixel columns 4 w .. 4 w + 3,
+// the four pixels of an MFMA, down the 16 rows for all nine taps: a row's G and
+// three shifted X are read from LDS once and serve nine MFMAs, the next two rows'
+// taps included.  The sums of a wave's 64 pixels are float32 MFMA accumulators,
+// those over tiles and waves float64.  Blocks go on to further tiles, the next
+// one's loads under way during a tile's MFMAs.
+// Bound: the MFMAs (31 us at 256 x 64^2) and the activations' traffic (27 us).
+// Nine waves, one per tap, on one tile per block took 144 us: one wave of nine
+// left its SIMD's share uneven, single floats were staged one load after
+// another, and 4096 blocks' partials went to memory (now at most 512); 256 x 64^2,
+// partial sums included: 180 -> 69 us; first layer 61 -> 26.
+constexpr int WG_T = 16, WG_H = WG_T + 2;
+constexpr int LP_WG_BLOCKS = 512;   // two per CU
 
-struct WgTile {
-    int b, y0, x0, ntile;   // image, tile row origin, first tile's column origin, tiles in the block
-};
-
-__device__ __forceinline__ WgTile wg_tile(int blk, int H, int W) {
-    const int tx = (W + 15) / 16, ty = (H + 15) / 16;
-    const int gx = (tx + LP_WG_TILES - 1) / LP_WG_TILES;
-    const int b = blk / (gx * ty);
-    const int rem = blk - b * gx * ty;
-    const int g = rem % gx;
-    WgTile T;
-    T.b = b;
-    T.y0 = (rem / gx) * 16;
-    T.x0 = g * LP_WG_TILES * 16;
-    T.ntile = min(LP_WG_TILES, tx - g * LP_WG_TILES);
-    return T;
-}
-
-// Stages tile j of the block: gs = G over the tile, xs = X over the tile and
-// a one-pixel halo (FI channels).
-template <int FI, int NT>
-__device__ __forceinline__ void wg_stage(const WgTile& T, int j, int H, int W, const float* __restrict__ G,
-                                         const float* __restrict__ X, float* gs, float* xs) {
-    const int x0 = T.x0 + 16 * j;
-    for (int q = threadIdx.x; q < 256 * LF; q += NT) {
-        const int p = q / LF, c = q - p * LF;
-        const int yy = T.y0 + p / 16, xx = x0 + p % 16;
-        gs[q] = in_img(yy, xx, H, W) ? G[(((size_t)T.b * H + yy) * W + xx) * LF + c] : 0.0f;
-    }
-    for (int q = threadIdx.x; q < 18 * 18 * FI; q += NT) {
-        const int p = q / FI, c = q - p * FI;
-        const int yy = T.y0 - 1 + p / 18, xx = x0 - 1 + p % 18;
-        xs[q] = in_img(yy, xx, H, W) ? X[(((size_t)T.b * H + yy) * W + xx) * FI + c] : 0.0f;
-    }
-}
-
-// First layer (FI = 1): 16 x 9 outputs, one thread each, on the VALU.
-__global__ __launch_bounds__(256) void k_lp_wgrad1(int B, int H, int W, const float* __restrict__ G,
-                                                   const float* __restrict__ X,
-                                                   float* __restrict__ partial) {
-    __shared__ float gs[256 * LF];
-    __shared__ float xs[18 * 18];
-    const WgTile T = wg_tile(blockIdx.x, H, W);
-    const int o = threadIdx.x / 9, t = threadIdx.x % 9;
-    float acc = 0.0f;
-    for (int j = 0; j < T.ntile; ++j) {
-        if (j) __syncthreads();             // the previous tile's reads are done
-        wg_stage<1, 256>(T, j, H, W, G, X, gs, xs);
-        __syncthreads();
-        if (threadIdx.x < LF * 9) {
-            for (int p = 0; p < 256; ++p) {
-                const int py = p / 16, px = p % 16;
-                acc = fmaf(gs[p * LF + o], xs[(py + t / 3) * 18 + px + t % 3], acc);
+template <int FI>
+__global__ __launch_bounds__(256, 2) void k_lp_wgrad(int B, int H, int W, const float* __restrict__ G,
+                                                     const float* __restrict__ X,
+                                                     double* __restrict__ partial) {
+    constexpr int NG = WG_T * WG_T * LF / 4, NX = WG_H * WG_H * FI, XV = FI == 1 ? 1 : 4;   // XV: floats per load of X
+    constexpr int NTAP = FI == 1 ? 1 : 9;
+    constexpr int PG = NG / 256, PX = (NX / XV + 255) / 256;   // loads per thread
+    __shared__ __attribute__((aligned(16))) float lds[WG_T * WG_T * LF + NX];
+    float* gs = lds;
+    float* xs = lds + WG_T * WG_T * LF;
+    const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tx = (W + WG_T - 1) / WG_T, ty = (H + WG_T - 1) / WG_T;
+    const unsigned ntile = (unsigned)B * tx * ty;
+    f4v rg[PG], rx[FI == 1 ? 1 : PX];
+    float rx1[FI == 1 ? PX : 1];
+    // a tile and its X with a halo of one pixel to registers, zero outside the image
+    auto fetch = [&](unsigned tile) {
+        const unsigned b = tile / (unsigned)(tx * ty), rem = tile - b * (unsigned)(tx * ty);
+        const int y0 = (int)(rem / (unsigned)tx) * WG_T, x0 = (int)(rem % (unsigned)tx) * WG_T;
+        const float* gb = G + (size_t)b * H * W * LF;
+        const float* xb = X + (size_t)b * H * W * FI;
+#pragma unroll
+        for (int q = 0; q < PG; ++q) {
+            const int e = threadIdx.x + 256 * q, y = y0 + e / (WG_T * 4), x = x0 + e / 4 % WG_T;
+            const bool ok = y < H && x < W;
+            const f4v v = *reinterpret_cast<const f4v*>(gb + (ok ? ((size_t)y * W + x) * LF : 0) + 4 * (e & 3));
+            rg[q] = ok ? v : f4v{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+#pragma unroll
+        for (int q = 0; q < PX; ++q) {
+            const int e = threadIdx.x + 256 * q, px = e * XV / FI, y = y0 - 1 + px / WG_H, x = x0 - 1 + px % WG_H;
+            const bool ok = px < WG_H * WG_H && in_img(y, x, H, W);
+            if constexpr (FI == 1) {
+                const float v = xb[ok ? (size_t)y * W + x : 0];
+                rx1[q] = ok ? v : 0.0f;
+            } else {
+                const f4v v = *reinterpret_cast<const f4v*>(xb + (ok ? ((size_t)y * W + x) * FI : 0) + 4 * (e & 3));
+                rx[q] = ok ? v : f4v{0.0f, 0.0f, 0.0f, 0.0f};
             }
         }
-    }
-    if (threadIdx.x < LF * 9) partial[(size_t)blockIdx.x * (LF * 9) + threadIdx.x] = acc;
-}
-
-// The 16 -> 16 weight gradient on MFMA: per tap t, dW_t[o][ci] = sum_p
-// G[p][o] X[p + t][ci] is a [16 x 256] x [256 x 16] product over a tile's
-// pixels.  Nine waves per block, one per tap, each 64 v_mfma_f32_16x16x4f32
-// per tile (A = G of 4 pixels, B = X of the same 4 pixels shifted by the tap)
-// over the LDS-staged tiles; no cross-wave sum, so the partial of a block is
-// written once per output.
-constexpr int LP_WG_THREADS = 64 * 9;
-
-__global__ __launch_bounds__(LP_WG_THREADS) void k_lp_wgrad_mfma(int B, int H, int W,
-                                                               const float* __restrict__ G,
-                                                               const float* __restrict__ X,
-                                                               float* __restrict__ partial) {
-    __shared__ float gs[256 * LF];
-    __shared__ float xs[18 * 18 * LF];
-    const WgTile T = wg_tile(blockIdx.x, H, W);
-    const int t = threadIdx.x >> 6;          // tap of this wave
-    const int lane = threadIdx.x & 63;
-    const int i = lane & 15, kq = lane >> 4;
-    const int dy = t / 3, dx = t % 3;
-    f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int j = 0; j < T.ntile; ++j) {
-        if (j) __syncthreads();             // the previous tile's reads are done
-        wg_stage<LF, LP_WG_THREADS>(T, j, H, W, G, X, gs, xs);
-        __syncthreads();
-#pragma unroll 4
-        for (int p0 = 0; p0 < 256; p0 += 4) {
-            const int p = p0 + kq;           // this lane's K slot: pixel p of the tile
-            const int py = p >> 4, px = p & 15;
-            const float a = gs[p * LF + i];                              // A[o = i][k] = G[p][o]
-            const float bv = xs[((py + dy) * 18 + px + dx) * LF + i];     // B[k][ci = i] = X[p + t][ci]
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc, 0, 0, 0);
-        }
-    }
-    // lane holds D[4 kq + r][i] = dW_t[o = 4 kq + r][ci = i]
-    float* dst = partial + (size_t)blockIdx.x * (LF * LF * 9);
+    };
+    double sum[NTAP][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) dst[((4 * kq + r) * LF + i) * 9 + t] = acc[r];
+    for (int t = 0; t < NTAP; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[t][r] = 0.0;
+    unsigned tile = blockIdx.x;
+    if (tile < ntile) fetch(tile);
+    for (; tile < ntile; tile += gridDim.x) {
+        __syncthreads();   // the previous tile's reads are done
+#pragma unroll
+        for (int q = 0; q < PG; ++q) *reinterpret_cast<f4v*>(gs + 4 * (threadIdx.x + 256 * q)) = rg[q];
+#pragma unroll
+        for (int q = 0; q < PX; ++q) {
+            const int e = threadIdx.x + 256 * q;
+            if (e * XV >= NX) break;
+            if constexpr (FI == 1) xs[e] = rx1[q];
+            else *reinterpret_cast<f4v*>(xs + 4 * e) = rx[q];
+        }
+        __syncthreads();
+        if (tile + gridDim.x < ntile) fetch(tile + gridDim.x);
+        f4v acc[NTAP];
+#pragma unroll
+        for (int t = 0; t < NTAP; ++t) acc[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+        const float* ga = gs + (4 * wave + kq) * LF + i;   // this lane's pixel of row 0: A[o = i][k = kq]
+        if constexpr (FI == 1) {
+            const int t = min(i, 8);
+            const float* xa = xs + t / 3 * WG_H + 4 * wave + kq + t % 3;   // B[k = kq][tap = i]
+#pragma unroll
+            for (int y = 0; y < WG_T; ++y) {
+                const float bv = i < 9 ? xa[y * WG_H] : 0.0f;
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[y * WG_T * LF], bv, acc[0], 0, 0, 0);
+            }
+        } else {
+            const float* xa = xs + (4 * wave + kq) * FI + i;   // B[k = kq][ci = i] of tap 0
+            float bv[3][3];   // rows y .. y + 2 of the halo, three columns
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) bv[y][dx] = xa[(y * WG_H + dx) * FI];
+#pragma unroll
+            for (int y = 0; y < WG_T; ++y) {
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) bv[(y + 2) % 3][dx] = xa[((y + 2) * WG_H + dx) * FI];
+                const float av = ga[y * WG_T * LF];
+#pragma unroll
+                for (int t = 0; t < 9; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[(y + t / 3) % 3][t % 3], acc[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < NTAP; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[t][r] += (double)acc[t][r];
+    }
+    // the four waves' sums in wave order; a lane holds D[o = 4 kq + r][i]
+    constexpr int NOUT = LF * FI * 9;
+    double* red = reinterpret_cast<double*>(lds);
+    static_assert(NOUT * 2 <= WG_T * WG_T * LF + NX, "LDS");
+    for (int w = 0; w < 4; ++w) {
+        __syncthreads();
+        if (wave != w) continue;
+#pragma unroll
+        for (int t = 0; t < NTAP; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int o = 4 * kq + r, e = FI == 1 ? o * 9 + min(i, 8) : (o * LF + i) * 9 + t;
+                if (FI != 1 || i < 9) red[e] = w ? red[e] + sum[t][r] : sum[t][r];
+            }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NOUT; e += 256) partial[(size_t)blockIdx.x * NOUT + e] = red[e];
 }
 
-// Two-level fixed-order float64 sum over blocks: tmp[chunk][q] sums the
-// partials of 64 consecutive blocks, then out[q] (+)= sum over chunks.
-constexpr int LP_CHUNK = 64;
-
-__global__ __launch_bounds__(256) void k_lp_reduce1(int nblk, int nout, const float* __restrict__ pa,
-                                                    double* __restrict__ tmp) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= nout) return;
-    const int k0 = blockIdx.y * LP_CHUNK, k1 = min(nblk, k0 + LP_CHUNK);
+// out[q] (+)= sum over the blocks' partials, float64 in a fixed order: 16 outputs
+// per workgroup, 16 groups of threads over every 16th block each, then the groups.
+__global__ __launch_bounds__(256) void k_lp_reduce(int nblk, int nout, const double* __restrict__ pa,
+                                                   int accumulate, float* __restrict__ out) {
+    __shared__ double red[256];
+    const int c = threadIdx.x & 15, grp = threadIdx.x >> 4, q = blockIdx.x * 16 + c;
     double s = 0.0;
-    for (int k = k0; k < k1; ++k) s += (double)pa[(size_t)k * nout + q];
-    tmp[(size_t)blockIdx.y * nout + q] = s;
-}
-
-__global__ __launch_bounds__(256) void k_lp_reduce2(int nchunk, int nout, const double* __restrict__ tmp,
-                                                    int accumulate, float* __restrict__ out) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= nout) return;
-    double s = 0.0;
-    for (int k = 0; k < nchunk; ++k) s += tmp[(size_t)k * nout + q];
-    out[q] = (float)(accumulate ? (double)out[q] + s : s);
+#pragma unroll 8
+    for (int k = grp; k < nblk; k += 16) s += pa[(size_t)k * nout + q];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (threadIdx.x >= 16) return;
+    double t = 0.0;
+    for (int g = 0; g < 16; ++g) t += red[g * 16 + c];
+    out[q] = (float)(accumulate ? (double)out[q] + t : t);
 }
 
 // gd partials: part[blk][c] = sum over the block's pixels of E[p][c] * A[p][c]
@@ -466,20 +488,21 @@ __global__ __launch_bounds__(256) void k_lp_gd_part(long npix, const float* __re
     }
 }
 
-// 16 groups of threads per channel sum strided blocks, then the groups are
-// added in order.
-__global__ __launch_bounds__(256) void k_lp_gd_final(int nblk, const double* __restrict__ part,
-                                                     const float* __restrict__ sg,
-                                                     float* __restrict__ gd) {
-    __shared__ double red[256];
+// 64 groups of threads per channel sum strided blocks, then the groups are added
+// in order.
+__global__ __launch_bounds__(1024) void k_lp_gd_final(int nblk, const double* __restrict__ part,
+                                                      const float* __restrict__ sg,
+                                                      float* __restrict__ gd) {
+    __shared__ double red[1024];
     const int c = threadIdx.x & (LF - 1), grp = threadIdx.x >> 4;
     double s = 0.0;
-    for (int k = grp; k < nblk; k += 16) s += part[(size_t)k * LF + c];
+#pragma unroll 8
+    for (int k = grp; k < nblk; k += 64) s += part[(size_t)k * LF + c];
     red[threadIdx.x] = s;
     __syncthreads();
     if (threadIdx.x < LF) {
         double t = 0.0;
-        for (int g = 0; g < 16; ++g) t += red[g * LF + threadIdx.x];
+        for (int g = 0; g < 64; ++g) t += red[g * LF + threadIdx.x];
         gd[threadIdx.x] = (float)(t * (double)sg[threadIdx.x]);
     }
 }
@@ -569,25 +592,17 @@ void lp_loss(hipStream_t st, int B, int H, int W, int margin, const float* z, co
 }
 
 int lp_wgrad_blocks(int B, int H, int W) {
-    return B * ((H + 15) / 16) * (((W + 15) / 16 + LP_WG_TILES - 1) / LP_WG_TILES);
+    return (int)std::min<long>(LP_WG_BLOCKS, (long)B * ((H + WG_T - 1) / WG_T) * ((W + WG_T - 1) / WG_T));
 }
 
-void lp_wgrad(hipStream_t st, int fi, int B, int H, int W, const float* G, const float* X, float* partial) {
+void lp_wgrad(hipStream_t st, int fi, int B, int H, int W, const float* G, const float* X, double* partial) {
     const unsigned g = (unsigned)lp_wgrad_blocks(B, H, W);
-    if (fi == LF)
-        hipLaunchKernelGGL(k_lp_wgrad_mfma, dim3(g), dim3(LP_WG_THREADS), 0, st, B, H, W, G, X, partial);
-    else
-        hipLaunchKernelGGL(k_lp_wgrad1, dim3(g), dim3(256), 0, st, B, H, W, G, X, partial);
+    if (fi == LF) hipLaunchKernelGGL(k_lp_wgrad<LF>, dim3(g), dim3(256), 0, st, B, H, W, G, X, partial);
+    else hipLaunchKernelGGL(k_lp_wgrad<1>, dim3(g), dim3(256), 0, st, B, H, W, G, X, partial);
 }
 
-int lp_reduce_chunks(int nb) { return (nb + LP_CHUNK - 1) / LP_CHUNK; }
-
-void lp_reduce(hipStream_t st, int nb, int nout, const float* pa, bool accumulate, float* out,
-               double* tmp) {
-    const int nch = lp_reduce_chunks(nb);
-    hipLaunchKernelGGL(k_lp_reduce1, dim3(nblk(nout, 256), nch), dim3(256), 0, st, nb, nout, pa, tmp);
-    hipLaunchKernelGGL(k_lp_reduce2, dim3(nblk(nout, 256)), dim3(256), 0, st, nch, nout, tmp,
-                       accumulate ? 1 : 0, out);
+void lp_reduce(hipStream_t st, int nb, int nout, const double* pa, bool accumulate, float* out) {
+    hipLaunchKernelGGL(k_lp_reduce, dim3(nout / 16), dim3(256), 0, st, nb, nout, pa, accumulate ? 1 : 0, out);
 }
 
 int lp_gd_blocks() { return 2048; }
@@ -595,7 +610,7 @@ int lp_gd_blocks() { return 2048; }
 void lp_gd(hipStream_t st, long npix, const float* E, const float* A, double* part, const float* sg,
            float* gd) {
     hipLaunchKernelGGL(k_lp_gd_part, dim3(lp_gd_blocks()), dim3(256), 0, st, npix, E, A, part);
-    hipLaunchKernelGGL(k_lp_gd_final, dim3(1), dim3(256), 0, st, lp_gd_blocks(), part, sg, gd);
+    hipLaunchKernelGGL(k_lp_gd_final, dim3(1), dim3(1024), 0, st, lp_gd_blocks(), part, sg, gd);
 }
 
 void lp_adam(hipStream_t st, int n, float* theta, float* m, float* v, const float* g, double lr,

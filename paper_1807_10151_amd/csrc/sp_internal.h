@@ -486,10 +486,8 @@ void lp_softplus(hipStream_t st, const float* d, float* sp_out, float* sg_out);
 void lp_loss(hipStream_t st, int B, int H, int W, int margin, const float* z, const float* v,
              const int32_t* idx, int nsrc, float* e0, double* lpart);
 int lp_wgrad_blocks(int B, int H, int W);
-void lp_wgrad(hipStream_t st, int fi, int B, int H, int W, const float* G, const float* X, float* partial);
-int lp_reduce_chunks(int nb);
-void lp_reduce(hipStream_t st, int nb, int nout, const float* pa, bool accumulate, float* out,
-               double* tmp);
+void lp_wgrad(hipStream_t st, int fi, int B, int H, int W, const float* G, const float* X, double* partial);
+void lp_reduce(hipStream_t st, int nb, int nout, const double* pa, bool accumulate, float* out);
 int lp_gd_blocks();
 void lp_gd(hipStream_t st, long npix, const float* E, const float* A, double* part, const float* sg,
            float* gd);
