@@ -76,6 +76,7 @@ struct sp_ctx {
     DevBuf vtb2, stv_y;                   // S_TV ping-pong: second t_bar (float), iterate (float64)
     DevBuf ox, oxh, oscal;                // sp_tv, sp_tv_grad, sp_tv_perturb
     DevBuf part_f, part_gp, part_qq, part_g, part_t, part_s, part_misc, part_se;
+    DevBuf part_g2, ell_next;             // S_TV steps that take their own decision (enqueue_stv)
     DevBuf stored_xT;                     // transposed image for the stored R product
     DevBuf art_u, art_nrm, art_sum;       // ART: auxiliary vector, ||R_i||^2, sum of b
     DevBuf scal, trace_d, replay_d, trials_tmp;
@@ -437,7 +438,9 @@ int ensure_partials(sp_ctx* c) {
     if ((rc = ensure(c, c->part_f, (size_t)std::max(project_blocks(G), G.pair ? project32_blocks(G) : 0) * 8))) return rc;
     if ((rc = ensure(c, c->part_qq, (size_t)vec_blocks(G.nA * G.nB) * 8))) return rc;
     if ((rc = ensure(c, c->part_gp, (size_t)vec_blocks(n) * 8))) return rc;
-    if ((rc = ensure(c, c->part_g, (size_t)tv_blocks(G.rows, G.cols) * 8))) return rc;
+    for (DevBuf* b : {&c->part_g, &c->part_g2})
+        if ((rc = ensure(c, *b, (size_t)tv_blocks(G.rows, G.cols) * 8))) return rc;
+    if ((rc = ensure(c, c->ell_next, 2 * sizeof(int32_t)))) return rc;
     if ((rc = ensure(c, c->part_t, (size_t)tv_blocks(G.rows, G.cols) * 9 * 8))) return rc;
     if ((rc = ensure(c, c->part_s, (size_t)std::max(tv_blocks(G.rows, G.cols), tv_prep_tiles(G.rows, G.cols)) * 8)))
         return rc;
@@ -538,13 +541,19 @@ void enqueue_stv(sp_ctx* c, Scalars* sc, int K, const double* x, double* xh, boo
                       c->vtb2.bytes >= (size_t)n * sizeof(float);
     const double* src = x;
     float* tb = dptr<float>(c->vtb);
-    launch_tv_grad(c->stream, G.rows, G.cols, src, tb, dptr<double>(c->part_g), halt);
+    // a fused step that takes its own decision reads ||t_bar||^2's partials while it
+    // writes the next ones, and leaves l beside the scalars, which it reads
+    const bool fold = fuse && tv_folds_decision(G.rows, G.cols);
+    double* pg[2] = {dptr<double>(c->part_g), fold ? dptr<double>(c->part_g2) : dptr<double>(c->part_g)};
+    const int32_t* ell = &sc->ell;
+    launch_tv_grad(c->stream, G.rows, G.cols, src, tb, pg[0], halt);
     for (int i = 0; i < K; ++i) {
         const int nb = i == 0 ? nb0 : nb1;
-        launch_tv_trials(c->stream, G.rows, G.cols, src, tb, dptr<double>(c->part_g), nb, sc, 4,
-                         dptr<double>(c->part_t), halt);
-        launch_tv_decide(c->stream, G.rows, G.cols, src, tb, dptr<double>(c->part_g), nb,
-                         dptr<double>(c->part_t), nt, 4, sc, tr, trials_out, halt);
+        const bool own = fold && i < K - 1;
+        launch_tv_trials(c->stream, G.rows, G.cols, src, tb, pg[i & 1], nb, sc, ell, dptr<double>(c->part_t), halt);
+        if (!own)
+            launch_tv_decide(c->stream, G.rows, G.cols, src, tb, pg[i & 1], nb, dptr<double>(c->part_t), nt, sc, ell,
+                             tr, trials_out, halt);
         const bool last = i == K - 1;
         if (last && xp) {
             launch_tv_apply_prep(c->stream, G, src, xh, tb, sc, snorm ? x : nullptr, dptr<double>(c->part_s),
@@ -553,13 +562,19 @@ void enqueue_stv(sp_ctx* c, Scalars* sc, int K, const double* x, double* xh, boo
             launch_tv_apply(c->stream, n, src, xh, tb, sc, (last && snorm) ? x : nullptr,
                             dptr<double>(c->part_s), halt);
             src = xh;
-            if (!last) launch_tv_grad(c->stream, G.rows, G.cols, src, tb, dptr<double>(c->part_g), halt, true);
+            if (!last) launch_tv_grad(c->stream, G.rows, G.cols, src, tb, pg[(i + 1) & 1], halt, true);
         } else {
             // iterate i + 1 goes to xh when K - 1 - (i + 1) is even, so iterate K - 1 is in xh
             double* dst = (K - 2 - i) % 2 == 0 ? xh : dptr<double>(c->stv_y);
             float* tbn = tb == dptr<float>(c->vtb) ? dptr<float>(c->vtb2) : dptr<float>(c->vtb);
-            launch_tv_apply_grad(c->stream, G.rows, G.cols, src, dst, tb, tbn, sc, dptr<double>(c->part_g),
-                                 halt);
+            TvStep step;
+            if (own) {
+                int32_t* next = dptr<int32_t>(c->ell_next) + (i & 1);
+                step = {pg[i & 1], nb, dptr<double>(c->part_t), nt, ell, next, i, tr, trials_out};
+                ell = next;
+            }
+            launch_tv_apply_grad(c->stream, G.rows, G.cols, src, dst, tb, tbn, sc, pg[(i + 1) & 1],
+                                 own ? &step : nullptr, halt);
             src = dst;
             tb = tbn;
         }
@@ -1088,7 +1103,7 @@ int sp_ctx_destroy(sp_ctx* c) {
     (void)drain_pending(c);
     for (DevBuf* b : {&c->ang, &c->quad, &c->pwave, &c->fwave, &c->ford, &c->xp, &c->xTp, &c->zp, &c->zTp, &c->yp, &c->ypd, &c->seg, &c->pord, &c->blob_tab, &c->tw, &c->S, &c->vx, &c->vxh, &c->vp, &c->vq, &c->vw, &c->ox, &c->oxh, &c->oscal,
                       &c->vg, &c->vgf, &c->vzf, &c->vz, &c->vtb, &c->vtb2, &c->stv_y, &c->part_f, &c->part_gp,
-                      &c->part_qq, &c->part_g, &c->part_t, &c->part_s, &c->part_misc, &c->part_se, &c->stored_xT, &c->art_u, &c->art_nrm, &c->art_sum, &c->scal,
+                      &c->part_qq, &c->part_g, &c->part_t, &c->part_s, &c->part_misc, &c->part_se, &c->part_g2, &c->ell_next, &c->stored_xT, &c->art_u, &c->art_nrm, &c->art_sum, &c->scal,
                       &c->trace_d, &c->replay_d, &c->trials_tmp})
         release(*b);
     if (c->own) (void)hipStreamDestroy(c->own);

@@ -353,12 +353,28 @@ int tv_blocks(int rows, int cols);
 // and of the trials launch (the trial partials).
 int tv_grad_blocks(int rows, int cols);
 int tv_tpx_blocks(int rows, int cols);
+// ell: where l is read (the scalars, or TvStep::ell_out of the step before).
 void launch_tv_trials(hipStream_t st, int rows, int cols, const double* y, const float* tb,
-                      const double* gpart, int ngpart, Scalars* sc, int J, double* tpart,
+                      const double* gpart, int ngpart, const Scalars* sc, const int32_t* ell, double* tpart,
                       const int* halt);
 void launch_tv_decide(hipStream_t st, int rows, int cols, const double* y, const float* tb,
-                      const double* gpart, int ngpart, const double* tpart, int ntpart, int J,
-                      Scalars* sc, TraceDev tr, int32_t* trials_out, const int* halt);
+                      const double* gpart, int ngpart, const double* tpart, int ntpart, Scalars* sc,
+                      const int32_t* ell, TraceDev tr, int32_t* trials_out, const int* halt);
+// The decision of inner step `slot` taken by launch_tv_apply_grad itself (where
+// tv_folds_decision): the inputs of launch_tv_decide; l after the step goes to
+// *ell_out, and gpart is not the launch's own partials.
+struct TvStep {
+    const double* gpart = nullptr;
+    int ngpart = 0;
+    const double* tpart = nullptr;
+    int ntpart = 0;
+    const int32_t* ell = nullptr;
+    int32_t* ell_out = nullptr;
+    int slot = 0;
+    TraceDev tr{};
+    int32_t* trials_out = nullptr;
+};
+bool tv_folds_decision(int rows, int cols);
 void launch_tv_apply(hipStream_t st, int n, const double* src, double* dst, const float* tb,
                      const Scalars* sc, const double* xk, double* partials, const int* halt);
 void launch_tv_value(hipStream_t st, int rows, int cols, const double* y, double* partials,
@@ -374,8 +390,8 @@ void launch_tv_apply_prep(hipStream_t st, const GeomDev& G, const double* src, d
                           const float* tb, const Scalars* sc, const double* xk, double* partials,
                           double* xp, double* xTp, const int* halt);
 void launch_tv_apply_grad(hipStream_t st, int rows, int cols, const double* src, double* dst,
-                          const float* tb_in, float* tb_out, const Scalars* sc, double* partials,
-                          const int* halt);
+                          const float* tb_in, float* tb_out, Scalars* sc, double* partials,
+                          const TvStep* step, const int* halt);
 
 // cg.hip (p, g, z, x and x_{k+1/2} in float64)
 int vec_blocks(int n);

@@ -1,6 +1,6 @@
 // Total-variation superiorization (Section 3.1, Algorithm 1) on the GPU.
 //
-// One S_TV inner step is four launches:
+// One S_TV inner step is up to four launches:
 //   k_tv_grad    t_bar (minus the TV gradient where defined, 0 elsewhere) and
 //                per-workgroup partials of ||t_bar||^2 (one pixel per thread
 //                for an S_TV call's first step, tv_px for later ones, whose
@@ -16,11 +16,11 @@
 //                J is accepted it evaluates further batches itself;
 //   k_tv_apply   y <- y + lam t_bar (and ||s_k||^2 partials on the last step).
 // The single-slice solver fuses two pairs: between inner steps the update and
-// the next t_bar are one launch (k_tv_apply_grad), and the last update also
-// writes R's padded copies of x_{k+1/2} (k_tv_apply_prep; the batched solver
-// runs the same body).  k_tv_apply_grad repeats the arithmetic of the two
-// launches it replaces, so results are bitwise those of the batched solver,
-// which keeps them separate.
+// the next t_bar are one launch (k_tv_apply_grad), on images below 2^18 pixels
+// with the decision before them, and the last update also writes R's padded
+// copies of x_{k+1/2} (k_tv_apply_prep; the batched solver runs the same body).
+// k_tv_apply_grad repeats the arithmetic of the launches it replaces, so results
+// are bitwise those of the batched solver, which keeps them separate.
 // Trial TVs are evaluated in float64 directly on y + lam t_bar (the trial image
 // is never rounded to float32), so the acceptance test sees the step itself.
 #include "sp_internal.h"
@@ -34,28 +34,43 @@ constexpr int TVJ = 4;   // trials evaluated per pass (the first is accepted in 
 // else 1.
 __host__ __device__ __forceinline__ int tv_px(size_t n) { return n >= ((size_t)1 << 18) ? 4 : 1; }
 
-// t_bar at pixel p = (i, j) of a rows x cols float64 image whose value at q
-// is y(q), evaluated in float64 and rounded to float32 (reading: the partial
-// derivative is undefined when a square-root term it enters is zero).
-template <class Y>
-__device__ __forceinline__ float tv_neg_grad_at(Y&& y, int rows, int cols, int i, int j, size_t p) {
-    const double v = y(p);
+// The values t_bar of pixel p = (i, j) depends on: its own and those to the
+// south, east, north, north-east, west and south-west (where they exist).
+template <class T>
+struct TvPix {
+    T c, s, e, n, ne, w, sw;
+    template <class Y>
+    __device__ __forceinline__ TvPix(Y&& y, int rows, int cols, int i, int j, size_t p) {
+        const bool S = i < rows - 1, E = j < cols - 1, N = i >= 1, W = j >= 1;
+        c = y(p);
+        s = y(S ? p + cols : p);
+        e = y(E ? p + 1 : p);
+        n = y(N ? p - cols : p);
+        ne = y(N && E ? p - cols + 1 : p);
+        w = y(W ? p - 1 : p);
+        sw = y(S && W ? p - 1 + cols : p);
+    }
+    __device__ __forceinline__ TvPix() {}
+};
+
+// t_bar at pixel (i, j) of a rows x cols float64 image, evaluated in float64 and
+// rounded to float32 (reading: the partial derivative is undefined when a
+// square-root term it enters is zero).
+__device__ __forceinline__ float tv_neg_grad_pix(const TvPix<double>& v, int rows, int cols, int i, int j) {
     double gsum = 0.0;
     bool bad = false;
     if (i < rows - 1 && j < cols - 1) {          // T_{i,j}
-        const double dv = v - y(p + cols), dh = v - y(p + 1);
+        const double dv = v.c - v.s, dh = v.c - v.e;
         if (dv == 0.0 && dh == 0.0) bad = true;
         else gsum += (dv + dh) / sqrt(dv * dv + dh * dh);
     }
     if (i >= 1 && j < cols - 1) {                // T_{i-1,j}
-        const double u = y(p - cols);
-        const double dv = u - v, dh = u - y(p - cols + 1);
+        const double dv = v.n - v.c, dh = v.n - v.ne;
         if (dv == 0.0 && dh == 0.0) bad = true;
         else gsum -= dv / sqrt(dv * dv + dh * dh);
     }
     if (i < rows - 1 && j >= 1) {                // T_{i,j-1}
-        const double u = y(p - 1);
-        const double dv = u - y(p - 1 + cols), dh = u - v;
+        const double dv = v.w - v.sw, dh = v.w - v.c;
         if (dv == 0.0 && dh == 0.0) bad = true;
         else gsum -= dh / sqrt(dv * dv + dh * dh);
     }
@@ -63,7 +78,7 @@ __device__ __forceinline__ float tv_neg_grad_at(Y&& y, int rows, int cols, int i
 }
 __device__ __forceinline__ float tv_neg_grad(const double* __restrict__ y, int rows, int cols,
                                              int i, int j, size_t p) {
-    return tv_neg_grad_at([&](size_t q) { return y[q]; }, rows, cols, i, j, p);
+    return tv_neg_grad_pix(TvPix<double>([&](size_t q) { return y[q]; }, rows, cols, i, j, p), rows, cols, i, j);
 }
 
 __device__ __forceinline__ void tv_grad_body(int rows, int cols, const double* __restrict__ y,
@@ -130,20 +145,20 @@ __device__ __forceinline__ void tv_terms(const double* __restrict__ y, const flo
     }
 }
 
-__device__ __forceinline__ double trial_lambda(const Scalars* sc, int trial, double tn) {
+__device__ __forceinline__ double trial_lambda(const Scalars* sc, int ell, int trial, double tn) {
     // trial = 0-based index from the current l: step gamma * a^(l + trial)
-    return tn > 0.0 ? sc->gamma * pow(sc->a, (double)(sc->ell + trial)) / tn : 0.0;
+    return tn > 0.0 ? sc->gamma * pow(sc->a, (double)(ell + trial)) / tn : 0.0;
 }
 
 __device__ __forceinline__ void tv_trials_body(int rows, int cols, const double* __restrict__ y,
                                                const float* __restrict__ tb,
                                                const double* __restrict__ gpart, int ngpart,
-                                               const Scalars* __restrict__ sc,
+                                               const Scalars* __restrict__ sc, int ell,
                                                double* __restrict__ tpart, int bx) {
     __shared__ double red[4];
     __shared__ double lam[TVJ];
     const double tn = sqrt(reduce_partials(gpart, ngpart, red));
-    if (threadIdx.x < TVJ) lam[threadIdx.x] = trial_lambda(sc, threadIdx.x, tn);
+    if (threadIdx.x < TVJ) lam[threadIdx.x] = trial_lambda(sc, ell, threadIdx.x, tn);
     __syncthreads();
     double lam_r[TVJ];
 #pragma unroll
@@ -172,18 +187,18 @@ __global__ __launch_bounds__(256) void k_tv_trials(int rows, int cols, const dou
                                                    const float* __restrict__ tb,
                                                    const double* __restrict__ gpart, int ngpart,
                                                    const Scalars* __restrict__ sc,
+                                                   const int32_t* __restrict__ ell,
                                                    double* __restrict__ tpart,
                                                    const int* __restrict__ halt) {
     if (halt && *halt) return;
-    tv_trials_body(rows, cols, y, tb, gpart, ngpart, sc, tpart, blockIdx.x);
+    tv_trials_body(rows, cols, y, tb, gpart, ngpart, sc, *ell, tpart, blockIdx.x);
 }
 
 void launch_tv_trials(hipStream_t st, int rows, int cols, const double* y, const float* tb,
-                      const double* gpart, int ngpart, Scalars* sc, int J, double* tpart,
+                      const double* gpart, int ngpart, const Scalars* sc, const int32_t* ell, double* tpart,
                       const int* halt) {
-    (void)J;
     hipLaunchKernelGGL(k_tv_trials, dim3(tv_tpx_blocks(rows, cols)), dim3(256), 0, st, rows, cols, y, tb,
-                       gpart, ngpart, sc, tpart, halt);
+                       gpart, ngpart, sc, ell, tpart, halt);
 }
 
 // One workgroup evaluates TV(y) and TV(y + lam_q t_bar), q < nq, over the whole
@@ -207,42 +222,51 @@ __device__ void tv_trials_wg(const double* __restrict__ y, const float* __restri
     __syncthreads();
 }
 
-__device__ __forceinline__ void tv_decide_body(int rows, int cols, const double* __restrict__ y,
-                                               const float* __restrict__ tb,
-                                               const double* __restrict__ gpart, int ngpart,
-                                               const double* __restrict__ tpart, int ntpart,
-                                               Scalars* __restrict__ sc, const TraceDev& tr,
-                                               int32_t* __restrict__ trials_out) {
+// The decision on one inner step (slot, with l = ell before it): the accepted
+// trial (1-based, 0 for none), its TV (TV(y) for none), and the step length.
+struct TvChoice {
+    int chosen;
+    double tv, lam;
+};
+__device__ __forceinline__ TvChoice tv_choose(int rows, int cols, const double* __restrict__ y,
+                                              const float* __restrict__ tb,
+                                              const double* __restrict__ gpart, int ngpart,
+                                              const double* __restrict__ tpart, int ntpart,
+                                              const Scalars* sc, int ell, int slot, const TraceDev& tr) {
     __shared__ double red[4];
     __shared__ double tv[TVJ + 1];
     __shared__ double lam[TVJ];
     __shared__ int chosen_s;
     __shared__ double tvc_s;
-    const double tn = sqrt(reduce_partials(gpart, ngpart, red));
+    __shared__ double tn_s;
     {
-        // per q, thread t adds entries t, t+256, ... in order (the q's interleaved)
-        double v[TVJ + 1];
+        // thread t adds entries t, t + 256, ... of ||t_bar||^2's partials and of each
+        // q's in order; one pair of barriers for all of them
+        double v[TVJ + 2];
 #pragma unroll
-        for (int q = 0; q <= TVJ; ++q) v[q] = 0.0;
+        for (int q = 0; q <= TVJ + 1; ++q) v[q] = 0.0;
+        for (int g = threadIdx.x; g < ngpart; g += 256) v[TVJ + 1] += gpart[g];
         for (int bidx = threadIdx.x; bidx < ntpart; bidx += 256) {
             const double* row = tpart + (size_t)bidx * (TVJ + 1);
 #pragma unroll
             for (int q = 0; q <= TVJ; ++q) v[q] += row[q];
         }
-        __shared__ double redn[4 * (TVJ + 1)];
-        block_sum_n<TVJ + 1>(v, redn);
+        __shared__ double redn[4 * (TVJ + 2)];
+        block_sum_n<TVJ + 2>(v, redn);
         if (threadIdx.x == 0) {
 #pragma unroll
             for (int q = 0; q <= TVJ; ++q) tv[q] = v[q];
+            tn_s = sqrt(v[TVJ + 1]);
         }
     }
     __syncthreads();
+    const double tn = tn_s;
     const int max_trials = sc->max_trials;
     if (threadIdx.x == 0) {
         chosen_s = -1;
         tvc_s = tv[0];
         if (sc->replay) {
-            const int want = tr.replay[(size_t)sc->iter * sc->K + sc->inner];
+            const int want = tr.replay[(size_t)sc->iter * sc->K + slot];
             if (want >= 1 && want <= max_trials) {
                 chosen_s = want;
                 tvc_s = want <= TVJ ? tv[want] : -1.0;   // -1: evaluate below
@@ -265,7 +289,7 @@ __device__ __forceinline__ void tv_decide_body(int rows, int cols, const double*
         for (int start = TVJ; start < max_trials && chosen_s < 0; start += TVJ) {
             const int nq = min(TVJ, max_trials - start);
             if (threadIdx.x < TVJ)
-                lam[threadIdx.x] = (int)threadIdx.x < nq ? trial_lambda(sc, start + threadIdx.x, tn) : 0.0;
+                lam[threadIdx.x] = (int)threadIdx.x < nq ? trial_lambda(sc, ell, start + threadIdx.x, tn) : 0.0;
             __syncthreads();
             tv_trials_wg(y, tb, rows, cols, lam, nq, out, red);
             if (threadIdx.x == 0) {
@@ -282,56 +306,65 @@ __device__ __forceinline__ void tv_decide_body(int rows, int cols, const double*
     }
     if (sc->replay && chosen_s > TVJ) {
         __shared__ double out[TVJ + 1];
-        if (threadIdx.x == 0) lam[0] = trial_lambda(sc, chosen_s - 1, tn);
+        if (threadIdx.x == 0) lam[0] = trial_lambda(sc, ell, chosen_s - 1, tn);
         __syncthreads();
         tv_trials_wg(y, tb, rows, cols, lam, 1, out, red);
         if (threadIdx.x == 0) tvc_s = out[1];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const int chosen = chosen_s;
-        const int ell0 = sc->ell;
-        const int slot = sc->inner;
-        int used;
-        if (chosen > 0) {
-            sc->lam = trial_lambda(sc, chosen - 1, tn);
-            sc->ell = ell0 + chosen;
-            sc->tv_new = tvc_s;
-            used = chosen;
-        } else {
-            sc->lam = 0.0;
-            sc->ell = ell0 + max_trials;
-            sc->tv_new = tv[0];
-            sc->exhausted = 1;
-            used = max_trials + 1;
-        }
-        if (trials_out) trials_out[slot] = used;
-        if (tr.trials && sc->iter < tr.cap) tr.trials[(size_t)sc->iter * sc->K + slot] = used;
-        if (slot == sc->K - 1 && sc->iter < tr.cap) {
-            if (tr.ell) tr.ell[sc->iter] = sc->ell;
-            if (tr.tv_half) tr.tv_half[sc->iter] = sc->tv_new;
-        }
-        sc->inner = slot + 1;
+    __shared__ double lam_s;
+    if (threadIdx.x == 0) lam_s = chosen_s > 0 ? trial_lambda(sc, ell, chosen_s - 1, tn) : 0.0;
+    __syncthreads();
+    if (chosen_s > 0) return {chosen_s, tvc_s, lam_s};
+    return {0, tv[0], 0.0};
+}
+
+// Records the decision; *ell_out receives l after the step.
+__device__ __forceinline__ void tv_commit(const TvChoice& c, Scalars* sc, const TraceDev& tr,
+                                          int32_t* __restrict__ trials_out, int ell, int slot, int32_t* ell_out) {
+    const int used = c.chosen > 0 ? c.chosen : sc->max_trials + 1;
+    const int ell1 = ell + (c.chosen > 0 ? c.chosen : sc->max_trials);
+    sc->lam = c.lam;
+    *ell_out = ell1;
+    sc->tv_new = c.tv;
+    if (c.chosen <= 0) sc->exhausted = 1;
+    if (trials_out) trials_out[slot] = used;
+    if (tr.trials && sc->iter < tr.cap) tr.trials[(size_t)sc->iter * sc->K + slot] = used;
+    if (slot == sc->K - 1 && sc->iter < tr.cap) {
+        if (tr.ell) tr.ell[sc->iter] = ell1;
+        if (tr.tv_half) tr.tv_half[sc->iter] = sc->tv_new;
     }
+    sc->inner = slot + 1;
+}
+
+// ell: where l is read (the scalars, or where k_tv_apply_grad left it).
+__device__ __forceinline__ void tv_decide_body(int rows, int cols, const double* __restrict__ y,
+                                               const float* __restrict__ tb,
+                                               const double* __restrict__ gpart, int ngpart,
+                                               const double* __restrict__ tpart, int ntpart,
+                                               Scalars* sc, const int32_t* ell, const TraceDev& tr,
+                                               int32_t* __restrict__ trials_out) {
+    const int l = *ell, slot = sc->inner;
+    const TvChoice c = tv_choose(rows, cols, y, tb, gpart, ngpart, tpart, ntpart, sc, l, slot, tr);
+    if (threadIdx.x == 0) tv_commit(c, sc, tr, trials_out, l, slot, &sc->ell);
 }
 
 __global__ __launch_bounds__(256) void k_tv_decide(int rows, int cols, const double* __restrict__ y,
                                                    const float* __restrict__ tb,
                                                    const double* __restrict__ gpart, int ngpart,
                                                    const double* __restrict__ tpart, int ntpart,
-                                                   Scalars* __restrict__ sc, TraceDev tr,
+                                                   Scalars* sc, const int32_t* ell, TraceDev tr,
                                                    int32_t* __restrict__ trials_out,
                                                    const int* __restrict__ halt) {
     if (halt && *halt) return;
-    tv_decide_body(rows, cols, y, tb, gpart, ngpart, tpart, ntpart, sc, tr, trials_out);
+    tv_decide_body(rows, cols, y, tb, gpart, ngpart, tpart, ntpart, sc, ell, tr, trials_out);
 }
 
 void launch_tv_decide(hipStream_t st, int rows, int cols, const double* y, const float* tb,
-                      const double* gpart, int ngpart, const double* tpart, int ntpart, int J,
-                      Scalars* sc, TraceDev tr, int32_t* trials_out, const int* halt) {
-    (void)J;
+                      const double* gpart, int ngpart, const double* tpart, int ntpart, Scalars* sc,
+                      const int32_t* ell, TraceDev tr, int32_t* trials_out, const int* halt) {
     hipLaunchKernelGGL(k_tv_decide, dim3(1), dim3(256), 0, st, rows, cols, y, tb, gpart, ngpart,
-                       tpart, ntpart, sc, tr, trials_out, halt);
+                       tpart, ntpart, sc, ell, tr, trials_out, halt);
 }
 
 __device__ __forceinline__ void tv_apply_body(int n, const double* __restrict__ src,
@@ -449,28 +482,51 @@ void launch_tv_apply_prep(hipStream_t st, const GeomDev& G, const double* src, d
 // pixel and at the neighbours its t_bar reads, with the same fma, so the
 // values are those of the two launches bit for bit; dst and src (and tb_in
 // and tb_out) must not overlap.
+// DECIDE: every workgroup takes the step's decision itself (slot's, from l at
+// *ell), workgroup 0 records it (l to *ell_out, which no workgroup reads).
+// Bound: latency; the decision's own launch took 4.4 us and the gap before it, the
+// sums of its partials 2.5 here, with the pixel's values on their way meanwhile
+// (243^2, 40 inner steps 655 -> 591 us).
+template <bool DECIDE>
 __global__ __launch_bounds__(256) void k_tv_apply_grad(int rows, int cols, const double* __restrict__ src,
                                                        double* __restrict__ dst,
                                                        const float* __restrict__ tb_in,
-                                                       float* __restrict__ tb_out,
-                                                       const Scalars* __restrict__ sc,
-                                                       double* __restrict__ partials,
-                                                       const int* __restrict__ halt) {
+                                                       float* __restrict__ tb_out, Scalars* sc,
+                                                       double* __restrict__ partials, TvStep step,
+                                                       const int* halt) {
     if (halt && *halt) return;
     __shared__ double red[4];
-    const double lam = sc->lam;
     const size_t n = (size_t)rows * cols;
-    auto y = [&](size_t q) { return fma(lam, (double)tb_in[q], src[q]); };
-    double sq = 0.0;
-    const int px = tv_px(n);
-    for (int r = 0; r < px; ++r) {   // the pixels and partial layout of a later k_tv_grad
-        const size_t p = ((size_t)blockIdx.x * px + r) * 256 + threadIdx.x;
+    const int px = DECIDE ? 1 : tv_px(n);   // the pixels and partial layout of a later k_tv_grad
+    double lam = 0.0, sq = 0.0;
+    if constexpr (!DECIDE) lam = sc->lam;
+    for (int r = 0; r < px; ++r) {
+        const size_t p = ((size_t)blockIdx.x * px + r) * 256 + threadIdx.x, pc = p < n ? p : 0;
+        const int i = (int)(pc / cols), j = (int)(pc - (size_t)i * cols);
+        // (on their way during the decision)
+        const TvPix<double> x([&](size_t q) { return src[q]; }, rows, cols, i, j, pc);
+        const TvPix<float> t([&](size_t q) { return tb_in[q]; }, rows, cols, i, j, pc);
+        if constexpr (DECIDE) {
+            const int l = *step.ell;
+            const TvChoice c = tv_choose(rows, cols, src, tb_in, step.gpart, step.ngpart, step.tpart, step.ntpart, sc,
+                                         l, step.slot, step.tr);
+            if (blockIdx.x == 0 && threadIdx.x == 0)
+                tv_commit(c, sc, step.tr, step.trials_out, l, step.slot, step.ell_out);
+            lam = c.lam;
+        }
         if (p < n) {
-            dst[p] = y(p);
-            const int i = (int)(p / cols), j = (int)(p - (size_t)i * cols);
-            const float t = tv_neg_grad_at(y, rows, cols, i, j, p);
-            tb_out[p] = t;
-            sq += (double)t * (double)t;
+            TvPix<double> y;
+            y.c = fma(lam, (double)t.c, x.c);
+            y.s = fma(lam, (double)t.s, x.s);
+            y.e = fma(lam, (double)t.e, x.e);
+            y.n = fma(lam, (double)t.n, x.n);
+            y.ne = fma(lam, (double)t.ne, x.ne);
+            y.w = fma(lam, (double)t.w, x.w);
+            y.sw = fma(lam, (double)t.sw, x.sw);
+            dst[p] = y.c;
+            const float tg = tv_neg_grad_pix(y, rows, cols, i, j);
+            tb_out[p] = tg;
+            sq += (double)tg * (double)tg;
         }
     }
     const double tot = block_sum(sq, red);
@@ -478,11 +534,21 @@ __global__ __launch_bounds__(256) void k_tv_apply_grad(int rows, int cols, const
 }
 
 void launch_tv_apply_grad(hipStream_t st, int rows, int cols, const double* src, double* dst,
-                          const float* tb_in, float* tb_out, const Scalars* sc, double* partials,
-                          const int* halt) {
-    hipLaunchKernelGGL(k_tv_apply_grad, dim3(tv_grad_blocks(rows, cols)), dim3(256), 0, st, rows, cols, src, dst,
-                       tb_in, tb_out, sc, partials, halt);
+                          const float* tb_in, float* tb_out, Scalars* sc, double* partials,
+                          const TvStep* step, const int* halt) {
+    const dim3 grid(tv_grad_blocks(rows, cols));
+    if (step)
+        hipLaunchKernelGGL(k_tv_apply_grad<true>, grid, dim3(256), 0, st, rows, cols, src, dst, tb_in, tb_out, sc,
+                           partials, *step, halt);
+    else
+        hipLaunchKernelGGL(k_tv_apply_grad<false>, grid, dim3(256), 0, st, rows, cols, src, dst, tb_in, tb_out, sc,
+                           partials, TvStep{}, halt);
 }
+
+// Small images only: a decision beyond the first trials goes over the whole image
+// in every workgroup, which up to 2^18 pixels (1,024 workgroups) takes no longer
+// than in one.
+bool tv_folds_decision(int rows, int cols) { return tv_px((size_t)rows * cols) == 1; }
 
 __global__ __launch_bounds__(256) void k_tv_value(int rows, int cols, const double* __restrict__ y,
                                                   double* __restrict__ partials,
@@ -525,7 +591,7 @@ __global__ __launch_bounds__(256) void kb_tv_trials(const SliceDev* __restrict__
         const SliceDev& S = sl[s];
         if (gmem(S.sc)->halt) return;
         tv_trials_body(S.G.rows, S.G.cols, batch_vec(S, src), gmem(S.tb), gmem(S.ptg), src == BV_X ? S.ntv : S.ntg,
-                       gmem(S.sc), gmem(S.ptt), lin);
+                       gmem(S.sc), gmem(S.sc)->ell, gmem(S.ptt), lin);
     });
 }
 
@@ -535,7 +601,7 @@ __global__ __launch_bounds__(256) void kb_tv_decide(const SliceDev* __restrict__
         if (gmem(S.sc)->halt) return;
         const TraceDev tr = S.tr;
         tv_decide_body(S.G.rows, S.G.cols, batch_vec(S, src), gmem(S.tb), gmem(S.ptg), src == BV_X ? S.ntv : S.ntg,
-                       gmem(S.ptt), S.ntt, gmem(S.sc), tr, nullptr);
+                       gmem(S.ptt), S.ntt, gmem(S.sc), &gmem(S.sc)->ell, tr, nullptr);
     });
 }
 
