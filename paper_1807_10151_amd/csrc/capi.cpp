@@ -617,7 +617,7 @@ int lp_enqueue_apply(sp_ctx* c, sp_learned* net, int B, int H, int W, const floa
     const int L = net->layers;
     float* cur = dptr<float>(net->ping);
     float* nxt = dptr<float>(net->pong);
-    lp_softplus(st, th + net->doff(), sps, sps + 16);
+    if (L == 1) lp_softplus(st, th + net->doff(), sps, nullptr);   // (the convolutions form it themselves)
     lp_conv_in(st, B, H, W, u, nullptr, B, cur, th + net->woff(1), halt, run);
     if (L == 1) {
         lp_scale(st, (long)npix, cur, sps, nxt);
@@ -626,7 +626,7 @@ int lp_enqueue_apply(sp_ctx* c, sp_learned* net, int B, int H, int W, const floa
     for (int l = 2; l <= L; ++l) {
         const bool last = l == L;   // b_L = softplus(d) * a_L is all the back path needs
         lp_conv_mid(st, false, B, H, W, cur, last ? nullptr : nxt, th + net->woff(l),
-                    last ? sps : nullptr, last ? nxt : nullptr, halt, run);
+                    last ? th + net->doff() : nullptr, last ? nxt : nullptr, halt, run);
         std::swap(cur, nxt);
     }
     for (int l = L; l >= 2; --l) {
@@ -1253,7 +1253,7 @@ int sp_lp_loss_grad(sp_ctx* c, sp_learned* net, int32_t rows, int32_t cols, cons
     lp_conv_in(st, B, H, W, A(0), nullptr, B, A(1), th + net->woff(1), nullptr, nullptr);
     for (int l = 2; l <= L; ++l)
         lp_conv_mid(st, false, B, H, W, A(l - 1), A(l), th + net->woff(l),
-                    l == L ? sps : nullptr, l == L ? Bb(L) : nullptr, nullptr, nullptr);
+                    l == L ? th + net->doff() : nullptr, l == L ? Bb(L) : nullptr, nullptr, nullptr);
     if (L == 1) lp_scale(st, (long)npix, A(1), sps, Bb(1));
     for (int l = L; l >= 2; --l)
         lp_conv_mid(st, true, B, H, W, Bb(l), Bb(l - 1), th + net->woff(l), nullptr, nullptr, nullptr, nullptr);
@@ -1272,7 +1272,7 @@ int sp_lp_loss_grad(sp_ctx* c, sp_learned* net, int32_t rows, int32_t cols, cons
     }
     // e_L and f_L = softplus(d) e_L (into b_L's buffer); d: sigmoid(d) * sum e_L a_L
     if (L == 1) lp_scale(st, (long)npix, E(1), sps, Bb(1));
-    else lp_conv_mid(st, false, B, H, W, E(L - 1), E(L), th + net->woff(L), sps, Bb(L), nullptr, nullptr);
+    else lp_conv_mid(st, false, B, H, W, E(L - 1), E(L), th + net->woff(L), th + net->doff(), Bb(L), nullptr, nullptr);
     lp_gd(st, (long)npix, E(L), A(L), dptr<double>(net->gdpart), sg, grad + net->doff());
     // forward chain: wgrad(f_l, a_{l-1}) into W_l, f_{l-1} = C_l^T f_l
     for (int l = L; l >= 1; --l) {

@@ -491,7 +491,7 @@ void launch_blob_synth(hipStream_t st, int rows, int cols, const BlobDev& B, con
 
 // learned.hip (learned preconditioner C^T diag(softplus(d)) C)
 void lp_conv_mid(hipStream_t st, bool trans, int B, int H, int W, const float* in, float* out,
-                 const float* Wl, const float* scale, float* out2, const int* halt, const int* run);
+                 const float* Wl, const float* d, float* out2, const int* halt, const int* run);
 void lp_conv_in(hipStream_t st, int B, int H, int W, const float* in, const int32_t* idx, int nsrc,
                 float* out, const float* W1, const int* halt, const int* run);
 void lp_conv_out(hipStream_t st, int B, int H, int W, const float* in, float* out, const float* W1,
