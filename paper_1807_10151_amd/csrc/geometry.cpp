@@ -274,7 +274,10 @@ int build_geometry_into(const sp_geometry* g, int n_cu, GeomDev& G, AngleDev* ta
     G.fwg = (G.fwaves + 3) / 4;
     G.parts = project_parts(g->rows, g->cols, G.nwaves, n_cu * 32);
     G.fparts = project32_parts(G.fwaves, n_cu * 32);
-    G.bp_quad = bp_quad_table(G, tab, nullptr) ? 1 : 0;
+    // The blocks sum axis-parallel angles over two candidate bins, which a
+    // geometry with oblique angles in blocks never exceeds; one of axis-parallel
+    // angles alone has no block to sum.
+    G.bp_quad = G.cls[2] > 0 && G.nbmax <= 2 && bp_quad_table(G, tab, nullptr) ? 1 : 0;
     G.bp_px = G.bp_quad ? 4 : backproject_px(g->rows, g->cols, n_cu * 32);
     if (G.bp_quad) backproject_shape(G, n_cu * 32);
     return SP_OK;

@@ -1,0 +1,48 @@
+// Host check of the forms and launch shapes the library picks for a geometry
+// (geometry.cpp), built with AddressSanitizer and UndefinedBehaviorSanitizer on
+// the host only.
+//
+// Input lines: rows cols n_angles n_bins pixel theta0 dtheta bin_spacing
+// bin_offset.  Prints one line per geometry; exits 1 at the first violation.
+#include <cstdio>
+#include <vector>
+
+#include "../../include/suppcg.h"
+#include "../../paper_1807_10151_amd/csrc/sp_internal.h"
+#include "../../paper_1807_10151_amd/csrc/sp_walk.h"
+
+using namespace sp;
+
+// R^T's blocks sum the axis-parallel angles over two candidate bins per pixel.
+static bool check_blocks(const GeomDev& G, const std::vector<AngleDev>& tab) {
+    if (!G.bp_quad) return true;
+    for (const AngleDev& A : tab)
+        if (A.nb > 2) return std::printf("blocks with %d candidate bins at row %d\n", A.nb, A.row), false;
+    return true;
+}
+
+int main() {
+    char line[512];
+    int count = 0;
+    while (std::fgets(line, sizeof line, stdin)) {
+        sp_geometry g{};
+        if (std::sscanf(line, "%d %d %d %d %lf %lf %lf %lf %lf", &g.rows, &g.cols, &g.n_angles, &g.n_bins, &g.pixel,
+                        &g.theta0, &g.dtheta, &g.bin_spacing, &g.bin_offset) != 9)
+            continue;
+        GeomDev G{};
+        std::vector<AngleDev> tab((size_t)g.n_angles);
+        char err[256] = {0};
+        ++count;
+        if (build_geometry_into(&g, 256, G, tab.data(), err, sizeof err) != SP_OK) {
+            std::printf("%dx%d %dx%d: refused\n", g.rows, g.cols, g.n_angles, g.n_bins);
+            continue;
+        }
+        if (!check_blocks(G, tab)) {
+            std::printf("%dx%d %dx%d ds %g: FAILED\n", g.rows, g.cols, g.n_angles, g.n_bins, G.ds);
+            return 1;
+        }
+        std::printf("%dx%d %dx%d ds %g: ok\n", g.rows, g.cols, g.n_angles, g.n_bins, G.ds);
+    }
+    std::printf("checked %d geometries\n", count);
+    return 0;
+}

@@ -1,0 +1,70 @@
+"""Forms and launch shapes per geometry (geometry.cpp).
+
+Host: tests/index_check/shape_check.cpp over the workload, ragged and random
+geometries, geometries of axis-parallel angles alone and bin spacings down to
+the smallest accepted.
+
+GPU: geometries of axis-parallel angles alone, where a pixel meets up to four
+bins, against the oracle at the operators' 1e-5 bar."""
+import math
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from oracle import projector as oproj
+from oracle.geometry import Geometry as OG
+from tests._problems import rel_l2
+from tests.test_index_safety import geometries
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def build_checker(name, *flags):
+    hipcc = "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = os.path.join(ROOT, "_build", name)
+    os.makedirs(os.path.dirname(exe), exist_ok=True)
+    subprocess.run([hipcc, "-std=c++17", "-ffp-contract=off", *flags, "-I", os.path.join(ROOT, "include"), "-o", exe,
+                    os.path.join(ROOT, "tests", "index_check", "shape_check.cpp"),
+                    os.path.join(ROOT, "paper_1807_10151_amd", "csrc", "geometry.cpp")],
+                   check=True, capture_output=True, text=True)
+    return exe
+
+
+def lines(rows):
+    return "\n".join(" ".join(repr(v) if isinstance(v, float) else str(v) for v in r) for r in rows) + "\n"
+
+
+def test_shapes_of_every_geometry():
+    exe = build_checker("shape_check", "-O1", "-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host",
+                        "-fsanitize=undefined", "-Xarch_host", "-fno-sanitize-recover=all")
+    rows = [g[:9] for g in geometries()]
+    rows += [(20, 30, a, 60, 1.0, t0, math.pi / 2, ds, 0.13) for a in (1, 2, 4) for t0 in (0.0, math.pi / 2)
+             for ds in (0.375, 0.4, 0.5, 0.51, 0.9, 1.0, 1.7)]
+    rows += [(50, 67, 61, 83, 1.0, 0.2, 0.05, ds, 0.3) for ds in (0.375, 0.5, 0.7, 0.94, 1.0, 1.2, 2.5)]
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0", UBSAN_OPTIONS="halt_on_error=1")
+    res = subprocess.run([exe], input=lines(rows), capture_output=True, text=True, env=env, timeout=600)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+    assert f"checked {len(rows)} geometries" in res.stdout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_angles,theta0", [(1, 0.0), (1, math.pi / 2), (2, 0.0), (4, 0.0)])
+@pytest.mark.parametrize("ds,offset", [(0.375, 0.13), (0.4, 0.13), (0.5, 0.0), (0.5, 0.13), (0.9, 0.13), (1.0, 0.0), (2.5, 0.13)])
+def test_axis_parallel_angles_alone(n_angles, theta0, ds, offset):
+    torch = pytest.importorskip("torch")
+    import paper_1807_10151_amd as sp
+    kw = {"theta0": theta0, "dtheta": math.pi / 2, "bin_spacing": ds, "bin_offset": offset}
+    og, g = OG(33, 20, n_angles, 70, **kw), sp.Geometry(33, 20, n_angles, 70, **kw)
+    rng = np.random.default_rng(n_angles)
+    y = rng.standard_normal((n_angles, 70)).astype(np.float32)
+    x = rng.standard_normal((33, 20)).astype(np.float32)
+    R, RT = oproj.matrix(og, "closed")
+    yt, xt = torch.from_numpy(y).cuda(), torch.from_numpy(x).cuda()
+    y64, x64 = y.astype(np.float64).ravel(), x.astype(np.float64).ravel()
+    assert rel_l2(sp.sp_project(g, xt).cpu().numpy(), R @ x64) <= 1e-5
+    assert rel_l2(sp.sp_backproject(g, yt).cpu().numpy(), RT @ y64) <= 1e-5
+    assert rel_l2(sp.sp_gradient(g, xt, yt)[0].cpu().numpy(), RT @ (R @ x64 - y64)) <= 1e-5
