@@ -1058,7 +1058,18 @@ __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* _
         double tot = part[m * 64 + lane];
         for (int sh = 1; sh < shares; ++sh) tot += part[(sh * NQ * PX + m) * 64 + lane];
         const int i = i0 + (p >> 1), j = j0 + n * BPQ_TILE + (p & 1);
-        if (i < G.rows && j < G.cols) out.put((size_t)i * G.cols + j, tot * G.pixel);
+        const bool in = i < G.rows && j < G.cols, finite = fabs(tot) < __builtin_inf();
+        if (__any(in && !finite)) {
+            // A block multiplies bins that only its other pixels meet by weight 0,
+            // which is NaN for a bin that is not finite: such a pixel is summed
+            // again over its own bins.  (A finite sum has met finite bins alone.)
+            const double xj[1] = {xc[n] + ((p & 1) ? 0.5 : -0.5)}, yi = yc + ((p & 2) ? -0.5 : 0.5);
+            double own = 0.0;
+            bp_class<false, 2, TY, 1>(G, ang, G.cls[0], G.cls[2], yp, xj, yi, &own);
+            bp_class<true, 2, TY, 1>(G, ang, G.cls[2], G.cls[4], yp, xj, yi, &own);
+            if (!finite) tot = own;
+        }
+        if (in) out.put((size_t)i * G.cols + j, tot * G.pixel);
     }
 }
 

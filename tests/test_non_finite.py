@@ -1,0 +1,72 @@
+"""Infinities and NaN in a sinogram or an image, whatever form the kernels take:
+they reach every pixel or ray that meets the entry (with a weight above 0), and
+none but those whose own candidate window holds it (where the entry's weight may
+be 0).
+
+A pixel's window is the two bins from the window index of its own footprint
+(plus the selection margin), a ray's the two pixels per band from the minor
+coordinate where it enters the band.  Entries within 1e-9 of a window's edge are
+left out of the comparison.  The finite results are those of the same data with
+the entry set to 0."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import projector as oproj
+from oracle.geometry import Geometry as OG
+from tests._problems import rel_l2
+
+CASES = [(40, 37, 30, 59, {}), (64, 64, 90, 91, {}), (130, 118, 24, 179, {}), (48, 40, 30, 65, {"bin_spacing": 0.96}),
+         (48, 40, 30, 65, {"bin_spacing": 0.9, "bin_offset": 0.37})]
+
+
+def angles(og):
+    th = og.theta0 + np.arange(og.n_angles) * (og.dtheta if og.dtheta is not None else math.pi / og.n_angles)
+    c, s = np.cos(th), np.sin(th)
+    c[abs(c) < 1e-12], s[abs(s) < 1e-12] = 0.0, 0.0
+    return c, s
+
+
+def reads_of_bin(og, a, k):
+    """(pixels that read bin k of angle a, pixels that may by rounding)."""
+    c, s = (v[a] for v in angles(og))
+    x = np.arange(og.cols) - (og.cols - 1) / 2.0
+    y = ((og.rows - 1) / 2.0 - np.arange(og.rows))[:, None]
+    ds = og.bin_spacing
+    s0 = -(og.n_bins - 1) / 2.0 * ds + og.bin_offset
+    margin = 1e-3 + 4e-7 * (og.rows + og.cols + og.n_bins)
+    kf = (x * c + y * s - s0 - (abs(c) + abs(s)) / 2.0 - margin) / ds + 1.0
+    o = np.floor(kf)
+    return (o == k) | (o + 1 == k), abs(kf - np.round(kf)) < 1e-9
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("rows,cols,n_angles,n_bins,kw", CASES)
+def test_backproject(rows, cols, n_angles, n_bins, kw, bad):
+    torch = pytest.importorskip("torch")
+    import paper_1807_10151_amd as sp
+    og, g = OG(rows, cols, n_angles, n_bins, **kw), sp.Geometry(rows, cols, n_angles, n_bins, **kw)
+    RT = oproj.matrix(og, "closed")[1]
+    rng = np.random.default_rng(3)
+    y = rng.standard_normal((n_angles, n_bins)).astype(np.float32)
+    oblique = [a for a, (c, s) in enumerate(zip(*angles(og))) if c != 0.0 and s != 0.0]
+    for count in (1, 1, 1, 4):
+        met, read, edge = (np.zeros((rows, cols), bool) for _ in range(3))
+        y0, yb = y.copy(), y.copy()
+        for a in rng.choice(oblique, count, replace=False):
+            k = int(rng.integers(n_bins // 4, 3 * n_bins // 4))
+            y0[a, k], yb[a, k] = 0.0, bad
+            r, e = reads_of_bin(og, a, k)
+            met |= RT[:, [a * n_bins + k]].toarray().reshape(rows, cols) > 1e-9
+            read |= r
+            edge |= e
+        want = (RT @ y0.astype(np.float64).ravel()).reshape(rows, cols)
+        zero = torch.zeros(rows, cols, device="cuda")
+        for got in (sp.sp_backproject(g, torch.from_numpy(yb).cuda()).cpu().numpy(),
+                    -sp.sp_gradient(g, zero, torch.from_numpy(yb).cuda())[0].cpu().numpy()):
+            assert not np.isfinite(got[met & ~edge]).any()
+            keep = ~read & ~edge
+            assert np.isfinite(got[keep]).all()
+            assert rel_l2(got[keep], want[keep]) <= 1e-5
