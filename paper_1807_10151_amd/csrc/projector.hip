@@ -294,28 +294,30 @@ __device__ __forceinline__ double ray_sum_axis(const GeomDev& G, const AngleDev&
 // or past it reads 0, where the pixels contribute 0.  The longest waves set
 // the launch's length and their walk is bound by the latency of its chain of
 // gathers, so U steps' gathers are issued before their math.
-template <bool HORIZ>
+template <bool HORIZ, class T>
 __device__ __forceinline__ double ray_split(const GeomDev& G, const AngleDev& A, double sk,
-                                            const double* __restrict__ img, int lo, int hi) {
+                                            const T* __restrict__ img, int lo, int hi) {
     const int pitch = HORIZ ? G.pitchXT : G.pitchX;
     double acc = 0.0;
     constexpr int U = 2;   // steps per iteration: their gathers are in flight together
     const double sig = A.slope;
     const double isg = 1.0 / fabs(sig);
     double lp = fma((double)lo, sig, split_b0<HORIZ>(G, A, sk));
-    const int rowbytes = pitch * 8;
+    const int rowbytes = pitch * (int)sizeof(T);
     const char* rowp = reinterpret_cast<const char*>(img - PAD) + (size_t)lo * rowbytes;
-    auto step = [&](const double (&v)[2], double lpv) {
+    auto step = [&](const T (&v)[2], double lpv) {
+        const double v0 = v[0], v1 = v[1];
         const double f = fmin(fmax(fma(__builtin_amdgcn_fract(lpv), -isg, isg), 0.0), 1.0);
-        acc += fma(f, v[0] - v[1], v[1]);
+        acc += fma(f, v0 - v1, v1);
     };
     int m = lo;
     for (; m + U <= hi; m += U) {
-        double lpu[U], v[U][2];
+        double lpu[U];
+        T v[U][2];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             lpu[u] = lp;
-            row_load<double, 2>(row_ref(rowp + u * rowbytes, rowbytes), (unsigned)(int)lp, v[u]);
+            row_load<T, 2>(row_ref(rowp + u * rowbytes, rowbytes), (unsigned)(int)lp, v[u]);
             lp += sig;
         }
 #pragma unroll
@@ -323,8 +325,8 @@ __device__ __forceinline__ double ray_split(const GeomDev& G, const AngleDev& A,
         rowp += U * rowbytes;
     }
     for (; m < hi; ++m) {
-        double v[2];
-        row_load<double, 2>(row_ref(rowp, rowbytes), (unsigned)(int)lp, v);
+        T v[2];
+        row_load<T, 2>(row_ref(rowp, rowbytes), (unsigned)(int)lp, v);
         step(v, lp);
         lp += sig;
         rowp += rowbytes;
@@ -503,6 +505,15 @@ struct LaneRays {
                 parts([&](int l, int h, double (&v)[2]) {
                     double w[2];
                     ray_pair<H>(G, A, sw ? s1 : s0, img, l, h, w);
+                    // The upper ray multiplies one pixel more per band than it
+                    // would by itself, by weight 0: NaN where that is not
+                    // finite, so it is then summed again by itself.  (A finite
+                    // sum has met finite pixels alone.)
+                    const bool finite = fabs(w[1]) < __builtin_inf();
+                    if (__any(!finite)) {
+                        const double own = ray_split<H>(G, A, sw ? s0 : s1, img, l, h);
+                        if (!finite) w[1] = own;
+                    }
                     v[0] = sw ? w[1] : w[0];
                     v[1] = sw ? w[0] : w[1];
                 });

@@ -70,3 +70,49 @@ def test_backproject(rows, cols, n_angles, n_bins, kw, bad):
             keep = ~read & ~edge
             assert np.isfinite(got[keep]).all()
             assert rel_l2(got[keep], want[keep]) <= 1e-5
+
+
+def rays_of_pixel(og, i, j):
+    """(rays whose band pair holds pixel (i, j), rays that may by rounding)."""
+    c, s = (v[:, None] for v in angles(og))
+    sk = (np.arange(og.n_bins) - (og.n_bins - 1) / 2.0) * og.bin_spacing + og.bin_offset
+    xoff, yoff = (og.cols - 1) / 2.0, (og.rows - 1) / 2.0
+    with np.errstate(divide="ignore", invalid="ignore"):
+        vert = (sk - (yoff + 0.5) * s) / c + xoff + 0.5 + np.minimum(s / c, 0.0) + i * (s / c)
+        horiz = yoff + 0.5 - (sk + (xoff + 0.5) * c) / s + np.minimum(c / s, 0.0) + j * (c / s)
+    lp = np.where(abs(s) > abs(c), horiz, vert)
+    q = np.where(abs(s) > abs(c), i, j)
+    o = np.floor(lp)
+    return (o == q) | (o + 1 == q), abs(lp - np.round(lp)) < 1e-9
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("rows,cols,n_angles,n_bins,kw", CASES + [(48, 40, 30, 65, {"bin_spacing": 1.3, "bin_offset": 0.37})])
+def test_project(rows, cols, n_angles, n_bins, kw, bad):
+    torch = pytest.importorskip("torch")
+    import paper_1807_10151_amd as sp
+    og, g = OG(rows, cols, n_angles, n_bins, **kw), sp.Geometry(rows, cols, n_angles, n_bins, **kw)
+    R = oproj.matrix(og, "closed")[0].tocsc()
+    rng = np.random.default_rng(4)
+    x = rng.standard_normal((rows, cols)).astype(np.float32)
+    oblique = np.array([c != 0.0 and s != 0.0 for c, s in zip(*angles(og))])
+    for count in (1, 1, 1, 4):
+        met, read, edge = (np.zeros((n_angles, n_bins), bool) for _ in range(3))
+        edge[~oblique] = True   # axis-parallel rays go by their own weights
+        x0, xb = x.copy(), x.copy()
+        for _ in range(count):
+            i, j = int(rng.integers(4, rows - 4)), int(rng.integers(4, cols - 4))
+            x0[i, j], xb[i, j] = 0.0, bad
+            r, e = rays_of_pixel(og, i, j)
+            met |= R[:, [i * cols + j]].toarray().reshape(n_angles, n_bins) > 1e-9
+            read |= r
+            edge |= e
+        want = (R @ x0.astype(np.float64).ravel()).reshape(n_angles, n_bins)
+        b = torch.zeros(n_angles, n_bins, device="cuda")
+        for got in (sp.sp_project(g, torch.from_numpy(xb).cuda()).cpu().numpy(),
+                    sp.sp_residual(g, torch.from_numpy(xb).cuda(), b)[0].cpu().numpy()):
+            assert not np.isfinite(got[met & ~edge]).any()
+            keep = ~read & ~edge
+            assert np.isfinite(got[keep]).all()
+            assert rel_l2(got[keep], want[keep]) <= 1e-5
