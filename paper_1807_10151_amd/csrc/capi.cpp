@@ -33,7 +33,7 @@ struct BatchState {
     std::vector<sp_geometry> geoms;
     int kind = -1;
     int nbmax = 1;
-    int bp_px = 2;                   // R^T pixels per lane for the whole batch
+    int bp_px = 2;                   // pixels per lane of R^T's pixel form for the whole batch
     int bp_forms = 0;                // forms of R^T among the slices (bp_form)
     int fft_threads = 0;             // of the preconditioner's workgroups
     int fft_forms = 0;               // its forms among the slices (fft_form)
@@ -865,17 +865,17 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         o.ptt = take((size_t)S.ntv * 9 * 8);
         o.pts = take((size_t)std::max(S.ntv, S.nsn) * 8);
     }
-    // one R^T tile shape for the whole batch: four pixels per lane when the
-    // batch's 4-pixel tiles still fill half the wave slots (the sums do not
-    // depend on it, so batched and single solves stay bitwise equal)
+    // one tile shape of R^T's pixel form for the whole batch: four pixels per lane
+    // when its slices' 4-pixel tiles still fill half the wave slots (the sums do
+    // not depend on it, so batched and single solves stay bitwise equal)
     {
         long waves4 = 0;
         B.bp_forms = 0;
         for (const SliceDev& S : B.hs) {
-            waves4 += (long)backproject_tiles(S.G, 4) * 4;
+            if (!S.G.bp_quad) waves4 += (long)backproject_tiles(S.G, 4) * 4;
             B.bp_forms |= bp_form(S.G);
         }
-        B.bp_px = !(B.bp_forms & BP_FORM_PIXEL) || waves4 >= (long)c->n_cu * 16 ? 4 : 2;
+        B.bp_px = waves4 >= (long)c->n_cu * 16 ? 4 : 2;
         // tuned shapes that agree for every slice take precedence
         int tpx = 0;
         bool all = true;

@@ -145,8 +145,7 @@ int project32_parts(int nwaves, int resident_waves) {
 
 int backproject_tiles(const GeomDev& G, int px) {
     if (G.bp_quad)
-        return ((G.cols + G.bp_nq * BPQ_TILE - 1) / (G.bp_nq * BPQ_TILE)) * ((G.rows + BPQ_TILE - 1) / BPQ_TILE) *
-               (px == 2 ? 2 : 1);
+        return ((G.cols + G.bp_nq * BPQ_TILE - 1) / (G.bp_nq * BPQ_TILE)) * ((G.rows + BPQ_TILE - 1) / BPQ_TILE);
     return ((G.cols + 8 * px - 1) / (8 * px)) * ((G.rows + BP_TILE - 1) / BP_TILE);
 }
 

@@ -901,9 +901,7 @@ __device__ __forceinline__ void backproject_body(const GeomDev& G, const AngleDe
 // sinogram with its padding pass 0.097 -> 0.070; 2048^2 x 2864: 5.3 -> 3.3 ms.
 // The accumulators are kept in the order A, B, C, D of BpAngle, which only
 // changes between runs of angles (the signs of cos and sin, and which is
-// larger); acc holds each block's pixels 2 r + c (row r, column c).  PX = 2:
-// the pixels with r + c even (diag 0; pixels 0 and 3) or odd (diag 1; pixels 1
-// and 2), which are A and D or B and C, with the same arithmetic.  One angle
+// larger); acc holds each block's pixels 2 r + c (row r, column c).  One angle
 // per iteration with two blocks, or many waves of one, hides the scalar loads
 // of its constants; two angles per iteration ran out of scalar registers.
 template <class TY>
@@ -935,100 +933,79 @@ __device__ __forceinline__ void swap_acc(double& a, double& b) {
     b = t;
 }
 
-template <class TY, int PX, int NQ>
+template <class TY, int NQ>
 __device__ __forceinline__ void bp_quads(const GeomDev& G, const BpAngle* __restrict__ quad, int beg, int end,
-                                         const TY* __restrict__ yp, const double (&xc)[NQ], double yc, int diag,
-                                         double (&acc)[NQ][PX]) {
+                                         const TY* __restrict__ yp, const double (&xc)[NQ], double yc,
+                                         double (&acc)[NQ][4]) {
     const int rowbytes = G.pitchB * (int)sizeof(TY);
     for (int a = beg; a < end;) {
         const int run = quad[a].run;
         const int stop = min(end, run >> BP_CODE_BITS);
         // to the corners' order (bp_quad_corner), and back after the run
         const bool fx = run & BP_FLIP_X, fy = run & BP_FLIP_Y, vert = run & BP_VERT;
-        const int c0 = bp_quad_corner(run, diag);   // PX = 2: the first pixel's corner
-        const bool ad = c0 == 0 || c0 == 3, swap2 = c0 >= 2;
-        auto to_corners = [&](double (&v)[PX]) {
-            if constexpr (PX == 4) {
-                if (fx) swap_acc(v[0], v[1]), swap_acc(v[2], v[3]);
-                if (fy) swap_acc(v[0], v[2]), swap_acc(v[1], v[3]);
-                if (vert) swap_acc(v[1], v[2]);
-            } else {
-                if (swap2) swap_acc(v[0], v[1]);
-            }
-        };
-        auto to_pixels = [&](double (&v)[PX]) {
-            if constexpr (PX == 4) {
-                if (vert) swap_acc(v[1], v[2]);
-                if (fy) swap_acc(v[0], v[2]), swap_acc(v[1], v[3]);
-                if (fx) swap_acc(v[0], v[1]), swap_acc(v[2], v[3]);
-            } else {
-                if (swap2) swap_acc(v[0], v[1]);
-            }
-        };
 #pragma unroll
-        for (int n = 0; n < NQ; ++n) to_corners(acc[n]);
-        auto angles = [&](auto first, auto second) {   // A and D / B and C
+        for (int n = 0; n < NQ; ++n) {
+            double (&v)[4] = acc[n];
+            if (fx) swap_acc(v[0], v[1]), swap_acc(v[2], v[3]);
+            if (fy) swap_acc(v[0], v[2]), swap_acc(v[1], v[3]);
+            if (vert) swap_acc(v[1], v[2]);
+        }
 #pragma unroll 1
-            for (int q = a; q < stop; ++q) {
-                const BpAngle Q = quad[q];
-                const __amdgpu_buffer_rsrc_t rs = row_rsrc(yp + (size_t)Q.row * G.pitchB, rowbytes);
-                double v[NQ][3], w[NQ];
+        for (int q = a; q < stop; ++q) {
+            const BpAngle Q = quad[q];
+            const __amdgpu_buffer_rsrc_t rs = row_rsrc(yp + (size_t)Q.row * G.pitchB, rowbytes);
+            double v[NQ][3], w[NQ];
 #pragma unroll
-                for (int n = 0; n < NQ; ++n) {
-                    const double kf = bp_quad_kf(xc[n], yc, Q);
-                    QuadBins<TY>::load(rs, (int)kf, v[n]);
-                    w[n] = bp_quad_w(__builtin_amdgcn_fract(kf), Q);
-                }
-#pragma unroll
-                for (int n = 0; n < NQ; ++n) {
-                    double u2[2], u3[3];
-                    double &aA = acc[n][0], &aB = acc[n][PX == 4 ? 1 : 0], &aC = acc[n][PX == 4 ? 2 : 1],
-                           &aD = acc[n][PX - 1];
-                    if constexpr (decltype(first)::value) {
-                        bp_quad_a(Q, w[n], u2);
-                        aA = fma(u2[0], v[n][0], aA);
-                        aA = fma(u2[1], v[n][1], aA);
-                        bp_quad_d(Q, w[n], u2);
-                        aD = fma(u2[0], v[n][1], aD);
-                        aD = fma(u2[1], v[n][2], aD);
-                    }
-                    if constexpr (decltype(second)::value) {
-                        bp_quad_b(Q, w[n], u3);
-                        aB = fma(u3[0], v[n][0], aB);
-                        aB = fma(u3[1], v[n][1], aB);
-                        aB = fma(u3[2], v[n][2], aB);
-                        bp_quad_c(Q, w[n], u3);
-                        aC = fma(u3[0], v[n][0], aC);
-                        aC = fma(u3[1], v[n][1], aC);
-                        aC = fma(u3[2], v[n][2], aC);
-                    }
-                }
+            for (int n = 0; n < NQ; ++n) {
+                const double kf = bp_quad_kf(xc[n], yc, Q);
+                QuadBins<TY>::load(rs, (int)kf, v[n]);
+                w[n] = bp_quad_w(__builtin_amdgcn_fract(kf), Q);
             }
-        };
-        if constexpr (PX == 4) angles(std::true_type{}, std::true_type{});
-        else if (ad) angles(std::true_type{}, std::false_type{});
-        else angles(std::false_type{}, std::true_type{});
 #pragma unroll
-        for (int n = 0; n < NQ; ++n) to_pixels(acc[n]);
+            for (int n = 0; n < NQ; ++n) {
+                double u2[2], u3[3];
+                double &aA = acc[n][0], &aB = acc[n][1], &aC = acc[n][2], &aD = acc[n][3];
+                bp_quad_a(Q, w[n], u2);
+                aA = fma(u2[0], v[n][0], aA);
+                aA = fma(u2[1], v[n][1], aA);
+                bp_quad_d(Q, w[n], u2);
+                aD = fma(u2[0], v[n][1], aD);
+                aD = fma(u2[1], v[n][2], aD);
+                bp_quad_b(Q, w[n], u3);
+                aB = fma(u3[0], v[n][0], aB);
+                aB = fma(u3[1], v[n][1], aB);
+                aB = fma(u3[2], v[n][2], aB);
+                bp_quad_c(Q, w[n], u3);
+                aC = fma(u3[0], v[n][0], aC);
+                aC = fma(u3[1], v[n][1], aC);
+                aC = fma(u3[2], v[n][2], aC);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) {
+            double (&v)[4] = acc[n];
+            if (vert) swap_acc(v[1], v[2]);
+            if (fy) swap_acc(v[0], v[2]), swap_acc(v[1], v[3]);
+            if (fx) swap_acc(v[0], v[1]), swap_acc(v[2], v[3]);
+        }
         a = stop;
     }
 }
 
 // R^T over 2 x 2 blocks: a workgroup owns NQ 16 x 16 pixel tiles side by side
-// (tile `id` in the order of bp_tile_of; PX = 2: two workgroups per tile,
-// one per diagonal), lane l block (l / 8, l % 8) of each.  The angles are
-// split into G.bp_shares shares; wave w of the workgroup's NW sums shares w,
-// w + NW, ..., and the shares are added in order through LDS, so the result
-// does not depend on NW, NQ or PX.
-template <class TY, int PX, int NW, int NQ>
+// (tile `id` in the order of bp_tile_of), lane l block (l / 8, l % 8) of each.
+// The angles are split into G.bp_shares shares; wave w of the workgroup's NW
+// sums shares w, w + NW, ..., and the shares are added in order through LDS, so
+// the result does not depend on NW or NQ.
+template <class TY, int NW, int NQ>
 __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* __restrict__ ang,
                                              const BpAngle* __restrict__ quad, const TY* __restrict__ yp,
                                              BpOut out, int id) {
+    constexpr int PX = 4;
     extern __shared__ double part[];   // [shares][NQ][PX][64]
     const int gx = (G.cols + NQ * BPQ_TILE - 1) / (NQ * BPQ_TILE), gy = (G.rows + BPQ_TILE - 1) / BPQ_TILE;
-    const int diag = PX == 2 && id >= gx * gy ? 1 : 0;
     int bx, by;
-    bp_tile_of(id - diag * gx * gy, gx, gy, bx, by);
+    bp_tile_of(id, gx, gy, bx, by);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i0 = by * BPQ_TILE + 2 * (lane >> 3), j0 = bx * NQ * BPQ_TILE + 2 * (lane & 7);
@@ -1036,7 +1013,6 @@ __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* _
     double xc[NQ];
 #pragma unroll
     for (int n = 0; n < NQ; ++n) xc[n] = (double)(j0 + n * BPQ_TILE) + 0.5 - G.xoff;
-    auto pixel = [&](int u) { return PX == 4 ? u : (diag ? 1 + u : 3 * u); };   // 2 r + c
     const int shares = G.bp_shares;
     for (int sh = wave; sh < shares; sh += NW) {
         double acc[NQ][PX];
@@ -1046,16 +1022,15 @@ __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* _
             for (int u = 0; u < PX; ++u) acc[n][u] = 0.0;
         int b, e;
         split_range(G.cls[0], G.cls[2], sh, shares, b, e);   // oblique angles of both orientations
-        bp_quads<TY, PX, NQ>(G, quad, b, e, yp, xc, yc, diag, acc);
+        bp_quads<TY, NQ>(G, quad, b, e, yp, xc, yc, acc);
         split_range(G.cls[2], G.cls[4], sh, shares, b, e);   // axis-parallel angles
         if (b < e) {
 #pragma unroll
             for (int n = 0; n < NQ; ++n)
 #pragma unroll
-                for (int u = 0; u < PX; ++u) {
-                    const int p = pixel(u);
+                for (int p = 0; p < PX; ++p) {
                     const double xj[1] = {xc[n] + ((p & 1) ? 0.5 : -0.5)};
-                    bp_class<true, 2, TY, 1>(G, ang, b, e, yp, xj, yc + ((p & 2) ? -0.5 : 0.5), &acc[n][u]);
+                    bp_class<true, 2, TY, 1>(G, ang, b, e, yp, xj, yc + ((p & 2) ? -0.5 : 0.5), &acc[n][p]);
                 }
         }
 #pragma unroll
@@ -1065,7 +1040,7 @@ __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* _
     }
     __syncthreads();
     for (int m = wave; m < NQ * PX; m += NW) {
-        const int n = m / PX, p = pixel(m % PX);
+        const int n = m / PX, p = m % PX;
         double tot = part[m * 64 + lane];
         for (int sh = 1; sh < shares; ++sh) tot += part[(sh * NQ * PX + m) * 64 + lane];
         const int i = i0 + (p >> 1), j = j0 + n * BPQ_TILE + (p & 1);
@@ -1084,7 +1059,7 @@ __device__ __forceinline__ void bp_quad_body(const GeomDev& G, const AngleDev* _
     }
 }
 
-size_t bp_quad_lds(int shares, int px, int nq) { return (size_t)shares * px * nq * 64 * sizeof(double); }
+size_t bp_quad_lds(int shares, int nq) { return (size_t)shares * nq * 4 * 64 * sizeof(double); }
 
 __device__ __forceinline__ void run_ride(const ScalarRide& ride) {
     if (ride.ps) scalar_body(OP_SNORM, ride.sc, ride.tr, ride.ps, ride.ns, nullptr, 0);
@@ -1103,14 +1078,14 @@ __global__ __launch_bounds__(256) void k_backproject(GeomDev G, const AngleDev* 
     if (ride.sc && blockIdx.x == 0 && blockIdx.y == 0) run_ride(ride);
 }
 
-template <class TY, int PX, int NW, int NQ>
+template <class TY, int NW, int NQ>
 __global__ __launch_bounds__(64 * NW) void k_backproject_quad(GeomDev G, const AngleDev* __restrict__ ang,
                                                               const BpAngle* __restrict__ quad,
                                                               const TY* __restrict__ yp, BpOut out,
                                                               ScalarRide ride,
                                                               const int* __restrict__ halt) {
     if (halt && *halt) return;
-    bp_quad_body<TY, PX, NW, NQ>(G, ang, quad, yp, out, blockIdx.x);
+    bp_quad_body<TY, NW, NQ>(G, ang, quad, yp, out, blockIdx.x);
     if (ride.sc && blockIdx.x == 0) {
         if (threadIdx.x >= 256) return;   // the scalar steps are those of a 256-thread workgroup
         run_ride(ride);
@@ -1137,14 +1112,14 @@ __global__ __launch_bounds__(256) void kb_backproject(const SliceDev* __restrict
 // wave (slices of 16 shares take two turns, so that their workgroups, of small
 // images, last about as long as those of 8 shares; with 4 waves the 16-slice
 // batch of 128^2 to 512^2 was 8% slower than pixel by pixel), 4 for two.
-template <int PX, int NW, int NQ>
+template <int NW, int NQ>
 __global__ __launch_bounds__(64 * NW) void kb_backproject_quad(const SliceDev* __restrict__ sl, ItemTable t,
                                                            int round) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
         if (!S.G.bp_quad || S.G.bp_nq != NQ || gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
-        bp_quad_body<double, PX, NW, NQ>(G, cmem(S.ang), cmem(S.quad), gmem(S.rpd),
+        bp_quad_body<double, NW, NQ>(G, cmem(S.ang), cmem(S.quad), gmem(S.rpd),
                                      BpOut{nullptr, gmem(S.g), round != 0}, lin);
     });
 }
@@ -1159,21 +1134,14 @@ void launch_bp_b_px(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, 
     }
 }
 
-template <int PX>
-void launch_bp_b_quads(hipStream_t st, const SliceDev* sl, ItemTable t, int forms, int round) {
-    if (forms & BP_FORM_QUAD)
-        hipLaunchKernelGGL((kb_backproject_quad<PX, 8, 1>), dim3(t.grid), dim3(512),
-                           bp_quad_lds(BPQ_MAX_SHARES, PX, 1), st, sl, t, round);
-    if (forms & BP_FORM_QUAD2)
-        hipLaunchKernelGGL((kb_backproject_quad<PX, 4, 2>), dim3(t.grid), dim3(256), bp_quad_lds(4, PX, 2), st, sl,
-                           t, round);
-}
-
 void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms,
                           bool round) {
     const int rd = round ? 1 : 0;
-    if (px == 4) launch_bp_b_quads<4>(st, sl, t, forms, rd);
-    else launch_bp_b_quads<2>(st, sl, t, forms, rd);
+    if (forms & BP_FORM_QUAD)
+        hipLaunchKernelGGL((kb_backproject_quad<8, 1>), dim3(t.grid), dim3(512), bp_quad_lds(BPQ_MAX_SHARES, 1), st, sl,
+                           t, rd);
+    if (forms & BP_FORM_QUAD2)
+        hipLaunchKernelGGL((kb_backproject_quad<4, 2>), dim3(t.grid), dim3(256), bp_quad_lds(4, 2), st, sl, t, rd);
     if (!(forms & BP_FORM_PIXEL)) return;
     if (px == 4) launch_bp_b_px<4>(st, sl, t, nbmax, rd);
     else launch_bp_b_px<2>(st, sl, t, nbmax, rd);
@@ -1191,27 +1159,21 @@ void launch_bp_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const T
     }
 }
 
-template <class TY, int PX, int NW, int NQ>
+template <class TY, int NW, int NQ>
 void launch_bp_quad(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
                     BpOut out, const int* halt, const ScalarRide& ride) {
-    hipLaunchKernelGGL((k_backproject_quad<TY, PX, NW, NQ>), dim3(backproject_tiles(G, PX)), dim3(64 * NW),
-                       bp_quad_lds(G.bp_shares, PX, NQ), st, G, ang, quad, yp, out, ride, halt);
+    hipLaunchKernelGGL((k_backproject_quad<TY, NW, NQ>), dim3(backproject_tiles(G, G.bp_px)), dim3(64 * NW),
+                       bp_quad_lds(G.bp_shares, NQ), st, G, ang, quad, yp, out, ride, halt);
 }
 
-// One wave per share (two tiles per wave go with 4 shares, see backproject_shape).
-template <class TY, int PX>
-void launch_bp_quad_px(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
-                       BpOut out, const int* halt, const ScalarRide& ride) {
-    if (G.bp_nq == 2) launch_bp_quad<TY, PX, 4, 2>(st, G, ang, quad, yp, out, halt, ride);
-    else if (G.bp_shares == 8) launch_bp_quad<TY, PX, 8, 1>(st, G, ang, quad, yp, out, halt, ride);
-    else launch_bp_quad<TY, PX, 16, 1>(st, G, ang, quad, yp, out, halt, ride);
-}
-
+// Blocks: one wave per share (two tiles per wave go with 4 shares, see
+// backproject_shape).
 template <class TY>
 void launch_bp(hipStream_t st, const GeomDev& G, const AngleDev* ang, const BpAngle* quad, const TY* yp,
                BpOut out, const int* halt, const ScalarRide& ride) {
-    if (G.bp_quad && G.bp_px == 4) launch_bp_quad_px<TY, 4>(st, G, ang, quad, yp, out, halt, ride);
-    else if (G.bp_quad) launch_bp_quad_px<TY, 2>(st, G, ang, quad, yp, out, halt, ride);
+    if (G.bp_quad && G.bp_nq == 2) launch_bp_quad<TY, 4, 2>(st, G, ang, quad, yp, out, halt, ride);
+    else if (G.bp_quad && G.bp_shares == 8) launch_bp_quad<TY, 8, 1>(st, G, ang, quad, yp, out, halt, ride);
+    else if (G.bp_quad) launch_bp_quad<TY, 16, 1>(st, G, ang, quad, yp, out, halt, ride);
     else if (G.bp_px == 4) launch_bp_px<TY, 4>(st, G, ang, yp, out, halt, ride);
     else launch_bp_px<TY, 2>(st, G, ang, yp, out, halt, ride);
 }

@@ -53,7 +53,7 @@ struct GeomDev {
     int pitchB;         // nB + 2 PAD: row pitch of the padded sinogram
     int nbmax;          // max backprojection candidates over the angles
     int parts;          // parts each ray's step range is split into by R (1: whole rays)
-    int bp_px;          // pixels per lane of R^T (2 or 4, see backproject_px)
+    int bp_px;          // pixels per lane of R^T's pixel form (2 or 4, see backproject_px)
     int bp_quad;        // 1: R^T sums oblique angles over 2 x 2 pixel blocks (see BpAngle)
     int bp_shares;      // shares each angle range is split into by R^T's blocks (4, 8 or 16)
     int bp_nq;          // 16 x 16 tiles side by side per wave of R^T's blocks (1 or 2)
@@ -305,9 +305,8 @@ int project_comb_blocks(const GeomDev& G);
 // WG_PARTS parts, else one per ray workgroup.
 int project_blocks(const GeomDev& G);
 int project32_blocks(const GeomDev& G);   // of launch_project32
-// R^T workgroups for px pixels per lane: 8 x 8 px pixel tiles, or with G.bp_quad
-// 16 x 16 G.bp_nq pixel tiles of 2 x 2 blocks (px = 4: a lane sums its blocks
-// whole; px = 2: half of them, two workgroups per tile).
+// R^T workgroups: 8 x 8 px pixel tiles for px pixels per lane, or with G.bp_quad
+// (whatever px) 16 x 16 G.bp_nq pixel tiles of 2 x 2 blocks.
 int backproject_tiles(const GeomDev& G, int px);
 // R^T's block constants for the oblique angles tab[0 .. G.cls[2]) (out: that
 // many entries); false, with out incomplete, for geometries whose footprints
@@ -589,8 +588,8 @@ void launch_prep_b(hipStream_t st, const SliceDev* sl, ItemTable t, int which);
 // residual: rpd = R xh - b with the f partials in pf; else w = R z (from the
 // prepared z) with the (R z)^T q partials in pf.
 void launch_project_b(hipStream_t st, const SliceDev* sl, ItemTable t, ItemTable tc, bool residual);
-// px: pixels per lane of every slice in the launch (their G.bp_px); forms: the
-// forms of R^T among the slices (bp_form).
+// px: pixels per lane of the launch's slices in the pixel form (their G.bp_px);
+// forms: the forms of R^T among the slices (bp_form).
 enum BpForm : int { BP_FORM_PIXEL = 1, BP_FORM_QUAD = 2, BP_FORM_QUAD2 = 4 };
 inline int bp_form(const GeomDev& G) { return !G.bp_quad ? BP_FORM_PIXEL : (G.bp_nq == 2 ? BP_FORM_QUAD2 : BP_FORM_QUAD); }
 // round: see launch_backproject.

@@ -21,6 +21,16 @@ static bool check_blocks(const GeomDev& G, const std::vector<AngleDev>& tab) {
     return true;
 }
 
+// R^T's blocks have one shape, whatever the pixels per lane of the pixel form.
+static bool check_tiles(const GeomDev& G) {
+    const int gx = G.bp_quad ? BPQ_TILE * G.bp_nq : 8 * G.bp_px, gy = G.bp_quad ? BPQ_TILE : BP_TILE;
+    if (backproject_tiles(G, G.bp_px) != ((G.cols + gx - 1) / gx) * ((G.rows + gy - 1) / gy))
+        return std::printf("tiles of the default shape\n"), false;
+    if (G.bp_quad && backproject_tiles(G, 2) != backproject_tiles(G, 4))
+        return std::printf("blocks with 2 pixels per lane\n"), false;
+    return true;
+}
+
 int main() {
     char line[512];
     int count = 0;
@@ -37,7 +47,7 @@ int main() {
             std::printf("%dx%d %dx%d: refused\n", g.rows, g.cols, g.n_angles, g.n_bins);
             continue;
         }
-        if (!check_blocks(G, tab)) {
+        if (!check_blocks(G, tab) || !check_tiles(G)) {
             std::printf("%dx%d %dx%d ds %g: FAILED\n", g.rows, g.cols, g.n_angles, g.n_bins, G.ds);
             return 1;
         }
