@@ -265,6 +265,7 @@ int build_geometry_into(sp_ctx* c, const sp_geometry* g, GeomDev& G, AngleDev* t
     int parts, px;
     if (shape_lookup(*g, parts, px)) {
         G.parts = G.fparts = parts;
+        G.pmem = parts > WG_PARTS ? 1 : 0;
         G.bp_px = px;
     }
     return SP_OK;
@@ -295,8 +296,8 @@ int setup_geometry(sp_ctx* c, const sp_geometry* g) {
     if (G.pair && ((rc = ensure(c, c->zp, nX * 4)) || (rc = ensure(c, c->zTp, nXT * 4)))) return rc;
     if ((rc = ensure(c, c->yp, nY * 4))) return rc;
     if ((rc = ensure(c, c->ypd, nY * 8))) return rc;
-    const int segs = std::max(G.parts, G.pair ? G.fparts : 1);
-    if (segs > WG_PARTS && (rc = ensure(c, c->seg, (size_t)segs * g->n_angles * g->n_bins * 8))) return rc;
+    const int segs = std::max(G.pmem ? G.parts : 0, G.pair && G.fparts > WG_PARTS ? G.fparts : 0);
+    if (segs && (rc = ensure(c, c->seg, (size_t)segs * g->n_angles * g->n_bins * 8))) return rc;
     if (relayout) {
         HIP_TRY(c, hipMemsetAsync(c->xp.ptr, 0, c->xp.bytes, c->stream));
         HIP_TRY(c, hipMemsetAsync(c->xTp.ptr, 0, c->xTp.bytes, c->stream));

@@ -121,26 +121,59 @@ int project_wave_count(const GeomDev& G) { return project_waves(G, nullptr); }
 int project_waves(const GeomDev& G, WaveDev* out) { return wave_table(G, false, out); }
 int project_pair_waves(const GeomDev& G, WaveDev* out) { return wave_table(G, true, out); }
 
-int project_parts(int rows, int cols, int nwaves, int resident_waves) {
+void project_shape(GeomDev& G, int resident_waves) {
+    const long W = resident_waves, nw = G.nwaves, side = ((long)G.rows + G.cols) / 2;
+    const bool longest = std::max(G.rows, G.cols) > 512;
+    auto set = [&](long parts, bool mem) {
+        G.parts = (int)parts;
+        G.pmem = mem ? 1 : 0;
+    };
     // Large images: 8 parts keep the resident waves on a band of the float64
     // copies (measured: 2048^2 x 2048 angles 9.3 -> 5.8 ms).
-    if ((long)rows * cols >= (1L << 21)) return 8;
-    // Otherwise split only a grid that would leave a tenth of the wave slots
-    // or more empty (a split costs a combine pass and a second walk set-up;
-    // 512^2 x 720, 8,159 waves on 8,192 slots: one part 0.095 ms, two 0.12).
-    if (10L * nwaves >= 9L * resident_waves) return 1;
-    const long p = (resident_waves + nwaves - 1) / nwaves;
-    return p > 4 ? 4 : (int)p;
+    if ((long)G.rows * G.cols >= (1L << 21)) return set(8, true);
+    // Otherwise split only a grid that would leave wave slots empty.  Parts summed
+    // in one workgroup save the second launch and the traffic of the sums, but a
+    // workgroup of 8 or 16 waves needs a CU's slots in one piece: a grid that
+    // exceeds a round of them (4 parts: a quarter of W waves, 2: a half) takes two
+    // (the last and shortest workgroups apart).  Times of one call in us:
+    if (10 * nw >= 9 * W) return set(1, false);
+    if (side > 512) {
+        // Long walks: any such tail costs more than the launch.  8 parts where 4 (or
+        // 3, 2) fill the slots; 900^2 x 150 angles, 3 parts in the workgroup /
+        // through memory / 8 through memory 106 / 75 / 76, 1300^2 x 36 (4 parts) 80
+        // / 77 / 63; 600^2 x 320 (2 parts) 70 / 75 / 75.
+        if (side < 724 && 2 * nw > W && 8 * nw <= 5 * W) return set(2, false);
+        return set(8, true);
+    }
+    // Short walks: one workgroup's 13 - 25 against 17 - 30; 100^2 x 1000 angles, 4 /
+    // 2 / 1 parts 20 / 17 / 21, x 2000 26 / 24 / 22.
+    if (side <= 128) return set(4 * nw <= W ? 4 : (2 * nw <= W ? 2 : 1), false);
+    // Few angles for the image's size (1.4 per pixel of a side are 0.03 waves per
+    // square pixel), or a grid between the two rounds: through memory, but where
+    // the workgroups are about one per CU.  400^2 x 180 angles, 4 parts 36 / 33, x
+    // 230 (3 parts) 51 / 40, x 113 30 / 31; 300^2 x 390 (3) 42 / 32.
+    const bool few = 54 * nw < side * side || (longest && 2 * nw < W);
+    const bool between = side >= 280 && 3 * nw > W && 5 * nw < 2 * W;
+    if ((few && 32 * nw > 5 * W) || between) return set(std::min(4L, (W + nw - 1) / nw), true);
+    // 243^2 x 360, 4 parts 24 / 27; 340^2 x 476, 2 in the workgroup / 3 through memory
+    // 39 / 46; 460^2 x 644, 1 / 2 parts 80 / 92.
+    return set(25 * nw <= 7 * W ? 4 : (25 * nw < 18 * W || longest ? 2 : 1), false);
 }
 
-int project32_parts(int nwaves, int resident_waves) {
+int project32_parts(const GeomDev& G, int resident_waves) {
+    const long W = resident_waves, nw = G.fwaves, side = std::max(G.rows, G.cols);
+    // Through memory where workgroups of several parts leave a tail, as above: 4
+    // or 2 in the workgroup / 8 through memory, 1300^2 x 10 angles 80 / 38, x 140
+    // 127 / 90, 900^2 x 90 60 / 46, 400^2 x 260 44 / 36; 600^2 x 520 84 / 83.
+    if (side > 512 && 8 * nw < 3 * W) return 8;
+    if (side >= 380 && (side >= 440 ? 8 : 7) * nw > W && 5 * nw < W) return 8;
     // Four waves per SIMD with four gathers in flight each keep the two-ray
     // form busy: split the rays of grids that stay below that.  Measured, 1 / 2
     // / 4 parts: 64^2 12.5 / 10.7 / 10.8 us, 243^2 x 340 28.8 / 21.0 / 19.7,
     // 300^2 x 424 37.0 / 34.2 / 37.1, 430^2 x 600 62.2 / 61.4 / 69.2, 512^2 x 720
     // 88.3 / 89.5 / 99.9, 2048^2 x 2048 (8 in its place) 2315 / 2318 / 2478.
-    if (8L * nwaves <= resident_waves) return WG_PARTS;
-    return 2L * nwaves < resident_waves ? 2 : 1;
+    if (8 * nw <= W) return WG_PARTS;
+    return 2 * nw < W ? 2 : 1;
 }
 
 int backproject_tiles(const GeomDev& G, int px) {
@@ -271,8 +304,8 @@ int build_geometry_into(const sp_geometry* g, int n_cu, GeomDev& G, AngleDev* ta
     G.nwg = (G.nwaves + 3) / 4;
     G.fwaves = project_pair_waves(G, nullptr);
     G.fwg = (G.fwaves + 3) / 4;
-    G.parts = project_parts(g->rows, g->cols, G.nwaves, n_cu * 32);
-    G.fparts = project32_parts(G.fwaves, n_cu * 32);
+    project_shape(G, n_cu * 32);
+    G.fparts = project32_parts(G, n_cu * 32);
     // The blocks sum axis-parallel angles over two candidate bins, which a
     // geometry with oblique angles in blocks never exceeds; one of axis-parallel
     // angles alone has no block to sum.

@@ -538,13 +538,15 @@ struct LaneRays {
 template <class T>
 __host__ __device__ inline int ray_parts(const GeomDev& G) { return sizeof(T) == 4 ? G.fparts : G.parts; }
 template <class T>
+inline bool ray_mem(const GeomDev& G) { return sizeof(T) == 4 ? G.fparts > WG_PARTS : G.pmem != 0; }
+template <class T>
 __host__ __device__ inline int ray_waves(const GeomDev& G) { return sizeof(T) == 4 ? G.fwaves : G.nwaves; }
 template <class T>
 inline int ray_wgs(const GeomDev& G) { return sizeof(T) == 4 ? G.fwg : G.nwg; }
 
 // Rays of ray workgroup wg (entries 4 wg .. 4 wg + 3 of the wave table), whole.
-// With at most WG_PARTS parts a workgroup has four waves per part: waves 4 p ..
-// sum part p, and the parts are added in order through LDS (no pass over
+// Parts that do not go through memory: a workgroup has four waves per part: waves
+// 4 p .. sum part p, and the parts are added in order through LDS (no pass over
 // memory, no second launch).  The batched form (SEQ) has one wave per table
 // entry, which sums the parts one after another: the same sums.
 template <bool SEQ, class T>
@@ -581,7 +583,7 @@ __device__ __forceinline__ void project_body(const GeomDev& G, const AngleDev* _
     R.store(G, acc, o, wg);
 }
 
-// Part `part` of the rays of workgroup wg (more than WG_PARTS parts), to
+// Part `part` of the rays of workgroup wg (parts through memory), to
 // seg[(part*nA + ai)*nB + k] (ai: class-sorted table index); the combine step
 // adds the parts in order.  The parts of a large image run one after another
 // (part the slowest grid index), so the resident waves read a band of it.
@@ -618,6 +620,23 @@ __device__ __forceinline__ void project_comb_body(const GeomDev& G, const AngleD
     project_partial(project_value(G, ang[bx].row, wmax, k, valid, acc, o), o, by * gx + bx);
 }
 
+// The same sums of at most WG_PARTS parts (one ray per lane) for ray workgroup wg,
+// with the partials of project_body.
+__device__ __forceinline__ void project_sum_body(const GeomDev& G, const AngleDev* __restrict__ ang,
+                                                 const WaveDev* __restrict__ waves,
+                                                 const double* __restrict__ seg, const RayOut& o, int wg) {
+    const int wi = 4 * wg + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const WaveDev W = waves[wi < G.nwaves ? wi : 0];
+    int ai, k;
+    const bool valid = wave_ray(W, threadIdx.x & 63, G.nB, ai, k) && wi < G.nwaves;
+    if (!valid) ai = W.a0, k = 0;
+    const double* v = seg + (size_t)ai * G.nB + k;
+    const size_t stride = (size_t)G.nA * G.nB;
+    double acc = valid ? v[0] : 0.0;
+    for (int j = 1; valid && j < G.parts; ++j) acc += v[j * stride];
+    project_partial(project_value(G, ang[ai].row, ang[ai].wmax, k, valid, acc, o), o, wg);
+}
+
 // 256 threads per part (at most WG_PARTS), one workgroup per ray workgroup.
 template <class T>
 __global__ __launch_bounds__(256 * WG_PARTS, sizeof(T) == 4 ? 4 : 8) void k_project(GeomDev G, const AngleDev* __restrict__ ang,
@@ -648,6 +667,14 @@ __global__ __launch_bounds__(256) void k_project_comb(GeomDev G, const AngleDev*
                                                       const int* __restrict__ halt) {
     if (halt && *halt) return;
     project_comb_body(G, ang, seg, o, parts, blockIdx.x, blockIdx.y, gridDim.x);
+}
+
+__global__ __launch_bounds__(256) void k_project_sum(GeomDev G, const AngleDev* __restrict__ ang,
+                                                     const WaveDev* __restrict__ waves,
+                                                     const double* __restrict__ seg, RayOut o,
+                                                     const int* __restrict__ halt) {
+    if (halt && *halt) return;
+    project_sum_body(G, ang, waves, seg, o, blockIdx.x);
 }
 
 // residual: rpd = R xh - b (float64) with f partials; else w = R z (float64)
@@ -720,11 +747,14 @@ void launch_project_form(hipStream_t st, const GeomDev& G, const AngleDev* ang, 
                          const T* xp, const T* xTp, const RayOut& o, double* seg, const int* ord,
                          const int* halt) {
     const int parts = ray_parts<T>(G);
-    if (parts > WG_PARTS) {
+    if (ray_mem<T>(G)) {
         hipLaunchKernelGGL((k_project_part<T>), dim3(ray_wgs<T>(G), parts), dim3(256), 0, st, G, ang, waves, xp,
                            xTp, seg, ord, halt);
-        hipLaunchKernelGGL(k_project_comb, dim3(G.nA, (G.nB + 255) / 256), dim3(256), 0, st, G,
-                           ang, (const double*)seg, o, parts, halt);
+        if (parts > WG_PARTS)
+            hipLaunchKernelGGL(k_project_comb, dim3(G.nA, (G.nB + 255) / 256), dim3(256), 0, st, G,
+                               ang, (const double*)seg, o, parts, halt);
+        else
+            hipLaunchKernelGGL(k_project_sum, dim3(G.nwg), dim3(256), 0, st, G, ang, waves, (const double*)seg, o, halt);
         return;
     }
     hipLaunchKernelGGL((k_project<T>), dim3(ray_wgs<T>(G)), dim3(256 * parts), 0, st, G, ang, waves, xp, xTp, o, ord,

@@ -53,6 +53,9 @@ struct GeomDev {
     int pitchB;         // nB + 2 PAD: row pitch of the padded sinogram
     int nbmax;          // max backprojection candidates over the angles
     int parts;          // parts each ray's step range is split into by R (1: whole rays)
+    int pmem;           // single-slice launches, 1: the parts' sums go through memory (seg) and a
+                        // second launch adds them; 0: the workgroup that sums them adds them
+                        // (at most WG_PARTS).  The same sums either way.
     int bp_px;          // pixels per lane of R^T's pixel form (2 or 4, see backproject_px)
     int bp_quad;        // 1: R^T sums oblique angles over 2 x 2 pixel blocks (see BpAngle)
     int bp_shares;      // shares each angle range is split into by R^T's blocks (4, 8 or 16)
@@ -63,7 +66,7 @@ struct GeomDev {
     int nwg;            // its ray workgroups, four waves each: ceil(nwaves / 4)
     int pair;           // 1: R of a float32 image sums two neighbouring rays per lane (see pair_fits)
     int fwaves, fwg;    // nwaves and nwg of that two-ray form
-    int fparts;         // its parts
+    int fparts;         // its parts (through memory with more than WG_PARTS)
 };
 
 // R^T's constants of one oblique angle for a 2 x 2 block of pixels (G.bp_quad),
@@ -227,8 +230,8 @@ struct RayOut {
     const double* dq = nullptr;
     double* wout = nullptr;
 };
-// R's parts that one workgroup sums and adds; with more, seg (parts * nA * nB
-// float64) receives the per-part sums before a second launch adds them.
+// Most parts that one workgroup sums and adds; where they go through memory seg
+// (parts * nA * nB float64) receives the per-part sums.
 constexpr int WG_PARTS = 4;
 // waves: the device copy of R's wave table (project_waves); ord: the device copy of
 // project_order, the ray workgroup each launched workgroup runs.
@@ -293,13 +296,15 @@ long wave_steps(const GeomDev& G, const AngleDev* tab, const WaveDev& W);
 // stay the same.
 std::vector<int32_t> project_order(const GeomDev& G, const AngleDev* tab, const WaveDev* waves,
                                    int nwaves, int n_cu);
-// Parts R splits each ray's step range into, chosen from the geometry and the
-// device's wave slots (both the single-slice and the batched solver use it,
-// so their sums agree): of a float64 image, and of a float32 image in the
-// two-ray form.
-int project32_parts(int nwaves, int resident_waves);
-int project_parts(int rows, int cols, int nwaves, int resident_waves);
-// Combine workgroups (more than WG_PARTS parts): one angle by one 256-bin chunk each.
+// Parts R splits each ray's step range into (both the single-slice and the batched
+// solver use them, so their sums agree) and whether their sums go through memory,
+// chosen from the geometry and the device's wave slots: of a float64 image
+// (G.parts, G.pmem; reads G.nwaves), and the parts of a float32 image in the
+// two-ray form (reads G.fwaves).
+void project_shape(GeomDev& G, int resident_waves);
+int project32_parts(const GeomDev& G, int resident_waves);
+// Combine workgroups of more than WG_PARTS parts: one angle by one 256-bin chunk
+// each.
 int project_comb_blocks(const GeomDev& G);
 // Number of float64 partials R writes: one per combine workgroup with more than
 // WG_PARTS parts, else one per ray workgroup.

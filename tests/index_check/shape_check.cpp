@@ -4,6 +4,7 @@
 //
 // Input lines: rows cols n_angles n_bins pixel theta0 dtheta bin_spacing
 // bin_offset.  Prints one line per geometry; exits 1 at the first violation.
+#include <algorithm>
 #include <cstdio>
 #include <vector>
 
@@ -31,6 +32,20 @@ static bool check_tiles(const GeomDev& G) {
     return true;
 }
 
+// R's parts: at most WG_PARTS in one workgroup, which has room for them; on long
+// walks only where their grid fills between a half and five eighths of the wave
+// slots (their tail costs more than a second launch elsewhere).
+static bool check_parts(const GeomDev& G, long W) {
+    if (G.parts < 1 || G.parts > 8 || G.fparts < 1 || G.fparts > 8) return std::printf("part counts\n"), false;
+    if (!G.pmem && G.parts > WG_PARTS) return std::printf("%d parts in a workgroup\n", G.parts), false;
+    if (project_blocks(G) != (G.parts > WG_PARTS ? project_comb_blocks(G) : G.nwg)) return std::printf("partials\n"), false;
+    if (G.rows + G.cols > 2 * 512 + 1 && G.parts > 1 && !G.pmem && !(2L * G.nwaves > W && 8L * G.nwaves <= 5 * W))
+        return std::printf("%d waves of %dx%d in %d parts in a workgroup\n", G.nwaves, G.rows, G.cols, G.parts), false;
+    if (std::max(G.rows, G.cols) > 512 && 8L * G.fwaves < 3 * W && G.fparts <= WG_PARTS)
+        return std::printf("%d two-ray waves of %dx%d in %d parts in a workgroup\n", G.fwaves, G.rows, G.cols, G.fparts), false;
+    return true;
+}
+
 int main() {
     char line[512];
     int count = 0;
@@ -47,7 +62,7 @@ int main() {
             std::printf("%dx%d %dx%d: refused\n", g.rows, g.cols, g.n_angles, g.n_bins);
             continue;
         }
-        if (!check_blocks(G, tab) || !check_tiles(G)) {
+        if (!check_blocks(G, tab) || !check_tiles(G) || !check_parts(G, 256 * 32)) {
             std::printf("%dx%d %dx%d ds %g: FAILED\n", g.rows, g.cols, g.n_angles, g.n_bins, G.ds);
             return 1;
         }
