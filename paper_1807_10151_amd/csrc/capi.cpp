@@ -33,6 +33,7 @@ struct BatchState {
     std::vector<sp_geometry> geoms;
     int kind = -1;
     int nbmax = 1;
+    int wg_parts = 0;                // R's parts side by side in a workgroup (ProjectTables)
     int bp_px = 2;                   // pixels per lane of R^T's pixel form for the whole batch
     int bp_forms = 0;                // forms of R^T among the slices (bp_form)
     int fft_threads = 0;             // of the preconditioner's workgroups
@@ -713,7 +714,9 @@ int stage_blocks(const SliceDev& S, int stage) {
     const GeomDev& G = S.G;
     switch (stage) {
     case BS_PREP: return ((G.cols + 31) / 32) * ((G.rows + 31) / 32);
-    case BS_PROJECT: return G.nwg * (G.parts > WG_PARTS ? G.parts : 1);
+    case BS_PROJECT: return G.pmem ? 0 : G.nwg;
+    case BS_PROJ_PART: return G.pmem ? G.nwg * G.parts : 0;
+    case BS_PROJ_SUM: return G.pmem && G.parts <= WG_PARTS ? G.nwg : 0;
     case BS_PROJ_COMB: return G.parts > WG_PARTS ? project_comb_blocks(G) : 0;
     case BS_BACKPROJECT: return backproject_tiles(G, G.bp_px);
     case BS_ROWS: return S.F.P ? ((G.rows + 1) / 2 + S.F.NF - 1) / S.F.NF : (G.rows + 1) / 2;
@@ -731,7 +734,8 @@ int stage_blocks(const SliceDev& S, int stage) {
 double item_cost(const SliceDev& S, int stage) {
     const GeomDev& G = S.G;
     switch (stage) {
-    case BS_PROJECT: return (double)std::max(G.rows, G.cols) / (G.parts > WG_PARTS ? G.parts : 1);
+    case BS_PROJECT: return (double)std::max(G.rows, G.cols);
+    case BS_PROJ_PART: return (double)std::max(G.rows, G.cols) / G.parts;
     case BS_PROJ_COMB: return (double)G.parts;
     case BS_BACKPROJECT: return (double)G.nA;
     case BS_ROWS:
@@ -786,6 +790,12 @@ ItemTable table(sp_ctx* c, int stage, int order = -1, int wpc = -1) {
     const long want = wpc > 0 ? (long)wpc * c->n_cu : (long)t.n;
     t.grid = (int)std::max(1L, std::min<long>(t.n, want));
     return t;
+}
+
+ProjectTables project_tables(sp_ctx* c, int order = -1, int wpc = -1) {
+    return {table(c, BS_PROJECT, order, wpc), table(c, BS_PROJ_PART, order, wpc),
+            table(c, BS_PROJ_COMB, order < 0 ? c->batch->order[BS_PROJECT] : order, 0),
+            table(c, BS_PROJ_SUM, order < 0 ? c->batch->order[BS_PROJECT] : order, 0), c->batch->wg_parts};
 }
 
 // (Re)builds the batch layout: geometry tables, one device arena holding every
@@ -853,7 +863,7 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         o.xp = take((size_t)G.rows * G.pitchX * 8);
         o.xTp = take((size_t)G.cols * G.pitchXT * 8);
         o.rpd = take((size_t)G.nA * G.pitchB * 8);
-        o.seg = take(G.parts > WG_PARTS ? (size_t)G.parts * G.nA * G.nB * 8 : 0);
+        o.seg = take(G.pmem ? (size_t)G.parts * G.nA * G.nB * 8 : 0);
         o.dvec = take((size_t)S.n * 8 * 5);  // x, x_half, p, g, z (float64)
         o.vec = take((size_t)S.n * 4);       // t_bar
         o.sq = take((size_t)S.m * 8 * 2);    // q = R p, w = R z
@@ -887,6 +897,11 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         }
         if (all && tpx) B.bp_px = tpx;
         for (SliceDev& S : B.hs) S.G.bp_px = B.bp_px;
+    }
+    {
+        std::vector<GeomDev*> gs;
+        for (SliceDev& S : B.hs) gs.push_back(&S.G);
+        B.wg_parts = project_batch(gs.data(), n, c->n_cu * 32);
     }
     for (SliceDev& S : B.hs)
         if (S.F.P) {
@@ -926,7 +941,7 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         S.xp = reinterpret_cast<double*>(base + o.xp);
         S.xTp = reinterpret_cast<double*>(base + o.xTp);
         S.rpd = reinterpret_cast<double*>(base + o.rpd);
-        S.seg = S.G.parts > WG_PARTS ? reinterpret_cast<double*>(base + o.seg) : nullptr;
+        S.seg = S.G.pmem ? reinterpret_cast<double*>(base + o.seg) : nullptr;
         double* dv = reinterpret_cast<double*>(base + o.dvec);
         S.x = dv;
         S.xh = dv + (size_t)S.n;
@@ -995,7 +1010,7 @@ void batch_stage(sp_ctx* c, int stage, int order, int wpc, double mu, double rho
     const ItemTable t = table(c, stage, order, wpc);
     switch (stage) {
     case BS_PREP: launch_prep_b(st, sl, t, BV_XH); break;
-    case BS_PROJECT: launch_project_b(st, sl, t, table(c, BS_PROJ_COMB, order, 0), true); break;
+    case BS_PROJECT: launch_project_b(st, sl, project_tables(c, order, wpc), true); break;
     case BS_BACKPROJECT: launch_backproject_b(st, sl, t, B.nbmax, B.bp_px, B.bp_forms, false); break;
     case BS_ROWS:
         launch_precond_b(st, sl, t, table(c, BS_COLS, order, wpc), B.fft_threads, B.fft_forms, mu, rho);
@@ -1040,6 +1055,10 @@ int batch_tune(sp_ctx* c, double mu, double rho) {
                     B.wpc[stage] = wpc;
                 }
             }
+        if (stage == BS_PROJECT) {
+            B.order[BS_PROJ_PART] = B.order[BS_PROJECT];
+            B.wpc[BS_PROJ_PART] = B.wpc[BS_PROJECT];
+        }
         if (stage == BS_ROWS) {
             B.order[BS_COLS] = B.order[BS_ROWS];
             B.wpc[BS_COLS] = B.wpc[BS_ROWS];
@@ -2688,18 +2707,18 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
     launch_init_b(st, sl, table(c, BS_VEC));                       // x_{1/2} = x_0
     if ((sp->flags & SP_FLAG_AUTOTUNE) && !B.tuned && (rc = batch_tune(c, mu, rho))) return rc;
     // Algorithm 3, steps 1-9, every slice in each launch
-    const ItemTable tprep = table(c, BS_PREP), tproj = table(c, BS_PROJECT),
+    const ProjectTables tproj = project_tables(c);
+    const ItemTable tprep = table(c, BS_PREP),
                     tbp = table(c, BS_BACKPROJECT), tvec = table(c, BS_VEC), ttv = table(c, BS_TV),
                     ttvt = table(c, BS_TVT), ttvg = table(c, BS_TVG),
-                    tone = table(c, BS_SLICE, 0, 0), tpq = table(c, BS_PQ),
-                    tcomb = table(c, BS_PROJ_COMB, B.order[BS_PROJECT], 0);
+                    tone = table(c, BS_SLICE, 0, 0), tpq = table(c, BS_PQ);
     launch_prep_b(st, sl, tprep, BV_XH);
-    launch_project_b(st, sl, tproj, tcomb, true);
+    launch_project_b(st, sl, tproj, true);
     launch_scalar_b(st, sl, tone, OP_F0);
     launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms, g32);
     batch_precond(c, mu, rho);
     launch_prep_b(st, sl, tprep, BV_Z);
-    launch_project_b(st, sl, tproj, tcomb, false);     // w = R z
+    launch_project_b(st, sl, tproj, false);            // w = R z
     launch_scalar_b(st, sl, tone, OP_BETA);
     launch_update_pq_b(st, sl, tpq);                             // p = -z, q = R p = -w
     launch_scalar_b(st, sl, tone, OP_ALPHA0);
@@ -2723,12 +2742,12 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
         } else {
             launch_tv_apply_prep_b(st, sl, tprep, BV_X, true, false);   // x_{k+1/2} = x_k, R's copies
         }
-        launch_project_b(st, sl, tproj, tcomb, true);
+        launch_project_b(st, sl, tproj, true);
         launch_scalar_b(st, sl, tone, OP_F);
         launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms, g32);
         batch_precond(c, mu, rho);
         launch_prep_b(st, sl, tprep, BV_Z);
-        launch_project_b(st, sl, tproj, tcomb, false); // w = R z, (R z)^T q
+        launch_project_b(st, sl, tproj, false);        // w = R z, (R z)^T q
         launch_scalar_b(st, sl, tone, OP_BETA);
         launch_update_pq_b(st, sl, tpq);
         launch_scalar_b(st, sl, tone, OP_ALPHA);

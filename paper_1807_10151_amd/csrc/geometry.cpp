@@ -253,6 +253,28 @@ void backproject_shape(GeomDev& G, int resident_waves) {
     G.bp_nq = tiles < resident_waves ? 1 : 2;
 }
 
+int project_batch(GeomDev* const* g, int n, int resident_waves) {
+    // A batch iteration in us, parts one after another / side by side: 1 x 64^2 96 /
+    // 87, 4 x 128^2 130 / 113, 1 x 250^2 164 / 133, 2 x 250^2 (3,900 waves) 197 / 181,
+    // 4 x 250^2 259 / 274, 16 x 96^2 (4,700) 144 / 154, 1 x 400^2 (5,000) 259 / 224,
+    // 1 x 400^2 x 30 223 / 145; on longer walks the empty slots cost more.
+    const long W = resident_waves;
+    long waves = 0, steps = 0;
+    for (int s = 0; s < n; ++s) {
+        if (g[s]->parts > WG_PARTS) continue;
+        waves += g[s]->nwaves;
+        steps += (long)g[s]->nwaves * std::max(g[s]->rows, g[s]->cols);
+    }
+    const bool side_by_side = 8 * waves <= (steps >= 160 * waves ? 5 : 4) * W;
+    int wg_parts = 0;
+    for (int s = 0; s < n; ++s) {
+        if (g[s]->parts > WG_PARTS) continue;
+        if (!side_by_side) g[s]->pmem = 0;
+        else if (!g[s]->pmem) wg_parts = std::max(wg_parts, (int)g[s]->parts);
+    }
+    return wg_parts;
+}
+
 int project_comb_blocks(const GeomDev& G) { return G.nA * ((G.nB + 255) / 256); }
 
 int project_blocks(const GeomDev& G) {

@@ -692,8 +692,8 @@ __device__ __forceinline__ RayOut batch_out(const SliceDev& S, bool residual) {
     return o;
 }
 
-// The slices with at most WG_PARTS parts: item lin runs ray workgroup lin of the
-// order, whole.  Apart from the split slices' body, and with the loop over the
+// The slices without pmem: item lin runs ray workgroup lin of the
+// order, whole, a wave summing its rays' parts one after another.  Apart from the split slices' body, and with the loop over the
 // parts inside each walk, it fits eight waves per SIMD (one kernel for both,
 // six: 16 slices of 128^2 to 512^2 246 -> 217 us; part sums through memory and
 // a second launch 223 + 22).
@@ -701,19 +701,35 @@ __global__ __launch_bounds__(256, 8) void kb_project(const SliceDev* __restrict_
                                                   int residual) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
-        if (S.G.parts > WG_PARTS || gmem(S.sc)->halt) return;
+        if (gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         project_body<true, double>(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), batch_out(S, residual),
                                    cmem(S.pord)[lin]);
     });
 }
 
-// The others: item lin = part * (ray workgroups) + i runs that part of ray
+// The same with the parts side by side in the workgroup, as the single-slice
+// launch: one item per workgroup, since the waves of the parts beyond the first
+// end before its sums are stored (and those of parts that the slice does not
+// have at once).
+__global__ __launch_bounds__(256 * WG_PARTS, 8) void kb_project_wg(const SliceDev* __restrict__ sl, ItemTable t,
+                                                              int residual) {
+    const uint32_t it = t.items[blockIdx.x];
+    if (it == ITEM_NONE) return;
+    const SliceDev& S = sl[it >> ITEM_SHIFT];
+    if (gmem(S.sc)->halt) return;
+    const GeomDev G = S.G;
+    if ((int)(threadIdx.x >> 8) >= G.parts) return;
+    project_body<false, double>(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), batch_out(S, residual),
+                                cmem(S.pord)[it & ITEM_MASK]);
+}
+
+// The slices with pmem: item lin = part * (ray workgroups) + i runs that part of ray
 // workgroup i of the order.
 __global__ __launch_bounds__(256, 8) void kb_project_part(const SliceDev* __restrict__ sl, ItemTable t) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
-        if (S.G.parts <= WG_PARTS || gmem(S.sc)->halt) return;
+        if (gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         project_part_body<double>(G, cmem(S.ang), cmem(S.pwave), gmem(S.xp), gmem(S.xTp), gmem(S.seg),
                                   cmem(S.pord)[lin % G.nwg], lin / G.nwg);
@@ -733,13 +749,25 @@ __global__ __launch_bounds__(256) void kb_project_comb(const SliceDev* __restric
     });
 }
 
-void launch_project_b(hipStream_t st, const SliceDev* sl, ItemTable t, ItemTable tc, bool residual) {
+// That of the slices with pmem and fewer; virtual block: the ray workgroup.
+__global__ __launch_bounds__(256) void kb_project_sum(const SliceDev* __restrict__ sl, ItemTable t, int residual) {
+    for_items(t, [&](int s, int lin) {
+        const SliceDev& S = sl[s];
+        if (gmem(S.sc)->halt) return;
+        const GeomDev G = S.G;
+        project_sum_body(G, cmem(S.ang), cmem(S.pwave), gmem(S.seg), batch_out(S, residual), lin);
+    });
+}
+
+void launch_project_b(hipStream_t st, const SliceDev* sl, const ProjectTables& T, bool residual) {
     const int r = residual ? 1 : 0;
-    hipLaunchKernelGGL(kb_project, dim3(t.grid), dim3(256), 0, st, sl, t, r);
-    if (tc.n > 0) {
-        hipLaunchKernelGGL(kb_project_part, dim3(t.grid), dim3(256), 0, st, sl, t);
-        hipLaunchKernelGGL(kb_project_comb, dim3(tc.grid), dim3(256), 0, st, sl, tc, r);
-    }
+    if (T.t.n > 0 && T.wg_parts > 0)
+        hipLaunchKernelGGL(kb_project_wg, dim3(T.t.n), dim3(256 * T.wg_parts), 0, st, sl, T.t, r);
+    else if (T.t.n > 0)
+        hipLaunchKernelGGL(kb_project, dim3(T.t.grid), dim3(256), 0, st, sl, T.t, r);
+    if (T.tp.n > 0) hipLaunchKernelGGL(kb_project_part, dim3(T.tp.grid), dim3(256), 0, st, sl, T.tp);
+    if (T.tc.n > 0) hipLaunchKernelGGL(kb_project_comb, dim3(T.tc.grid), dim3(256), 0, st, sl, T.tc, r);
+    if (T.ts.n > 0) hipLaunchKernelGGL(kb_project_sum, dim3(T.ts.grid), dim3(256), 0, st, sl, T.ts, r);
 }
 
 template <class T>

@@ -53,9 +53,9 @@ struct GeomDev {
     int pitchB;         // nB + 2 PAD: row pitch of the padded sinogram
     int nbmax;          // max backprojection candidates over the angles
     int parts;          // parts each ray's step range is split into by R (1: whole rays)
-    int pmem;           // single-slice launches, 1: the parts' sums go through memory (seg) and a
-                        // second launch adds them; 0: the workgroup that sums them adds them
-                        // (at most WG_PARTS).  The same sums either way.
+    int pmem;           // 1: the parts' sums go through memory (seg) and a second launch adds them;
+                        // 0: the workgroup that sums them adds them (at most WG_PARTS).
+                        // The same sums either way.
     int bp_px;          // pixels per lane of R^T's pixel form (2 or 4, see backproject_px)
     int bp_quad;        // 1: R^T sums oblique angles over 2 x 2 pixel blocks (see BpAngle)
     int bp_shares;      // shares each angle range is split into by R^T's blocks (4, 8 or 16)
@@ -303,6 +303,11 @@ std::vector<int32_t> project_order(const GeomDev& G, const AngleDev* tab, const 
 // two-ray form (reads G.fwaves).
 void project_shape(GeomDev& G, int resident_waves);
 int project32_parts(const GeomDev& G, int resident_waves);
+// How a batch sums the parts of its slices with at most WG_PARTS of them: as their
+// own solves would while the batch leaves wave slots empty (returns the most parts
+// in a workgroup), else one after another in a wave, which needs neither seg nor a
+// second launch (G.pmem cleared; returns 0).  The sums are the same.
+int project_batch(GeomDev* const* g, int n, int resident_waves);
 // Combine workgroups of more than WG_PARTS parts: one angle by one 256-bin chunk
 // each.
 int project_comb_blocks(const GeomDev& G);
@@ -538,7 +543,7 @@ struct SliceDev {
     double *q, *w;      // R p and R z, nA x nB (float64)
     double *xp, *xTp;   // float64 padded copies
     double* rpd;        // float64 padded sinogram (residual)
-    double* seg;        // R's per-part ray sums, [parts][nA][nB] (more than WG_PARTS parts)
+    double* seg;        // R's per-part ray sums, [parts][nA][nB] (G.pmem)
     const int* pord;    // R's ray-workgroup order (project_order)
     double *pf, *pgp, *pqq, *ptg, *ptt, *pts;   // pf: f, then (R z)^T q
     Scalars* sc;
@@ -550,7 +555,8 @@ struct SliceDev {
 enum BatchVec : int { BV_XH = 0, BV_X = 1, BV_P = 2, BV_Z = 3 };
 enum BatchStage : int {
     BS_PREP = 0, BS_PROJECT, BS_BACKPROJECT, BS_ROWS, BS_COLS, BS_TV, BS_VEC, BS_SLICE, BS_PROJ_COMB,
-    BS_PQ, BS_TVT, BS_TVG, BS_COUNT
+    BS_PQ, BS_TVT, BS_TVG, BS_PROJ_PART, BS_PROJ_SUM,
+    BS_COUNT
 };
 struct ItemTable {
     const uint32_t* items;
@@ -592,7 +598,15 @@ __device__ __forceinline__ double* batch_vec(const SliceDev& S, int which) {
 void launch_prep_b(hipStream_t st, const SliceDev* sl, ItemTable t, int which);
 // residual: rpd = R xh - b with the f partials in pf; else w = R z (from the
 // prepared z) with the (R z)^T q partials in pf.
-void launch_project_b(hipStream_t st, const SliceDev* sl, ItemTable t, ItemTable tc, bool residual);
+// The slices without G.pmem (table t) sum their rays' parts one after another in a
+// wave, or with wg_parts > 0 side by side in a workgroup (wg_parts: their most
+// parts; one workgroup per item); those with it per part (tp), to be added by a
+// second launch (tc: more than WG_PARTS parts, ts: the others).
+struct ProjectTables {
+    ItemTable t, tp, tc, ts;
+    int wg_parts;
+};
+void launch_project_b(hipStream_t st, const SliceDev* sl, const ProjectTables& T, bool residual);
 // px: pixels per lane of the launch's slices in the pixel form (their G.bp_px);
 // forms: the forms of R^T among the slices (bp_form).
 enum BpForm : int { BP_FORM_PIXEL = 1, BP_FORM_QUAD = 2, BP_FORM_QUAD2 = 4 };

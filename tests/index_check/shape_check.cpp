@@ -46,6 +46,29 @@ static bool check_parts(const GeomDev& G, long W) {
     return true;
 }
 
+// A batch of n such slices: parts side by side as in the slice's own solve while the
+// waves leave slots empty, in sequence once they fill them; more than WG_PARTS parts
+// stay as they are.
+static bool check_batch(const GeomDev& G, long W) {
+    for (int n : {1, 2, 64}) {
+        std::vector<GeomDev> g((size_t)n, G);
+        std::vector<GeomDev*> p;
+        for (GeomDev& q : g) p.push_back(&q);
+        const int wg = project_batch(p.data(), n, (int)W);
+        const long waves = (long)n * G.nwaves;
+        for (const GeomDev& q : g) {
+            if (q.parts != G.parts || q.pmem > G.pmem || (q.parts > WG_PARTS && !q.pmem))
+                return std::printf("batch of %d: parts\n", n), false;
+            if (q.parts > WG_PARTS) continue;
+            const int own = q.pmem ? 0 : q.parts;   // parts in a workgroup side by side
+            if (2 * waves <= W && (wg != own || q.pmem != G.pmem))
+                return std::printf("batch of %d, %ld waves: %d of %d parts side by side\n", n, waves, wg, own), false;
+            if (8 * waves > 5 * W && (wg || q.pmem)) return std::printf("batch of %d, %ld waves: split\n", n, waves), false;
+        }
+    }
+    return true;
+}
+
 int main() {
     char line[512];
     int count = 0;
@@ -62,7 +85,8 @@ int main() {
             std::printf("%dx%d %dx%d: refused\n", g.rows, g.cols, g.n_angles, g.n_bins);
             continue;
         }
-        if (!check_blocks(G, tab) || !check_tiles(G) || !check_parts(G, 256 * 32)) {
+        if (!check_blocks(G, tab) || !check_tiles(G) || !check_parts(G, 256 * 32) ||
+            !check_batch(G, 256 * 32)) {
             std::printf("%dx%d %dx%d ds %g: FAILED\n", g.rows, g.cols, g.n_angles, g.n_bins, G.ds);
             return 1;
         }
