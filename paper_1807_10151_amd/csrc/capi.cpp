@@ -32,10 +32,9 @@ struct DevBuf {
 struct BatchState {
     std::vector<sp_geometry> geoms;
     int kind = -1;
-    int nbmax = 1;
+    int nbmax = 1;                   // most candidate bins of the slices in R^T's pixel form
     int wg_parts = 0;                // R's parts side by side in a workgroup (ProjectTables)
     int bp_px = 2;                   // pixels per lane of R^T's pixel form for the whole batch
-    int bp_forms = 0;                // forms of R^T among the slices (bp_form)
     int fft_threads = 0;             // of the preconditioner's workgroups
     int fft_forms = 0;               // its forms among the slices (fft_form)
     std::vector<SliceDev> hs;        // host copies; per-call pointers filled in each call
@@ -718,7 +717,10 @@ int stage_blocks(const SliceDev& S, int stage) {
     case BS_PROJ_PART: return G.pmem ? G.nwg * G.parts : 0;
     case BS_PROJ_SUM: return G.pmem && G.parts <= WG_PARTS ? G.nwg : 0;
     case BS_PROJ_COMB: return G.parts > WG_PARTS ? project_comb_blocks(G) : 0;
-    case BS_BACKPROJECT: return backproject_tiles(G, G.bp_px);
+    case BS_BACKPROJECT:
+    case BS_BPQ16:
+    case BS_BPQ8:
+    case BS_BPQ2: return bp_stage(G) == stage ? backproject_tiles(G, G.bp_px) : 0;
     case BS_ROWS: return S.F.P ? ((G.rows + 1) / 2 + S.F.NF - 1) / S.F.NF : (G.rows + 1) / 2;
     case BS_COLS: return S.F.P ? (S.F.SP + S.F.NF - 1) / S.F.NF : 0;
     case BS_TV: return tv_blocks(G.rows, G.cols);
@@ -737,7 +739,10 @@ double item_cost(const SliceDev& S, int stage) {
     case BS_PROJECT: return (double)std::max(G.rows, G.cols);
     case BS_PROJ_PART: return (double)std::max(G.rows, G.cols) / G.parts;
     case BS_PROJ_COMB: return (double)G.parts;
-    case BS_BACKPROJECT: return (double)G.nA;
+    case BS_BACKPROJECT:
+    case BS_BPQ16:
+    case BS_BPQ8:
+    case BS_BPQ2: return (double)G.nA;
     case BS_ROWS:
     case BS_COLS: return S.F.P ? (double)S.F.P * S.F.logP : 0.0;
     case BS_VEC: return (double)S.n / std::max(1, vec_blocks(S.n));
@@ -798,6 +803,12 @@ ProjectTables project_tables(sp_ctx* c, int order = -1, int wpc = -1) {
             table(c, BS_PROJ_SUM, order < 0 ? c->batch->order[BS_PROJECT] : order, 0), c->batch->wg_parts};
 }
 
+BackprojectTables backproject_tables(sp_ctx* c, int order = -1, int wpc = -1) {
+    const BatchState& B = *c->batch;
+    return {table(c, BS_BACKPROJECT, order, wpc), table(c, BS_BPQ16, order, wpc), table(c, BS_BPQ8, order, wpc),
+            table(c, BS_BPQ2, order, wpc), B.nbmax, B.bp_px, c->n_cu};
+}
+
 // (Re)builds the batch layout: geometry tables, one device arena holding every
 // slice's padded copies, vectors, FFT scratch, twiddles and partials, and the
 // item tables.  Kept while the geometries and preconditioner kind repeat.
@@ -829,7 +840,7 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         SliceDev& S = B.hs[s];
         if ((rc = build_geometry(c, &geoms[s], S.G, tabs[s]))) return fail(c, rc, "slice %d: %s", s, c->err);
         const GeomDev& G = S.G;
-        B.nbmax = std::max(B.nbmax, G.nbmax);
+        if (!G.bp_quad) B.nbmax = std::max(B.nbmax, G.nbmax);
         S.n = G.rows * G.cols;
         S.F = FFTPlan{};
         if (kind == SP_PRECOND_RAMP) {
@@ -881,11 +892,8 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
     // not depend on it, so batched and single solves stay bitwise equal)
     {
         long waves4 = 0;
-        B.bp_forms = 0;
-        for (const SliceDev& S : B.hs) {
+        for (const SliceDev& S : B.hs)
             if (!S.G.bp_quad) waves4 += (long)backproject_tiles(S.G, 4) * 4;
-            B.bp_forms |= bp_form(S.G);
-        }
         B.bp_px = waves4 >= (long)c->n_cu * 16 ? 4 : 2;
         // tuned shapes that agree for every slice take precedence
         int tpx = 0;
@@ -993,6 +1001,11 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         B.count[st][1] = (int)o1.size();
         all.insert(all.end(), o1.begin(), o1.end());
     }
+    // R^T over blocks reads a slice's angle constants through the scalar cache: with
+    // the slices grouped by XCD, where they balance, a CU's workgroups share them
+    // (16 x 250^2 699 -> 651 us an iteration, 8 x 400^2 1121 -> 1069)
+    for (int st : {BS_BPQ16, BS_BPQ8, BS_BPQ2})
+        if (10L * B.count[st][1] <= 11L * B.count[st][0]) B.order[st] = 1;
     if ((rc = ensure(c, B.items, all.size() * sizeof(uint32_t)))) return rc;
     HIP_TRY(c, hipMemcpyAsync(B.items.ptr, all.data(), all.size() * sizeof(uint32_t),
                               hipMemcpyHostToDevice, c->stream));
@@ -1011,7 +1024,7 @@ void batch_stage(sp_ctx* c, int stage, int order, int wpc, double mu, double rho
     switch (stage) {
     case BS_PREP: launch_prep_b(st, sl, t, BV_XH); break;
     case BS_PROJECT: launch_project_b(st, sl, project_tables(c, order, wpc), true); break;
-    case BS_BACKPROJECT: launch_backproject_b(st, sl, t, B.nbmax, B.bp_px, B.bp_forms, false); break;
+    case BS_BACKPROJECT: launch_backproject_b(st, sl, backproject_tables(c, order, wpc), false); break;
     case BS_ROWS:
         launch_precond_b(st, sl, t, table(c, BS_COLS, order, wpc), B.fft_threads, B.fft_forms, mu, rho);
         break;
@@ -1058,6 +1071,12 @@ int batch_tune(sp_ctx* c, double mu, double rho) {
         if (stage == BS_PROJECT) {
             B.order[BS_PROJ_PART] = B.order[BS_PROJECT];
             B.wpc[BS_PROJ_PART] = B.wpc[BS_PROJECT];
+        }
+        if (stage == BS_BACKPROJECT) {
+            for (int s : {BS_BPQ16, BS_BPQ8, BS_BPQ2}) {
+                B.order[s] = B.order[BS_BACKPROJECT];
+                B.wpc[s] = B.wpc[BS_BACKPROJECT];
+            }
         }
         if (stage == BS_ROWS) {
             B.order[BS_COLS] = B.order[BS_ROWS];
@@ -2708,14 +2727,15 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
     if ((sp->flags & SP_FLAG_AUTOTUNE) && !B.tuned && (rc = batch_tune(c, mu, rho))) return rc;
     // Algorithm 3, steps 1-9, every slice in each launch
     const ProjectTables tproj = project_tables(c);
+    const BackprojectTables tbp = backproject_tables(c);
     const ItemTable tprep = table(c, BS_PREP),
-                    tbp = table(c, BS_BACKPROJECT), tvec = table(c, BS_VEC), ttv = table(c, BS_TV),
+                    tvec = table(c, BS_VEC), ttv = table(c, BS_TV),
                     ttvt = table(c, BS_TVT), ttvg = table(c, BS_TVG),
                     tone = table(c, BS_SLICE, 0, 0), tpq = table(c, BS_PQ);
     launch_prep_b(st, sl, tprep, BV_XH);
     launch_project_b(st, sl, tproj, true);
     launch_scalar_b(st, sl, tone, OP_F0);
-    launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms, g32);
+    launch_backproject_b(st, sl, tbp, g32);
     batch_precond(c, mu, rho);
     launch_prep_b(st, sl, tprep, BV_Z);
     launch_project_b(st, sl, tproj, false);            // w = R z
@@ -2744,7 +2764,7 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
         }
         launch_project_b(st, sl, tproj, true);
         launch_scalar_b(st, sl, tone, OP_F);
-        launch_backproject_b(st, sl, tbp, B.nbmax, B.bp_px, B.bp_forms, g32);
+        launch_backproject_b(st, sl, tbp, g32);
         batch_precond(c, mu, rho);
         launch_prep_b(st, sl, tprep, BV_Z);
         launch_project_b(st, sl, tproj, false);        // w = R z, (R z)^T q

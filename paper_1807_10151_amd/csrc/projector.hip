@@ -1151,13 +1151,12 @@ __global__ __launch_bounds__(64 * NW) void k_backproject_quad(GeomDev G, const A
 }
 
 // g = R^T rpd from the float64 residual.  NB is the largest candidate count of
-// the batch (extra candidates weigh exactly 0).  Each of this kernel and the
-// two of kb_backproject_quad sums the slices of its own form.
+// the batch (extra candidates weigh exactly 0).
 template <int NB, int PX>
 __global__ __launch_bounds__(256) void kb_backproject(const SliceDev* __restrict__ sl, ItemTable t, int round) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
-        if (S.G.bp_quad || gmem(S.sc)->halt) return;
+        if (gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         int bx, by;
         bp_tile_of(lin, (G.cols + 8 * PX - 1) / (8 * PX), (G.rows + BP_TILE - 1) / BP_TILE, bx, by);
@@ -1166,16 +1165,13 @@ __global__ __launch_bounds__(256) void kb_backproject(const SliceDev* __restrict
     });
 }
 
-// NW waves per workgroup, each summing every NW-th share: 8 for one tile per
-// wave (slices of 16 shares take two turns, so that their workgroups, of small
-// images, last about as long as those of 8 shares; with 4 waves the 16-slice
-// batch of 128^2 to 512^2 was 8% slower than pixel by pixel), 4 for two.
+// NW waves per workgroup, each summing every NW-th share.
 template <int NW, int NQ>
 __global__ __launch_bounds__(64 * NW) void kb_backproject_quad(const SliceDev* __restrict__ sl, ItemTable t,
                                                            int round) {
     for_items(t, [&](int s, int lin) {
         const SliceDev& S = sl[s];
-        if (!S.G.bp_quad || S.G.bp_nq != NQ || gmem(S.sc)->halt) return;
+        if (gmem(S.sc)->halt) return;
         const GeomDev G = S.G;
         bp_quad_body<double, NW, NQ>(G, cmem(S.ang), cmem(S.quad), gmem(S.rpd),
                                      BpOut{nullptr, gmem(S.g), round != 0}, lin);
@@ -1192,17 +1188,26 @@ void launch_bp_b_px(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, 
     }
 }
 
-void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms,
-                          bool round) {
+template <int NW, int NQ>
+void launch_bp_b_quad(hipStream_t st, const SliceDev* sl, ItemTable t, int shares, int round) {
+    if (t.n > 0)
+        hipLaunchKernelGGL((kb_backproject_quad<NW, NQ>), dim3(t.grid), dim3(64 * NW), bp_quad_lds(shares, NQ), st, sl, t,
+                           round);
+}
+
+void launch_backproject_b(hipStream_t st, const SliceDev* sl, const BackprojectTables& T, bool round) {
     const int rd = round ? 1 : 0;
-    if (forms & BP_FORM_QUAD)
-        hipLaunchKernelGGL((kb_backproject_quad<8, 1>), dim3(t.grid), dim3(512), bp_quad_lds(BPQ_MAX_SHARES, 1), st, sl,
-                           t, rd);
-    if (forms & BP_FORM_QUAD2)
-        hipLaunchKernelGGL((kb_backproject_quad<4, 2>), dim3(t.grid), dim3(256), bp_quad_lds(4, 2), st, sl, t, rd);
-    if (!(forms & BP_FORM_PIXEL)) return;
-    if (px == 4) launch_bp_b_px<4>(st, sl, t, nbmax, rd);
-    else launch_bp_b_px<2>(st, sl, t, nbmax, rd);
+    // (The wave slots hold the 16 shares of q16_wide tiles at once; more take their
+    // shares in two turns, so that workgroups of one CU overlap.  Iteration, 8 / 16
+    // waves: 1 x 64^2 85 / 83 us, 4 x 128^2 114 / 109, 1 x 250^2 131 / 124, 2 x 250^2
+    // 180 / 184, 16 x 180^2 361 / 396.)
+    if (T.q16.n <= T.q16_wide) launch_bp_b_quad<16, 1>(st, sl, T.q16, 16, rd);
+    else launch_bp_b_quad<8, 1>(st, sl, T.q16, 16, rd);
+    launch_bp_b_quad<8, 1>(st, sl, T.q8, 8, rd);
+    launch_bp_b_quad<4, 2>(st, sl, T.q2, 4, rd);
+    if (T.pixel.n == 0) return;
+    if (T.px == 4) launch_bp_b_px<4>(st, sl, T.pixel, T.nbmax, rd);
+    else launch_bp_b_px<2>(st, sl, T.pixel, T.nbmax, rd);
 }
 
 template <class TY, int PX>

@@ -555,8 +555,8 @@ struct SliceDev {
 enum BatchVec : int { BV_XH = 0, BV_X = 1, BV_P = 2, BV_Z = 3 };
 enum BatchStage : int {
     BS_PREP = 0, BS_PROJECT, BS_BACKPROJECT, BS_ROWS, BS_COLS, BS_TV, BS_VEC, BS_SLICE, BS_PROJ_COMB,
-    BS_PQ, BS_TVT, BS_TVG, BS_PROJ_PART, BS_PROJ_SUM,
-    BS_COUNT
+    BS_PQ, BS_TVT, BS_TVG, BS_PROJ_PART, BS_PROJ_SUM, BS_BPQ16,
+    BS_BPQ8, BS_BPQ2, BS_COUNT
 };
 struct ItemTable {
     const uint32_t* items;
@@ -607,12 +607,19 @@ struct ProjectTables {
     int wg_parts;
 };
 void launch_project_b(hipStream_t st, const SliceDev* sl, const ProjectTables& T, bool residual);
-// px: pixels per lane of the launch's slices in the pixel form (their G.bp_px);
-// forms: the forms of R^T among the slices (bp_form).
-enum BpForm : int { BP_FORM_PIXEL = 1, BP_FORM_QUAD = 2, BP_FORM_QUAD2 = 4 };
-inline int bp_form(const GeomDev& G) { return !G.bp_quad ? BP_FORM_PIXEL : (G.bp_nq == 2 ? BP_FORM_QUAD2 : BP_FORM_QUAD); }
+// The item tables of R^T: the slices in the pixel form (px: pixels per lane, their
+// G.bp_px; nbmax: their most candidate bins) and those over blocks with 16 shares
+// (a wave each for up to q16_wide items), with 8 shares, and with two tiles per
+// wave.
+struct BackprojectTables {
+    ItemTable pixel, q16, q8, q2;
+    int nbmax, px, q16_wide;
+};
+inline int bp_stage(const GeomDev& G) {
+    return !G.bp_quad ? BS_BACKPROJECT : (G.bp_nq == 2 ? BS_BPQ2 : (G.bp_shares == 8 ? BS_BPQ8 : BS_BPQ16));
+}
 // round: see launch_backproject.
-void launch_backproject_b(hipStream_t st, const SliceDev* sl, ItemTable t, int nbmax, int px, int forms, bool round);
+void launch_backproject_b(hipStream_t st, const SliceDev* sl, const BackprojectTables& T, bool round);
 // fft.hip (z = M g); forms: those among the slices (fft_form)
 void launch_precond_b(hipStream_t st, const SliceDev* sl, ItemTable rows, ItemTable cols, int threads, int forms,
                       double mu, double rho);

@@ -125,3 +125,23 @@ def test_batched_equals_single(rows, cols, n_angles, n_bins):
         one = sp.sp_suppcg_solve(g, b, None, **kw)
         np.testing.assert_array_equal(got.x_half.cpu().numpy(), one.x_half.cpu().numpy())
         np.testing.assert_array_equal(got.x_last.cpu().numpy(), one.x_last.cpu().numpy())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("slices", [
+    [(40, 37, 30, 59, 1.0), (48, 40, 30, 65, 0.9)],                              # 16 shares, a wave each; pixels
+    [(300, 290, 20, 419, 1.0), (300, 300, 20, 426, 1.0), (33, 20, 30, 40, 0.9)],   # 16 shares in two turns; pixels
+    [(420, 430, 24, 602, 1.0), (40, 37, 30, 59, 1.0)] * 4,                       # 8 shares and 16, grouped by XCD
+    [(1441, 1473, 6, 2062, 1.0), (420, 430, 24, 602, 1.0), (20, 30, 9, 37, 1.0)],  # two tiles per wave and the others
+])
+def test_batched_backprojection_of_every_form(slices):
+    torch = pytest.importorskip("torch")
+    import paper_1807_10151_amd as sp
+    gs = [sp.Geometry(r, c, a, b, bin_spacing=ds) for r, c, a, b, ds in slices]
+    rng = np.random.default_rng(len(slices))
+    bs = [torch.from_numpy(rng.uniform(0, 10, (g.n_angles, g.n_bins)).astype(np.float32)).cuda() for g in gs]
+    kw = dict(K=0, mu=1e-5, rho=0.8, max_iter=3)
+    for g, b, got in zip(gs, bs, sp.sp_suppcg_solve_batched(gs, bs, **kw)):
+        one = sp.sp_suppcg_solve(g, b, None, **kw)
+        np.testing.assert_array_equal(got.x_half.cpu().numpy(), one.x_half.cpu().numpy())
+        np.testing.assert_array_equal(got.x_last.cpu().numpy(), one.x_last.cpu().numpy())
