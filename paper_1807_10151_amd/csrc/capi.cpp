@@ -836,9 +836,14 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
     std::vector<Off> off(n);
     size_t total = 0;
     int rc;
+    std::vector<GeomDev*> gs(n);
+    for (int s = 0; s < n; ++s) {
+        gs[s] = &B.hs[s].G;
+        if ((rc = build_geometry(c, &geoms[s], *gs[s], tabs[s]))) return fail(c, rc, "slice %d: %s", s, c->err);
+    }
+    B.wg_parts = project_batch(gs.data(), n, c->n_cu * 32);
     for (int s = 0; s < n; ++s) {
         SliceDev& S = B.hs[s];
-        if ((rc = build_geometry(c, &geoms[s], S.G, tabs[s]))) return fail(c, rc, "slice %d: %s", s, c->err);
         const GeomDev& G = S.G;
         if (!G.bp_quad) B.nbmax = std::max(B.nbmax, G.nbmax);
         S.n = G.rows * G.cols;
@@ -905,11 +910,6 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         }
         if (all && tpx) B.bp_px = tpx;
         for (SliceDev& S : B.hs) S.G.bp_px = B.bp_px;
-    }
-    {
-        std::vector<GeomDev*> gs;
-        for (SliceDev& S : B.hs) gs.push_back(&S.G);
-        B.wg_parts = project_batch(gs.data(), n, c->n_cu * 32);
     }
     for (SliceDev& S : B.hs)
         if (S.F.P) {

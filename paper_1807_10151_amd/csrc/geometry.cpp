@@ -260,19 +260,24 @@ int project_batch(GeomDev* const* g, int n, int resident_waves) {
     // 1 x 400^2 x 30 223 / 145; on longer walks the empty slots cost more.
     const long W = resident_waves;
     long waves = 0, steps = 0;
+    int most = 0;
+    bool uneven = false, any_mem = false;   // among the slices: part counts, sums through memory
     for (int s = 0; s < n; ++s) {
         if (g[s]->parts > WG_PARTS) continue;
         waves += g[s]->nwaves;
         steps += (long)g[s]->nwaves * std::max(g[s]->rows, g[s]->cols);
+        uneven |= most && g[s]->parts != most;
+        any_mem |= g[s]->pmem != 0;
+        most = std::max(most, (int)g[s]->parts);
     }
     const bool side_by_side = 8 * waves <= (steps >= 160 * waves ? 5 : 4) * W;
-    int wg_parts = 0;
-    for (int s = 0; s < n; ++s) {
-        if (g[s]->parts > WG_PARTS) continue;
-        if (!side_by_side) g[s]->pmem = 0;
-        else if (!g[s]->pmem) wg_parts = std::max(wg_parts, (int)g[s]->parts);
-    }
-    return wg_parts;
+    // Workgroups of one launch have the waves of the most parts, which slices of
+    // fewer leave empty: uneven batches take the parts through memory, in one launch
+    // for all slices (144^2 and 386^2: 2 x R 117 -> 92 us).
+    const bool mem = side_by_side && (uneven || any_mem);
+    for (int s = 0; s < n; ++s)
+        if (g[s]->parts <= WG_PARTS) g[s]->pmem = mem ? 1 : 0;
+    return side_by_side && !mem ? most : 0;
 }
 
 int project_comb_blocks(const GeomDev& G) { return G.nA * ((G.nB + 255) / 256); }

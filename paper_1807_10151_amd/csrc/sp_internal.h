@@ -303,10 +303,10 @@ std::vector<int32_t> project_order(const GeomDev& G, const AngleDev* tab, const 
 // two-ray form (reads G.fwaves).
 void project_shape(GeomDev& G, int resident_waves);
 int project32_parts(const GeomDev& G, int resident_waves);
-// How a batch sums the parts of its slices with at most WG_PARTS of them: as their
-// own solves would while the batch leaves wave slots empty (returns the most parts
-// in a workgroup), else one after another in a wave, which needs neither seg nor a
-// second launch (G.pmem cleared; returns 0).  The sums are the same.
+// How a batch sums the parts of its slices with at most WG_PARTS of them: side by
+// side while the batch leaves wave slots empty, in a workgroup (returns their
+// count) or through memory (G.pmem), else one after another in a wave, which needs
+// neither seg nor a second launch (returns 0).  The sums are the same.
 int project_batch(GeomDev* const* g, int n, int resident_waves);
 // Combine workgroups of more than WG_PARTS parts: one angle by one 256-bin chunk
 // each.

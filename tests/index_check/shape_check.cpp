@@ -46,32 +46,46 @@ static bool check_parts(const GeomDev& G, long W) {
     return true;
 }
 
-// A batch of n such slices: parts side by side as in the slice's own solve while the
-// waves leave slots empty, in sequence once they fill them; more than WG_PARTS parts
-// stay as they are.
-static bool check_batch(const GeomDev& G, long W) {
-    for (int n : {1, 2, 64}) {
-        std::vector<GeomDev> g((size_t)n, G);
-        std::vector<GeomDev*> p;
-        for (GeomDev& q : g) p.push_back(&q);
-        const int wg = project_batch(p.data(), n, (int)W);
-        const long waves = (long)n * G.nwaves;
-        for (const GeomDev& q : g) {
-            if (q.parts != G.parts || q.pmem > G.pmem || (q.parts > WG_PARTS && !q.pmem))
-                return std::printf("batch of %d: parts\n", n), false;
-            if (q.parts > WG_PARTS) continue;
-            const int own = q.pmem ? 0 : q.parts;   // parts in a workgroup side by side
-            if (2 * waves <= W && (wg != own || q.pmem != G.pmem))
-                return std::printf("batch of %d, %ld waves: %d of %d parts side by side\n", n, waves, wg, own), false;
-            if (8 * waves > 5 * W && (wg || q.pmem)) return std::printf("batch of %d, %ld waves: split\n", n, waves), false;
+// A batch of n such slices, alone or beside a small one: parts side by side as in the
+// slice's own solve while the waves leave slots empty (through memory in one launch
+// for all where part counts differ), in sequence once they fill them; more than
+// WG_PARTS parts stay as they are.
+static bool check_batch(const GeomDev& G, const GeomDev& small, long W) {
+    for (int n : {1, 2, 64})
+        for (int beside : {0, 1}) {
+            std::vector<GeomDev> g((size_t)n, G);
+            if (beside) g.push_back(small);
+            std::vector<GeomDev*> p;
+            long waves = 0;
+            bool uneven = false;
+            for (GeomDev& q : g) {
+                p.push_back(&q);
+                if (q.parts <= WG_PARTS) waves += q.nwaves;
+                if (q.parts <= WG_PARTS && G.parts <= WG_PARTS && q.parts != G.parts) uneven = true;
+            }
+            const int wg = project_batch(p.data(), (int)p.size(), (int)W);
+            for (const GeomDev& q : g) {
+                const GeomDev& was = &q == &g.back() && beside ? small : G;
+                if (q.parts != was.parts || (q.parts > WG_PARTS && !q.pmem)) return std::printf("batch of %d: parts\n", n), false;
+                if (q.parts > WG_PARTS) continue;
+                const bool mem = uneven || (G.parts <= WG_PARTS && G.pmem);
+                if (2 * waves <= W && (q.pmem != (mem ? 1 : 0) || wg != (mem ? 0 : q.parts)))
+                    return std::printf("batch of %d, %ld waves: %d of %d parts in a workgroup\n", n, waves, wg, q.parts), false;
+                if (8 * waves > 5 * W && (wg || q.pmem)) return std::printf("batch of %d, %ld waves: split\n", n, waves), false;
+            }
         }
-    }
     return true;
 }
 
 int main() {
     char line[512];
     int count = 0;
+    sp_geometry sg{};
+    sg.rows = 20, sg.cols = 24, sg.n_angles = 30, sg.n_bins = 35, sg.pixel = sg.bin_spacing = 1.0;
+    GeomDev small{};
+    std::vector<AngleDev> stab((size_t)sg.n_angles);
+    char serr[256] = {0};
+    if (build_geometry_into(&sg, 256, small, stab.data(), serr, sizeof serr) != SP_OK) return 1;
     while (std::fgets(line, sizeof line, stdin)) {
         sp_geometry g{};
         if (std::sscanf(line, "%d %d %d %d %lf %lf %lf %lf %lf", &g.rows, &g.cols, &g.n_angles, &g.n_bins, &g.pixel,
@@ -86,7 +100,7 @@ int main() {
             continue;
         }
         if (!check_blocks(G, tab) || !check_tiles(G) || !check_parts(G, 256 * 32) ||
-            !check_batch(G, 256 * 32)) {
+            !check_batch(G, small, 256 * 32)) {
             std::printf("%dx%d %dx%d ds %g: FAILED\n", g.rows, g.cols, g.n_angles, g.n_bins, G.ds);
             return 1;
         }
