@@ -16,7 +16,7 @@
 //                J is accepted it evaluates further batches itself;
 //   k_tv_apply   y <- y + lam t_bar (and ||s_k||^2 partials on the last step).
 // The single-slice solver fuses two pairs: between inner steps the update and
-// the next t_bar are one launch (k_tv_apply_grad), on images below 2^18 pixels
+// the next t_bar are one launch (k_tv_apply_grad), on images up to 2^16 pixels
 // with the decision before them, and the last update also writes R's padded
 // copies of x_{k+1/2} (k_tv_apply_prep; the batched solver runs the same body).
 // k_tv_apply_grad repeats the arithmetic of the launches it replaces, so results
@@ -208,10 +208,11 @@ __device__ void tv_trials_wg(const double* __restrict__ y, const float* __restri
     double acc[TVJ + 1];
 #pragma unroll
     for (int q = 0; q <= TVJ; ++q) acc[q] = 0.0;
-    const size_t n = (size_t)rows * cols;
-    for (size_t p = threadIdx.x; p < n; p += 256) {
-        const int i = (int)(p / cols), j = (int)(p - (size_t)i * cols);
-        if (i < rows - 1 && j < cols - 1) tv_terms<TVJ>(y, tb, cols, p, lam, nq, acc);
+    // (at most 2^26 pixels: the quotient in 32 bits)
+    const unsigned n = (unsigned)rows * (unsigned)cols;
+    for (unsigned p = threadIdx.x; p < n; p += 256) {
+        const unsigned i = p / (unsigned)cols, j = p - i * (unsigned)cols;
+        if ((int)i < rows - 1 && (int)j < cols - 1) tv_terms<TVJ>(y, tb, cols, p, lam, nq, acc);
     }
     __shared__ double redn[4 * (TVJ + 1)];
     (void)red;
@@ -486,18 +487,16 @@ void launch_tv_apply_prep(hipStream_t st, const GeomDev& G, const double* src, d
 // *ell), workgroup 0 records it (l to *ell_out, which no workgroup reads).
 // Bound: latency; the decision's own launch took 4.4 us and the gap before it, the
 // sums of its partials 2.5 here, with the pixel's values on their way meanwhile
-// (243^2, 40 inner steps 655 -> 591 us).
+// (243^2, 40 inner steps 668 -> 622 us).
 template <bool DECIDE>
-__global__ __launch_bounds__(256) void k_tv_apply_grad(int rows, int cols, const double* __restrict__ src,
-                                                       double* __restrict__ dst,
-                                                       const float* __restrict__ tb_in,
-                                                       float* __restrict__ tb_out, Scalars* sc,
-                                                       double* __restrict__ partials, TvStep step,
-                                                       const int* halt) {
-    if (halt && *halt) return;
+__device__ __forceinline__ void tv_apply_grad_body(int rows, int cols, const double* __restrict__ src,
+                                                   double* __restrict__ dst,
+                                                   const float* __restrict__ tb_in,
+                                                   float* __restrict__ tb_out, Scalars* sc,
+                                                   double* __restrict__ partials, const TvStep& step) {
     __shared__ double red[4];
     const size_t n = (size_t)rows * cols;
-    const int px = DECIDE ? 1 : tv_px(n);   // the pixels and partial layout of a later k_tv_grad
+    const int px = DECIDE ? 1 : tv_px(n);   // the pixels and partial layout of a later k_tv_grad (1 where steps decide)
     double lam = 0.0, sq = 0.0;
     if constexpr (!DECIDE) lam = sc->lam;
     for (int r = 0; r < px; ++r) {
@@ -533,22 +532,43 @@ __global__ __launch_bounds__(256) void k_tv_apply_grad(int rows, int cols, const
     if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
+// (The launch without a decision carries no TvStep: half a microsecond a step.)
+__global__ __launch_bounds__(256) void k_tv_apply_grad(int rows, int cols, const double* __restrict__ src,
+                                                       double* __restrict__ dst,
+                                                       const float* __restrict__ tb_in,
+                                                       float* __restrict__ tb_out, Scalars* sc,
+                                                       double* __restrict__ partials,
+                                                       const int* halt) {
+    if (halt && *halt) return;
+    tv_apply_grad_body<false>(rows, cols, src, dst, tb_in, tb_out, sc, partials, TvStep{});
+}
+__global__ __launch_bounds__(256) void k_tv_step(int rows, int cols, const double* __restrict__ src,
+                                                 double* __restrict__ dst, const float* __restrict__ tb_in,
+                                                 float* __restrict__ tb_out, Scalars* sc,
+                                                 double* __restrict__ partials, TvStep step, const int* halt) {
+    if (halt && *halt) return;
+    tv_apply_grad_body<true>(rows, cols, src, dst, tb_in, tb_out, sc, partials, step);
+}
+
 void launch_tv_apply_grad(hipStream_t st, int rows, int cols, const double* src, double* dst,
                           const float* tb_in, float* tb_out, Scalars* sc, double* partials,
                           const TvStep* step, const int* halt) {
     const dim3 grid(tv_grad_blocks(rows, cols));
     if (step)
-        hipLaunchKernelGGL(k_tv_apply_grad<true>, grid, dim3(256), 0, st, rows, cols, src, dst, tb_in, tb_out, sc,
+        hipLaunchKernelGGL(k_tv_step, grid, dim3(256), 0, st, rows, cols, src, dst, tb_in, tb_out, sc,
                            partials, *step, halt);
     else
-        hipLaunchKernelGGL(k_tv_apply_grad<false>, grid, dim3(256), 0, st, rows, cols, src, dst, tb_in, tb_out, sc,
-                           partials, TvStep{}, halt);
+        hipLaunchKernelGGL(k_tv_apply_grad, grid, dim3(256), 0, st, rows, cols, src, dst, tb_in, tb_out, sc, partials,
+                           halt);
 }
 
 // Small images only: a decision beyond the first trials goes over the whole image
-// in every workgroup, which up to 2^18 pixels (1,024 workgroups) takes no longer
-// than in one.
-bool tv_folds_decision(int rows, int cols) { return tv_px((size_t)rows * cols) == 1; }
+// in every workgroup.  Up to 2^16 pixels these are one per CU and take no longer
+// than one alone; more share a CU's units.  Five steps that try all of 100 trials,
+// the decision in one workgroup / in each, ms: 243^2 15.5 / 15.2, 300^2 22.6 / 33.0,
+// 440^2 48.0 / 90.9, 511 x 513 64.5 / 151.9; 40 steps that accept the first one, us:
+// 243^2 668 / 622, 300^2 760 / 722, 440^2 877 / 892, 511^2 973 / 1043.
+bool tv_folds_decision(int rows, int cols) { return (size_t)rows * cols <= (size_t)1 << 16; }
 
 __global__ __launch_bounds__(256) void k_tv_value(int rows, int cols, const double* __restrict__ y,
                                                   double* __restrict__ partials,
