@@ -430,30 +430,38 @@ int sp_blobart_solve(sp_ctx* ctx, const sp_geometry* g, const float* b, double r
                      const sp_solve_params* sp, float* x_out, sp_trace* trace);
 
 /* ---- launch shapes ------------------------------------------------------------
- * Two launch shapes of the projector pair can be chosen per geometry: the
- * number of parts R splits each ray's walk into (1, 2, 4 or 8; the parts'
- * float64 sums are added in part order, so the choice changes R's results by
- * rounding) and the pixels per lane of R^T (2 or 4; the results do not
- * depend on it).  By default a rule of the image size and the wave slots
- * picks them.  The choices live in one process-wide table keyed by the whole
+ * Launch shapes of the projector pair can be chosen per geometry: the number of
+ * parts R splits each ray's walk into (1 to 8; the parts' float64 sums are added
+ * in part order, so the choice changes R's results by rounding) and the pixels
+ * per lane of R^T (2 or 4; the results do not depend on it, and geometries whose
+ * R^T sums 2 x 2 pixel blocks have only one shape).  R has a part count per form:
+ * that of the solvers' float64 vectors (also of a float32 image at bin spacings
+ * below a pixel or above about 1.41), and that of a float32 image otherwise, in
+ * sp_project, sp_residual and sp_gradient.  By default a rule of the image size
+ * and the wave slots picks them.  The choices live in one process-wide table keyed by the whole
  * geometry; every solve, operator and batch of that geometry built after an
  * update uses them, so single and batched solves of a geometry stay bitwise
  * equal (a batch takes 4 pixels per lane for all slices only if all of them
  * agree on it).  Updating the table between the two halves of a resumed run
  * changes R's rounding between them.
- * sp_tune_shapes: times sp_project (and, where a float32 image takes another
- * form of R than the solvers' float64 vectors, that form too: their mean) for
- * each part count (with the default pixels per lane) and then sp_backproject
- * for 2 and 4 pixels per lane on the context's stream, keeps the fastest (the default wins ties within 2%), and
- * stores it; ms (HOST double[6], nullable) receives the best-of-5 times of R
- * at 1, 2, 4, 8 parts and of R^T at 2, 4 pixels per lane.  Synchronises.
- * sp_tuning_set: stores a choice (parts 1..8, px 2 or 4; both 0 erases the
- * entry); SP_ERR_ARG for other values or an invalid geometry.
+ * sp_tune_shapes: times R of float64 vectors for 1, 2, 4 and 8 parts, then
+ * sp_project likewise where it takes the other form, then sp_backproject for 2
+ * and 4 pixels per lane on the context's stream, keeps the fastest of each (the
+ * shape in use wins ties within 2%), and stores them; ms (HOST double[6],
+ * nullable) receives the best-of-5 times of the first four and of R^T at 2, 4
+ * pixels per lane.  Synchronises.
+ * sp_tuning_set: stores a choice (parts of float64 vectors 1..8, px 2 or 4; both
+ * 0 erases the entry), with the other form's count left to the rule; SP_ERR_ARG
+ * for other values or an invalid geometry.
+ * sp_tuning_set32: the other form's count of g's entry (1..8, or 0: by rule);
+ * SP_ERR_ARG without an entry.  sp_tuning_get32: that count (0 without an entry).
  * sp_tuning_list: *count = entries; copies up to cap of them to HOST arrays
- * (each nullable).  sp_tuning_clear: erases all entries.  These three touch no
+ * (each nullable).  sp_tuning_clear: erases all entries.  These five touch no
  * device. */
 int sp_tune_shapes(sp_ctx* ctx, const sp_geometry* g, int32_t* parts, int32_t* px, double* ms);
 int sp_tuning_set(const sp_geometry* g, int32_t parts, int32_t px);
+int sp_tuning_set32(const sp_geometry* g, int32_t parts);
+int sp_tuning_get32(const sp_geometry* g, int32_t* parts);
 int sp_tuning_list(sp_geometry* geoms, int32_t* parts, int32_t* px, int32_t cap, int32_t* count);
 int sp_tuning_clear(void);
 

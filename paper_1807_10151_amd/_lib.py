@@ -136,6 +136,8 @@ _SIGS = {
     "sp_tune_shapes": (c_int, [c_void_p, POINTER(sp_geometry), POINTER(c_int32), POINTER(c_int32),
                                POINTER(c_double)]),
     "sp_tuning_set": (c_int, [POINTER(sp_geometry), c_int32, c_int32]),
+    "sp_tuning_set32": (c_int, [POINTER(sp_geometry), c_int32]),
+    "sp_tuning_get32": (c_int, [POINTER(sp_geometry), POINTER(c_int32)]),
     "sp_tuning_list": (c_int, [POINTER(sp_geometry), POINTER(c_int32), POINTER(c_int32), c_int32,
                                POINTER(c_int32)]),
     "sp_tuning_clear": (c_int, []),

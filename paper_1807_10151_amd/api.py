@@ -292,8 +292,9 @@ def batch_tuning(ctx: Context | None = None) -> dict:
 
 
 def tune_shapes(g: Geometry, ctx: Context | None = None) -> dict:
-    """Times R's ray parts (1, 2, 4, 8) and R^T's pixels per lane (2, 4) for g on
-    the GPU and stores the fastest in the process-wide shape table."""
+    """Times R's ray parts (1, 2, 4, 8) of either form and R^T's pixels per lane
+    (2, 4) for g on the GPU and stores the fastest in the process-wide shape
+    table.  R_ms: of the solvers' form."""
     ctx = ctx or context(0)
     parts, px = ctypes.c_int32(0), ctypes.c_int32(0)
     ms = (ctypes.c_double * 6)()
@@ -305,12 +306,28 @@ def tune_shapes(g: Geometry, ctx: Context | None = None) -> dict:
             "RT_ms": {2: ms[4], 4: ms[5]}}
 
 
-def tuning_set(g: Geometry, parts: int, px: int):
-    """Stores launch shapes for g (parts = px = 0 erases the entry)."""
+def tuning_set(g: Geometry, parts: int, px: int, parts32: int = 0):
+    """Stores launch shapes for g (parts = px = 0 erases the entry); parts32: R's
+    parts of a float32 image where it takes the two-ray form (0: by rule)."""
     gc = g.c()
-    rc = L.load().sp_tuning_set(ctypes.byref(gc), parts, px)
+    lib = L.load()
+    if not 0 <= parts32 <= 8:
+        raise SupPCGError(L.SP_ERR_ARG, f"sp_tuning_set32 rejected parts={parts32}")
+    rc = lib.sp_tuning_set(ctypes.byref(gc), parts, px)
     if rc != L.SP_OK:
         raise SupPCGError(rc, f"sp_tuning_set rejected parts={parts} px={px}")
+    if parts32:
+        rc = lib.sp_tuning_set32(ctypes.byref(gc), parts32)
+        if rc != L.SP_OK:
+            raise SupPCGError(rc, f"sp_tuning_set32 rejected parts={parts32}")
+
+
+def tuning_parts32(g: Geometry) -> int:
+    """R's parts of a float32 image in g's entry (0: by rule, or no entry)."""
+    parts = ctypes.c_int32(0)
+    gc = g.c()
+    L.load().sp_tuning_get32(ctypes.byref(gc), ctypes.byref(parts))
+    return parts.value
 
 
 def tuning_list():
@@ -341,7 +358,7 @@ def tuning_save(path: str):
     import json
     recs = [{"rows": g.rows, "cols": g.cols, "n_angles": g.n_angles, "n_bins": g.n_bins, "pixel": g.pixel,
              "theta0": g.theta0, "dtheta": g.dtheta, "bin_spacing": g.bin_spacing, "bin_offset": g.bin_offset,
-             "parts": p_, "px": x_} for g, p_, x_ in tuning_list()]
+             "parts": p_, "px": x_, "parts32": tuning_parts32(g)} for g, p_, x_ in tuning_list()]
     with open(path, "w") as f:
         json.dump({"shapes": recs}, f, indent=1)
 
@@ -354,7 +371,7 @@ def tuning_load(path: str):
     for r in recs:
         g = Geometry(r["rows"], r["cols"], r["n_angles"], r["n_bins"], r["pixel"], r["theta0"], r["dtheta"],
                      r["bin_spacing"], r["bin_offset"])
-        tuning_set(g, int(r["parts"]), int(r["px"]))
+        tuning_set(g, int(r["parts"]), int(r["px"]), int(r.get("parts32", 0)))
 
 
 class StoredMatrix:

@@ -219,40 +219,40 @@ int validate_geometry(sp_ctx* c, const sp_geometry* g) {
 }
 
 // Launch shapes of the projector pair per geometry (sp_tune_shapes,
-// sp_tuning_set): R's ray parts and R^T's pixels per lane, process-wide.
+// sp_tuning_set): R's ray parts (parts: one ray per lane; parts32: the two-ray form,
+// 0: by rule) and R^T's pixels per lane, process-wide.
 // Every table built for a geometry takes its entry, so single and batched
 // solves of one geometry use the same shapes; the epoch changes with every
 // update, which makes the contexts rebuild their cached tables.
 struct ShapeEntry {
     sp_geometry g;
-    int32_t parts, px;
+    int32_t parts, px, parts32;
 };
 std::mutex g_shape_mu;
 std::vector<ShapeEntry> g_shapes;
 std::atomic<uint64_t> g_shape_epoch{1};
 
-bool shape_lookup(const sp_geometry& g, int& parts, int& px) {
+bool shape_lookup(const sp_geometry& g, ShapeEntry& out) {
     std::lock_guard<std::mutex> lk(g_shape_mu);
     for (const ShapeEntry& e : g_shapes)
         if (same_geom(e.g, g)) {
-            parts = e.parts;
-            px = e.px;
+            out = e;
             return true;
         }
     return false;
 }
 
 // parts == 0 erases the entry
-void shape_store(const sp_geometry& g, int parts, int px) {
+void shape_store(const ShapeEntry& e) {
     std::lock_guard<std::mutex> lk(g_shape_mu);
     for (size_t i = 0; i < g_shapes.size(); ++i)
-        if (same_geom(g_shapes[i].g, g)) {
-            if (parts == 0) g_shapes.erase(g_shapes.begin() + (long)i);
-            else g_shapes[i].parts = parts, g_shapes[i].px = px;
+        if (same_geom(g_shapes[i].g, e.g)) {
+            if (e.parts == 0) g_shapes.erase(g_shapes.begin() + (long)i);
+            else g_shapes[i] = e;
             ++g_shape_epoch;
             return;
         }
-    if (parts != 0) g_shapes.push_back(ShapeEntry{g, parts, px});
+    if (e.parts != 0) g_shapes.push_back(e);
     ++g_shape_epoch;
 }
 
@@ -262,11 +262,14 @@ int build_geometry_into(sp_ctx* c, const sp_geometry* g, GeomDev& G, AngleDev* t
     char msg[256];
     const int rc = sp::build_geometry_into(g, c->n_cu, G, tab, msg, sizeof msg);
     if (rc) return fail(c, rc, "%s", msg);
-    int parts, px;
-    if (shape_lookup(*g, parts, px)) {
-        G.parts = G.fparts = parts;
-        G.pmem = parts > WG_PARTS ? 1 : 0;
-        G.bp_px = px;
+    ShapeEntry e;
+    if (shape_lookup(*g, e)) {
+        if (e.parts != G.parts) {
+            G.parts = e.parts;
+            G.pmem = e.parts > WG_PARTS ? 1 : 0;
+        }
+        if (e.parts32) G.fparts = e.parts32;
+        G.bp_px = e.px;
     }
     return SP_OK;
 }
@@ -900,13 +903,14 @@ int batch_setup(sp_ctx* c, int n, const sp_geometry* geoms, int kind) {
         for (const SliceDev& S : B.hs)
             if (!S.G.bp_quad) waves4 += (long)backproject_tiles(S.G, 4) * 4;
         B.bp_px = waves4 >= (long)c->n_cu * 16 ? 4 : 2;
-        // tuned shapes that agree for every slice take precedence
+        // tuned shapes that agree for every such slice take precedence
         int tpx = 0;
         bool all = true;
         for (int s = 0; s < n && all; ++s) {
-            int tp, tx;
-            if (!shape_lookup(geoms[s], tp, tx) || (tpx && tx != tpx)) all = false;
-            else tpx = tx;
+            ShapeEntry e;
+            if (B.hs[(size_t)s].G.bp_quad) continue;
+            if (!shape_lookup(geoms[s], e) || (tpx && e.px != tpx)) all = false;
+            else tpx = e.px;
         }
         if (all && tpx) B.bp_px = tpx;
         for (SliceDev& S : B.hs) S.G.bp_px = B.bp_px;
@@ -1436,9 +1440,11 @@ int sp_tune_shapes(sp_ctx* c, const sp_geometry* g, int32_t* parts_out, int32_t*
     int rc = drain_pending(c);
     if (rc) return rc;
     if ((rc = setup_geometry(c, g))) return rc;
-    const int def_parts = c->G.parts, def_px = c->G.bp_px;
-    int old_parts = 0, old_px = 0;
-    const bool had = shape_lookup(*g, old_parts, old_px);
+    ShapeEntry old{};
+    const bool had = shape_lookup(*g, old);
+    // the shapes in use now, in which a part count of the rule keeps its way of
+    // adding the parts
+    const ShapeEntry def{*g, c->G.parts, c->G.bp_px, c->G.fparts};
     DevBuf xb, yb;
     struct Tmp {
         DevBuf *a, *b;
@@ -1456,19 +1462,14 @@ int sp_tune_shapes(sp_ctx* c, const sp_geometry* g, int32_t* parts_out, int32_t*
         return fail(c, SP_ERR_HIP, "hipEventCreate failed");
     }
     // fastest of 5 calls after a warm-up (data values do not change the work)
-    auto time_call = [&](bool back, float& best) -> int {
+    auto time_shape = [&](const ShapeEntry& e, auto call, float& best) -> int {
+        shape_store(e);
         best = 1e30f;
         for (int r = 0; r < 6; ++r) {
-            (void)hipEventRecord(e0, c->stream);
-            const int q = back ? sp_backproject(c, g, dptr<float>(yb), dptr<float>(xb))
-                               : sp_project(c, g, dptr<float>(xb), dptr<float>(yb));
+            int q = setup_geometry(c, g);
             if (q) return q;
-            if (!back && c->G.pair) {   // a loop body's other R: the float64 iterate, ray by ray
-                RayOut o;
-                o.out = dptr<float>(yb);
-                launch_project(c->stream, c->G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->pwave), dptr<double>(c->xp),
-                               dptr<double>(c->xTp), o, dptr<double>(c->seg), dptr<int>(c->pord), nullptr);
-            }
+            (void)hipEventRecord(e0, c->stream);
+            if ((q = call())) return q;
             (void)hipEventRecord(e1, c->stream);
             if (hipEventSynchronize(e1) != hipSuccess) return fail(c, SP_ERR_HIP, "timing the launch shapes failed");
             float t = 0.0f;
@@ -1477,43 +1478,55 @@ int sp_tune_shapes(sp_ctx* c, const sp_geometry* g, int32_t* parts_out, int32_t*
         }
         return SP_OK;
     };
-    const int parts_c[4] = {1, 2, 4, 8}, px_c[2] = {2, 4};
+    auto one_ray = [&]() {   // R of the solvers' vectors
+        launch_prep(c->stream, c->G, dptr<float>(xb), dptr<double>(c->xp), dptr<double>(c->xTp), nullptr);
+        RayOut o;
+        o.out = dptr<float>(yb);
+        launch_project(c->stream, c->G, dptr<AngleDev>(c->ang), dptr<WaveDev>(c->pwave), dptr<double>(c->xp),
+                       dptr<double>(c->xTp), o, dptr<double>(c->seg), dptr<int>(c->pord), nullptr);
+        return check_launch(c);
+    };
+    auto image = [&]() { return sp_project(c, g, dptr<float>(xb), dptr<float>(yb)); };
+    auto back = [&]() { return sp_backproject(c, g, dptr<float>(yb), dptr<float>(xb)); };
+    const int counts[4] = {1, 2, 4, 8}, px_c[2] = {2, 4};
     float tr[4], tb[2];
-    int best_parts = def_parts, best_px = def_px;
-    rc = SP_OK;
-    for (int i = 0; i < 4 && !rc; ++i) {
-        shape_store(*g, parts_c[i], def_px);
-        rc = time_call(false, tr[i]);
-        if (c->G.pair) tr[i] *= 0.5f;   // the mean of the two forms
-    }
-    if (!rc) {
-        // the default wins ties within 2%
-        float tdef = 1e30f;
-        for (int i = 0; i < 4; ++i)
-            if (parts_c[i] == def_parts) tdef = tr[i];
-        float best = tdef;
-        for (int i = 0; i < 4; ++i)
-            if (tr[i] < 0.98f * best) best = tr[i], best_parts = parts_c[i];
+    ShapeEntry best = def, e;
+    // The fastest part count of one form (field); the one in use wins ties within 2%.
+    auto pick_parts = [&](int32_t ShapeEntry::*field, auto call, float (&t)[4]) -> int {
+        float low;
+        if (int q = time_shape(best, call, low)) return q;
+        const ShapeEntry base = best;
+        for (int i = 0; i < 4; ++i) {
+            e = base;
+            e.*field = counts[i];
+            if (int q = time_shape(e, call, t[i])) return q;
+            if (t[i] < 0.98f * low && e.*field != base.*field) low = t[i], best.*field = counts[i];
+        }
+        return SP_OK;
+    };
+    rc = pick_parts(&ShapeEntry::parts, one_ray, tr);
+    if (!rc && c->G.pair) {
+        float t32[4];
+        rc = pick_parts(&ShapeEntry::parts32, image, t32);
     }
     for (int i = 0; i < 2 && !rc; ++i) {
-        shape_store(*g, best_parts, px_c[i]);
-        rc = time_call(true, tb[i]);
+        e = best;
+        e.px = px_c[i];
+        rc = time_shape(e, back, tb[i]);
     }
-    if (!rc) {
-        float tdef = def_px == 4 ? tb[1] : tb[0], best = tdef;
-        for (int i = 0; i < 2; ++i)
-            if (tb[i] < 0.98f * best) best = tb[i], best_px = px_c[i];
-    }
+    // (R^T over blocks has one shape)
+    if (!rc && !c->G.bp_quad && tb[def.px == 4 ? 0 : 1] < 0.98f * tb[def.px == 4 ? 1 : 0]) best.px = def.px == 4 ? 2 : 4;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) {   // leave the cache as it was
-        if (had) shape_store(*g, old_parts, old_px);
-        else shape_store(*g, 0, 0);
+        if (!had) old = ShapeEntry{*g, 0, 0, 0};
+        shape_store(old);
         return rc;
     }
-    shape_store(*g, best_parts, best_px);
-    if (parts_out) *parts_out = best_parts;
-    if (px_out) *px_out = best_px;
+    if (best.parts32 == def.parts32) best.parts32 = had ? old.parts32 : 0;   // by rule, as it was
+    shape_store(best);
+    if (parts_out) *parts_out = best.parts;
+    if (px_out) *px_out = best.px;
     if (ms) {
         for (int i = 0; i < 4; ++i) ms[i] = tr[i];
         for (int i = 0; i < 2; ++i) ms[4 + i] = tb[i];
@@ -1524,7 +1537,7 @@ int sp_tune_shapes(sp_ctx* c, const sp_geometry* g, int32_t* parts_out, int32_t*
 int sp_tuning_set(const sp_geometry* g, int32_t parts, int32_t px) {
     if (!g) return SP_ERR_ARG;
     if (parts == 0 && px == 0) {
-        shape_store(*g, 0, 0);
+        shape_store(ShapeEntry{*g, 0, 0, 0});
         return SP_OK;
     }
     if (parts < 1 || parts > 8 || (px != 2 && px != 4)) return SP_ERR_ARG;
@@ -1533,7 +1546,22 @@ int sp_tuning_set(const sp_geometry* g, int32_t parts, int32_t px) {
     std::vector<AngleDev> tab((size_t)std::max(g->n_angles, 1));
     if (g->n_angles < 1 || sp::build_geometry_into(g, 256, G, tab.data(), msg, sizeof msg) != SP_OK)
         return SP_ERR_ARG;
-    shape_store(*g, parts, px);
+    shape_store(ShapeEntry{*g, parts, px, 0});
+    return SP_OK;
+}
+
+int sp_tuning_set32(const sp_geometry* g, int32_t parts) {
+    ShapeEntry e;
+    if (!g || parts < 0 || parts > 8 || !shape_lookup(*g, e)) return SP_ERR_ARG;
+    e.parts32 = parts;
+    shape_store(e);
+    return SP_OK;
+}
+
+int sp_tuning_get32(const sp_geometry* g, int32_t* parts) {
+    ShapeEntry e;
+    if (!g || !parts) return SP_ERR_ARG;
+    *parts = shape_lookup(*g, e) ? e.parts32 : 0;
     return SP_OK;
 }
 
@@ -2678,8 +2706,8 @@ int sp_suppcg_solve_batched(sp_ctx* c, int32_t n, const sp_geometry* geoms, cons
     if (sp->flags & SP_FLAG_AUTOTUNE) {
         // launch shapes of every geometry the table does not hold yet
         for (int s = 0; s < n; ++s) {
-            int tp, tx;
-            if (shape_lookup(geoms[s], tp, tx)) continue;
+            ShapeEntry e;
+            if (shape_lookup(geoms[s], e)) continue;
             if ((rc = sp_tune_shapes(c, &geoms[s], nullptr, nullptr, nullptr)))
                 return fail(c, rc, "slice %d: tuning its launch shapes: %s", s, c->err);
         }
