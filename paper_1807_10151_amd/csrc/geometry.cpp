@@ -319,12 +319,12 @@ int build_geometry_into(const sp_geometry* g, int n_cu, GeomDev& G, AngleDev* ta
     }
     for (int q = 1; q <= 4; ++q) G.cls[q] += G.cls[q - 1];
     // stable counting sort by class, no allocation
-    int pos = 0;
-    for (int q = 0; q < 4; ++q)
-        for (int a = 0; a < g->n_angles; ++a) {
-            const AngleDev A = angle_entry(*g, a, ds, s0, margin);
-            if (angle_class(A) == q) tab[pos++] = A;
-        }
+    int pos[4];
+    for (int q = 0; q < 4; ++q) pos[q] = G.cls[q];
+    for (int a = 0; a < g->n_angles; ++a) {
+        const AngleDev A = angle_entry(*g, a, ds, s0, margin);
+        tab[pos[angle_class(A)]++] = A;
+    }
     G.pair = 1;
     for (int a = 0; a < G.cls[2]; ++a) G.pair &= pair_fits(G, tab[a]) ? 1 : 0;
     G.nwaves = project_wave_count(G);
@@ -358,31 +358,46 @@ bool lane_steps(const GeomDev& G, const AngleDev& A, int k, int& lo, int& hi) {
 }  // namespace
 
 long wave_steps(const GeomDev& G, const AngleDev* tab, const WaveDev& W) {
+    // A wave's lanes hold runs of consecutive bins of one angle.  The rays of an
+    // angle that meet the image are consecutive bins, and a ray's range moves
+    // monotonically with its bin, so the first and last nonempty ranges of a run
+    // bound its union: two rays to evaluate where a lane-by-lane loop took 16 to 64
+    // (both forms' tables and orders on one core, 512^2 x 720 13.8 -> 3.7 ms, 243^2 x
+    // 360 3.4 -> 1.1; the one-ray form's alone took 15.1 and 3.6).
     int lo = 1 << 30, hi = -1;
-    auto add = [&](int lane) {
-        int ai, k, l, h;
-        const bool pair = W.tail == WAVE_PAIR_BLOCK || W.tail == WAVE_PAIR_TAIL;
-        if (!(pair ? wave_pair(W, lane, G.nB, ai, k) : wave_ray(W, lane, G.nB, ai, k))) return false;
-        bool met = false;
-        for (int q = k; q <= k + (pair ? 1 : 0) && q < G.nB; ++q) {
-            if (!lane_steps(G, tab[ai], q, l, h)) continue;
-            lo = std::min(lo, l);
-            hi = std::max(hi, h);
-            met = true;
-        }
-        return met;
+    auto add = [&](int ai, int ka, int kb) {
+        const AngleDev& A = tab[ai];
+        int la, ha, lb, hb;
+        bool first = lane_steps(G, A, ka, la, ha), last = lane_steps(G, A, kb, lb, hb);
+        // both past the same end of the image: so are those between
+        if (!first && !last && la == lb && A.slope != 0.0) return;
+        while (!first && ka < kb) first = lane_steps(G, A, ++ka, la, ha);
+        if (!first) return;
+        while (!last) last = lane_steps(G, A, --kb, lb, hb);
+        lo = std::min(lo, std::min(la, lb));
+        hi = std::max(hi, std::max(ha, hb));
     };
-    if (W.tail != WAVE_ROW) {
-        for (int l = 0; l < 64; ++l) add(l);
+    if (W.tail == WAVE_ROW) {
+        add(W.a0, W.k0, std::min(W.k0 + 63, G.nB - 1));
+        return hi > lo ? (long)(hi - lo) : 0;
+    }
+    // (in units of pairs of bins for the two-ray form)
+    const bool pair = W.tail >= WAVE_PAIR_BLOCK;
+    const int n = pair ? (G.nB + 1) / 2 : G.nB;
+    auto add_units = [&](int ai, int qa, int qb) {
+        if (pair) add(ai, 2 * qa, std::min(2 * qb + 1, G.nB - 1));
+        else add(ai, qa, qb);
+    };
+    if (W.tail == WAVE_BLOCK || W.tail == WAVE_PAIR_BLOCK) {
+        for (int a = W.a0; a < std::min(W.a0 + WAVE_ANGLES, W.aend); ++a)
+            add_units(a, W.k0, std::min(W.k0 + WAVE_BINS, n) - 1);
     } else {
-        // the rays of one angle that meet the image are consecutive bins, and a
-        // ray's range moves monotonically with its bin: the first and last
-        // lanes with a nonempty range bound the union
-        const int last = std::min(63, G.nB - 1 - W.k0);
-        int l = 0;
-        while (l <= last && !add(l)) ++l;
-        int m = last;
-        while (m > l && !add(m)) --m;
+        const int r = n % WAVE_BINS;
+        for (int e = W.k0, a = W.a0 + e / r, off = e % r; e < W.k0 + 64 && a < W.aend; ++a, off = 0) {
+            const int m = std::min(r - off, W.k0 + 64 - e);
+            add_units(a, n - r + off, n - r + off + m - 1);
+            e += m;
+        }
     }
     return hi > lo ? (long)(hi - lo) : 0;
 }

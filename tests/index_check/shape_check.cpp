@@ -4,8 +4,14 @@
 //
 // Input lines: rows cols n_angles n_bins pixel theta0 dtheta bin_spacing
 // bin_offset.  Prints one line per geometry; exits 1 at the first violation.
+// With the argument "time" (and built with optimisation) it checks instead that
+// both forms' wave tables and dispatch orders, which every geometry's set-up
+// builds, take at most 1.5 times as long as evaluating the rays of the one-ray table
+// lane by lane.
 #include <algorithm>
+#include <chrono>
 #include <cstdio>
+#include <cstring>
 #include <vector>
 
 #include "../../include/suppcg.h"
@@ -77,7 +83,46 @@ static bool check_batch(const GeomDev& G, const GeomDev& small, long W) {
     return true;
 }
 
-int main() {
+// Steps of a wave of the one-ray table, every lane's ray evaluated.
+static long steps_by_lane(const GeomDev& G, const std::vector<AngleDev>& tab, const WaveDev& W) {
+    int lo = 1 << 30, hi = -1;
+    for (int lane = 0; lane < 64; ++lane) {
+        int ai, k, l, h;
+        if (!wave_ray(W, lane, G.nB, ai, k)) continue;
+        const AngleDev& A = tab[(size_t)ai];
+        if (A.flags & ANG_HORIZ) ray_steps<true>(G, A, bin_pos((double)k, G), l, h);
+        else ray_steps<false>(G, A, bin_pos((double)k, G), l, h);
+        if (l < h) lo = std::min(lo, l), hi = std::max(hi, h);
+    }
+    return hi > lo ? hi - lo : 0;
+}
+
+static bool check_time(const GeomDev& G, const std::vector<AngleDev>& tab) {
+    using clock = std::chrono::steady_clock;
+    auto ms = [](clock::duration d) { return std::chrono::duration<double, std::milli>(d).count(); };
+    double tables = 1e30, lanes = 1e30;
+    long sum = 0;
+    std::vector<WaveDev> w((size_t)G.nwaves), f((size_t)G.fwaves);
+    for (int r = 0; r < 5; ++r) {
+        const auto t0 = clock::now();
+        project_waves(G, w.data());
+        sum += project_order(G, tab.data(), w.data(), G.nwaves, 256)[0];
+        project_pair_waves(G, f.data());
+        sum += project_order(G, tab.data(), f.data(), G.fwaves, 256)[0];
+        const auto t1 = clock::now();
+        for (const WaveDev& W : w) sum += steps_by_lane(G, tab, W);
+        const auto t2 = clock::now();
+        tables = std::min(tables, ms(t1 - t0));
+        lanes = std::min(lanes, ms(t2 - t1));
+    }
+    for (const WaveDev& W : w)
+        if (wave_steps(G, tab.data(), W) != steps_by_lane(G, tab, W)) return std::printf("steps of a wave\n"), false;
+    std::printf("tables %.3f ms, lanes %.3f ms (%ld)\n", tables, lanes, sum);
+    return tables < 1.5 * lanes;   // (lane by lane the two tables cost more than twice that)
+}
+
+int main(int argc, char** argv) {
+    const bool timed = argc > 1 && !std::strcmp(argv[1], "time");
     char line[512];
     int count = 0;
     sp_geometry sg{};
@@ -99,7 +144,7 @@ int main() {
             std::printf("%dx%d %dx%d: refused\n", g.rows, g.cols, g.n_angles, g.n_bins);
             continue;
         }
-        if (!check_blocks(G, tab) || !check_tiles(G) || !check_parts(G, 256 * 32) ||
+        if (timed ? !check_time(G, tab) : !check_blocks(G, tab) || !check_tiles(G) || !check_parts(G, 256 * 32) ||
             !check_batch(G, small, 256 * 32)) {
             std::printf("%dx%d %dx%d ds %g: FAILED\n", g.rows, g.cols, g.n_angles, g.n_bins, G.ds);
             return 1;

@@ -56,6 +56,15 @@ def test_shapes_of_every_geometry():
     assert f"checked {len(rows)} geometries" in res.stdout
 
 
+def test_set_up_evaluates_few_rays():
+    exe = build_checker("shape_time", "-O2")
+    rows = [(64, 64, 90, 91, 1.0, 0.0, -1.0, 1.0, 0.0), (243, 243, 360, 345, 0.0752, 0.0, -1.0, 0.0752, 0.0),
+            (512, 512, 720, 725, 1.0, 0.0, -1.0, 1.0, 0.0), (300, 420, 200, 700, 1.0, 0.1, -1.0, 0.93, 0.3)]
+    res = subprocess.run([exe, "time"], input=lines(rows), capture_output=True, text=True, timeout=600)
+    print(res.stdout)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_angles,theta0", [(1, 0.0), (1, math.pi / 2), (2, 0.0), (4, 0.0)])
 @pytest.mark.parametrize("ds,offset", [(0.375, 0.13), (0.4, 0.13), (0.5, 0.0), (0.5, 0.13), (0.9, 0.13), (1.0, 0.0), (2.5, 0.13)])
