@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256) void k_lp_conv_in(int B, int H, int W, int S, 
 // 25 -> 15).
 constexpr int LP_OUT = 16, LP_OUTH = LP_OUT + 2;
 
-__global__ __launch_bounds__(256) void k_lp_conv_out(int B, int H, int W, const float* __restrict__ in,
+__global__ __launch_bounds__(256) void k_lp_conv_out(unsigned ntile, int H, int W, const float* __restrict__ in,
                                                      float* __restrict__ out,
                                                      const float* __restrict__ W1,
                                                      const int* __restrict__ halt,
@@ -233,41 +233,44 @@ __global__ __launch_bounds__(256) void k_lp_conv_out(int B, int H, int W, const 
     __shared__ float s[NT * 16][9];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, kq = lane >> 4;
     const int tx = (W + LP_OUT - 1) / LP_OUT, ty = (H + LP_OUT - 1) / LP_OUT;
-    const unsigned b = blockIdx.x / (unsigned)(tx * ty), rem = blockIdx.x - b * (unsigned)(tx * ty);
-    const int y0 = (int)(rem / (unsigned)tx) * LP_OUT, x0 = (int)(rem % (unsigned)tx) * LP_OUT;
     f4v wr;   // channel 4 kq + cg, tap i
 #pragma unroll
     for (int cg = 0; cg < 4; ++cg) wr[cg] = i < 9 ? W1[(4 * kq + cg) * 9 + i] : 0.0f;
-    const float* img = in + (size_t)b * H * W * LF;
-    constexpr int PW = (NT + 3) / 4;   // tiles per wave
-    f4v a[PW];
+    for (unsigned t0 = blockIdx.x; t0 < ntile; t0 += gridDim.x) {
+        const unsigned b = t0 / (unsigned)(tx * ty), rem = t0 - b * (unsigned)(tx * ty);
+        const int y0 = (int)(rem / (unsigned)tx) * LP_OUT, x0 = (int)(rem % (unsigned)tx) * LP_OUT;
+        const float* img = in + (size_t)b * H * W * LF;
+        constexpr int PW = (NT + 3) / 4;   // tiles per wave
+        f4v a[PW];
 #pragma unroll
-    for (int q = 0; q < PW; ++q) {
-        const int p = (4 * q + wave) * 16 + i;   // pixel of the 18 x 18
-        const int y = y0 - 1 + p / LP_OUTH, x = x0 - 1 + p % LP_OUTH;
-        const bool ok = p < NP && in_img(y, x, H, W);
-        const f4v v = *reinterpret_cast<const f4v*>(img + (ok ? ((size_t)y * W + x) * LF : 0) + 4 * kq);
-        a[q] = ok ? v : f4v{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-#pragma unroll
-    for (int q = 0; q < PW; ++q) {
-        const int tile = 4 * q + wave;
-        if (tile >= NT) break;
-        f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][cg], wr[cg], acc, 0, 0, 0);
-        // lane holds pixel 4 kq + r of the tile, tap i
-        if (i < 9) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) s[tile * 16 + 4 * kq + r][i] = acc[r];
+        for (int q = 0; q < PW; ++q) {
+            const int p = (4 * q + wave) * 16 + i;   // pixel of the 18 x 18
+            const int y = y0 - 1 + p / LP_OUTH, x = x0 - 1 + p % LP_OUTH;
+            const bool ok = p < NP && in_img(y, x, H, W);
+            const f4v v = *reinterpret_cast<const f4v*>(img + (ok ? ((size_t)y * W + x) * LF : 0) + 4 * kq);
+            a[q] = ok ? v : f4v{0.0f, 0.0f, 0.0f, 0.0f};
         }
-    }
-    __syncthreads();
-    const int py = threadIdx.x / LP_OUT, px = threadIdx.x % LP_OUT;
-    float sum = 0.0f;
+        if (t0 != blockIdx.x) __syncthreads();   // the previous sums are done
 #pragma unroll
-    for (int t = 0; t < 9; ++t) sum += s[(py + 2 - t / 3) * LP_OUTH + px + 2 - t % 3][t];
-    if (y0 + py < H && x0 + px < W) out[(size_t)b * H * W + (size_t)(y0 + py) * W + x0 + px] = sum;
+        for (int q = 0; q < PW; ++q) {
+            const int tile = 4 * q + wave;
+            if (tile >= NT) break;
+            f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int cg = 0; cg < 4; ++cg) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][cg], wr[cg], acc, 0, 0, 0);
+            // lane holds pixel 4 kq + r of the tile, tap i
+            if (i < 9) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[tile * 16 + 4 * kq + r][i] = acc[r];
+            }
+        }
+        __syncthreads();
+        const int py = threadIdx.x / LP_OUT, px = threadIdx.x % LP_OUT;
+        float sum = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) sum += s[(py + 2 - t / 3) * LP_OUTH + px + 2 - t % 3][t];
+        if (y0 + py < H && x0 + px < W) out[(size_t)b * H * W + (size_t)(y0 + py) * W + x0 + px] = sum;
+    }
 }
 
 // out = scale[c] * in, channels-last
@@ -577,9 +580,10 @@ void lp_gather(hipStream_t st, int B, int HW, const float* src, const int32_t* i
 
 void lp_conv_out(hipStream_t st, int B, int H, int W, const float* in, float* out, const float* W1,
                  const int* halt, const int* run) {
-    const long g = (long)B * ((H + LP_OUT - 1) / LP_OUT) * ((W + LP_OUT - 1) / LP_OUT);
-    hipLaunchKernelGGL(k_lp_conv_out, dim3((unsigned)g), dim3(256), 0, st, B, H, W,
-                       in, out, W1, halt, run);
+    // (a launch holds fewer than 2^32 threads: images of less than a tile take several
+    // tiles per workgroup beyond 2^22 of them)
+    const unsigned g = (unsigned)((long)B * ((H + LP_OUT - 1) / LP_OUT) * ((W + LP_OUT - 1) / LP_OUT));
+    hipLaunchKernelGGL(k_lp_conv_out, dim3(std::min(g, 1u << 22)), dim3(256), 0, st, g, H, W, in, out, W1, halt, run);
 }
 
 void lp_scale(hipStream_t st, long npix, const float* in, const float* scale, float* out) {
