@@ -176,6 +176,7 @@ int ensure(sp_ctx* c, DevBuf& b, size_t bytes) {
     }
     bytes = std::max<size_t>(bytes, 256);
     if (hipMalloc(&b.ptr, bytes) != hipSuccess) {
+        (void)hipGetLastError();   // reported here, not by the next launch check
         b.ptr = nullptr;
         return fail(c, SP_ERR_ALLOC, "hipMalloc of %zu bytes failed", bytes);
     }
@@ -290,10 +291,11 @@ int setup_geometry(sp_ctx* c, const sp_geometry* g) {
     const size_t nX = (size_t)g->rows * G.pitchX, nXT = (size_t)g->cols * G.pitchXT;
     const size_t nY = (size_t)g->n_angles * G.pitchB;
     // Padded buffers must have zero pads: re-zero when the layout changes.
-    if ((rc = ensure(c, c->ang, tab.size() * sizeof(AngleDev)))) return rc;
     const bool relayout = !c->have_geom || c->G.pitchX != G.pitchX || c->G.pitchXT != G.pitchXT ||
                           c->G.pitchB != G.pitchB || c->G.rows != G.rows || c->G.cols != G.cols ||
                           c->G.nA != G.nA || c->G.pair != G.pair;
+    c->have_geom = false;   // until every table and buffer is in place: a failure on the way leaves none
+    if ((rc = ensure(c, c->ang, tab.size() * sizeof(AngleDev)))) return rc;
     if ((rc = ensure(c, c->xp, nX * 8))) return rc;
     if ((rc = ensure(c, c->xTp, nXT * 8))) return rc;
     if (G.pair && ((rc = ensure(c, c->zp, nX * 4)) || (rc = ensure(c, c->zTp, nXT * 4)))) return rc;
@@ -367,6 +369,7 @@ int setup_fft(sp_ctx* c, FFTPlan& F) {
             const double ang = -2.0 * M_PI * (double)k / (double)P;
             tw[k] = make_double2(std::cos(ang), std::sin(ang));
         }
+        c->fftP = 0;   // until the table is in place
         if ((rc = ensure(c, c->tw, tw.size() * sizeof(double2)))) return rc;
         HIP_TRY(c, hipMemcpyAsync(c->tw.ptr, tw.data(), tw.size() * sizeof(double2),
                                   hipMemcpyHostToDevice, c->stream));
