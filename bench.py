@@ -6,7 +6,9 @@ gamma = 0.5 (first trial step 0.5^k), ramp-Hamming preconditioner
 (mu = 1e-5, rho = 0.8).  One step = one SupPCG iteration (S_TV + U_PCG: the
 projections R x_{k+1/2} and R z, one backprojection R^T, one preconditioner
 apply, TV work and the CG updates; U_PCG's h = A p enters through R p, which
-the solver carries).  Prints one JSON line.
+the solver carries).  Prints one JSON line of under 2 kB; the run's full records
+(batches, stored matrices, curves, the learned preconditioner, ...) go to stderr
+before it, as one line "bench details: {...}".
 
     python bench.py [--gpus 1] [--steps 100] [--warmup 5] [--no-cpu]
 """
@@ -63,6 +65,26 @@ COUNTERS = {"measured_at": "kernels of d362e45",
 L1_ACCESS = {"measured_at": "kernels of d362e45",
              "per_launch": {"project": 5.703e7, "backproject": 3.012e7},
              "per_cu_per_cycle": {"project": 1.01, "backproject": 0.74}}
+
+
+def result_lines(out):
+    """(the result line, the line of all records) of a run.  The result line has to be
+    found whole in the last 2 kB of stdout, so it names what it takes of each record."""
+    keep = {"metric": 0, "value": 0, "unit": 0, "n_gpus": 0, "steps": 0, "warmup": 0, "ms_per_step": 0,
+            "higher_is_better": 0, "scaling": 0, "vs_baseline": 0, "dtype": 0, "data": 0,
+            "config": ("workload",),
+            "roofline": ("bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "kernels"),
+            "stored_matrix_equivalent": ("project_GBps", "backproject_GBps"),
+            "time_to_target": ("plain_ms_median", "learned_ms_to_both_median", "learned_reached_f_and_tv_within_400"),
+            "batched": ("slice_iterations_per_s",),
+            "cpu_baseline": ("value", "unit", "cores", "kind", "sample")}
+    line = {k: {f: out[k][f] for f in fields if f in out[k]} if fields else out[k]
+            for k, fields in keep.items() if k in out}
+    if "kernels" in line.get("roofline", {}):
+        line["roofline"]["kernels"] = {
+            name: {"ms": k["ms"], "frac": k["frac"], "valu_issue": {"frac": k["valu_issue"]["frac"]}}
+            for name, k in line["roofline"]["kernels"].items()}
+    return json.dumps(line), json.dumps(out)
 
 
 def log(msg):
@@ -684,7 +706,9 @@ def main():
     if not args.no_cpu:
         out["cpu_baseline"] = cpu_baseline(img, b_np)
         log("cpu baseline done")
-    print(json.dumps(out), flush=True)
+    line, details = result_lines(out)
+    print(f"bench details: {details}", file=sys.stderr, flush=True)
+    print(line, flush=True)
 
 
 if __name__ == "__main__":
