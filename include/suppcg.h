@@ -199,24 +199,33 @@ const char* sp_version(void);
 
 /* ---- operators ------------------------------------------------------------ */
 /* y = R x (Section 2: the projection matrix applied to image x).
+ * A NaN or infinity in x reaches the rays that meet its pixel and those whose own
+ * walk reads it with weight 0: a ray reads two pixels of each row (or column) it
+ * crosses at oblique angles, up to three at axis-parallel ones.
+ * A context holds the tables of one geometry; a call with another builds its own
+ * (host time 0.17 ms at 64 x 64 x 90, 2 ms at 512 x 512 x 720).
  * x: [rows][cols] float32 (device, read); y: [n_angles][n_bins] (device, written). */
 int sp_project(sp_ctx* ctx, const sp_geometry* g, const float* x, float* y);
 
 /* x = R^T y, the transpose of sp_project's weights, pixel-driven, no atomics
  * (eq. 2.2).  Each (ray, pixel) weight is the same chord length sp_project
  * uses, equal to float64 rounding (bit for bit at axis-parallel angles; R
- * splits oblique rays band by band, R^T evaluates the trapezoid).
+ * splits oblique rays band by band, R^T evaluates the trapezoid).  A NaN or
+ * infinity in y reaches the pixels that meet its ray and those for which it is a
+ * candidate of weight 0: a pixel reads the one to four consecutive bins (two at
+ * oblique angles and unit spacing) that can meet it at the angle.
  * y: [n_angles][n_bins] (device, read); x: [rows][cols] (device, written). */
 int sp_backproject(sp_ctx* ctx, const sp_geometry* g, const float* y, float* x);
 
 /* sp_backproject for callers that cannot allocate device memory (code being
  * captured into a HIP graph, tight serving loops, harnesses that forbid
  * hipMalloc): the same x = R^T y, bit for bit, with the context's workspace
- * replaced by one static 32 MiB scratch array per GPU (the angle table and
- * the padded, wmax-scaled sinogram; held until the process ends).  The call
+ * replaced by one static 33 MiB scratch array per GPU (the angle table and
+ * the padded, wmax-scaled sinogram, 32 MiB, and the angles' constants of the
+ * 2 x 2 pixel blocks, 1 MiB; held until the process ends).  The call
  * allocates no device or host memory.  It needs n_angles <= 8192 and
  * n_angles * 96 (rounded up to 256) + n_angles * (n_bins + 8) * 4 bytes to
- * fit in the 32 MiB, else SP_ERR_ARG and nothing is enqueued.  Every call on a GPU
+ * fit in those 32 MiB, else SP_ERR_ARG and nothing is enqueued.  Every call on a GPU
  * shares that GPU's array and rewrites it whole; calls that overlap on one
  * GPU (other streams, other contexts, other threads) race and must be
  * ordered by the caller.  y: [n_angles][n_bins], x: [rows][cols] (device). */

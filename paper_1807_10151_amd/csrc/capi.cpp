@@ -591,7 +591,6 @@ void enqueue_stv(sp_ctx* c, Scalars* sc, int K, const double* x, double* xh, boo
                       xp ? tv_prep_tiles(G.rows, G.cols) : nb0, nullptr, 0);
 }
 
-// z = M g with the partial dots z^T dotv (dotv nullable).
 // Sizes the learned preconditioner's workspace for npix pixels (training
 // buffers only when `train`).
 int lp_reserve(sp_ctx* c, sp_learned* net, size_t npix, bool train, int B, int H, int W) {

@@ -825,7 +825,7 @@ void launch_pad_sino(hipStream_t st, const GeomDev& G, const AngleDev* ang, cons
 // Sum over the angles [beg, end) of one class for pixel row yi and the PX
 // pixels xj[u] of this lane.  The angle and its sinogram row are wave-uniform
 // (scalar loads); lanes differ only in the pixel.  The padded sinogram rows
-// arrive multiplied by their angle's wmax (project_store, k_pad_sino), so each
+// arrive multiplied by their angle's wmax (project_value, k_pad_sino), so each
 // candidate adds u * y' with the u of chord_u: the same weights as the
 // projector's wmax * u.
 //

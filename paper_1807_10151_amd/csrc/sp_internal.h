@@ -198,8 +198,10 @@ __host__ __device__ inline double chord_u(double d, double einv, double inv) {
 __host__ __device__ inline double bin_pos(double k, const GeomDev& G) { return fma(k, G.ds, G.s0); }
 
 // ---- allocation-free entry point (noalloc.hip) ---------------------------------
-// Bytes of the static per-GPU scratch array and the largest angle count the
-// allocation-free backprojection accepts (its host staging is sized for it).
+// Bytes the angle table and the padded sinogram may take of the static per-GPU
+// scratch array, and the largest angle count the allocation-free backprojection
+// accepts (its host staging is sized for it); the array has that many of R^T's
+// block constants (BpAngle) behind them.
 constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(32) << 20;
 constexpr int NOALLOC_MAX_ANGLES = 8192;
 // Device address of the scratch array on `device` (looked up once per device,
