@@ -53,18 +53,18 @@ OPS_PER_NNZ = 4
 # memory fabric per launch (FETCH_SIZE + WRITE_SIZE, scaled by the counters of
 # a 64 MiB device copy).  R^T: its float64 (residual) sinogram form, the one
 # the loop body runs.
-COUNTERS = {"measured_at": "kernels of d362e45",
-            "valu_instr": {"project": 2.678e7, "backproject": 2.639e7},
-            "traffic_bytes": {"project": 43.72e6, "backproject": 15.69e6}}
+COUNTERS = {"measured_at": "kernels of 94cfcb7",
+            "valu_instr": {"project": 2.678e7, "backproject": 2.640e7},
+            "traffic_bytes": {"project": 43.36e6, "backproject": 15.70e6}}
 # The vector L1's access rate, the limit R's gathers run into
 # (profiles/counters_ct512.md; the study behind it, of earlier kernels, in
 # profiles/memory_pipe_ct512.md):
 # TCP_TOTAL_CACHE_ACCESSES per launch and per compute unit and cycle of the
 # kernel's own run (about one access per CU and cycle is the L1's rate; R^T:
 # its float64 form, as above).
-L1_ACCESS = {"measured_at": "kernels of d362e45",
-             "per_launch": {"project": 5.703e7, "backproject": 3.012e7},
-             "per_cu_per_cycle": {"project": 1.01, "backproject": 0.74}}
+L1_ACCESS = {"measured_at": "kernels of 94cfcb7",
+             "per_launch": {"project": 5.702e7, "backproject": 3.012e7},
+             "per_cu_per_cycle": {"project": 1.02, "backproject": 0.74}}
 
 
 def result_lines(out):
