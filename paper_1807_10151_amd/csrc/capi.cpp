@@ -1553,11 +1553,15 @@ int sp_tuning_set(const sp_geometry* g, int32_t parts, int32_t px) {
 }
 
 int sp_tuning_set32(const sp_geometry* g, int32_t parts) {
-    ShapeEntry e;
-    if (!g || parts < 0 || parts > 8 || !shape_lookup(*g, e)) return SP_ERR_ARG;
-    e.parts32 = parts;
-    shape_store(e);
-    return SP_OK;
+    if (!g || parts < 0 || parts > 8) return SP_ERR_ARG;
+    std::lock_guard<std::mutex> lk(g_shape_mu);   // an update of the entry, which others may store meanwhile
+    for (ShapeEntry& e : g_shapes)
+        if (same_geom(e.g, *g)) {
+            e.parts32 = parts;
+            ++g_shape_epoch;
+            return SP_OK;
+        }
+    return SP_ERR_ARG;
 }
 
 int sp_tuning_get32(const sp_geometry* g, int32_t* parts) {
